@@ -147,12 +147,13 @@ __device__ inline void slot_sums4(float (&v)[4][N], float (&out)[N]) {
   for (int q = 0; q < N; ++q) out[q] = dpp_add<0xB1>(out[q]);
 }
 
-// The same for eight slots: slot s ends, fully summed, in lanes 8s .. 8s+7.
-// Three halving steps (half-wave swap, odd/even row swap, row mirror with a
-// select), then three butterflies over the eight lanes of a slot (lane xor
-// 7, 2, 1).  18 instructions per value for eight slots.
+// Eight slots of N values each, summed over the eight lanes of a wave that
+// share an index mod 8 (for an 8 x 8 pixel block: over its rows); lane l ends
+// with slot l / 8's sums of column l % 8.  Three halving steps: half-wave
+// swap, odd/even row swap, and a rotation by eight lanes with a select.  15
+// instructions per value for eight slots.  All 64 lanes must be active.
 template <int N>
-__device__ inline void slot_sums8(float (&v)[8][N], float (&out)[N]) {
+__device__ inline void slot_row_sums8(float (&v)[8][N], float (&out)[N]) {
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -170,16 +171,22 @@ __device__ inline void slot_sums8(float (&v)[8][N], float (&out)[N]) {
   const bool low = (__lane_id() & 8) == 0;
 #pragma unroll
   for (int q = 0; q < N; ++q) {     // lanes 0-7 of a row keep v[0], lanes 8-15 v[1]
-    const float a = dpp_add<0x140>(v[0][q]);
-    const float b = dpp_add<0x140>(v[1][q]);
+    const float a = dpp_add<0x128>(v[0][q]);
+    const float b = dpp_add<0x128>(v[1][q]);
     out[q] = low ? a : b;
   }
+}
+
+// Sums over the eight lanes of a group (8s .. 8s+7), in every one of them
+// (half-row mirror, two quad permutations).
+template <int N>
+__device__ inline void group_sums8(float (&v)[N]) {
 #pragma unroll
-  for (int q = 0; q < N; ++q) out[q] = dpp_add<0x141>(out[q]);
+  for (int q = 0; q < N; ++q) v[q] = dpp_add<0x141>(v[q]);
 #pragma unroll
-  for (int q = 0; q < N; ++q) out[q] = dpp_add<0x4E>(out[q]);
+  for (int q = 0; q < N; ++q) v[q] = dpp_add<0x4E>(v[q]);
 #pragma unroll
-  for (int q = 0; q < N; ++q) out[q] = dpp_add<0xB1>(out[q]);
+  for (int q = 0; q < N; ++q) v[q] = dpp_add<0xB1>(v[q]);
 }
 
 // Float add into LDS through an integer compare-and-swap loop.  On gfx950

@@ -18,9 +18,10 @@
 //                     (depth bits, index) order
 //   ranges            tile boundaries in the sorted entries (written by the
 //                     tile sort's scatter when it takes one pass)
-//   blend             (tile, 256-entry chunk) work items over a resident
-//                     grid; chunk composites, per-tile combine, restart of
-//                     the stop chunk; the adjoint over 64-entry sub-chunks
+//   blend             one workgroup per 8 x 8 pixel block: its waves composite
+//                     consecutive 64-entry sub-chunks of the tile's list side
+//                     by side and stop as soon as the block has; the adjoint
+//                     over the sub-chunks that were composited
 // Stable ranking inside a radix pass uses wave64 ballots (11 ballots give
 // the lanes that share a digit) and mbcnt-style lane masks.
 #include "common.h"
@@ -37,10 +38,9 @@ constexpr int kItemsD = 8;       // per thread, passes over the duplicates
 constexpr int kItemsN = 2;       // per thread, passes over the splats
 constexpr int kBlockD = kRadixThreads * kItemsD;
 constexpr int kBlockN = kRadixThreads * kItemsN;
-constexpr int kChunk = 256;      // splats per blend work item
-constexpr int kSub = 64;         // splats per work item of the blend adjoint
-constexpr int kSubs = kChunk / kSub;
-constexpr int kQueues = 8;       // item queues of the blend adjoint, one 256-byte line each
+constexpr int kSub = 64;         // list entries per sub-chunk of the blend passes
+constexpr int kBlocks = 4;       // 8 x 8 pixel blocks of a tile
+constexpr int kGrad = 16;        // floats per splat of the adjoint sums (9 used, one 64-byte line)
 constexpr float kHalfNegLog2e = -0.72134752f;   // -log2(e) / 2
 constexpr float kInvHalfLog2e = 1.38629436f;    // 2 / log2(e) = 2 ln 2
 constexpr int kDigitBits = 11;   // radix digit width of the tile sort: 2048 bins
@@ -49,13 +49,23 @@ constexpr int kWideBits = 12;    // one tile pass of 4096 bins for 2049 .. 4096 
 constexpr int kDepthBits = 11;   // digit width of the depth sort: 3 passes over 32-bit keys
 constexpr int kDepthPasses = (32 + kDepthBits - 1) / kDepthBits;
 
+// Parts a tile's list is walked in (see the blend), so that about 5,000
+// workgroups share the work of few deep lists: the mean number of splats
+// per tile decides, known before the lists are.  (A list's length is about
+// half of it times the tiles a splat touches, over the share of the tiles
+// that the avatar covers.)
+inline int list_parts(int64_t n, int64_t tiles) {
+  if (n < 192 * tiles || tiles > 512) return 1;
+  return n < 1024 * tiles ? 4 : (tiles > 64 ? 8 : 32);
+}
+
 struct Layout {
   size_t rec, mean2d, conic, depth, rect, touched, fp64, keys0, vals0, keys1, vals1, offs;
-  size_t tk0, tv0, tk1, tv1, ranges, hist, binoff, bintot, bsum, boff, count, queue, grad;
-  size_t item_off, item_tile, item_chunk, item_sub, cstate, sstate, sub_item, total;
+  size_t tk0, tv0, tk1, tv1, ranges, hist, binoff, bintot, bsum, boff, count, grad;
+  size_t nlive, mask, state, part, part_t, total;
   int tiles_x, tiles_y, nb_n, nb_cap, nb_max, tile_passes;
+  int parts;       // parts a tile's list is walked in
   int tile_bits;   // digit width of a one-pass tile sort: kDigitBits or kWideBits
-  int64_t max_items, max_subs;
 };
 
 Layout make_layout(int n, int width, int height, int64_t cap) {
@@ -100,18 +110,17 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   L.bintot = take((1 << kWideBits) * 4);
   L.bsum = take((size_t)L.nb_n * 4);
   L.boff = take((size_t)L.nb_n * 4);
-  L.count = take(32);   // int64 [0] = D, [1] = work items, [3] = adjoint items; uint32 [4] = scan ticket
-  L.queue = take(kQueues * 256);   // item queues of the blend adjoint, a line each
-  L.grad = take(N * 9 * 4);   // adjoint sums: mean2d, conic [5][n], opacity [n], colour [3][n]
-  L.max_items = rga::ceil_div(cap > 0 ? cap : 1, kChunk) + tiles;
-  L.item_off = take(((size_t)tiles + 1) * 4);
-  L.item_tile = take((size_t)L.max_items * 4);
-  L.item_chunk = take((size_t)L.max_items * 4);
-  L.item_sub = take((size_t)L.max_items * 4);
-  L.cstate = take((size_t)L.max_items * 4 * 256 * 4);
-  L.sstate = take((size_t)L.max_items * (kSubs - 1) * 4 * 256 * 4);
-  L.max_subs = rga::ceil_div(cap > 0 ? cap : 1, kSub) + tiles;
-  L.sub_item = take((size_t)L.max_subs * 4);
+  L.count = take(32);   // int64 [0] = D; uint32 [4] = scan ticket
+  L.grad = take(N * kGrad * 4);   // adjoint sums per splat: mean2d, conic, opacity, colour
+  // blend state: tile t's sub-chunk m of its list [start, end) has the slot
+  // start / 64 + t + m, distinct for every (tile, sub-chunk)
+  const size_t slots = C / kSub + (size_t)tiles + 1;
+  L.parts = list_parts(n, tiles);
+  L.nlive = take((size_t)tiles * kBlocks * L.parts * 4);
+  L.mask = take(slots * kBlocks * 8);
+  L.state = take(slots * 4 * 256 * 4);
+  L.part = take(L.parts > 1 ? (size_t)tiles * kBlocks * L.parts * 64 * 16 : 0);
+  L.part_t = take(L.parts > 1 ? (size_t)tiles * kBlocks * L.parts * 64 * 4 : 0);
   L.total = o;
   return L;
 }
@@ -138,6 +147,8 @@ CamDev to_dev(const rga_camera* c) {
   d.H = c->height;
   return d;
 }
+
+constexpr uint32_t kNoPart = 0xFFFFFFFFu;   // a part not finished (the bits of a NaN)
 
 // exp for the scales: Cody-Waite reduction by ln 2, degree-7 Taylor
 // polynomial, fixed FP32 operation order (reproducible bit for bit).
@@ -268,16 +279,15 @@ preprocess_kernel(int n, CamDev cam, int TX, int TY, const float* __restrict__ x
                   int32_t* __restrict__ touched, uint8_t* __restrict__ fp64,
                   uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
                   uint32_t* __restrict__ ranges_u32, int64_t nranges, uint32_t* __restrict__ cnt4,
-                  float* __restrict__ grad9, uint32_t* __restrict__ queue) {
+                  float4* __restrict__ grad, uint4* __restrict__ part_t, int64_t nparts4) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   // the frame's tile ranges start empty, its counters at zero, and so do the
-  // adjoint's per-splat sums and item queues
+  // adjoint's sums of the splats in the lists (below); no part is finished
+  for (int64_t i = g; i < nparts4; i += (int64_t)gridDim.x * blockDim.x)
+    part_t[i] = make_uint4(kNoPart, kNoPart, kNoPart, kNoPart);
   if (g < nranges) ranges_u32[g] = 0u;
   if (g < 8) cnt4[g] = 0u;
-  if (g < kQueues) queue[g * 64] = 0u;
   if (g >= n) return;
-#pragma unroll
-  for (int q = 0; q < 9; ++q) grad9[(size_t)q * n + g] = 0.f;
   Geo G;
   bool okq;
   geo_forward(cam, x, A, quat, log_s, n, g, G, okq);
@@ -350,6 +360,10 @@ preprocess_kernel(int n, CamDev cam, int TX, int TY, const float* __restrict__ x
   rect[2 * n + g] = tx1;
   rect[3 * n + g] = ty1;
   touched[g] = cnt;
+  if (cnt > 0) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) grad[(size_t)g * (kGrad / 4) + q] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
   fp64[g] = used64;
   keys[g] = cnt > 0 ? __float_as_uint(G.Z) : 0xFFFFFFFFu;
   vals[g] = (uint32_t)g;
@@ -382,66 +396,6 @@ __device__ inline SplatRec load_rec(const float4* __restrict__ rec, const float*
   R.r2.x = color[2 * (size_t)n + g];
   return R;
 }
-
-// ---- blend work items -------------------------------------------------------
-// Work items: (tile, chunk of kChunk entries) for the forward passes, and
-// (item, sub-chunk of kSub entries) for the adjoint, numbered tile by tile
-// with one scan over the tiles (the two counts packed in one 64-bit sum),
-// by one workgroup of NT threads, each a run of tiles; len(t) is tile t's
-// list length.  Each item gets its tile, chunk index and first sub-item; the
-// chunk pass lists the sub-items.
-template <int NT, class Len>
-__device__ void make_work_items(int tiles, Len&& len, uint32_t* __restrict__ item_off,
-                                uint32_t* __restrict__ item_tile, uint32_t* __restrict__ item_chunk,
-                                uint32_t* __restrict__ item_sub, int64_t max_items,
-                                int64_t* __restrict__ counters, uint64_t* part) {
-  const int per = (tiles + NT - 1) / NT;
-  const int t0 = min(tiles, (int)threadIdx.x * per), t1 = min(tiles, t0 + per);
-  uint64_t s = 0;
-  for (int t = t0; t < t1; ++t) {
-    const int l = len(t);
-    s += (uint64_t)((l + kChunk - 1) / kChunk) | ((uint64_t)((l + kSub - 1) / kSub) << 32);
-  }
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 1; o < NT; o <<= 1) {
-    const uint64_t v = threadIdx.x >= o ? part[threadIdx.x - o] : 0ull;
-    __syncthreads();
-    part[threadIdx.x] += v;
-    __syncthreads();
-  }
-  const uint64_t before = threadIdx.x ? part[threadIdx.x - 1] : 0ull;
-  uint32_t off = (uint32_t)before, soff = (uint32_t)(before >> 32);
-  for (int t = t0; t < t1; ++t) {
-    item_off[t] = off;
-    const int l = len(t);
-    const int nch = (l + kChunk - 1) / kChunk;
-    for (int j = 0; j < nch; ++j) {
-      const int64_t b = (int64_t)off + j;
-      if (b == max_items) counters[3] = (int64_t)soff;   // lists truncated: existing items' only
-      if (b < max_items) {
-        item_tile[b] = (uint32_t)t;
-        item_chunk[b] = (uint32_t)j;
-        item_sub[b] = soff;
-      }
-      soff += (uint32_t)min(kSubs, (l - j * kChunk + kSub - 1) / kSub);
-    }
-    off += nch;
-  }
-  if (threadIdx.x == NT - 1) {
-    const uint64_t tot = part[NT - 1];
-    item_off[tiles] = (uint32_t)tot;
-    counters[1] = (int64_t)(uint32_t)tot;
-    if ((int64_t)(uint32_t)tot <= max_items) counters[3] = (int64_t)(tot >> 32);
-  }
-}
-
-// Where the items go (passed to the tile sort's one-pass scatter).
-struct ItemOut {
-  uint32_t *off, *tile, *chunk, *sub;
-  int64_t max_items;
-  int64_t* counters;
-};
 
 // ---- radix sort (reduce-then-scan, stable) ----------------------------------
 __device__ inline int64_t live_count(const int64_t* cnt_ptr, int64_t fixed, int64_t cap) {
@@ -549,19 +503,18 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
                 uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                 const int64_t* cnt_ptr, int64_t fixed, int64_t cap, int shift,
                 const uint32_t* __restrict__ binoff, const uint32_t* __restrict__ bintot,
-                int32_t* __restrict__ ranges, int nranges, ItemOut items) {
+                int32_t* __restrict__ ranges, int nranges) {
   constexpr int kRadix = 1 << BITS;
   constexpr int kWavesR = kRadixThreads / 64;
   constexpr int kPer = kRadix / kRadixThreads;   // digits per thread in the digit scan
   static_assert(kPer >= 1, "at least one digit per thread");
   __shared__ uint32_t run[kWavesR][kRadix];
   __shared__ uint32_t wtot[kWavesR];
-  __shared__ uint64_t ipart[kRadixThreads];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t count = live_count(cnt_ptr, fixed, cap);
   const int64_t blk = (int64_t)blockIdx.x * (kRadixThreads * ITEMS);
-  // block 0 of a one-pass tile sort writes the ranges and work items even
-  // when there are no entries
+  // block 0 of a one-pass tile sort writes the ranges even when there are no
+  // entries
   if (blk >= count && !(ranges && blockIdx.x == 0)) return;
   uint32_t* wrun = run[wave];
   for (int d = lane; d < kRadix; d += 64) wrun[d] = 0u;
@@ -630,11 +583,6 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
     start += tot[q];
   }
   __syncthreads();
-  // ... and the blend's work items from the tile lengths (the digit totals)
-  if (ranges && blockIdx.x == 0)
-    make_work_items<kRadixThreads>(nranges, [&](int t) { return (int)bintot[t]; }, items.off,
-                                   items.tile, items.chunk, items.sub, items.max_items,
-                                   items.counters, ipart);
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     if (info[r] != 0xFFFFFFFFu) {
@@ -754,25 +702,44 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 }
 
 // ---- blend ------------------------------------------------------------------
-// Work items are (tile, chunk of <= 256 consecutive list entries); heavy
-// tiles therefore spread over many workgroups.  Pass 1 composites each chunk
-// independently (transmittance starting at 1); the combine pass walks a
-// tile's chunks front to back per pixel: a chunk whose end transmittance
-// keeps T_in * T_chunk >= 1e-4 cannot contain the stop (T is monotone), so
-// it contributes T_in * C_chunk; the first chunk that may contain the stop
-// is re-walked sequentially from T_in with the exact stop rule.  The
-// combine leaves (C before the chunk, a code for T_in) per (chunk, pixel)
-// for the adjoint.  The codes only flip signs, so T_in comes back exactly:
-//   code >= 0          whole chunk used, T_in = code
-//   -1 <= code < 0     the chunk where the walk stops, T_in = -code
-//   code = kPastStop   chunk past the stop
-// For the adjoint, which works on sub-chunks of kSub entries so that no
-// workgroup walks a long chunk alone, the chunk pass also leaves each
-// pixel's (C, T) at the sub-chunk boundaries, measured from the chunk's
-// start (T = 1, C = 0), with T negated once the walk has stopped; the
-// restart pass overwrites them, for the pixels it re-walks, with absolute
-// states: T_in * T_local and C_before + T_in * C_local up to the sub-chunk
-// it starts in, then those of its sequential walk.
+// One workgroup of four waves per 8 x 8 pixel block of a tile walks the
+// tile's list front to back, 256 entries a round: each wave stages 64 of them
+// (lane = entry) and tests them against the block's four 4 x 4 sub-blocks;
+// then each wave composites the entries that can reach its sub-block, four at
+// a time: lane = (pixel, one of four consecutive entries), the transmittance
+// before each entry by a product scan over the four lanes of a pixel.  The
+// product T of every listed entry's 1 - alpha is monotone, so an entry
+// contributes exactly if T after it is still >= 1e-4 (the stop rule), and
+// the pixel has stopped once T is not.
+// The workgroup ends with its list or when its 64 pixels have stopped.
+//
+// Bound by vector issue and, per block, by the chain of its rounds.  Stopping
+// is what counts: of the (entry, 8 x 8 block) pairs that can meet, 35 % lie
+// before the block's stop at 100k Gaussians / 512^2 and 16 % at 300k / 1080^2.
+// (Compositing 256-entry chunks of every list side by side, then combining
+// them per pixel and restarting the chunk with the stop, walked all of them:
+// 85 us at 100k / 512^2 and 416 us at 300k / 1080^2, this 76 and 164 us.)
+// Four entries per step shorten the chain of the longest walk (1,250 entries)
+// fourfold, and the 4 x 4 sub-blocks waste fewer lanes on pixels an entry
+// does not reach than 8 x 8 blocks do.  Two steps are taken together: all but
+// one product of a step does not depend on the step before.
+//
+// What the adjoint needs is left per (sub-chunk of 64 entries, pixel): the
+// (C, T) before it, T negative once the pixel has stopped; per (sub-chunk,
+// block) the entries that can reach pixels not stopped before it; per block
+// the number of sub-chunks that some pixel entered.
+//
+// Where the blocks alone would not keep the CUs busy until the longest list is
+// done (list_parts: 50k splats on 200^2 take 58 us in 4 parts, 73 us in one,
+// 200k on 200^2 106 us in 8 and 262 us), a list is walked in parts side by side, each from T = 1,
+// C = 0; a join finds every part's incoming (C, T) per pixel and the part in
+// which the pixel stops, and a restart walks that part's sub-chunk with the
+// stop again from its true state.  The states of such a list are relative to
+// their part.  A part leaves its pixels' T where the later parts of the block
+// look for it once a round (no one waits for it): pixels that the earlier
+// parts finished so far have stopped for certain need no walk any more.  The
+// join decides on its own; what it reads of a part that ended early lies past
+// the stop.
 constexpr float kPastStop = -2.f;
 
 // One front-to-back compositing step for the pixel centre (px, py), written
@@ -802,12 +769,29 @@ __device__ inline float blend_step(const float4& a, const float4& c1, float px, 
   return w;
 }
 
-// The pixels of a tile in the blend passes: wave w covers the 8 x 8 block
-// (w & 1, w >> 1) of the 16 x 16 tile, lane l its pixel (l & 7, l >> 3).
-__device__ inline void tile_pixel(int t, int TX, int& px, int& py) {
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  px = (t % TX) * kTile + 8 * (w & 1) + (l & 7);
-  py = (t / TX) * kTile + 8 * (w >> 1) + (l >> 3);
+// The 8 x 8 block (tile, index in the tile) of a blend workgroup: the four
+// blocks of a tile, which read the same records, follow each other on one XCD
+// (workgroups with equal index mod 8), and neighbouring tiles go to different
+// ones.  The grid is block_grid(tiles) workgroups.
+struct PixelBlock {
+  int t, blk, ox, oy;     // tile, block in the tile, first pixel
+  __device__ inline int id() const { return kBlocks * t + blk; }
+};
+__device__ inline PixelBlock pixel_block(int TX) {
+  PixelBlock b;
+  const int k = blockIdx.x >> 3;
+  b.t = (k >> 2) * 8 + (blockIdx.x & 7);
+  b.blk = k & 3;
+  b.ox = (b.t % TX) * kTile + 8 * (b.blk & 1);
+  b.oy = (b.t / TX) * kTile + 8 * (b.blk >> 1);
+  return b;
+}
+inline int64_t block_grid(int64_t tiles) { return (tiles + 7) / 8 * 8 * kBlocks; }
+
+__device__ inline void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Whether a splat record can give alpha >= 1/255 at any pixel centre of
@@ -830,412 +814,452 @@ __device__ inline bool reaches(const float4& r0, const float4& r1, const float4&
   return inside || !(fmaxf(fmaxf(e0, e1), fmaxf(e2, e3)) < r2.w);
 }
 
-// Staging-time culling: the calling thread holds the record of entry
-// 64 * qw + lane (valid if `ok`) and tests it against the 8 x 8 pixel block
-// of each of the four waves; one ballot per wave gives that wave's mask for
-// this quarter, stored in wmask[wave][qw].  All 64 lanes must be active.
-__device__ inline void cull_entry(const float4& r0, const float4& r1, const float4& r2, bool ok,
-                                  int t, int TX, int qw, uint64_t (*wmask)[kSubs]) {
-  const float bx = (float)((t % TX) * kTile) + 0.5f, by = (float)((t / TX) * kTile) + 0.5f;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float x0 = bx + 8.f * (w & 1), y0 = by + 8.f * (w >> 1);
-    const uint64_t m = __ballot(ok && reaches(r0, r1, r2, x0, x0 + 7.f, y0, y0 + 7.f));
-    if ((threadIdx.x & 63) == 0) wmask[w][qw] = m;
-  }
+// Sub-chunks per part of a list of L entries walked in `parts` parts.
+__device__ inline int part_subs(int L, int parts) {
+  return ((L + kSub - 1) / kSub + parts - 1) / parts;
 }
 
-// The blend's work items from the tile ranges, for the cases the tile sort's
-// scatter does not build them (no splats, or a tile sort of several passes).
-__global__ void __launch_bounds__(1024)
-chunk_index_kernel(int tiles, const int32_t* __restrict__ ranges, uint32_t* __restrict__ item_off,
-                   uint32_t* __restrict__ item_tile, uint32_t* __restrict__ item_chunk,
-                   uint32_t* __restrict__ item_sub, int64_t max_items,
-                   int64_t* __restrict__ counters) {
-  __shared__ uint64_t part[1024];
-  make_work_items<1024>(tiles, [&](int t) { return ranges[2 * t + 1] - ranges[2 * t]; }, item_off,
-                        item_tile, item_chunk, item_sub, max_items, counters, part);
+template <int CTRL>
+__device__ inline float quad(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// sum over the four lanes of a pixel, in each of them
+__device__ inline float quad_sum(float v) {
+  v += quad<0xB1>(v);
+  return v + quad<0x4E>(v);
 }
 
-// One pixel's (C, T code) into a 1024-float state block: C0, C1, C2, code,
-// each 256 floats in pixel order.
-__device__ inline void put_state(float* q, float C0, float C1, float C2, float code) {
-  q[threadIdx.x] = C0;
-  q[256 + threadIdx.x] = C1;
-  q[512 + threadIdx.x] = C2;
-  q[768 + threadIdx.x] = code;
-}
-
-// The blend passes run a grid of as many workgroups as fit on the device at
-// once (the item count lives on the device, so the grid cannot be sized to
-// it without a host sync).  The forward passes take items i, i + grid, ...;
-// the adjoint, whose items vary more in cost and which fits fewer
-// workgroups per CU, takes the next item from a queue with one atomic (no
-// workgroup ever waits for another).  There are kQueues queues, one per
-// group of workgroups with equal index mod kQueues (on this part, those of
-// one XCD), each a 256-byte line of its own: queue x hands out items x,
-// x + kQueues, ..., so the groups share out the items evenly, and the
-// atomics of one line are a kQueues-th of the total (on one counter their
-// round trips took about 12 ns each, one after another: 90 us per launch).
-// The counters are zeroed on the stream before the launch.
-__device__ inline int next_item(uint32_t* queue, int* slot) {
-  __syncthreads();                // every thread is done with the last item
-  if (threadIdx.x == 0) {
-    const int nq = gridDim.x < kQueues ? 1 : kQueues;
-    const int x = (int)blockIdx.x % nq;
-    *slot = x + nq * (int)atomicAdd(queue + 64 * x, 1u);
-  }
-  __syncthreads();
-  return *slot;
-}
-
+template <int P>
 __global__ void __launch_bounds__(256)
-blend_chunk_kernel(int W, int H, int TX, int n, const int32_t* __restrict__ ranges,
-                   const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
-                   const float* __restrict__ color,
-                   const uint32_t* __restrict__ item_tile, const uint32_t* __restrict__ item_chunk,
-                   const int64_t* __restrict__ counters, int64_t max_items,
-                   const uint32_t* __restrict__ item_sub, uint32_t* __restrict__ sub_item,
-                   int64_t max_subs, float* __restrict__ cstate, float* __restrict__ sstate) {
-  __shared__ float4 s0[kChunk], s1[kChunk], s2[kChunk];
-  __shared__ uint64_t wmask[4][kSubs];    // per wave and quarter: entries that can reach its pixels
-  __shared__ uint32_t lists[4][kChunk];   // the same, as a list per wave
-  const int64_t nitems = min(counters[1], max_items);
-  for (int b = blockIdx.x; b < nitems; b += gridDim.x) {
-  __syncthreads();                        // the previous item's records are done
-  const int t = item_tile[b], j = item_chunk[b];
-  int px, py;
-  tile_pixel(t, TX, px, py);
-  const int e0 = ranges[2 * t] + j * kChunk;
-  const int cnt = min(kChunk, ranges[2 * t + 1] - e0);
-  if ((int)threadIdx.x * kSub < cnt) {    // the adjoint's sub-items of this chunk
-    const int64_t u = (int64_t)item_sub[b] + threadIdx.x;
-    if (u < max_subs) sub_item[u] = ((uint32_t)b << 2) | threadIdx.x;
-  }
-  {
-    const bool ok = (int)threadIdx.x < cnt;
-    float4 r0 = {}, r1 = {}, r2 = {};
-    if (ok) {
-      const SplatRec R = load_rec(rec, color, n, sorted[e0 + threadIdx.x]);
-      r0 = R.r0;
-      r1 = R.r1;
-      r2 = R.r2;
-      s0[threadIdx.x] = r0;
-      s1[threadIdx.x] = r1;
-      s2[threadIdx.x] = r2;
-    }
-    cull_entry(r0, r1, r2, ok, t, TX, threadIdx.x >> 6, wmask);
-  }
-  __syncthreads();
-  const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
-  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
-  bool sat = !(px < W && py < H);
-  const bool outside = sat;
-  float* sub = sstate + (size_t)b * (kSubs - 1) * 1024;
-  // this wave's entries as a list (quarter after quarter), nq[q] per quarter
-  uint32_t* lst = lists[threadIdx.x >> 6];
-  int nq[kSubs];
-  {
-    const int lane = threadIdx.x & 63;
-    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    int base = 0;
-#pragma unroll
-    for (int q = 0; q < kSubs; ++q) {
-      const uint64_t m = wmask[threadIdx.x >> 6][q];
-      if ((m >> lane) & 1ull) lst[base + __popcll(m & below)] = (uint32_t)(q * kSub + lane);
-      nq[q] = __popcll(m);
-      base += nq[q];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave reads what its lanes wrote
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  bool live = true;                       // some pixel of this wave not saturated
-  int pos = 0;
-#pragma unroll
-  for (int q = 0; q < kSubs; ++q) {
-    if (q * kSub >= cnt) break;
-    if (q > 0) put_state(sub + (q - 1) * 1024, C0, C1, C2, sat ? -T : T);
-    if (live && __ballot(!sat) == 0ull) live = false;
-    const int end = live ? pos + nq[q] : pos;
-#pragma unroll 4
-    for (int i = pos; i < end; ++i) {
-      const int k = (int)lst[i];
-      const float4 a = s0[k], c1 = s1[k];
-      bool applied;
-      float alpha, dx, dy, G, araw;
-      const float w = blend_step(a, c1, fpx, fpy, T, sat, applied, alpha, dx, dy, G, araw);
-      C0 = fmaf(c1.z, w, C0);
-      C1 = fmaf(c1.w, w, C1);
-      C2 = fmaf(s2[k].x, w, C2);
-    }
-    pos += nq[q];
-  }
-  sat = sat && !outside;
-  put_state(cstate + (size_t)b * 1024, C0, C1, C2, sat ? -T : T);   // T >= 1e-4 > 0 at a stop
-  }
-}
-
-// Prefix pass, one workgroup per tile, no splat is touched: per pixel, walk
-// the tile's chunk results front to back, leave for every chunk the colour
-// before it and its incoming transmittance, find the chunk that may contain
-// the stop (saturated, or T_in * T_chunk < 1e-4) and mark it; chunks past it
-// are marked past the stop.  Pixels that never stop get their final colour
-// here, and so do pixels that stop in the tile's first chunk: that chunk
-// was walked from the true incoming T = 1, so its result is already exact.
-// The chunk pass leaves T (>= 0) or, where it stopped, -(T at the stop).
-// The state codes it leaves are those described above.
-__global__ void __launch_bounds__(256)
-blend_prefix_kernel(int W, int H, int TX, const uint32_t* __restrict__ item_off,
-                    float* __restrict__ cstate, int64_t max_items, float* __restrict__ image,
-                    float* __restrict__ Tfinal, const int64_t* __restrict__ counters,
-                    int64_t capacity) {
-  const int t = blockIdx.x;
-  int px, py;
-  tile_pixel(t, TX, px, py);
+blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__ ranges,
+             const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
+             const float* __restrict__ color, const int64_t* __restrict__ counters,
+             int64_t capacity, float* __restrict__ state, uint64_t* __restrict__ mask,
+             uint32_t* __restrict__ nlive, float4* __restrict__ part, uint32_t* part_t,
+             float* __restrict__ image, float* __restrict__ Tfinal) {
+  constexpr int kRound = 4 * kSub;        // entries per round
+  // the staged records of two rounds, each with an entry past them with
+  // opacity 0 that fills up a step of four
+  __shared__ float4 s0[2][kRound + 1], s1[2][kRound + 1];
+  __shared__ float s2[2][kRound + 1];
+  __shared__ uint64_t reach[2][4][4];     // [round][sub-block][sub-chunk]
+  __shared__ uint64_t used[2][4][4];      // the same, of sub-blocks not stopped yet
+  // a wave's entries, each sub-chunk's padded to eights; per eight the two of
+  // lane e (the e-th of either four) follow each other
+  __shared__ uint16_t lists[4][kRound];
+  __shared__ int open[2][4];              // sub-chunks entered in the round, per wave; 0: stopped
+  const PixelBlock B = pixel_block(TX);
+  if (B.t >= tiles) return;
+  const int lane = threadIdx.x & 63, e = lane & 3;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // this lane's pixel in the block, wave w having the sub-block (w & 1, w >> 1)
+  const int bx = 4 * (wave & 1) + ((lane >> 2) & 3), by = 4 * (wave >> 1) + (lane >> 4);
+  const int px = B.ox + bx, py = B.oy + by;
   const bool inside = px < W && py < H;
-  const int64_t i0 = min((int64_t)item_off[t], max_items);
-  const int nch = (int)(min((int64_t)item_off[t + 1], max_items) - i0);
-  float Tin = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
-  bool active = inside;
-  for (int j = 0; j < nch; ++j) {
-    float* st = cstate + (size_t)(i0 + j) * 1024;
-    const float Cj0 = st[threadIdx.x], Cj1 = st[256 + threadIdx.x], Cj2 = st[512 + threadIdx.x];
-    const float Tj = st[768 + threadIdx.x];
-    st[threadIdx.x] = C0;
-    st[256 + threadIdx.x] = C1;
-    st[512 + threadIdx.x] = C2;
-    if (!active) {
-      st[768 + threadIdx.x] = kPastStop;
-      continue;
-    }
-    if (Tj < 0.f || Tin * Tj < 1e-4f) {
-      st[768 + threadIdx.x] = -Tin;
-      active = false;
-      if (j == 0 && Tj < 0.f && inside) {   // exact already; else the restart pass
-        const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
-        image[p] = Cj0;
-        image[HW + p] = Cj1;
-        image[2 * HW + p] = Cj2;
-        Tfinal[p] = -Tj;
-      }
-      continue;
-    }
-    st[768 + threadIdx.x] = Tin;
-    C0 = fmaf(Tin, Cj0, C0);
-    C1 = fmaf(Tin, Cj1, C1);
-    C2 = fmaf(Tin, Cj2, C2);
-    Tin *= Tj;
-  }
-  if (inside && active) {
+  const size_t pi = (size_t)B.id() * P + blockIdx.y;
+  // lane e < 3 of a pixel writes channel e, lane 3 the transmittance
+  auto put_pixel = [&](float c0, float c1, float c2, float T) {
     const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
-    image[p] = C0;
-    image[HW + p] = C1;
-    image[2 * HW + p] = C2;
-    Tfinal[p] = Tin;
-  }
+    const float v = e == 0 ? c0 : (e == 1 ? c1 : (e == 2 ? c2 : T));
+    if (inside) (e == 3 ? Tfinal : image + e * HW)[p] = v;
+  };
   // more duplicates than the workspace holds: the lists were truncated, so
   // the frame is poisoned (NaN) rather than silently wrong
-  if (inside && counters[0] > capacity) {
-    const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
+  if (counters[0] > capacity) {
     const float nan = __builtin_nanf("");
-    image[p] = nan;
-    image[HW + p] = nan;
-    image[2 * HW + p] = nan;
-    Tfinal[p] = nan;
+    if (blockIdx.y == 0) put_pixel(nan, nan, nan, nan);
+    if (threadIdx.x == 0) nlive[pi] = 0u;
+    return;
   }
-}
-
-// Restart pass, one workgroup per work item after a tile's first, in
-// parallel: pixels whose walk stops in this chunk re-walk it from T_in with
-// the exact stop rule, starting at the sub-chunk that may hold the stop, and
-// write their final colour and transmittance.  (A pixel whose stop test
-// does not fire here because of rounding keeps the chunk's end state.)
-__global__ void __launch_bounds__(256)
-blend_restart_kernel(int W, int H, int TX, int n, const int32_t* __restrict__ ranges,
-                     const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
-                     const float* __restrict__ color,
-                     const uint32_t* __restrict__ item_tile, const uint32_t* __restrict__ item_chunk,
-                     const int64_t* __restrict__ counters, int64_t max_items,
-                     const float* __restrict__ cstate, float* __restrict__ sstate,
-                     float* __restrict__ image, float* __restrict__ Tfinal, int64_t capacity) {
-  __shared__ float4 s0[kChunk], s1[kChunk], s2[kChunk];
-  if (counters[0] > capacity) return;     // truncated lists: the prefix pass poisoned the frame
-  const int64_t nitems = min(counters[1], max_items);
-  for (int b = blockIdx.x; b < nitems; b += gridDim.x) {
-  __syncthreads();                        // the previous item's records are done
-  const int j = item_chunk[b], t = item_tile[b];
-  const float* st = cstate + (size_t)b * 1024;
-  const float code = st[768 + threadIdx.x];
-  if (j == 0) continue;                    // finished by the prefix pass
-  const bool mine = code < 0.f && code >= -1.f;
-  if (!__syncthreads_or(mine)) continue;
-  int px, py;
-  tile_pixel(t, TX, px, py);
-  const int e0 = ranges[2 * t] + j * kChunk;
-  const int cnt = min(kChunk, ranges[2 * t + 1] - e0);
-  // This pixel's colour before the chunk and its states at the sub-chunk
-  // boundaries, read while the records are staged.
-  float* sub = sstate + (size_t)b * (kSubs - 1) * 1024;
-  float B0 = 0.f, B1 = 0.f, B2 = 0.f, bq[kSubs - 1][4];
-  if (mine) {
-    B0 = st[threadIdx.x];
-    B1 = st[256 + threadIdx.x];
-    B2 = st[512 + threadIdx.x];
-#pragma unroll
-    for (int q = 0; q < kSubs - 1; ++q)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) bq[q][c] = sub[q * 1024 + c * 256 + threadIdx.x];
-  }
-  if ((int)threadIdx.x < cnt) {
-    const SplatRec R = load_rec(rec, color, n, sorted[e0 + threadIdx.x]);
-    s0[threadIdx.x] = R.r0;
-    s1[threadIdx.x] = R.r1;
-    s2[threadIdx.x] = R.r2;
-  }
-  __syncthreads();
-  if (!mine || !(px < W && py < H)) continue;
+  const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
+  const int slot0 = start / kSub + B.t;
+  const int per = kSub * part_subs(L, P);
+  const int a0 = min(L, per * (int)blockIdx.y), a1 = min(L, a0 + per);
   const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
-  const float Tin = -code;
-  float T = Tin, C0 = B0, C1 = B1, C2 = B2;
-  bool stopped = false;
-  // Skip the sub-chunks that cannot hold the stop (chunk pass not
-  // saturated there and T_in * T_local >= 1e-4; T is monotone): start from
-  // the product state at the last such boundary, and leave the absolute
-  // states for the adjoint.
-  int m = 1;                              // next sub-chunk boundary to record
-  bool skip = true;
+  if (threadIdx.x < 2) {
+    s0[threadIdx.x][kRound] = make_float4(0.f, 0.f, 0.f, 0.f);
+    s1[threadIdx.x][kRound] = make_float4(0.f, 0.f, 0.f, 0.f);
+    s2[threadIdx.x][kRound] = 0.f;
+  }
+  float T = inside ? 1.f : 0.f;           // the pixel is live while T >= 1e-4
+  // this lane's entries only: their colour, T after the last that counted
+  float Tl = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+  int nl = 0;
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  // this wave's entry of the round and of the next one, read ahead
+  const int mine = a0 + kSub * wave + lane;
+  SplatRec R = {};
+  uint32_t gnext = 0u;
+  if (mine < a1) R = load_rec(rec, color, n, sorted[start + mine]);
+  if (mine + kRound < a1) gnext = sorted[start + mine + kRound];
+  // the masks of a finished round (all waves are past it) for the adjoint
+  auto finish = [&](int r, int c0) {
+    if (threadIdx.x < 4 && (int)threadIdx.x < (a1 - c0 + kSub - 1) / kSub)
+      mask[(size_t)(slot0 + c0 / kSub + threadIdx.x) * kBlocks + B.blk] =
+          (used[r][0][threadIdx.x] | used[r][1][threadIdx.x]) |
+          (used[r][2][threadIdx.x] | used[r][3][threadIdx.x]);
+    int m = 0;
 #pragma unroll
-  for (int q = 1; q < kSubs; ++q) {
-    skip = skip && q * kSub < cnt && !(bq[q - 1][3] < 0.f || Tin * bq[q - 1][3] < 1e-4f);
-    if (skip) {
-      T = Tin * bq[q - 1][3];
-      C0 = fmaf(Tin, bq[q - 1][0], B0);
-      C1 = fmaf(Tin, bq[q - 1][1], B1);
-      C2 = fmaf(Tin, bq[q - 1][2], B2);
-      put_state(sub + (q - 1) * 1024, C0, C1, C2, T);
-      m = q + 1;
+    for (int w = 0; w < 4; ++w) m = max(m, open[r][w] >> 1);
+    if (m) nl = (c0 - a0) / kSub + m;
+    return ((open[r][0] | open[r][1]) | (open[r][2] | open[r][3])) & 1;   // some wave goes on
+  };
+  // the T of the block's earlier parts at this pixel, as far as they are
+  // finished, looked up a round ahead
+  uint32_t seen[P > 1 ? P - 1 : 1];
+  auto look = [&]() {
+    if constexpr (P > 1) {
+#pragma unroll
+      for (int y = 0; y < P - 1; ++y)
+        if (y < (int)blockIdx.y)
+          seen[y] = __hip_atomic_load(part_t + ((size_t)B.id() * P + y) * 64 + 8 * by + bx,
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-  }
-  for (int k0 = (m - 1) * kSub; k0 < cnt && !stopped; k0 += 32) {
-    if (k0 == m * kSub) put_state(sub + (m++ - 1) * 1024, C0, C1, C2, T);
-    const int k1 = min(cnt, k0 + 32);
-    for (int k = k0; k < k1; ++k) {
-      const float4 a = s0[k], c1 = s1[k];
-      bool applied;
-      float alpha, dx, dy, G, araw;
-      const float w = blend_step(a, c1, fpx, fpy, T, stopped, applied, alpha, dx, dy, G, araw);
-      C0 = fmaf(c1.z, w, C0);
-      C1 = fmaf(c1.w, w, C1);
-      C2 = fmaf(s2[k].x, w, C2);
+  };
+  look();
+  int par = 0, c0 = a0;
+  for (; c0 < a1; c0 += kRound, par ^= 1) {
+    if constexpr (P > 1) {
+      float before = 1.f;
+#pragma unroll
+      for (int y = 0; y < P - 1; ++y)
+        if (y < (int)blockIdx.y && seen[y] != kNoPart) before *= __uint_as_float(seen[y]);
+      // (a margin for the order of the product)
+      if (before * T < 0.9e-4f) T = 0.f;
+      look();
     }
-  }
-  for (; m < kSubs && m * kSub < cnt; ++m) put_state(sub + (m - 1) * 1024, C0, C1, C2, stopped ? -T : T);
-  const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
-  image[p] = C0;
-  image[HW + p] = C1;
-  image[2 * HW + p] = C2;
-  Tfinal[p] = T;
-  }
-}
-
-// ---- adjoint: blend ----------------------------------------------------------
-// Per work item (chunk, sub-chunk of kSub entries) and pixel, starting from
-// the sub-chunk's incoming state (the chunk's T_in and colour before it for
-// the first sub-chunk; for later ones T_in * T_local and C_before +
-// T_in * C_local inside a whole chunk, the restart's exact state inside the
-// stop chunk), the entries are re-walked front to back with the same
-// decisions:
-//   dL/dc_i     = alpha_i T_i g
-//   dL/dalpha_i = sum_c g_c (c_ic T_i - (C_c - C_<=i,c) / (1 - alpha_i))
-// with C the forward colour, then alpha = o exp(power) (unless clamped).
-// Per-splat sums over the tile's pixels: the partials of eight entries that
-// touch a wave's pixels are summed over the wave together (lane swaps and
-// DPP) and stored into the wave's LDS slice; after the sub-chunk the four
-// slices are added and each splat gets one set of global atomics per item.
-__global__ void __launch_bounds__(256)
-blend_bwd_kernel(int W, int H, int TX, int n, const int32_t* __restrict__ ranges,
-                 const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
-                 const float* __restrict__ color,
-                 const uint32_t* __restrict__ item_tile, const uint32_t* __restrict__ item_chunk,
-                 const uint32_t* __restrict__ sub_item, const int64_t* __restrict__ counters,
-                 int64_t max_items, int64_t max_subs, uint32_t* __restrict__ queue,
-                 const float* __restrict__ cstate, const float* __restrict__ sstate,
-                 const float* __restrict__ image, const float* __restrict__ dimage,
-                 float* __restrict__ gmean_conic /*[5][n]*/, float* __restrict__ dopac,
-                 float* __restrict__ dcolor) {
-  __shared__ float4 s0[kSub], s1[kSub], s2[kSub];
-  __shared__ uint32_t sg[kSub];
-  __shared__ float acc[4][9][kSub];       // per wave: entry sums over its 64 pixels
-  __shared__ int slot;
-  const int64_t nitems = min(counters[1], max_items);
-  const int64_t nsubs = min(counters[3], max_subs);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, myslot = lane >> 3;
-  for (;;) {
-  const int u = next_item(queue, &slot);
-  if (u >= nsubs) break;
-  const uint32_t su = sub_item[u];
-  const int b = (int)(su >> 2), m = (int)(su & 3u);
-  if (b >= nitems) continue;
-  const int t = item_tile[b], j = item_chunk[b];
-  int px, py;
-  tile_pixel(t, TX, px, py);
-  const bool inside = px < W && py < H;
-  const int e0 = ranges[2 * t] + j * kChunk + m * kSub;
-  const int cnt = min(kSub, ranges[2 * t + 1] - e0);
-  // Every wave reads the sub-chunk's records (lane = entry) and keeps a mask
-  // of the entries that can reach its 8 x 8 block; wave 0 stages them.
-  uint64_t mm;
-  {
-    const bool ok = lane < cnt;
-    float4 r0 = {}, r1 = {}, r2 = {};
-    if (ok) {
-      const uint32_t g = sorted[e0 + lane];
-      r0 = rec[3 * g];
-      r1 = rec[3 * g + 1];
-      r2 = rec[3 * g + 2];
-      if (wave == 0) {
-        float4 c1 = r1, c2 = r2;
-        c1.z = color[g];
-        c1.w = color[(size_t)n + g];
-        c2.x = color[2 * (size_t)n + g];
-        s0[lane] = r0;
-        s1[lane] = c1;
-        s2[lane] = c2;
-        sg[lane] = g;
+    {
+      const bool ok = c0 - a0 + mine < a1;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float x0 = (float)(B.ox + 4 * (w & 1)) + 0.5f, y0 = (float)(B.oy + 4 * (w >> 1)) + 0.5f;
+        const uint64_t m = __ballot(ok && reaches(R.r0, R.r1, R.r2, x0, x0 + 3.f, y0, y0 + 3.f));
+        if (lane == 0) reach[par][w][wave] = m;
+      }
+      if (ok) {
+        s0[par][kSub * wave + lane] = R.r0;
+        s1[par][kSub * wave + lane] = R.r1;
+        s2[par][kSub * wave + lane] = R.r2.x;
+      }
+      if (c0 - a0 + kRound + mine < a1) R = load_rec(rec, color, n, gnext);
+      if (c0 - a0 + 2 * kRound + mine < a1) gnext = sorted[start + c0 - a0 + 2 * kRound + mine];
+    }
+    __syncthreads();
+    // every wave is done with the round before this one: its masks go out,
+    // and if all its waves had stopped, so does the workgroup
+    if (c0 > a0 && !finish(par ^ 1, c0 - kRound)) break;
+    const int nq = min(4, (a1 - c0 + kSub - 1) / kSub);
+    // this wave's entries as a list
+    uint16_t* lst = lists[wave];
+    int pairq[5];                         // first pair of steps of each sub-chunk
+    pairq[0] = 0;
+    auto place = [](int i) { return (i & ~7) | ((i & 3) << 1) | ((i >> 2) & 1); };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t m = reach[par][wave][q];
+      const int cnt = __popcll(m), at = 8 * pairq[q];
+      if ((m >> lane) & 1ull) lst[place(at + __popcll(m & below))] = (uint16_t)(q * kSub + lane);
+      if (lane < ((8 - cnt) & 7)) lst[place(at + cnt + lane)] = (uint16_t)kRound;
+      pairq[q + 1] = __builtin_amdgcn_readfirstlane(pairq[q] + (cnt + 7) / 8);
+    }
+    wave_fence();
+    const uint32_t* pairs = reinterpret_cast<const uint32_t*>(lst) + e;
+    auto take = [&](uint32_t k, float4 (&a)[2], float4 (&c1)[2], float (&c2)[2]) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t ku = u ? k >> 16 : k & 0xFFFFu;
+        a[u] = s0[par][ku];
+        c1[u] = s1[par][ku];
+        c2[u] = s2[par][ku];
+      }
+    };
+    int entered = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q >= nq) break;
+      const bool live = __ballot(T >= 1e-4f) != 0ull;
+      if (lane == 0) used[par][wave][q] = live ? reach[par][wave][q] : 0ull;
+      {
+        // the state before the sub-chunk
+        const float c0s = quad_sum(C0), c1s = quad_sum(C1), c2s = quad_sum(C2);
+        float* st = state + (size_t)(slot0 + c0 / kSub + q) * 1024 + 64 * B.blk + 8 * by + bx;
+        const float v = e == 0 ? c0s : (e == 1 ? c1s : (e == 2 ? c2s : (T >= 1e-4f ? T : kPastStop)));
+        st[256 * e] = v;
+      }
+      if (!live) continue;
+      entered = q + 1;
+      const int i1 = pairq[q + 1];
+      if (pairq[q] == i1) continue;
+      float4 a[2], c1[2];
+      float c2[2];
+      take(pairs[4 * pairq[q]], a, c1, c2);
+      uint32_t kn = pairs[4 * min(pairq[q] + 1, i1 - 1)];
+      for (int i = pairq[q]; i < i1; ++i) {
+        // the next pair's entries are read while this one is composited
+        float4 an[2], c1n[2];
+        float c2n[2];
+        take(kn, an, c1n, c2n);
+        kn = pairs[4 * min(i + 2, i1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float dx = a[u].x - fpx, dy = a[u].y - fpy;
+          const float e2 = fmaf(a[u].z * dx, dx, fmaf(c1[u].x * dy, dy, (a[u].w * dx) * dy));
+          const float alpha = fminf(0.99f, c1[u].y * __builtin_amdgcn_exp2f(e2));
+          const bool use = e2 <= 0.f && alpha >= 1.f / 255.f;
+          // product of 1 - alpha over the entries up to this lane's, and
+          // before it (quad_perm [0, 0, 1, 2], then [0, 1, 0, 1])
+          float m = use ? 1.f - alpha : 1.f;
+          const float m1 = m * quad<0x90>(m);
+          m = e >= 1 ? m1 : m;
+          const float m2 = m * quad<0x44>(m);
+          m = e >= 2 ? m2 : m;
+          const float ml = quad<0x90>(m);
+          const float after = T * m, before = T * (e >= 1 ? ml : 1.f);
+          const bool on = use && after >= 1e-4f;
+          const float w = on ? alpha * before : 0.f;
+          C0 = fmaf(c1[u].z, w, C0);
+          C1 = fmaf(c1[u].w, w, C1);
+          C2 = fmaf(c2[u], w, C2);
+          Tl = on ? after : Tl;
+          T = quad<0xFF>(after);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          a[u] = an[u];
+          c1[u] = c1n[u];
+          c2[u] = c2n[u];
+        }
+        if (__ballot(T >= 1e-4f) == 0ull) break;
       }
     }
-    const float x0 = (float)((t % TX) * kTile + 8 * (wave & 1)) + 0.5f;
-    const float y0 = (float)((t / TX) * kTile + 8 * (wave >> 1)) + 0.5f;
-    mm = __ballot(ok && reaches(r0, r1, r2, x0, x0 + 7.f, y0, y0 + 7.f));
+    const int on = __ballot(T >= 1e-4f) != 0ull ? 1 : 0;
+    if (lane == 0) open[par][wave] = 2 * entered + on;
   }
+  if (c0 >= a1 && a1 > a0) {              // the list ended: its last round's masks
+    __syncthreads();
+    finish(par ^ 1, c0 - kRound);
+  }
+  C0 = quad_sum(C0);
+  C1 = quad_sum(C1);
+  C2 = quad_sum(C2);
+  Tl = fminf(Tl, quad<0xB1>(Tl));
+  Tl = fminf(Tl, quad<0x4E>(Tl));
+  if constexpr (P > 1) {
+    if (e == 0) {
+      const bool whole = T >= 1e-4f || !inside;
+      part[pi * 64 + 8 * by + bx] = make_float4(C0, C1, C2, whole ? T : -Tl);
+      __hip_atomic_store(part_t + pi * 64 + 8 * by + bx, __float_as_uint(whole ? T : 0.f),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  } else {
+    put_pixel(C0, C1, C2, Tl);
+  }
+  if (threadIdx.x == 0) nlive[pi] = (uint32_t)nl;
+}
+
+// Join of a list's parts (one thread per pixel): each part's (C, T) becomes
+// the (C, T) before it, with the code of T_in that only flips signs: T_in for
+// a whole part, -T_in for the part where the pixel stops (its own walk
+// stopped, or T_in T < 1e-4), kPastStop past it.  Pixels that stop in the
+// first part, walked from the true T = 1, and pixels that never stop are
+// written here.
+template <int P>
+__global__ void __launch_bounds__(256)
+blend_join_kernel(int W, int H, int TX, float4* __restrict__ part,
+                  const int64_t* __restrict__ counters, int64_t capacity,
+                  float* __restrict__ image, float* __restrict__ Tfinal) {
+  if (counters[0] > capacity) return;     // poisoned
+  const int t = blockIdx.x, blk = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int px = (t % TX) * kTile + 8 * (blk & 1) + (lane & 7);
+  const int py = (t / TX) * kTile + 8 * (blk >> 1) + (lane >> 3);
+  const bool inside = px < W && py < H;
+  float4* p = part + (size_t)(kBlocks * t + blk) * P * 64 + lane;
+  float4 r[P];
 #pragma unroll
-  for (int q = 0; q < 9; ++q) (&acc[0][0][0])[q * 256 + threadIdx.x] = 0.f;
-  const float* st = cstate + (size_t)b * 1024;
-  const float code = st[768 + threadIdx.x];
-  bool done = !inside || code < -1.f;
-  float T = fabsf(code);
-  float A0 = st[threadIdx.x], A1 = st[256 + threadIdx.x], A2 = st[512 + threadIdx.x];
-  if (m > 0 && !done) {
-    const float* q = sstate + ((size_t)b * (kSubs - 1) + (m - 1)) * 1024;
-    const float Tr = q[768 + threadIdx.x];
-    const float R0 = q[threadIdx.x], R1 = q[256 + threadIdx.x], R2 = q[512 + threadIdx.x];
-    if (code >= 0.f) {                    // whole chunk: local state from the chunk start
-      A0 = fmaf(code, R0, A0);
-      A1 = fmaf(code, R1, A1);
-      A2 = fmaf(code, R2, A2);
-      T = code * Tr;
-    } else {                              // stop chunk: the exact walk's state
-      done = Tr < 0.f;
-      T = Tr;
-      A0 = R0;
-      A1 = R1;
-      A2 = R2;
+  for (int y = 0; y < P; ++y) r[y] = p[64 * y];
+  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Tout = 1.f;
+  bool active = inside, done = false;
+#pragma unroll
+  for (int y = 0; y < P; ++y) {
+    const bool stop = active && (r[y].w < 0.f || T * r[y].w < 1e-4f);
+    p[64 * y] = make_float4(C0, C1, C2, active ? (stop ? -T : T) : kPastStop);
+    if (stop) {
+      active = false;
+      if (y == 0) {
+        C0 = r[0].x;
+        C1 = r[0].y;
+        C2 = r[0].z;
+        Tout = -r[0].w;
+        done = true;
+      }
+    }
+    if (active) {
+      C0 = fmaf(T, r[y].x, C0);
+      C1 = fmaf(T, r[y].y, C1);
+      C2 = fmaf(T, r[y].z, C2);
+      T *= r[y].w;
     }
   }
+  if (inside && (active || done)) {
+    const size_t q = (size_t)py * W + px, HW = (size_t)H * W;
+    image[q] = C0;
+    image[HW + q] = C1;
+    image[2 * HW + q] = C2;
+    Tfinal[q] = active ? T : Tout;
+  }
+}
+
+// Restart (kSplitsPart workgroups per block and part after the first, their
+// waves over the part's sub-chunks; lane = pixel): the pixels whose walk stops in a
+// sub-chunk -- T_in T >= 1e-4 before it, not after it -- walk it from that
+// state with the exact stop rule and are written.  (A pixel whose stop test
+// does not fire there because of rounding ends with the sub-chunk.)
+__global__ void __launch_bounds__(256)
+blend_restart_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__ ranges,
+                     const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
+                     const float* __restrict__ color, const float* __restrict__ state,
+                     const uint64_t* __restrict__ mask, const uint32_t* __restrict__ nlive,
+                     const float4* __restrict__ part, float* __restrict__ image,
+                     float* __restrict__ Tfinal) {
+  // the staged records, and one past them with opacity 0
+  __shared__ float4 s0[4][kSub + 1], s1[4][kSub + 1];
+  __shared__ float s2[4][kSub + 1];
+  const PixelBlock B = pixel_block(TX);
+  if (B.t >= tiles || blockIdx.y == 0) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t pi = (size_t)B.id() * gridDim.y + blockIdx.y;
+  const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
+  const int slot0 = start / kSub + B.t;
+  const int per = part_subs(L, gridDim.y), m0 = per * blockIdx.y;
+  const int nl = min((int)nlive[pi], per);   // 0 in a poisoned frame
+  const int j0 = wave + 4 * blockIdx.z;
+  if (j0 >= nl) return;
+  const float4 base = part[pi * 64 + lane];
+  const bool mine = base.w < 0.f && base.w >= -1.f;
+  if (__ballot(mine) == 0ull) return;
+  const float Tin = -base.w;
+  const int px = B.ox + (lane & 7), py = B.oy + (lane >> 3);
+  const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
+  if (lane == 0) {
+    s0[wave][kSub] = make_float4(0.f, 0.f, 0.f, 0.f);
+    s1[wave][kSub] = make_float4(0.f, 0.f, 0.f, 0.f);
+    s2[wave][kSub] = 0.f;
+  }
+  for (int j = j0; j < nl; j += 4 * gridDim.z) {
+    const size_t slot = (size_t)slot0 + m0 + j;
+    const float* st = state + slot * 1024 + 64 * B.blk + lane;
+    float T = Tin * st[768];
+    const float Tn = j + 1 < nl ? Tin * st[1024 + 768] : -1.f;
+    const bool here = mine && T >= 1e-4f && !(Tn >= 1e-4f);
+    if (__ballot(here) == 0ull) continue;
+    uint64_t mm = mask[slot * kBlocks + B.blk];
+    mm = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(mm >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)mm);
+    const int en = (m0 + j) * kSub + lane;
+    if (((mm >> lane) & 1ull) && en < L) {
+      const SplatRec R = load_rec(rec, color, n, sorted[start + en]);
+      s0[wave][lane] = R.r0;
+      s1[wave][lane] = R.r1;
+      s2[wave][lane] = R.r2.x;
+    }
+    float C0 = fmaf(Tin, st[0], base.x), C1 = fmaf(Tin, st[256], base.y),
+          C2 = fmaf(Tin, st[512], base.z);
+    wave_fence();
+    bool stopped = !here;
+    while (mm && __ballot(!stopped) != 0ull) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = mm ? (int)__builtin_ctzll(mm) : kSub;
+        mm &= mm - 1;
+        bool applied;
+        float alpha, dx, dy, G, araw;
+        const float4 c1 = s1[wave][k];
+        const float w = blend_step(s0[wave][k], c1, fpx, fpy, T, stopped, applied, alpha, dx, dy, G, araw);
+        C0 = fmaf(c1.z, w, C0);
+        C1 = fmaf(c1.w, w, C1);
+        C2 = fmaf(s2[wave][k], w, C2);
+      }
+    }
+    if (here) {
+      const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
+      image[p] = C0;
+      image[HW + p] = C1;
+      image[2 * HW + p] = C2;
+      Tfinal[p] = T;
+    }
+    wave_fence();   // the next sub-chunk's records replace these
+  }
+}
+
+// Workgroups per block of the adjoint (a block's sub-chunks are dealt out to
+// them four at a time), so that a long list does not keep one of them alone;
+// with many blocks fewer do, since every further workgroup of a short list
+// is started for nothing.
+inline int splits(int64_t tiles) { return tiles >= 4096 ? 2 : 4; }
+constexpr int kSplitsPart = 2;           // the same, per part of a list walked in parts
+
+// ---- adjoint: blend ----------------------------------------------------------
+// One workgroup per 8 x 8 pixel block again; its waves take the sub-chunks
+// that the forward entered, wave by wave, each from the recorded state, and
+// re-walk the entries that contributed front to back with the same decisions:
+//   dL/dc_i     = alpha_i T_i g
+//   dL/dalpha_i = T_i g.c_i - Q_i / (1 - alpha_i),  Q_i = g.(C - C_<=i)
+// with C the forward colour, then alpha = o exp(power) (unless clamped).
+// A wave takes eight entries at a time.  The exponent is quadratic in the
+// offset (dx, dy), dx depends on the pixel's column and dy on its row, so
+// only s = dL/dpower, s dy, s dy^2 and the three colour terms are summed
+// over the pixels' rows (eight entries together, ending with entry l / 8 and
+// column l % 8 in lane l); the terms in dx are formed per column and nine
+// values are summed over the columns.  Each entry's nine sums go to its
+// splat's line of the sums in one 32-byte atomic request and one single add
+// (as nine planes they were 64 scattered lines per request).
+//
+// Bound by vector issue (about 500 slots per eight entries): 67 us at 100k /
+// 512^2 and 205 us at 300k / 1080^2, where one item queue over the sub-chunks
+// of whole lists, most of them past the stop, took 88 and 390 us.  No
+// workgroup waits for another and the waves share nothing; the next
+// sub-chunk's loads are issued before the current one is walked.
+__global__ void __launch_bounds__(256)
+blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__ ranges,
+                 const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
+                 const float* __restrict__ color, const float* __restrict__ state,
+                 const uint64_t* __restrict__ mask, const uint32_t* __restrict__ nlive,
+                 const float4* __restrict__ part, const float* __restrict__ image,
+                 const float* __restrict__ dimage, float* __restrict__ grad) {
+  __shared__ float4 s0[4][kSub], s1[4][kSub];
+  __shared__ float s2[4][kSub];
+  __shared__ uint32_t sg[4][kSub];
+  const PixelBlock B = pixel_block(TX);
+  if (B.t >= tiles) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int myslot = lane >> 3, col = lane & 7;
+  const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
+  const int slot0 = start / kSub + B.t;
+  // the sub-chunks of this workgroup: every gridDim.y-th four of the list's,
+  // or, of a list walked in parts, every gridDim.z-th four of part blockIdx.y's
+  int first, end, step;
+  float4 base = make_float4(0.f, 0.f, 0.f, 1.f);
+  if (part) {
+    const int per = part_subs(L, gridDim.y);
+    const size_t pi = (size_t)B.id() * gridDim.y + blockIdx.y;
+    first = per * blockIdx.y + wave + 4 * blockIdx.z;
+    end = per * blockIdx.y + min((int)nlive[pi], per);
+    step = 4 * gridDim.z;
+    base = part[pi * 64 + lane];
+  } else {
+    first = wave + 4 * blockIdx.y;
+    end = nlive[B.id()];
+    step = 4 * gridDim.y;
+  }
+  end = min(end, (L + kSub - 1) / kSub);
+  if (first >= end) return;
+  const int px = B.ox + (lane & 7), py = B.oy + (lane >> 3);
   const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
   float Cf0 = 0.f, Cf1 = 0.f, Cf2 = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
-  if (!done) {
+  if (px < W && py < H) {
     const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
     Cf0 = image[p];
     Cf1 = image[HW + p];
@@ -1244,78 +1268,108 @@ blend_bwd_kernel(int W, int H, int TX, int n, const int32_t* __restrict__ ranges
     g1 = dimage[HW + p];
     g2 = dimage[2 * HW + p];
   }
-  __syncthreads();
-  // The listed entries, eight at a time and without branching on whether
-  // any pixel uses them, fill eight slots of partials, which are then summed
-  // over the wave in one go (slot s ends in lanes 8s .. 8s+7) and stored
-  // into this wave's LDS slice.
-  while (mm && __ballot(!done) != 0ull) {
-    float v[8][9];
-    int kv = 0;                             // entry of this lane's slot
-    int ns = 0;                             // slots filled
+  const float Tin = fabsf(base.w);
+  // a sub-chunk's loads (entry indices, then the masks, records and states)
+  // are issued while the one before is walked
+  auto index = [&](int sub) {
+    const int e = sub * kSub + lane;
+    return sub < end && e < L ? sorted[start + e] : 0u;
+  };
+  struct Item {
+    uint64_t mm;
+    uint32_t g;
+    SplatRec R;
+    float C0, C1, C2, T;
+  };
+  auto fetch = [&](int sub, uint32_t g) {
+    Item I = {};
+    if (sub < end) {
+      I.mm = mask[(size_t)(slot0 + sub) * kBlocks + B.blk];
+      I.g = g;
+      I.R = load_rec(rec, color, n, g);
+      const float* st = state + (size_t)(slot0 + sub) * 1024 + 64 * B.blk + lane;
+      I.C0 = st[0];
+      I.C1 = st[256];
+      I.C2 = st[512];
+      I.T = st[768];
+    }
+    return I;
+  };
+  Item I = fetch(first, index(first));
+  uint32_t gnext = index(first + step);
+  for (int sub = first; sub < end; sub += step) {
+    uint64_t mm = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(I.mm >> 32)) << 32) |
+                  (uint32_t)__builtin_amdgcn_readfirstlane((int)I.mm);
+    s0[wave][lane] = I.R.r0;
+    s1[wave][lane] = I.R.r1;
+    s2[wave][lane] = I.R.r2.x;
+    sg[wave][lane] = I.g;
+    // the pixel's state before the sub-chunk (base: 0, 1 for a whole list)
+    float T = Tin * I.T;
+    bool done = !(T >= 1e-4f) || base.w < -1.f;
+    float Q = 0.f;
+    if (!done)
+      Q = fmaf(g2, Cf2 - fmaf(Tin, I.C2, base.z),
+               fmaf(g1, Cf1 - fmaf(Tin, I.C1, base.y), g0 * (Cf0 - fmaf(Tin, I.C0, base.x))));
+    I = fetch(sub + step, gnext);
+    gnext = index(sub + 2 * step);
+    wave_fence();
+    while (mm && __ballot(!done) != 0ull) {
+      float v[8][6];
+      int kv = 0;                             // entry of this lane's slot
+      int ns = 0;                             // slots filled
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
+      for (int s = 0; s < 8; ++s) {
 #pragma unroll
-      for (int q = 0; q < 9; ++q) v[s][q] = 0.f;
-      if (mm) {
-        const int k = (int)__builtin_ctzll(mm);
-        mm &= mm - 1;
-        const float4 a = s0[k], c1 = s1[k];
-        const float col2 = s2[k].x;
-        const float Tb = T;
-        bool applied;
-        float alpha, dx, dy, G, araw;
-        const float w = blend_step(a, c1, fpx, fpy, T, done, applied, alpha, dx, dy, G, araw);
-        A0 = fmaf(c1.z, w, A0);
-        A1 = fmaf(c1.w, w, A1);
-        A2 = fmaf(col2, w, A2);
-        const float inv1m = __builtin_amdgcn_rcpf(1.f - alpha);   // alpha <= 0.99
-        const float dal = g0 * (c1.z * Tb - (Cf0 - A0) * inv1m) +
-                          g1 * (c1.w * Tb - (Cf1 - A1) * inv1m) +
-                          g2 * (col2 * Tb - (Cf2 - A2) * inv1m);
-        const bool lin = applied && araw <= 0.99f;   // alpha not clamped
-        const float dp = lin ? dal * alpha : 0.f;     // d/d power
-        const float q = dp * kInvHalfLog2e;           // unscale the record's conic
-        v[s][0] = q * fmaf(0.5f * a.w, dy, a.z * dx);  // d/d mean x
-        v[s][1] = q * fmaf(0.5f * a.w, dx, c1.x * dy); // d/d mean y
-        v[s][2] = -0.5f * dp * dx * dx;               // d/d conic A
-        v[s][3] = -dp * dx * dy;                      // d/d conic B
-        v[s][4] = -0.5f * dp * dy * dy;               // d/d conic C
-        v[s][5] = lin ? dal * G : 0.f;                // d/d opacity
-        v[s][6] = w * g0;                             // d/d colour
-        v[s][7] = w * g1;
-        v[s][8] = w * g2;
-        kv = myslot == s ? k : kv;
-        ++ns;
+        for (int q = 0; q < 6; ++q) v[s][q] = 0.f;
+        if (mm) {
+          const int k = (int)__builtin_ctzll(mm);
+          mm &= mm - 1;
+          const float4 a = s0[wave][k], c1 = s1[wave][k];
+          const float gc = fmaf(g2, s2[wave][k], fmaf(g1, c1.w, g0 * c1.z));
+          const float Tb = T;
+          bool applied;
+          float alpha, dx, dy, G, araw;
+          const float w = blend_step(a, c1, fpx, fpy, T, done, applied, alpha, dx, dy, G, araw);
+          Q = fmaf(-gc, w, Q);
+          const float dal = fmaf(gc, Tb, -(Q * __builtin_amdgcn_rcpf(1.f - alpha)));   // alpha <= 0.99
+          const float dp = applied && araw <= 0.99f ? dal * alpha : 0.f;   // unless clamped
+          v[s][0] = dp;
+          v[s][1] = dp * dy;
+          v[s][2] = dp * dy * dy;
+          v[s][3] = w * g0;
+          v[s][4] = w * g1;
+          v[s][5] = w * g2;
+          kv = myslot == s ? k : kv;
+          ++ns;
+        }
+      }
+      float c[6];
+      rga::slot_row_sums8(v, c);
+      // this lane's entry and column: the sums over the column's pixels
+      const float4 a = s0[wave][kv], c1 = s1[wave][kv];
+      const float dx = a.x - fpx, hb = 0.5f * a.w;
+      float r[9];
+      r[0] = kInvHalfLog2e * fmaf(hb, c[1], a.z * dx * c[0]);   // d/d mean x (the record's conic unscaled)
+      r[1] = kInvHalfLog2e * fmaf(c1.x, c[1], hb * dx * c[0]);  // d/d mean y
+      r[2] = -0.5f * dx * dx * c[0];                            // d/d conic A
+      r[3] = -dx * c[1];                                        // d/d conic B
+      r[4] = -0.5f * c[2];                                      // d/d conic C
+      r[5] = c[0] / c1.y;                                       // d/d opacity
+      r[6] = c[3];                                              // d/d colour
+      r[7] = c[4];
+      r[8] = c[5];
+      rga::group_sums8(r);
+      if (myslot < ns) {
+        float* row = grad + (size_t)sg[wave][kv] * kGrad;
+        float x = r[0];
+#pragma unroll
+        for (int q = 1; q < 8; ++q) x = col == q ? r[q] : x;
+        atomicAdd(row + col, x);
+        if (col == 0) atomicAdd(row + 8, r[8]);
       }
     }
-    float r[9];
-    rga::slot_sums8(v, r);
-    if ((lane & 7) == 0 && myslot < ns) {
-#pragma unroll
-      for (int q = 0; q < 9; ++q) acc[wave][q][kv] = r[q];
-    }
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < cnt) {
-    const int e = threadIdx.x;
-    const uint32_t g = sg[e];
-    float sum[9];
-    bool nz = false;
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-      sum[q] = (acc[0][q][e] + acc[1][q][e]) + (acc[2][q][e] + acc[3][q][e]);
-      nz |= sum[q] != 0.f;
-    }
-    if (nz) {
-#pragma unroll
-      for (int q = 0; q < 5; ++q) atomicAdd(&gmean_conic[(size_t)q * n + g], sum[q]);
-      atomicAdd(&dopac[g], sum[5]);
-      atomicAdd(&dcolor[g], sum[6]);
-      atomicAdd(&dcolor[(size_t)n + g], sum[7]);
-      atomicAdd(&dcolor[(size_t)2 * n + g], sum[8]);
-    }
-  }
+    wave_fence();   // the next sub-chunk's records replace these
   }
 }
 
@@ -1371,20 +1425,24 @@ __global__ void __launch_bounds__(256)
 preprocess_bwd_kernel(int n, CamDev cam, const float* __restrict__ x, const float* __restrict__ A,
                       const float* __restrict__ quat, const float* __restrict__ log_s,
                       const float* __restrict__ opac, const uint8_t* __restrict__ front,
-                      float* __restrict__ grad9, uint32_t* __restrict__ queue,
+                      const int32_t* __restrict__ touched, float* __restrict__ grad,
                       float* __restrict__ dx, float* __restrict__ dquat,
                       float* __restrict__ dlog_s, float* __restrict__ dopac,
                       float* __restrict__ dcolor, float* __restrict__ dA,
                       const int64_t* __restrict__ counters, int64_t capacity) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < kQueues) queue[g * 64] = 0u;
   if (g >= n) return;
   // take the blend adjoint's sums and leave them zero for another backward
-  float gs[9];
+  // (a splat in no list has none)
+  float gs[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (touched[g] > 0) {
+    float4* row = reinterpret_cast<float4*>(grad + (size_t)g * kGrad);
+    const float4 a = row[0], b = row[1], c = row[2];
+    gs[0] = a.x; gs[1] = a.y; gs[2] = a.z; gs[3] = a.w;
+    gs[4] = b.x; gs[5] = b.y; gs[6] = b.z; gs[7] = b.w;
+    gs[8] = c.x;
 #pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    gs[q] = grad9[(size_t)q * n + g];
-    grad9[(size_t)q * n + g] = 0.f;
+    for (int q = 0; q < 3; ++q) row[q] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (counters[0] > capacity) {
     // the forward's lists were truncated: poison the gradients (NaN)
@@ -1476,25 +1534,6 @@ preprocess_bwd_kernel(int n, CamDev cam, const float* __restrict__ x, const floa
   dquat[(size_t)n + g] = (gx - qx * dot) * G.inv;
   dquat[(size_t)2 * n + g] = (gy - qy * dot) * G.inv;
   dquat[(size_t)3 * n + g] = (gz - qz * dot) * G.inv;
-}
-
-// Workgroups of a 256-thread blend kernel that fit on the current device at
-// once (the grid of the grid-stride blend passes), cached per device.
-template <int K>
-int resident_groups(const void* kernel) {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  if (cache[dev] == 0) {
-    int cus = 0, per = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, 256, 0) != hipSuccess ||
-        per < 1)
-      per = 1;
-    cache[dev] = (cus > 0 ? cus : 1) * per;
-  }
-  return cache[dev];
 }
 
 // ---- storage order of the Gaussians --------------------------------------------
@@ -1617,8 +1656,8 @@ extern "C" int splat_read_count(void* stream, const void* ws, int n, int width, 
   return RGA_OK;
 }
 
-// Projection, depth sort, duplication, tile sort, tile ranges and the
-// blend's work items: everything of the forward that the colours do not enter.
+// Projection, depth sort, duplication, tile sort, tile ranges: everything of
+// the forward that the colours do not enter.
 extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float* x,
                          const float* A, const float* quat, const float* log_s,
                          const float* opac, const uint8_t* front, void* ws, size_t ws_bytes,
@@ -1653,7 +1692,8 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
                dim3(256), 0, s, n, cd, L.tiles_x, L.tiles_y, x, A, quat, log_s, opac, front, at<float4>(ws, L.rec), at<float>(ws, L.mean2d), at<float>(ws, L.conic),
                at<float>(ws, L.depth), at<int32_t>(ws, L.rect), at<int32_t>(ws, L.touched),
                at<uint8_t>(ws, L.fp64), k0, v0, reinterpret_cast<uint32_t*>(ranges), 2 * tiles,
-               reinterpret_cast<uint32_t*>(cnt), at<float>(ws, L.grad), at<uint32_t>(ws, L.queue));
+               reinterpret_cast<uint32_t*>(cnt), at<float4>(ws, L.grad), at<uint4>(ws, L.part_t),
+               L.parts > 1 ? tiles * kBlocks * L.parts * 16 : (int64_t)0);
     // depth sort: 3 passes of 11 bits over n 32-bit keys (4 passes of 8
     // bits, with 8x smaller digit tables, take longer: the passes are
     // latency-bound launches)
@@ -1665,7 +1705,7 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
                  (const int64_t*)nullptr, (int64_t)n, (int64_t)n, kBlockN, binoff, bintot);
       RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsN, kDepthBits>), dim3(L.nb_n), dim3(kRadixThreads), 0, s, k0,
                  v0, k1, v1, (const int64_t*)nullptr, (int64_t)n, (int64_t)n, shift, binoff, bintot,
-                 (int32_t*)nullptr, 0, ItemOut{});
+                 (int32_t*)nullptr, 0);
       uint32_t* t = k0; k0 = k1; k1 = t;
       t = v0; v0 = v1; v1 = t;
     }
@@ -1682,12 +1722,9 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
     RGA_LAUNCH("splat_duplicate", duplicate_kernel, dim3(L.nb_n), dim3(kBlockN), 0, s, n,
                L.tiles_x, capacity, v0, at<int32_t>(ws, L.touched), at<int32_t>(ws, L.rect), boff,
                tk0, tv0);
-    const ItemOut items{at<uint32_t>(ws, L.item_off), at<uint32_t>(ws, L.item_tile),
-                        at<uint32_t>(ws, L.item_chunk), at<uint32_t>(ws, L.item_sub), L.max_items,
-                        cnt};
     if (L.tile_passes == 1 && L.tile_bits == kWideBits) {
       // 2049 .. 4096 tiles: one pass of 12-bit digits, whose scatter also
-      // writes the tile ranges and the work items
+      // writes the tile ranges
       constexpr int kWide = 1 << kWideBits;
       RGA_LAUNCH("radix_upsweep", (radix_upsweep<kItemsD, kWideBits>), dim3(L.nb_cap),
                  dim3(kRadixThreads), 0, s, tk0, (const int64_t*)cnt, (int64_t)0, capacity, 0, hist);
@@ -1695,7 +1732,7 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
                  L.nb_cap, (const int64_t*)cnt, (int64_t)0, capacity, kBlockD, binoff, bintot);
       RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsD, kWideBits>), dim3(L.nb_cap),
                  dim3(kRadixThreads), 0, s, tk0, tv0, tk1, tv1, (const int64_t*)cnt, (int64_t)0,
-                 capacity, 0, binoff, bintot, ranges, (int)tiles, items);
+                 capacity, 0, binoff, bintot, ranges, (int)tiles);
       uint32_t* t = tk0; tk0 = tk1; tk1 = t;
       t = tv0; tv0 = tv1; tv1 = t;
     }
@@ -1709,7 +1746,7 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
       const bool one = L.tile_passes == 1;
       RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsD, kDigitBits>), dim3(L.nb_cap), dim3(kRadixThreads), 0, s, tk0,
                  tv0, tk1, tv1, (const int64_t*)cnt, (int64_t)0, capacity, shift, binoff, bintot,
-                 one ? ranges : (int32_t*)nullptr, one ? (int)tiles : 0, items);
+                 one ? ranges : (int32_t*)nullptr, one ? (int)tiles : 0);
       uint32_t* t = tk0; tk0 = tk1; tk1 = t;
       t = tv0; tv0 = tv1; tv1 = t;
     }
@@ -1717,17 +1754,11 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
       RGA_LAUNCH("tile_ranges", tile_ranges_kernel, dim3(rga::ceil_div(capacity, 256)), dim3(256), 0,
                  s, tk0, (const int64_t*)cnt, capacity, ranges);
   }
-  // work items (tile, chunk) unless the one-pass tile sort built them
-  if (n == 0 || L.tile_passes > 1)
-    RGA_LAUNCH("chunk_index", chunk_index_kernel, dim3(1), dim3(1024), 0, s, (int)tiles, ranges,
-               at<uint32_t>(ws, L.item_off), at<uint32_t>(ws, L.item_tile),
-               at<uint32_t>(ws, L.item_chunk), at<uint32_t>(ws, L.item_sub), L.max_items, cnt);
   RGA_CHECK_LAUNCH("splat_bin");
   return RGA_OK;
 }
 
-// The colours into the records, chunk composites, front-to-back combine,
-// restarts: the rest of the forward, on the lists splat_bin left in ws.
+// The compositing: the rest of the forward, on the lists splat_bin left in ws.
 extern "C" int splat_blend(void* stream, int n, const rga_camera* cam, const float* color,
                            void* ws, size_t ws_bytes, int64_t capacity, float* image,
                            float* T_final) {
@@ -1742,22 +1773,24 @@ extern "C" int splat_blend(void* stream, int n, const rga_camera* cam, const flo
   int64_t* cnt = at<int64_t>(ws, L.count);
   int32_t* ranges = at<int32_t>(ws, L.ranges);
   const uint32_t* sorted = at<uint32_t>(ws, (L.tile_passes & 1) ? L.tv1 : L.tv0);
-  const int64_t g_chunk =
-      std::min<int64_t>(L.max_items, resident_groups<0>((const void*)blend_chunk_kernel));
-  const int64_t g_restart =
-      std::min<int64_t>(L.max_items, resident_groups<1>((const void*)blend_restart_kernel));
-  RGA_LAUNCH("blend_chunk", blend_chunk_kernel, dim3(g_chunk), dim3(256), 0, s, W, H, L.tiles_x,
-             n, ranges, sorted, at<float4>(ws, L.rec), color, at<uint32_t>(ws, L.item_tile),
-             at<uint32_t>(ws, L.item_chunk), cnt, L.max_items, at<uint32_t>(ws, L.item_sub),
-             at<uint32_t>(ws, L.sub_item), L.max_subs, at<float>(ws, L.cstate),
-             at<float>(ws, L.sstate));
-  RGA_LAUNCH("blend_prefix", blend_prefix_kernel, dim3(tiles), dim3(256), 0, s, W, H, L.tiles_x,
-             at<uint32_t>(ws, L.item_off), at<float>(ws, L.cstate), L.max_items, image, T_final,
-             (const int64_t*)cnt, capacity);
-  RGA_LAUNCH("blend_restart", blend_restart_kernel, dim3(g_restart), dim3(256), 0, s, W, H,
-             L.tiles_x, n, ranges, sorted, at<float4>(ws, L.rec), color, at<uint32_t>(ws, L.item_tile),
-             at<uint32_t>(ws, L.item_chunk), cnt, L.max_items, at<float>(ws, L.cstate),
-             at<float>(ws, L.sstate), image, T_final, capacity);
+  float4* part = at<float4>(ws, L.part);
+  auto blend = blend_kernel<1>;
+  auto join = blend_join_kernel<4>;
+  if (L.parts == 4) blend = blend_kernel<4>;
+  if (L.parts == 8) blend = blend_kernel<8>, join = blend_join_kernel<8>;
+  if (L.parts == 32) blend = blend_kernel<32>, join = blend_join_kernel<32>;
+  RGA_LAUNCH("blend", blend, dim3(block_grid(tiles), L.parts), dim3(256), 0, s, W, H, L.tiles_x,
+             (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color, cnt, capacity,
+             at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive), part,
+             at<uint32_t>(ws, L.part_t), image, T_final);
+  if (L.parts > 1) {
+    RGA_LAUNCH("blend_join", join, dim3(tiles), dim3(256), 0, s, W, H, L.tiles_x, part, cnt,
+               capacity, image, T_final);
+    RGA_LAUNCH("blend_restart", blend_restart_kernel, dim3(block_grid(tiles), L.parts, kSplitsPart),
+               dim3(256), 0, s, W, H, L.tiles_x, (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color,
+               at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive), part,
+               image, T_final);
+  }
   RGA_CHECK_LAUNCH("splat_blend");
   return RGA_OK;
 }
@@ -1793,23 +1826,22 @@ extern "C" int splat_backward(void* stream, int n, const rga_camera* cam, const 
     return rga::fail(RGA_EINVAL, "splat_backward: null pointer");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const CamDev cd = to_dev(cam);
-  // The per-splat sums and the item queue were zeroed by splat_forward's
-  // projection, and the projection adjoint zeroes them again after use.
-  float* grad9 = at<float>(ws, L.grad);
-  uint32_t* queue = at<uint32_t>(ws, L.queue);
-  const int64_t g_bwd =
-      std::min<int64_t>(L.max_subs, resident_groups<2>((const void*)blend_bwd_kernel));
+  // The per-splat sums were zeroed by splat_forward's projection, and the
+  // projection adjoint zeroes them again after use.
+  float* grad = at<float>(ws, L.grad);
+  const int64_t tiles = (int64_t)L.tiles_x * L.tiles_y;
   const uint32_t* sorted = at<uint32_t>(ws, (L.tile_passes & 1) ? L.tv1 : L.tv0);
-  RGA_LAUNCH("blend_bwd", blend_bwd_kernel, dim3(g_bwd), dim3(256), 0, s, cam->width,
-             cam->height, L.tiles_x, n, at<int32_t>(ws, L.ranges), sorted, at<float4>(ws, L.rec),
-             color,
-             at<uint32_t>(ws, L.item_tile), at<uint32_t>(ws, L.item_chunk),
-             at<uint32_t>(ws, L.sub_item), at<int64_t>(ws, L.count), L.max_items, L.max_subs,
-             queue, at<float>(ws, L.cstate), at<float>(ws, L.sstate), image, dimage, grad9,
-             grad9 + (size_t)5 * n, grad9 + (size_t)6 * n);
+  RGA_LAUNCH("blend_bwd", blend_bwd_kernel,
+             L.parts > 1 ? dim3(block_grid(tiles), L.parts, kSplitsPart)
+                         : dim3(block_grid(tiles), splits(tiles)),
+             dim3(256), 0, s,
+             cam->width, cam->height, L.tiles_x, (int)tiles, n, at<int32_t>(ws, L.ranges), sorted,
+             at<float4>(ws, L.rec), color, at<float>(ws, L.state), at<uint64_t>(ws, L.mask),
+             at<uint32_t>(ws, L.nlive),
+             L.parts > 1 ? at<float4>(ws, L.part) : (float4*)nullptr, image, dimage, grad);
   RGA_LAUNCH("preprocess_bwd", preprocess_bwd_kernel, dim3(rga::ceil_div(n, 256)), dim3(256), 0, s,
-             n, cd, x, A, quat, log_s, opac, front, grad9, queue, dx, dquat, dlog_s, dopac, dcolor,
-             dA, (const int64_t*)at<int64_t>(ws, L.count), capacity);
+             n, cd, x, A, quat, log_s, opac, front, at<int32_t>(ws, L.touched), grad, dx, dquat,
+             dlog_s, dopac, dcolor, dA, (const int64_t*)at<int64_t>(ws, L.count), capacity);
   RGA_CHECK_LAUNCH("splat_backward");
   return RGA_OK;
 }
@@ -1852,7 +1884,7 @@ extern "C" int vertex_order(void* stream, int n, const int32_t* vidx, int nv, in
                (const int64_t*)nullptr, (int64_t)n, (int64_t)n, kBlockN, binoff, bintot);
     RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsN, kDigitBits>), dim3(L.nb), dim3(kRadixThreads), 0, s,
                k0, v0, k1, vout, (const int64_t*)nullptr, (int64_t)n, (int64_t)n, shift, binoff,
-               bintot, (int32_t*)nullptr, 0, ItemOut{});
+               bintot, (int32_t*)nullptr, 0);
     uint32_t* t = k0; k0 = k1; k1 = t;
     t = v0; v0 = v1; v1 = t;
   }
