@@ -22,14 +22,14 @@
 // direction test, the count rows and the ring from the adjoint.  The BF16X3
 // form's MFMA forward writes the same tape (its pairs in step order), and
 // its adjoint given one is this replay.
+#include <algorithm>
+
 #include "common.h"
 
 #include <math.h>
 
 namespace {
 
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * 64;
 constexpr int kRing = 128;
 constexpr float kPi = 3.14159265358979323846f;
 
@@ -126,32 +126,6 @@ __device__ inline void attr_load(const ShadeArgs& a, int g, Attr& A) {
   }
   A.rough = pin<UNI>(a.rough[g]);
   A.tint = pin<UNI>(a.tint[g]);
-}
-
-// The three visibility-count rows of a Gaussian (3 V bytes, V % 16 == 0) are
-// copied straight from global memory into the wave's LDS slot with
-// global_load_lds (16 bytes per lane, NQ = ceil(3 V / 1024) per lane), one
-// Gaussian ahead, into the other half of a double buffer.
-template <int NQ>
-__device__ inline void rows_dma(const ShadeArgs& a, const Attr& A, uint8_t* lds, int lane) {
-  const int nq = 3 * a.V / 16;
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const int q = lane + 64 * i;
-    if (q < nq) {
-      const int byte = 16 * q;
-      const int j = byte / a.V;
-      const int off = byte - j * a.V;
-      const int vi = j == 0 ? A.vidx[0] : (j == 1 ? A.vidx[1] : A.vidx[2]);
-      __builtin_amdgcn_global_load_lds(a.count + (size_t)vi * a.V + off, lds + 1024 * i, 16, 0, 0);
-    }
-  }
-}
-
-// Wait for every outstanding memory operation of the wave (the row copies).
-__device__ inline void wait_all() {
-  __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Reciprocal and reciprocal square root on the transcendental unit (about
@@ -300,17 +274,23 @@ __device__ inline void wave_fence() {
 }
 
 // ---- FP32 form: one wave per front-facing Gaussian ---------------------------
-// A wave owns the Gaussians first, first + stride, first + 2 stride, ...
-// (stride = number of waves in the grid).  It takes them 64 at a time: each
-// lane loads one Gaussian's position and normal and decides the back-face
-// rule; a back-facing Gaussian's outputs are written at once (it needs
-// nothing else, and its count rows are never copied), and a ballot gives
-// the front-facing ones, which the wave shades one after the other: per
-// chunk of 64 directions each lane tests its direction, a ballot compacts
-// the live ones into the wave's LDS ring, and whole waves of ring entries
-// go to the BRDF stage.  The next front Gaussian's count rows are copied
-// into the other half of an LDS double buffer, and its attributes loaded,
-// while the current one is shaded.
+// A workgroup takes up to `cap` Gaussians at a time: each thread loads one
+// Gaussian's position and normal and decides the back-face rule; a back-facing
+// Gaussian's outputs are written at once (it needs nothing else, and its count
+// rows are never read), and the front-facing ones are listed in LDS with their
+// three nearest vertices.  The waves then take entries of the list from a
+// shared counter until it is empty: per chunk of 64 directions each lane tests
+// its direction, a ballot compacts the live ones into the wave's LDS ring, and
+// whole waves of ring entries go to the BRDF stage.  The next entry's count
+// rows and attributes are loaded into registers while the current one is
+// shaded, and the rows then written to the wave's LDS slot.
+//
+// Bound by vector issue (87 % of the slots forward, 95 % adjoint at 200k
+// Gaussians and 2048 directions).  A wave that walked its own fixed share of
+// the Gaussians left the others waiting (the back-facing ones come in runs),
+// and two sets of rows per wave in LDS left two waves per SIMD at 2048
+// directions: 200k Gaussians there 663 -> 294 us forward, 457 -> 280 us adjoint;
+// 100k at 512 directions 80 -> 53 us and 85 -> 65 us.
 
 // Per-lane plan of the count-row copies (depends only on the lane and V):
 // 16-byte piece q = lane + 64 i is byte 16 q of the three rows laid end to
@@ -332,105 +312,134 @@ __device__ inline void row_plan(int V, int lane, RowPlan<NQ>& P) {
   }
 }
 
-template <class Plan>
-__device__ inline void rows_copy(const ShadeArgs& a, const Plan& P, const int* vidx,
-                                 uint8_t* lds) {
-  constexpr int NQ = sizeof(P.p) / sizeof(P.p[0]);
+// the three count rows of a Gaussian, in registers
+template <int NQ>
+struct Rows {
+  uint4 q[NQ];
+};
+
+template <int NQ>
+__device__ inline void rows_load(const ShadeArgs& a, const RowPlan<NQ>& P, const int* vidx,
+                                 Rows<NQ>& R) {
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
     const int j = P.p[i] & 3;
-    if (j != 3) {
-      const int vi = j == 0 ? vidx[0] : (j == 1 ? vidx[1] : vidx[2]);
-#if defined(__HIP_DEVICE_COMPILE__)   // a device builtin: the host pass only parses the body
-      __builtin_amdgcn_global_load_lds(a.count + (size_t)vi * a.V + (P.p[i] >> 2),
-                                       lds + 1024 * i, 16, 0, 0);
-#endif
-    }
+    const int vi = j == 0 ? vidx[0] : (j == 1 ? vidx[1] : vidx[2]);
+    R.q[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (j != 3)
+      R.q[i] = *reinterpret_cast<const uint4*>(a.count + (size_t)vi * a.V + (P.p[i] >> 2));
   }
 }
 
-// One lane's candidate Gaussian of a block: its index, the back-face rule
-// and, if it faces the camera, its three nearest vertices.
-struct Cand {
-  int g;
-  bool front;
-  int vidx[3];
-};
+template <int NQ>
+__device__ inline void rows_store(const RowPlan<NQ>& P, const Rows<NQ>& R, uint8_t* lds, int lane) {
+#pragma unroll
+  for (int i = 0; i < NQ; ++i)
+    if ((P.p[i] & 3) != 3) *reinterpret_cast<uint4*>(lds + 16 * lane + 1024 * i) = R.q[i];
+}
 
-// The wave's slots of the walk: first, first + stride, ... below `end`.
-// With a grid of whole groups of 8 workgroups, the workgroups that share a
-// remainder modulo 8 (dispatched to the same XCD, whose L2 they share)
-// take one contiguous eighth of the Gaussians: with the Gaussians stored
-// grouped by nearest vertex, each XCD then gathers count rows from about an
-// eighth of the table, and its L2 holds them.
+// The workgroup's Gaussians at(0) .. at(count - 1).  With a grid of whole
+// groups of 8 workgroups, those that share a remainder modulo 8 (dispatched to
+// the same XCD, whose L2 they share) take every eighth of 64 contiguous
+// segments: with the Gaussians stored grouped by nearest vertex, each XCD
+// gathers count rows from about an eighth of the table, and its L2 holds them,
+// and each has its share of every part of the body.  Within the XCD the
+// workgroups take every (grid / 8)-th.
+constexpr int kSegments = 64;
+
 struct Walk {
-  int first, stride, end;
+  int first, stride, count, seg, x;
 };
 
-__device__ inline Walk wave_walk(int n, int wave) {
+__device__ inline Walk group_walk(int n) {
   Walk w;
   const int grid = gridDim.x, b = blockIdx.x;
-  if (grid % 8 == 0 && grid >= 8) {
-    const int x = b % 8, j = b / 8;
-    const int lo = (int)((int64_t)n * x / 8), hi = (int)((int64_t)n * (x + 1) / 8);
-    w.first = lo + j * kWaves + wave;
-    w.stride = (grid / 8) * kWaves;
-    w.end = hi;
-  } else {
-    w.first = b * kWaves + wave;
-    w.stride = grid * kWaves;
-    w.end = n;
-  }
+  const bool xcd = grid % 8 == 0;
+  w.x = xcd ? b % 8 : -1;
+  w.first = xcd ? b / 8 : b;
+  w.stride = xcd ? grid / 8 : grid;
+  w.seg = (n + kSegments - 1) / kSegments;
+  const int len = xcd ? (kSegments / 8) * w.seg : n;
+  w.count = w.first < len ? (len - 1 - w.first) / w.stride + 1 : 0;
   return w;
 }
 
-__device__ inline int walk_count(const Walk& w) {
-  return w.first < w.end ? (w.end - 1 - w.first) / w.stride + 1 : 0;
+// index of the m-th Gaussian, -1 if there is none
+__device__ inline int walk_at(const Walk& w, int n, int m) {
+  if (m >= w.count) return -1;
+  const int q = w.first + m * w.stride;
+  if (w.x < 0) return q;
+  const int s = q / w.seg;
+  const int g = (8 * s + w.x) * w.seg + (q - s * w.seg);
+  return g < n ? g : -1;
 }
 
-// Load block bb of the wave's Gaussians (lane i: Gaussian first + (64 bb + i)
-// stride) and decide the back-face rule (FP32, fixed order, as gauss_setup).
-__device__ inline void cand_load(const ShadeArgs& a, const Walk& w, int bb, int lane, Cand& C) {
-  const int64_t idx = (int64_t)(64 * bb + lane) * w.stride + w.first;
-  const bool valid = idx < w.end;
-  C.g = valid ? (int)idx : -1;
-  C.front = false;
-  if (valid) {
-    const int n = a.n, g = C.g;
-    float x[3], m[3];
+// Fill the list with the front-facing ones of the workgroup's Gaussians m0 ..
+// m0 + cap - 1 (FP32 test, fixed order, as gauss_setup); back(g) finishes a
+// back-facing one, each(g, front) sees every one.
+template <class Each>
+__device__ inline void list_fill(const ShadeArgs& a, const Walk& w, int m0, int cap, int4* list,
+                                 int* count, uint64_t lt, Each&& each) {
+  for (int t = threadIdx.x; t - (int)(threadIdx.x & 63) < cap; t += blockDim.x) {
+    const int g = t < cap ? walk_at(w, a.n, m0 + t) : -1;
+    bool front = false;
+    int4 e = make_int4(g, 0, 0, 0);
+    if (g >= 0) {
+      const int n = a.n;
+      float x[3], m[3];
+      int vi[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      x[c] = a.x[(size_t)c * n + g];
-      m[c] = a.nrm[(size_t)c * n + g];
+      for (int c = 0; c < 3; ++c) {
+        x[c] = a.x[(size_t)c * n + g];
+        m[c] = a.nrm[(size_t)c * n + g];
+        vi[c] = a.vidx[(size_t)c * n + g];
+      }
+      const float w0 = a.cam[0] - x[0], w1 = a.cam[1] - x[1], w2 = a.cam[2] - x[2];
+      front = fmaf(m[2], w2, fmaf(m[1], w1, m[0] * w0)) > 0.f;
+      each(g, front);
+      e.y = rga::clampi(vi[0], 0, a.nv - 1);
+      e.z = rga::clampi(vi[1], 0, a.nv - 1);
+      e.w = rga::clampi(vi[2], 0, a.nv - 1);
     }
-    const float w0 = a.cam[0] - x[0], w1 = a.cam[1] - x[1], w2 = a.cam[2] - x[2];
-    C.front = fmaf(m[2], w2, fmaf(m[1], w1, m[0] * w0)) > 0.f;
-    if (C.front) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) C.vidx[c] = rga::clampi(a.vidx[(size_t)c * n + g], 0, a.nv - 1);
-    }
+    const uint64_t f = __ballot(front);
+    if (f == 0ull) continue;
+    int at = 0;
+    if ((threadIdx.x & 63) == 0) at = atomicAdd(count, (int)__popcll(f));
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (front) list[at + __popcll(f & lt)] = e;
   }
 }
 
-// The front Gaussian held by lane j of the block: its index and vertices
-// from that lane, the other attributes loaded with a wave-uniform address
-// (scalar loads into scalar registers).
-__device__ inline int cand_take(const ShadeArgs& a, const Cand& C, int j, Attr& A) {
-  const int n = a.n;
-  const int g = __builtin_amdgcn_readlane(C.g, j);
+// The wave's next entry of the list: its number, from the shared counter.
+__device__ inline int list_take(int* next, int lane) {
+  int t = 0;
+  if (lane == 0) t = atomicAdd(next, 1);
+  return __builtin_amdgcn_readfirstlane(t);
+}
+
+// A listed Gaussian's attributes are loaded by one instruction, lane i the i-th
+// of x, n, albedo, weights (three each), roughness and tint, and read from the
+// lanes when its turn comes (held in scalar registers from the load on, with
+// the arrays' addresses, they were spilled).
+__device__ inline const float* attr_lane(const ShadeArgs& a, int lane) {
+  const int c = lane % 3, q = lane / 3;
+  const float* p = q == 0 ? a.x : (q == 1 ? a.nrm : (q == 2 ? a.albedo : a.vw));
+  p += (size_t)c * a.n;
+  return lane < 12 ? p : (lane == 12 ? a.rough : a.tint);
+}
+
+__device__ inline void attr_read(float v, Attr& A) {
+  auto at = [v](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); };
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    A.vidx[c] = __builtin_amdgcn_readlane(C.vidx[c], j);
-    A.x[c] = uni(a.x[(size_t)c * n + g]);
-    A.m[c] = uni(a.nrm[(size_t)c * n + g]);
-    A.alb[c] = uni(a.albedo[(size_t)c * n + g]);
-    A.vw[c] = uni(a.vw[(size_t)c * n + g]);
+    A.x[c] = at(c);
+    A.m[c] = at(3 + c);
+    A.alb[c] = at(6 + c);
+    A.vw[c] = at(9 + c);
   }
-  A.rough = uni(a.rough[g]);
-  A.tint = uni(a.tint[g]);
-  return g;
+  A.rough = at(12);
+  A.tint = at(13);
 }
-
 
 // Walk the K directions of one Gaussian 64 at a time: lane = direction,
 // the live ones (n.w_k > 0 and visibility > 0) appended with their
@@ -469,107 +478,121 @@ __device__ inline int live_walk(const GaussCtx& G, const float* tab, int K, int 
   return tail;
 }
 
-// (up to 512 views: three workgroups per CU, six waves per SIMD)
-template <int NQ>
-__global__ void __launch_bounds__(kThreads, NQ <= 2 ? 6 : 4)
-shade_fwd_kernel(ShadeArgs a, float* __restrict__ color, uint8_t* __restrict__ front) {
-  extern __shared__ __align__(16) float tab[];
-  __shared__ int qk[kWaves][kRing];
-  __shared__ float qv[kWaves][kRing];
+// LDS of the FP32 kernels: the direction table (8 K floats; the adjoint adds
+// 3 K for the environment gradient), then per wave the count rows (3 V bytes)
+// and the ring (none in the adjoint that reads a tape), then the list.
+template <int WAVES>
+struct Lds {
+  float* tab;
+  uint8_t* rows;
+  int* qk;
+  float* qv;
+  int4* list;
+};
+
+template <int WAVES>
+__device__ inline Lds<WAVES> lds_of(float* smem, int tab_floats, int V, int wave, bool walks) {
+  Lds<WAVES> L;
+  L.tab = smem;
+  uint8_t* p = reinterpret_cast<uint8_t*>(smem + tab_floats);
+  L.rows = p + (size_t)wave * 3 * V;
+  if (walks) p += (size_t)WAVES * 3 * V;
+  L.qk = reinterpret_cast<int*>(p) + wave * kRing;
+  L.qv = reinterpret_cast<float*>(p) + (WAVES + wave) * kRing;
+  if (walks) p += (size_t)WAVES * kRing * 8;
+  L.list = reinterpret_cast<int4*>(p);
+  return L;
+}
+
+template <int NQ, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64, NQ <= 2 ? 8 : 4)
+shade_fwd_kernel(ShadeArgs a, int cap, float* __restrict__ color, uint8_t* __restrict__ front) {
+  extern __shared__ __align__(16) float smem[];
+  __shared__ int ctl[2][2];   // entries listed and taken, of alternate rounds
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int K = a.K, n = a.n, V = a.V;
-  uint8_t* rows0 = reinterpret_cast<uint8_t*>(tab + 8 * K) + (size_t)wave * 6 * V;
-  build_table(a, tab);
-  __syncthreads();
+  const Lds<WAVES> L = lds_of<WAVES>(smem, 8 * K, V, wave, true);
+  const float* tab = L.tab;
+  if (threadIdx.x < 4) (&ctl[0][0])[threadIdx.x] = 0;
+  build_table(a, smem);
   const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   RowPlan<NQ> plan;
   row_plan<NQ>(V, lane, plan);
-  const Walk walk = wave_walk(n, wave);
-  const int nblk = (walk_count(walk) + 63) / 64;
-  Cand C;
-  int b = -1;
-  uint64_t fm = 0ull;
-  // next block with a front-facing Gaussian; back-facing ones are finished here
-  auto advance = [&]() {
-    while (fm == 0ull && b + 1 < nblk) {
-      ++b;
-      cand_load(a, walk, b, lane, C);
-      if (C.g >= 0) {
-        front[C.g] = C.front ? 1 : 0;
-        if (!C.front) {
+  const float* pattr = attr_lane(a, lane);
+  const Walk walk = group_walk(n);
+  for (int m0 = 0, r = 0; m0 < walk.count; m0 += cap, r ^= 1) {
+    __syncthreads();          // the last round's list is done with
+    if (threadIdx.x < 2) ctl[r ^ 1][threadIdx.x] = 0;
+    list_fill(a, walk, m0, cap, L.list, &ctl[r][0], lt, [&](int g, bool f) {
+      front[g] = f ? 1 : 0;
+      if (f) return;
 #pragma unroll
-          for (int c = 0; c < 3; ++c) color[(size_t)c * n + C.g] = 0.f;
-          if (a.tape_n) a.tape_n[C.g] = 0;
-        }
-      }
-      fm = __ballot(C.front);
-    }
-  };
-  advance();
-  if (fm == 0ull) return;
-  Attr A;
-  int g = cand_take(a, C, __builtin_ctzll(fm), A);
-  fm &= fm - 1;
-  rows_copy(a, plan, A.vidx, rows0);
-  wait_all();
-  int cur = 0;
-  int og = -1;   // each Gaussian's colour is stored when the next one starts
-  float o_col = 0.f;
-  for (;;) {
-    if (og >= 0 && lane < 3) color[(size_t)lane * n + og] = o_col;
-    // the next front-facing Gaussian: its rows and attributes are fetched
-    // while this one is shaded
-    advance();
-    const bool more = fm != 0ull;
-    Attr An;
-    int gn = -1;
-    if (more) {
-      gn = cand_take(a, C, __builtin_ctzll(fm), An);
-      fm &= fm - 1;
-      rows_copy(a, plan, An.vidx, rows0 + (cur ^ 1) * 3 * V);
-    }
-    GaussCtx G;
-    gauss_setup<true>(a, A, rows0 + cur * 3 * V, G);
-    float sd0 = 0.f, sd1 = 0.f, sd2 = 0.f, ss0 = 0.f, ss1 = 0.f, ss2 = 0.f;
-    // this Gaussian's row of the tape (a wave-uniform address)
-    uint2* const trow = a.tape ? a.tape + (size_t)uni(g) * K : nullptr;
-    const int nlive = live_walk(G, tab, K, V, qk[wave], qv[wave], lane, lt,
-                                [&](int k, float v, bool on, int base) {
-      if (on) {
-        if (trow) trow[base + lane] = make_uint2((uint32_t)k, __float_as_uint(v));
-        Pair P;
-        pair_eval(G, tab, K, k, v, P);
-        sd0 = fmaf(P.Wd, P.E[0], sd0);
-        sd1 = fmaf(P.Wd, P.E[1], sd1);
-        sd2 = fmaf(P.Wd, P.E[2], sd2);
-        ss0 = fmaf(P.Ws, P.E[0], ss0);
-        ss1 = fmaf(P.Ws, P.E[1], ss1);
-        ss2 = fmaf(P.Ws, P.E[2], ss2);
-      }
+      for (int c = 0; c < 3; ++c) color[(size_t)c * n + g] = 0.f;
+      if (a.tape_n) a.tape_n[g] = 0;
     });
-    if (trow && lane == 0) a.tape_n[g] = nlive;
-    sd0 = rga::wave_sum(sd0);
-    sd1 = rga::wave_sum(sd1);
-    sd2 = rga::wave_sum(sd2);
-    ss0 = rga::wave_sum(ss0);
-    ss1 = rga::wave_sum(ss1);
-    ss2 = rga::wave_sum(ss2);
-    if (lane < 3) {
-      const float sd = lane == 0 ? sd0 : (lane == 1 ? sd1 : sd2);
-      const float ss = lane == 0 ? ss0 : (lane == 1 ? ss1 : ss2);
-      const float alb = lane == 0 ? A.alb[0] : (lane == 1 ? A.alb[1] : A.alb[2]);
-      o_col = srgb(alb * (1.f / kPi) * sd + A.tint * ss);
+    __syncthreads();
+    const int entries = ctl[r][0];
+    int t = list_take(&ctl[r][1], lane);
+    Rows<NQ> R;
+    int g = 0;
+    float v = 0.f;
+    auto load = [&](int e) {
+      const int4 le = L.list[e];
+      const int gg = uni(le.x);
+      const int vidx[3] = {uni(le.y), uni(le.z), uni(le.w)};
+      v = pattr[gg];
+      rows_load(a, plan, vidx, R);
+      return gg;
+    };
+    if (t < entries) {
+      g = load(t);
+      rows_store(plan, R, L.rows, lane);
     }
-    og = g;
-    wait_all();
-    wave_fence();
-    if (!more) break;
-    A = An;
-    g = gn;
-    cur ^= 1;
+    while (t < entries) {
+      Attr A;
+      attr_read(v, A);
+      t = list_take(&ctl[r][1], lane);
+      int gn = 0;
+      if (t < entries) gn = load(t);
+      wave_fence();
+      GaussCtx G;
+      gauss_setup<true>(a, A, L.rows, G);
+      float sd0 = 0.f, sd1 = 0.f, sd2 = 0.f, ss0 = 0.f, ss1 = 0.f, ss2 = 0.f;
+      // this Gaussian's row of the tape (a wave-uniform address)
+      uint2* const trow = a.tape ? a.tape + (size_t)uni(g) * K : nullptr;
+      const int nlive = live_walk(G, tab, K, V, L.qk, L.qv, lane, lt,
+                                  [&](int k, float v, bool on, int base) {
+        if (on) {
+          if (trow) trow[base + lane] = make_uint2((uint32_t)k, __float_as_uint(v));
+          Pair P;
+          pair_eval(G, tab, K, k, v, P);
+          sd0 = fmaf(P.Wd, P.E[0], sd0);
+          sd1 = fmaf(P.Wd, P.E[1], sd1);
+          sd2 = fmaf(P.Wd, P.E[2], sd2);
+          ss0 = fmaf(P.Ws, P.E[0], ss0);
+          ss1 = fmaf(P.Ws, P.E[1], ss1);
+          ss2 = fmaf(P.Ws, P.E[2], ss2);
+        }
+      });
+      if (trow && lane == 0) a.tape_n[g] = nlive;
+      sd0 = rga::wave_sum(sd0);
+      sd1 = rga::wave_sum(sd1);
+      sd2 = rga::wave_sum(sd2);
+      ss0 = rga::wave_sum(ss0);
+      ss1 = rga::wave_sum(ss1);
+      ss2 = rga::wave_sum(ss2);
+      if (lane < 3) {
+        const float sd = lane == 0 ? sd0 : (lane == 1 ? sd1 : sd2);
+        const float ss = lane == 0 ? ss0 : (lane == 1 ? ss1 : ss2);
+        const float alb = lane == 0 ? A.alb[0] : (lane == 1 ? A.alb[1] : A.alb[2]);
+        color[(size_t)lane * n + g] = srgb(alb * (1.f / kPi) * sd + A.tint * ss);
+      }
+      wave_fence();
+      if (t < entries) rows_store(plan, R, L.rows, lane);
+      g = gn;
+    }
   }
-  if (lane < 3) color[(size_t)lane * n + og] = o_col;
 }
 
 // ---- BF16X3 form: the contraction on MFMA -----------------------------------
@@ -1013,110 +1036,92 @@ shade_bwd_mfma_kernel(ShadeArgs a, int ratio, const float* __restrict__ color,
   }
 }
 
-// (up to 512 views: two workgroups per CU, four waves per SIMD, at most
-// 128 VGPRs).  With TAPE the live pairs of each Gaussian are read from the
-// forward's tape, in the order and 64-pair groups the walk would produce
-// them (so the sums are the same), instead of testing every direction: no
-// count rows, no ring.
-template <int NQ, bool TAPE>
-__global__ void __launch_bounds__(kThreads, NQ <= 2 ? 4 : 2)
-shade_bwd_kernel(ShadeArgs a, const float* __restrict__ color, const float* __restrict__ dcolor,
-                 float* __restrict__ dx, float* __restrict__ dn, float* __restrict__ dalbedo,
-                 float* __restrict__ drough, float* __restrict__ dtint,
-                 float* __restrict__ denv_part /*[grid][K][3]*/) {
-  extern __shared__ __align__(16) float tab[];
-  __shared__ int qk[kWaves][kRing];
-  __shared__ float qv[kWaves][kRing];
+// With TAPE the live pairs of each Gaussian are read from the forward's tape,
+// in the order and 64-pair groups the walk would produce them (so the sums are
+// the same), instead of testing every direction: no count rows, no ring.  (At
+// most 128 VGPRs: four waves per SIMD.)
+template <int NQ, bool TAPE, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64, TAPE || NQ <= 2 ? 4 : 2)
+shade_bwd_kernel(ShadeArgs a, int cap, const float* __restrict__ color,
+                 const float* __restrict__ dcolor, float* __restrict__ dx, float* __restrict__ dn,
+                 float* __restrict__ dalbedo, float* __restrict__ drough,
+                 float* __restrict__ dtint, float* __restrict__ denv_part /*[grid][K][3]*/) {
+  extern __shared__ __align__(16) float smem[];
+  __shared__ int ctl[2][2];   // entries listed and taken, of alternate rounds
   const int K = a.K, n = a.n, V = a.V;
-  float* denv_lds = tab + 8 * K;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  uint8_t* rows0 = TAPE ? nullptr : reinterpret_cast<uint8_t*>(tab + 11 * K) + (size_t)wave * 6 * V;
-  build_table(a, tab);
+  const Lds<WAVES> L = lds_of<WAVES>(smem, 11 * K, V, wave, !TAPE);
+  const float* tab = L.tab;
+  float* denv_lds = smem + 8 * K;
+  if (threadIdx.x < 4) (&ctl[0][0])[threadIdx.x] = 0;
+  build_table(a, smem);
   for (int i = threadIdx.x; i < 3 * K; i += blockDim.x) denv_lds[i] = 0.f;
-  __syncthreads();
   const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   RowPlan<NQ> plan;
   row_plan<NQ>(V, lane, plan);
-  const Walk walk = wave_walk(n, wave);
-  const int nblk = (walk_count(walk) + 63) / 64;
+  const float* pattr = attr_lane(a, lane);
+  const Walk walk = group_walk(n);
   // Lane c < 3 handles channel c of the per-Gaussian inputs and outputs.
   const int ch = min(lane, 2);
-  Cand C;
-  int b = -1;
-  uint64_t fm = 0ull;
-  // next block with a front-facing Gaussian; a back-facing one gets zero
-  // gradients (dx, accumulated, is left as it is)
-  auto advance = [&]() {
-    while (fm == 0ull && b + 1 < nblk) {
-      ++b;
-      cand_load(a, walk, b, lane, C);
-      if (C.g >= 0 && !C.front) {
+  for (int m0 = 0, r = 0; m0 < walk.count; m0 += cap, r ^= 1) {
+    __syncthreads();          // the last round's list is done with
+    if (threadIdx.x < 2) ctl[r ^ 1][threadIdx.x] = 0;
+    // a back-facing Gaussian gets zero gradients (dx, accumulated, is left as
+    // it is)
+    list_fill(a, walk, m0, cap, L.list, &ctl[r][0], lt, [&](int g, bool f) {
+      if (f) return;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          dn[(size_t)c * n + C.g] = 0.f;
-          dalbedo[(size_t)c * n + C.g] = 0.f;
-        }
-        drough[C.g] = 0.f;
-        dtint[C.g] = 0.f;
+      for (int c = 0; c < 3; ++c) {
+        dn[(size_t)c * n + g] = 0.f;
+        dalbedo[(size_t)c * n + g] = 0.f;
       }
-      fm = __ballot(C.front);
-    }
-  };
-  advance();
-  if (fm != 0ull) {
-    Attr A;
-    int g = cand_take(a, C, __builtin_ctzll(fm), A);
-    fm &= fm - 1;
+      drough[g] = 0.f;
+      dtint[g] = 0.f;
+    });
+    __syncthreads();
+    const int entries = ctl[r][0];
+    int t = list_take(&ctl[r][1], lane);
+    Rows<NQ> R;
+    int g = 0;
+    float v = 0.f;
     // TAPE: the Gaussian's live count and first 64 pairs (lane < K keeps
     // the read inside the Gaussian's row of the tape)
     int tl = 0;
     uint2 tw = make_uint2(0u, 0u);
-    if constexpr (TAPE) {
-      tl = a.tape_n[g];
-      if (lane < K) tw = a.tape[(size_t)g * K + lane];
-    } else {
-      rows_copy(a, plan, A.vidx, rows0);
-    }
-    float pcol = color[(size_t)ch * n + g], pdc = dcolor[(size_t)ch * n + g];
-    wait_all();
-    int cur = 0;
-    int og = -1;   // Gaussian whose outputs are pending
-    float o_dn = 0.f, o_dalb = 0.f, o_dx = 0.f, o_rough = 0.f, o_tint = 0.f;
-    for (;;) {
-      if (og >= 0) {
-        if (lane < 3) {
-          dn[(size_t)lane * n + og] = o_dn;
-          dalbedo[(size_t)lane * n + og] = o_dalb;
-          dx[(size_t)lane * n + og] = o_dx;
-        }
-        if (lane == 0) {
-          drough[og] = o_rough;
-          dtint[og] = o_tint;
-        }
+    float pcol = 0.f, pdc = 0.f, pdx = 0.f;
+    auto load = [&](int e, int& len, uint2& w) {
+      const int4 le = L.list[e];
+      const int gg = uni(le.x);
+      v = pattr[gg];
+      if constexpr (TAPE) {
+        len = a.tape_n[gg];
+        if (lane < K) w = a.tape[(size_t)gg * K + lane];
+      } else {
+        const int vidx[3] = {uni(le.y), uni(le.z), uni(le.w)};
+        rows_load(a, plan, vidx, R);
       }
-      const float col = pcol, dcol = pdc;
-      const float dx_in = dx[(size_t)ch * n + g];
-      advance();
-      const bool more = fm != 0ull;
-      Attr An;
-      int gn = -1;
+      pcol = color[(size_t)ch * n + gg];
+      pdc = dcolor[(size_t)ch * n + gg];
+      pdx = dx[(size_t)ch * n + gg];
+      return gg;
+    };
+    if (t < entries) {
+      g = load(t, tl, tw);
+      if constexpr (!TAPE) rows_store(plan, R, L.rows, lane);
+    }
+    while (t < entries) {
+      const float col = pcol, dcol = pdc, dx_in = pdx;
+      Attr A;
+      attr_read(v, A);
+      t = list_take(&ctl[r][1], lane);
+      int gn = 0;
       int tln = 0;
       uint2 twn = make_uint2(0u, 0u);
-      if (more) {
-        gn = cand_take(a, C, __builtin_ctzll(fm), An);
-        fm &= fm - 1;
-        if constexpr (TAPE) {
-          tln = a.tape_n[gn];
-          if (lane < K) twn = a.tape[(size_t)gn * K + lane];
-        } else {
-          rows_copy(a, plan, An.vidx, rows0 + (cur ^ 1) * 3 * V);
-        }
-        pcol = color[(size_t)ch * n + gn];
-        pdc = dcolor[(size_t)ch * n + gn];
-      }
+      if (t < entries) gn = load(t, tln, twn);
+      wave_fence();
       GaussCtx G;
-      gauss_setup<true>(a, A, TAPE ? nullptr : rows0 + cur * 3 * V, G);
+      gauss_setup<true>(a, A, L.rows, G);
       // dL/dL_o: lane c < 3 takes channel c, every lane reads the three
       float dLo[3], aop[3], qd[3];
       {
@@ -1143,13 +1148,13 @@ shade_bwd_kernel(ShadeArgs a, const float* __restrict__ color, const float* __re
           w = wn2;
         }
       } else {
-        live_walk(G, tab, K, V, qk[wave], qv[wave], lane, lt, [&](int k, float v, bool on, int) {
+        live_walk(G, tab, K, V, L.qk, L.qv, lane, lt, [&](int k, float v, bool on, int) {
           if (on) pair_bwd(G, tab, denv_lds, K, k, v, qd, dLo, tint, aop, acc);
         });
       }
       // per-Gaussian sums of the twelve partials over the wave: four slots
       // of three values (lane swaps and DPP), slot s summed in row s
-      float r[12];
+      float r12[12];
       {
         float v4[4][3] = {{acc.gn[0], acc.gn[1], acc.gn[2]},
                           {acc.gw[0], acc.gw[1], acc.gw[2]},
@@ -1161,13 +1166,13 @@ shade_bwd_kernel(ShadeArgs a, const float* __restrict__ color, const float* __re
         for (int sl = 0; sl < 4; ++sl)
 #pragma unroll
           for (int q = 0; q < 3; ++q)
-            r[3 * sl + q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o3[q]), 16 * sl));
+            r12[3 * sl + q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o3[q]), 16 * sl));
       }
-      // r: gn 0-2, gw 3-5, gco 6, gga 7, ts 8, sd 9-11
+      // r12: gn 0-2, gw 3-5, gco 6, gga 7, ts 8, sd 9-11
       {
-        const float gco = r[6];
-        float gn3[3] = {r[0] + gco * G.wo[0], r[1] + gco * G.wo[1], r[2] + gco * G.wo[2]};
-        float gw[3] = {r[3] + gco * G.nn[0], r[4] + gco * G.nn[1], r[5] + gco * G.nn[2]};
+        const float gco = r12[6];
+        float gn3[3] = {r12[0] + gco * G.wo[0], r12[1] + gco * G.wo[1], r12[2] + gco * G.wo[2]};
+        float gw[3] = {r12[3] + gco * G.nn[0], r12[4] + gco * G.nn[1], r12[5] + gco * G.nn[2]};
         const float pn = gn3[0] * G.nn[0] + gn3[1] * G.nn[1] + gn3[2] * G.nn[2];
         const float pw = gw[0] * G.wo[0] + gw[1] * G.wo[1] + gw[2] * G.wo[2];
         const int c = ch;
@@ -1176,32 +1181,25 @@ shade_bwd_kernel(ShadeArgs a, const float* __restrict__ color, const float* __re
         const float nnc = c == 0 ? G.nn[0] : (c == 1 ? G.nn[1] : G.nn[2]);
         const float woc = c == 0 ? G.wo[0] : (c == 1 ? G.wo[1] : G.wo[2]);
         const float dlc = c == 0 ? dLo[0] : (c == 1 ? dLo[1] : dLo[2]);
-        const float sdc = c == 0 ? r[9] : (c == 1 ? r[10] : r[11]);
-        o_dn = (gnc - nnc * pn) * G.inn;
-        // w_o = (cam - x)/|cam - x|: d/dx = -(I - w w^T)/|cam - x|
-        o_dx = dx_in - (gwc - woc * pw) * G.iwo;
-        o_dalb = dlc * sdc * (1.f / kPi);
-        o_rough = r[7];
-        o_tint = r[8];
+        const float sdc = c == 0 ? r12[9] : (c == 1 ? r12[10] : r12[11]);
+        if (lane < 3) {
+          dn[(size_t)lane * n + g] = (gnc - nnc * pn) * G.inn;
+          // w_o = (cam - x)/|cam - x|: d/dx = -(I - w w^T)/|cam - x|
+          dx[(size_t)lane * n + g] = dx_in - (gwc - woc * pw) * G.iwo;
+          dalbedo[(size_t)lane * n + g] = dlc * sdc * (1.f / kPi);
+        }
+        if (lane == 0) {
+          drough[g] = r12[7];
+          dtint[g] = r12[8];
+        }
       }
-      og = g;
-      wait_all();
       wave_fence();
-      if (!more) break;
-      A = An;
+      if constexpr (!TAPE) {
+        if (t < entries) rows_store(plan, R, L.rows, lane);
+      }
       g = gn;
       tl = tln;
       tw = twn;
-      cur ^= 1;
-    }
-    if (lane < 3) {
-      dn[(size_t)lane * n + og] = o_dn;
-      dalbedo[(size_t)lane * n + og] = o_dalb;
-      dx[(size_t)lane * n + og] = o_dx;
-    }
-    if (lane == 0) {
-      drough[og] = o_rough;
-      dtint[og] = o_tint;
     }
   }
   __syncthreads();
@@ -1243,64 +1241,76 @@ denv_reduce_kernel(int K, int he, int we, int parts, const float* __restrict__ p
   }
 }
 
-template <int NQ>
-void set_lds_limits_nq() {
-  const void* ks[] = {reinterpret_cast<const void*>(shade_fwd_kernel<NQ>),
-                      reinterpret_cast<const void*>(shade_bwd_kernel<NQ, false>),
-                      reinterpret_cast<const void*>(shade_bwd_kernel<NQ, true>)};
-  for (const void* k : ks) hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+constexpr size_t kLdsMax = 160 * 1024;
+constexpr size_t kLdsStatic = 64;    // the kernels' counters
+
+// What the FP32 kernels accept: the direction table (8 K floats; the adjoint
+// adds 3 K for the environment gradient) and two sets of count rows for each of
+// eight waves in 152 KB (with a tape: the table and the environment sums).
+inline size_t fp32_need(int K, int V, bool adjoint, bool taped) {
+  return (size_t)(adjoint ? 11 : 8) * K * sizeof(float) + (taped ? 0 : (size_t)48 * V);
 }
 
-void set_lds_limits() {
-  static bool done = false;
-  if (done) return;
-  set_lds_limits_nq<2>();
-  set_lds_limits_nq<6>();
-  done = true;
+// LDS of a kernel of `waves` waves without its list
+inline size_t fp32_lds(int K, int V, bool adjoint, bool taped, int waves) {
+  return (size_t)(adjoint ? 11 : 8) * K * sizeof(float) +
+         (taped ? 0 : (size_t)waves * (3 * (size_t)V + 8 * kRing));
 }
 
-// LDS of the FP32 kernels (dynamic part, at most 152 KB beside the static
-// 8 KB of the rings): the direction table (8 K floats; the adjoint adds 3 K
-// for the environment gradient) and each wave's double buffer of three
-// count rows (6 V bytes).
-inline size_t fp32_lds(int K, int V, bool adjoint) {
-  return (size_t)(adjoint ? 11 : 8) * K * sizeof(float) + (size_t)kWaves * 6 * V;
+template <int NQ, int WAVES>
+const void* fp32_kernel_of(bool adjoint, bool taped) {
+  // (the adjoint that reads a tape copies no rows: one instance serves every
+  // view count)
+  if (adjoint && taped) return reinterpret_cast<const void*>(shade_bwd_kernel<2, true, WAVES>);
+  // (the adjoint without one keeps six pieces of rows in eight waves only: 128
+  // registers of 16 do not hold them)
+  if (adjoint) return reinterpret_cast<const void*>(shade_bwd_kernel<NQ, false, NQ <= 2 ? WAVES : 8>);
+  return reinterpret_cast<const void*>(shade_fwd_kernel<NQ, WAVES>);
 }
 
-// Persistent grid: as many workgroups as the device holds at once (every
-// workgroup resident, so the static division of the Gaussians over the
-// waves is also the division of the work), from the occupancy of the exact
-// kernel at its LDS size; never more than one wave per Gaussian.
-int grid_for(const void* kernel, int n, size_t lds) {
-  set_lds_limits();
-  static int ncu = 0;
-  if (ncu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        ncu <= 0)
-      ncu = 256;
-  }
+struct Launch {
+  const void* kernel;
+  int waves, grid, cap;
+  size_t lds;
+};
+
+// The FP32 kernel for these sizes and its launch.  A persistent grid, as many
+// workgroups as the device holds at once (from the occupancy of the exact
+// kernel at its LDS size), never more than one wave per Gaussian.
+Launch fp32_launch(int n, int K, int V, bool adjoint, bool taped) {
+  Launch l;
+  int dev = 0, ncu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
+    ncu = 256;
+  const bool small = 3 * V <= 2048;      // pieces of 1024 bytes of three count rows: at most 2
+  const size_t room = kLdsMax - kLdsStatic;
+  // Sixteen waves share one table where the LDS holds their rows and a list, so
+  // that four waves per SIMD are resident up to 2048 directions and 1024 views
+  // (eight -> sixteen, forward: 200k Gaussians there 491 -> 294 us, 100k at 512
+  // directions 57 -> 53 us, 10k 18 -> 17 us); below one Gaussian per wave of
+  // such workgroups on every CU, eight spread over more CUs.
+  l.waves = n > 16 * ncu && fp32_lds(K, V, adjoint, taped, 16) + 16 * 256 <= room &&
+                    !(adjoint && !taped && !small) ? 16 : 8;
+  if (l.waves == 16)
+    l.kernel = small ? fp32_kernel_of<2, 16>(adjoint, taped) : fp32_kernel_of<6, 16>(adjoint, taped);
+  else
+    l.kernel = small ? fp32_kernel_of<2, 8>(adjoint, taped) : fp32_kernel_of<6, 8>(adjoint, taped);
+  const size_t base = fp32_lds(K, V, adjoint, taped, l.waves);
+  const size_t least = base + std::min<size_t>(16 * 128, room - base);
+  if (2 * least > kLdsMax)   // (the attribute is kept per device)
+    hipFuncSetAttribute(l.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)room);
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, lds) != hipSuccess ||
-      per_cu < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, l.kernel, 64 * l.waves, least) !=
+          hipSuccess || per_cu < 1)
     per_cu = 1;
-  int grid = ncu * per_cu;
-  const int need = (int)rga::ceil_div(n, kWaves);
-  return grid < need ? grid : (need > 0 ? need : 1);
-}
-
-// The FP32 kernel instance for the number of 1024-byte pieces of a
-// Gaussian's three count rows.
-// (The adjoint that reads a tape copies no rows: one instance serves every
-// view count.)
-const void* fp32_kernel(bool adjoint, int nq, bool tape = false) {
-  if (adjoint && tape) return reinterpret_cast<const void*>(shade_bwd_kernel<2, true>);
-  if (nq <= 2)
-    return adjoint ? reinterpret_cast<const void*>(shade_bwd_kernel<2, false>)
-                   : reinterpret_cast<const void*>(shade_fwd_kernel<2>);
-  return adjoint ? reinterpret_cast<const void*>(shade_bwd_kernel<6, false>)
-                 : reinterpret_cast<const void*>(shade_fwd_kernel<6>);
+  // the longest list, up to 1024 entries, that leaves room for as many
+  // workgroups (LDS is given in steps of 1280 bytes)
+  const size_t share = kLdsMax / 1280 / per_cu * 1280 - kLdsStatic;
+  l.cap = (int)(std::min<size_t>(share > least ? share - base : least - base, 16 * 1024) / 16);
+  l.lds = base + 16 * (size_t)l.cap;
+  l.grid = std::max(1, std::min(ncu * per_cu, (int)rga::ceil_div(n, l.waves)));
+  return l;
 }
 
 int check_args(const char* fn, int n, const float* x, const float* nrm, const float* albedo,
@@ -1421,18 +1431,16 @@ extern "C" int shade_gaussians(void* stream, int n, const float* x, const float*
     RGA_CHECK_LAUNCH("shade_gaussians");
     return RGA_OK;
   }
-  const size_t lds = fp32_lds(a.K, a.V, false);
-  if (lds > 152 * 1024)
+  const size_t need = fp32_need(a.K, a.V, false, false);
+  if (need > 152 * 1024)
     return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians: %d directions and %d views need %zu B of LDS",
-                     a.K, a.V, lds);
+                     a.K, a.V, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int nq = (int)rga::ceil_div(3 * a.V, 1024);
-  const void* kern = fp32_kernel(false, nq);
-  const dim3 grid(grid_for(kern, n, lds));
+  Launch l = fp32_launch(n, a.K, a.V, false, false);
   {
     rga::TimedLaunch tl("shade_fwd", s);
-    void* args[] = {&a, &color, &front};
-    if (hipLaunchKernel(kern, grid, dim3(kThreads), args, lds, s) != hipSuccess)
+    void* args[] = {&a, &l.cap, &color, &front};
+    if (hipLaunchKernel(l.kernel, dim3(l.grid), dim3(64 * l.waves), args, l.lds, s) != hipSuccess)
       return rga::fail(RGA_EHIP, "shade_gaussians: launch failed");
   }
   RGA_CHECK_LAUNCH("shade_gaussians");
@@ -1506,23 +1514,21 @@ extern "C" int shade_gaussians_backward(void* stream, int n, const float* x, con
     return RGA_OK;
   }
   const bool taped = a.tape != nullptr;
-  // with a tape: the direction table and the environment sums only
-  const size_t lds = taped ? (size_t)11 * a.K * sizeof(float) : fp32_lds(a.K, a.V, true);
-  if (lds > 152 * 1024)
+  const size_t need = fp32_need(a.K, a.V, true, taped);
+  if (need > 152 * 1024)
     return rga::fail(RGA_EUNSUPPORTED,
                      "shade_gaussians_backward: %d directions and %d views need %zu B of LDS", a.K,
-                     a.V, lds);
-  const int nq = (int)rga::ceil_div(3 * a.V, 1024);
-  const void* kern = fp32_kernel(true, nq, taped);
-  const int grid = grid_for(kern, n, lds);
+                     a.V, need);
+  Launch l = fp32_launch(n, a.K, a.V, true, taped);
+  const int grid = l.grid;
   if (!ws || ws_bytes < (size_t)grid * 3 * a.K * sizeof(float))
     return rga::fail(RGA_ECAPACITY, "shade_gaussians_backward: workspace too small");
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* part = static_cast<float*>(ws);
   if (n > 0) {
     rga::TimedLaunch tl("shade_bwd", s);
-    void* args[] = {&a, &color, &dcolor, &dx, &dn, &dalbedo, &drough, &dtint, &part};
-    if (hipLaunchKernel(kern, dim3(grid), dim3(kThreads), args, lds, s) != hipSuccess)
+    void* args[] = {&a, &l.cap, &color, &dcolor, &dx, &dn, &dalbedo, &drough, &dtint, &part};
+    if (hipLaunchKernel(l.kernel, dim3(grid), dim3(64 * l.waves), args, l.lds, s) != hipSuccess)
       return rga::fail(RGA_EHIP, "shade_gaussians_backward: launch failed");
   }
   RGA_LAUNCH("shade_denv", denv_reduce_kernel, dim3(rga::ceil_div(3 * a.K, 64)), dim3(1024), 0, s,
