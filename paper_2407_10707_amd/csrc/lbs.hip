@@ -98,75 +98,143 @@ lbs_bwd_kernel(int n, int J, const float* __restrict__ skin, const int32_t* __re
 namespace {
 
 // Pose gradient: dS_j[r][c] = sum_i w_ij (dx'_i[r] (x_i, 1)[c] + dn'_i[r] (n_i, 0)[c]
-// + dA_i[r][c] for c < 3),
-// w_ij the summed weights of joint j in Gaussian i's slots.  Workgroups over
-// (chunk of Gaussians, joint); per-workgroup sums, then a fixed-order sum
-// over the chunks (no atomics: every joint is shared by many Gaussians).
-constexpr int kPoseChunk = 2048;
+// + dA_i[r][c] for c < 3), w_ij the summed weights of joint j in Gaussian i's
+// slots.  A wave owns two Gaussians per lane: the twelve factors of each, which
+// all of its joints share, stay in registers, and the wave takes the distinct
+// joints of its 512 slots one after the other (Gaussians that are neighbours
+// share them) and adds each joint's wave sum into its own LDS row.  The waves'
+// rows, then the workgroups' rows, are added in a fixed order (no atomics).
+// Every input is read once: with a workgroup per joint and chunk that read all
+// indices and skipped the other joints', 100k Gaussians and 24 joints took
+// 33 us and the sum over the chunks 12 us, now 9 and 4 us.
+constexpr int kPoseWaves = 4;
+constexpr int kPoseLane = 2;                                   // Gaussians per lane
+constexpr int kPoseChunk = kPoseWaves * 64 * kPoseLane;        // per workgroup
 
-__global__ void __launch_bounds__(kBlock)
-lbs_pose_grad_kernel(int n, const int32_t* __restrict__ jidx, const float* __restrict__ jw,
+__global__ void __launch_bounds__(kPoseWaves * 64)
+lbs_pose_grad_kernel(int n, int J, const int32_t* __restrict__ jidx, const float* __restrict__ jw,
                      const float* __restrict__ x, const float* __restrict__ disp,
                      const float* __restrict__ nrm, const float* __restrict__ dxo,
                      const float* __restrict__ dno, const float* __restrict__ dA,
                      float* __restrict__ part) {
-  __shared__ float red[12][kBlock];
-  const int j = blockIdx.y, c = blockIdx.x;
-  const int i0 = c * kPoseChunk, i1 = min(n, i0 + kPoseChunk);
-  float acc[12];
+  extern __shared__ float rows[];                              // [wave][J][12]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int k = threadIdx.x; k < kPoseWaves * J * 12; k += blockDim.x) rows[k] = 0.f;
+  __syncthreads();
+  float* row = rows + wave * J * 12;
+  const int i0 = blockIdx.x * kPoseChunk + wave * 64 * kPoseLane + lane;
+  float M[kPoseLane][12], w[kPoseLane][4];
+  int id[kPoseLane][4];
 #pragma unroll
-  for (int q = 0; q < 12; ++q) acc[q] = 0.f;
-  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-    float w = 0.f;
+  for (int k = 0; k < kPoseLane; ++k) {
+    const int i = i0 + 64 * k;
+    const bool have = i < n;
+    const size_t c = have ? i : 0;
+    // (slots that add nothing: no weight, or no such joint)
+#pragma unroll
+    for (int sl = 0; sl < 4; ++sl) {
+      id[k][sl] = jidx[(size_t)sl * n + c];
+      w[k][sl] = jw[(size_t)sl * n + c];
+    }
 #pragma unroll
     for (int sl = 0; sl < 4; ++sl)
-      if (jidx[(size_t)sl * n + i] == j) w += jw[(size_t)sl * n + i];
-    if (w == 0.f) continue;
-    const float xv[3] = {disp ? x[i] + disp[i] : x[i], disp ? x[n + i] + disp[n + i] : x[n + i],
-                         disp ? x[2 * n + i] + disp[2 * n + i] : x[2 * n + i]};
+      if (!have || w[k][sl] == 0.f || id[k][sl] < 0 || id[k][sl] >= J) id[k][sl] = -1;
+    float xv[3], g[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      xv[q] = x[(size_t)q * n + c];
+      if (disp) xv[q] += disp[(size_t)q * n + c];
+      g[q] = dxo[(size_t)q * n + c];
+    }
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
-      const float g = w * dxo[(size_t)r * n + i];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) acc[4 * r + q] = fmaf(g, xv[q], acc[4 * r + q]);
-      acc[4 * r + 3] += g;
+      for (int q = 0; q < 3; ++q) M[k][4 * r + q] = g[r] * xv[q];
+      M[k][4 * r + 3] = g[r];
     }
     if (dA)
 #pragma unroll
       for (int r = 0; r < 3; ++r)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) acc[4 * r + q] = fmaf(w, dA[(size_t)(3 * r + q) * n + i], acc[4 * r + q]);
-    if (dno) {
-      const float nv[3] = {nrm[i], nrm[n + i], nrm[2 * n + i]};
+        for (int q = 0; q < 3; ++q) M[k][4 * r + q] += dA[(size_t)(3 * r + q) * n + c];
+    if (dno)
 #pragma unroll
-      for (int r = 0; r < 3; ++r) {
-        const float g = w * dno[(size_t)r * n + i];
+      for (int r = 0; r < 3; ++r)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) acc[4 * r + q] = fmaf(g, nv[q], acc[4 * r + q]);
+        for (int q = 0; q < 3; ++q)
+          M[k][4 * r + q] = fmaf(dno[(size_t)r * n + c], nrm[(size_t)q * n + c], M[k][4 * r + q]);
+  }
+  for (;;) {
+    // the next joint: that of the first lane with a slot left
+    int mine = -1;
+#pragma unroll
+    for (int k = 0; k < kPoseLane; ++k)
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl) mine = max(mine, id[k][sl]);
+    const uint64_t left = __ballot(mine >= 0);
+    if (left == 0ull) break;
+    const int j = __builtin_amdgcn_readlane(mine, __builtin_ctzll(left));
+    float v[4][3] = {};
+#pragma unroll
+    for (int k = 0; k < kPoseLane; ++k) {
+      float wj = 0.f;
+      bool has = false;
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl) {
+        const bool hit = id[k][sl] == j;
+        wj += hit ? w[k][sl] : 0.f;
+        has |= hit;
+        id[k][sl] = hit ? -1 : id[k][sl];
+      }
+      if (has) {
+#pragma unroll
+        for (int q = 0; q < 12; ++q) v[q / 3][q % 3] = fmaf(wj, M[k][q], v[q / 3][q % 3]);
       }
     }
+    float o[3];
+    rga::slot_sums4<3>(v, o);
+    // row s of the wave holds values 3 s .. 3 s + 2
+    if ((lane & 15) < 3) {
+      const int q = lane & 15;
+      row[12 * j + 3 * (lane >> 4) + q] = q == 0 ? o[0] : (q == 1 ? o[1] : o[2]);
+    }
   }
-#pragma unroll
-  for (int q = 0; q < 12; ++q) red[q][threadIdx.x] = acc[q];
   __syncthreads();
-  for (int o = kBlock / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
+  for (int k = threadIdx.x; k < J * 12; k += blockDim.x) {
+    float t = rows[k];
 #pragma unroll
-      for (int q = 0; q < 12; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + o];
-    __syncthreads();
+    for (int v = 1; v < kPoseWaves; ++v) t += rows[v * J * 12 + k];
+    part[(size_t)blockIdx.x * J * 12 + k] = t;
   }
-  if (threadIdx.x < 12)
-    part[((size_t)c * gridDim.y + j) * 12 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void __launch_bounds__(kBlock)
+// 64 values per workgroup; its 16 waves add every sixteenth chunk each.
+__global__ void __launch_bounds__(1024)
 lbs_pose_grad_final(int n_joints, int chunks, const float* __restrict__ part,
                     float* __restrict__ dskin) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 12 * n_joints) return;
-  float s = 0.f;
-  for (int c = 0; c < chunks; ++c) s += part[(size_t)c * n_joints * 12 + t];
-  dskin[t] = s;
+  __shared__ float red[16][64];
+  const int o = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int t = blockIdx.x * 64 + o, count = 12 * n_joints;
+  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+  if (t < count) {
+    const float* p = part + t;
+    int c = grp;
+    for (; c + 48 < chunks; c += 64) {
+      s0 += p[(size_t)c * count];
+      s1 += p[(size_t)(c + 16) * count];
+      s2 += p[(size_t)(c + 32) * count];
+      s3 += p[(size_t)(c + 48) * count];
+    }
+    for (; c < chunks; c += 16) s0 += p[(size_t)c * count];
+  }
+  red[grp][o] = (s0 + s1) + (s2 + s3);
+  __syncthreads();
+  for (int h = 8; h > 0; h >>= 1) {
+    if (grp < h) red[grp][o] += red[grp + h][o];
+    __syncthreads();
+  }
+  if (grp == 0 && t < count) dskin[t] = red[0][o];
 }
 
 int pose_chunks(int n) { return (int)rga::ceil_div(n > 0 ? n : 1, kPoseChunk); }
@@ -179,8 +247,10 @@ namespace {
 // R_j = exp([theta_j]x) = I + a K + b K^2 (a = sin t / t, b = (1 - cos t) / t^2,
 // series near t = 0), G_j = G_p R_j, P_j = P_p + G_p (J_j - J_p), a root
 // (parent outside 0..j-1) has G = R, P = J; skin_j = [G_j | P_j - G_j J_j].
-// One workgroup: the Rodrigues matrices in parallel, the chain in joint order
-// by one thread, the rows written in parallel.
+// One workgroup, a thread per joint (at most 256): the Rodrigues matrices, then
+// the chain one depth of the tree at a time, its joints in parallel.  Bound by
+// latency (one thread walked the joints in order: 24 joints 14 us, the adjoint
+// 35 us; now 8 and 13 us).
 __device__ inline void rodrigues(const float* th, float* R, float& a, float& b, float& ap,
                                  float& bp) {
   const float t2 = fmaf(th[2], th[2], fmaf(th[1], th[1], th[0] * th[0]));
@@ -213,9 +283,12 @@ __device__ inline void rodrigues(const float* th, float* R, float& a, float& b, 
 }
 
 __device__ inline void mat3_mul(const float* A, const float* B, float* C) {
+#pragma unroll
   for (int r = 0; r < 3; ++r)
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
       float v = 0.f;
+#pragma unroll
       for (int m = 0; m < 3; ++m) v = fmaf(A[3 * r + m], B[3 * m + c], v);
       C[3 * r + c] = v;
     }
@@ -226,35 +299,65 @@ __device__ inline int parent_of(const int32_t* parents, int j) {
   return (p >= 0 && p < j) ? p : -1;
 }
 
+static_assert(kMaxJoints <= kBlock, "a thread per joint");
+
 struct Chain {
   float R[kMaxJoints][9], G[kMaxJoints][9], P[kMaxJoints][3];
+  float at[kMaxJoints][3];   // rest joints
+  int parent[kMaxJoints];
+  int deepest;
 };
 
-__device__ void forward_chain(int J, const float* theta, const float* joints,
-                              const int32_t* parents, Chain& ch) {
-  for (int j = threadIdx.x; j < J; j += blockDim.x) {
-    float a, b, ap, bp;
-    rodrigues(theta + 3 * j, ch.R[j], a, b, ap, bp);
+// The Rodrigues factors and depth of this thread's joint.
+struct Joint {
+  float a, b, ap, bp;
+  int p, depth;
+};
+
+__device__ Joint forward_chain(int J, const float* theta, const float* joints,
+                               const int32_t* parents, Chain& ch) {
+  const int j = threadIdx.x;
+  Joint t = {};
+  t.p = -1;
+  t.depth = -1;
+  if (j == 0) ch.deepest = 0;
+  if (j < J) {
+    t.p = parent_of(parents, j);
+    ch.parent[j] = t.p;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) ch.at[j][q] = joints[3 * j + q];
+    rodrigues(theta + 3 * j, ch.R[j], t.a, t.b, t.ap, t.bp);
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int j = 0; j < J; ++j) {
-      const int p = parent_of(parents, j);
-      if (p < 0) {
+  if (j < J) {
+    t.depth = 0;
+    for (int p = t.p; p >= 0; p = ch.parent[p]) ++t.depth;
+    if (t.depth > 0) atomicMax(&ch.deepest, t.depth);
+  }
+  __syncthreads();
+  const int deepest = ch.deepest;
+  for (int d = 0; d <= deepest; ++d) {
+    if (t.depth == d) {
+      if (t.p < 0) {
+#pragma unroll
         for (int q = 0; q < 9; ++q) ch.G[j][q] = ch.R[j][q];
-        for (int q = 0; q < 3; ++q) ch.P[j][q] = joints[3 * j + q];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) ch.P[j][q] = ch.at[j][q];
       } else {
-        mat3_mul(ch.G[p], ch.R[j], ch.G[j]);
+        mat3_mul(ch.G[t.p], ch.R[j], ch.G[j]);
+#pragma unroll
         for (int r = 0; r < 3; ++r) {
-          float v = ch.P[p][r];
+          float v = ch.P[t.p][r];
+#pragma unroll
           for (int m = 0; m < 3; ++m)
-            v = fmaf(ch.G[p][3 * r + m], joints[3 * j + m] - joints[3 * p + m], v);
+            v = fmaf(ch.G[t.p][3 * r + m], ch.at[j][m] - ch.at[t.p][m], v);
           ch.P[j][r] = v;
         }
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
+  return t;
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -262,58 +365,90 @@ pose_skin_kernel(int J, const float* __restrict__ theta, const float* __restrict
                  const int32_t* __restrict__ parents, float* __restrict__ skin) {
   __shared__ Chain ch;
   forward_chain(J, theta, joints, parents, ch);
-  for (int j = threadIdx.x; j < J; j += blockDim.x)
-    for (int r = 0; r < 3; ++r) {
-      float t = ch.P[j][r];
-      for (int m = 0; m < 3; ++m) t = fmaf(-ch.G[j][3 * r + m], joints[3 * j + m], t);
-      for (int c = 0; c < 3; ++c) skin[12 * j + 4 * r + c] = ch.G[j][3 * r + c];
-      skin[12 * j + 4 * r + 3] = t;
-    }
+  const int j = threadIdx.x;
+  if (j >= J) return;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    float t = ch.P[j][r];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) t = fmaf(-ch.G[j][3 * r + m], ch.at[j][m], t);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) skin[12 * j + 4 * r + c] = ch.G[j][3 * r + c];
+    skin[12 * j + 4 * r + 3] = t;
+  }
 }
 
-// Adjoint: dG_j = dS_j[:, :3] - dt_j J_j^T, dP_j = dt_j; in reverse joint
-// order dG_p += dG_j R_j^T + dP_j (J_j - J_p)^T, dP_p += dP_j, dR_j = G_p^T dG_j
-// (dR_j = dG_j at a root); then dtheta_j from dR_j through Rodrigues.
+// Adjoint: dG_j = dS_j[:, :3] - dt_j J_j^T, dP_j = dt_j; from the deepest joints
+// up dG_p += dG_j R_j^T + dP_j (J_j - J_p)^T, dP_p += dP_j (a joint adds its
+// children's shares in descending order), dR_j = G_p^T dG_j (dR_j = dG_j at a
+// root); then dtheta_j from dR_j through Rodrigues.
 __global__ void __launch_bounds__(kBlock)
 pose_skin_bwd_kernel(int J, const float* __restrict__ theta, const float* __restrict__ joints,
                      const int32_t* __restrict__ parents, const float* __restrict__ dskin,
                      float* __restrict__ dtheta, int accumulate) {
   __shared__ Chain ch;
-  __shared__ float dG[kMaxJoints][9], dP[kMaxJoints][3], dR[kMaxJoints][9];
-  forward_chain(J, theta, joints, parents, ch);
-  for (int j = threadIdx.x; j < J; j += blockDim.x)
+  __shared__ float share[kMaxJoints][12];   // a joint's addition to its parent's dG and dP
+  __shared__ int child[kMaxJoints], next[kMaxJoints];   // highest child, next lower sibling
+  const int j = threadIdx.x;
+  float dG[9], dP[3], D[9];
+  if (j < J) {
+    child[j] = -1;
+#pragma unroll
     for (int r = 0; r < 3; ++r) {
-      const float dt = dskin[12 * j + 4 * r + 3];
-      dP[j][r] = dt;
-      for (int c = 0; c < 3; ++c) dG[j][3 * r + c] = dskin[12 * j + 4 * r + c] - dt * joints[3 * j + c];
-    }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int j = J - 1; j >= 0; --j) {
-      const int p = parent_of(parents, j);
-      if (p < 0) {
-        for (int q = 0; q < 9; ++q) dR[j][q] = dG[j][q];
-        continue;
-      }
-      for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) {
-          float vR = 0.f, vG = 0.f;
-          for (int m = 0; m < 3; ++m) {
-            vR = fmaf(ch.G[p][3 * m + r], dG[j][3 * m + c], vR);       // G_p^T dG_j
-            vG = fmaf(dG[j][3 * r + m], ch.R[j][3 * c + m], vG);       // dG_j R_j^T
-          }
-          dR[j][3 * r + c] = vR;
-          dG[p][3 * r + c] += vG + dP[j][r] * (joints[3 * j + c] - joints[3 * p + c]);
-        }
-      for (int r = 0; r < 3; ++r) dP[p][r] += dP[j][r];
+      dP[r] = dskin[12 * j + 4 * r + 3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) dG[3 * r + c] = dskin[12 * j + 4 * r + c];
     }
   }
+  const Joint t = forward_chain(J, theta, joints, parents, ch);
+  if (j < J) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) dG[3 * r + c] -= dP[r] * ch.at[j][c];
+    int s = -1;
+    if (t.p >= 0) {
+      atomicMax(&child[t.p], j);
+      for (int k = t.p + 1; k < j; ++k)
+        if (ch.parent[k] == t.p) s = k;
+    }
+    next[j] = s;
+  }
   __syncthreads();
-  for (int j = threadIdx.x; j < J; j += blockDim.x) {
+  for (int d = ch.deepest; d >= 0; --d) {
+    if (t.depth == d) {
+      for (int k = child[j]; k >= 0; k = next[k]) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) dG[q] += share[k][q];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dP[q] += share[k][9 + q];
+      }
+      if (t.p < 0) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) D[q] = dG[q];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            float vR = 0.f, vG = 0.f;
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+              vR = fmaf(ch.G[t.p][3 * m + r], dG[3 * m + c], vR);      // G_p^T dG_j
+              vG = fmaf(dG[3 * r + m], ch.R[j][3 * c + m], vG);        // dG_j R_j^T
+            }
+            D[3 * r + c] = vR;
+            share[j][3 * r + c] = vG + dP[r] * (ch.at[j][c] - ch.at[t.p][c]);
+          }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) share[j][9 + r] = dP[r];
+      }
+    }
+    __syncthreads();
+  }
+  if (j < J) {
     const float* th = theta + 3 * j;
-    float R[9], a, b, ap, bp;
-    rodrigues(th, R, a, b, ap, bp);
-    const float* D = dR[j];
+    const float a = t.a, b = t.b, ap = t.ap, bp = t.bp;
     const float K[9] = {0.f, -th[2], th[1], th[2], 0.f, -th[0], -th[1], th[0], 0.f};
     float K2[9];
     mat3_mul(K, K, K2);
@@ -322,6 +457,7 @@ pose_skin_bwd_kernel(int J, const float* __restrict__ theta, const float* __rest
       dK = fmaf(D[q], K[q], dK);
       dK2 = fmaf(D[q], K2[q], dK2);
     }
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
       float E[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       if (k == 0) { E[5] = -1.f; E[7] = 1.f; }
@@ -390,10 +526,11 @@ extern "C" int lbs_skin_pose_grad(void* stream, int n, int n_joints, const int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int chunks = pose_chunks(n);
   float* part = static_cast<float*>(ws);
-  RGA_LAUNCH("lbs_pose_grad", lbs_pose_grad_kernel, dim3(chunks, n_joints), dim3(kBlock), 0, s, n,
-             jidx, jw, x, disp, nrm, dx_out, dn_out, dA, part);
-  RGA_LAUNCH("lbs_pose_grad_final", lbs_pose_grad_final, dim3(rga::ceil_div(12 * n_joints, kBlock)),
-             dim3(kBlock), 0, s, n_joints, chunks, part, dskin);
+  RGA_LAUNCH("lbs_pose_grad", lbs_pose_grad_kernel, dim3(chunks), dim3(kPoseWaves * 64),
+             (size_t)kPoseWaves * n_joints * 12 * sizeof(float), s, n, n_joints, jidx, jw, x, disp, nrm,
+             dx_out, dn_out, dA, part);
+  RGA_LAUNCH("lbs_pose_grad_final", lbs_pose_grad_final, dim3(rga::ceil_div(12 * n_joints, 64)),
+             dim3(1024), 0, s, n_joints, chunks, part, dskin);
   RGA_CHECK_LAUNCH("lbs_skin_pose_grad");
   return RGA_OK;
 }
