@@ -163,30 +163,34 @@ knn_count_kernel(int nr, const float* __restrict__ ref, const float* __restrict_
   rank[i] = atomicAdd(&count[c], 1u);
 }
 
-// exclusive scan of the cell counts, one workgroup
+// Exclusive scan of the cell counts, one workgroup of eight cells per thread
+// (counts past the last cell are taken as zero, so the entry after it is the
+// total).
 __global__ void __launch_bounds__(1024)
 knn_scan_kernel(const float* __restrict__ bounds, const uint32_t* __restrict__ count,
                 uint32_t* __restrict__ start) {
-  __shared__ uint32_t part[1024];
+  static_assert(kMaxCells == 8 * 1024, "eight cells per thread");
+  __shared__ uint32_t part[16];
   const int cells = (int)bounds[8];
-  const int per = (cells + 1023) / 1024;
-  const int c0 = threadIdx.x * per, c1 = min(cells, c0 + per);
-  uint32_t s = 0;
-  for (int c = c0; c < c1; ++c) s += count[c];
-  part[threadIdx.x] = s;
+  const int c0 = 8 * threadIdx.x;
+  uint32_t v[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t] = count[c0 + t];
+  uint32_t s = 0u;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const uint32_t x = c0 + t < cells ? v[t] : 0u;
+    v[t] = s;
+    s += x;
+  }
+  const uint32_t inc = rga::wave_scan(s);
+  if ((threadIdx.x & 63) == 63) part[threadIdx.x >> 6] = inc;
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const uint32_t v = threadIdx.x >= o ? part[threadIdx.x - o] : 0u;
-    __syncthreads();
-    part[threadIdx.x] += v;
-    __syncthreads();
-  }
-  uint32_t run = threadIdx.x ? part[threadIdx.x - 1] : 0u;
-  for (int c = c0; c < c1; ++c) {
-    start[c] = run;
-    run += count[c];
-  }
-  if (threadIdx.x == 1023) start[cells] = part[1023];
+  uint32_t base = inc - s;
+  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) base += part[w];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) start[c0 + t] = base + v[t];
+  if (threadIdx.x == 1023) start[kMaxCells] = base + s;
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -203,20 +207,33 @@ __device__ inline bool before(float d, int j, float e, int l) { return d < e || 
 
 // Queries are taken in the order of their grid cells (a counting sort:
 // per-cell counts with ranks, one-workgroup scan, fill), so that the lanes
-// of a wave search the same or neighbouring cells.
+// of a wave search the same or neighbouring cells.  Consecutive queries of one
+// cell (points stored grouped by vertex) take their ranks with one atomic: one
+// each returned one after the other in the L2 (100k Gaussians over 3.4k cells
+// 33 us, now 9 us).
 __global__ void __launch_bounds__(kBlock)
 knn_qcell_kernel(int n, const float* __restrict__ q, const float* __restrict__ bounds,
                  uint32_t* __restrict__ qcount, uint32_t* __restrict__ qcell,
                  uint32_t* __restrict__ qrank) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const int l = min(i, n - 1);            // every lane takes part in the runs
   const int gx = (int)bounds[5], gy = (int)bounds[6], gz = (int)bounds[7];
-  const int cx = cell_of(q[i], bounds[0], bounds[3], gx);
-  const int cy = cell_of(q[n + i], bounds[1], bounds[3], gy);
-  const int cz = cell_of(q[2 * n + i], bounds[2], bounds[3], gz);
+  const int cx = cell_of(q[l], bounds[0], bounds[3], gx);
+  const int cy = cell_of(q[n + l], bounds[1], bounds[3], gy);
+  const int cz = cell_of(q[2 * n + l], bounds[2], bounds[3], gz);
   const uint32_t c = (uint32_t)((cz * gy + cy) * gx + cx);
-  qcell[i] = c;
-  qrank[i] = atomicAdd(&qcount[c], 1u);
+  const int lane = threadIdx.x & 63;
+  int end;
+  const bool head = rga::wave_run(i < n ? (int)c : -1, end);
+  const uint64_t heads = __ballot(head);
+  const int first = 63 - __builtin_clzll(heads & (~0ull >> (63 - lane)));
+  uint32_t at = 0u;
+  if (head && i < n) at = atomicAdd(&qcount[c], (uint32_t)(end - lane));
+  at = __shfl(at, first, 64);
+  if (i < n) {
+    qcell[i] = c;
+    qrank[i] = at + (uint32_t)(lane - first);
+  }
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -228,41 +245,60 @@ knn_qfill_kernel(int n, const uint32_t* __restrict__ qstart, const uint32_t* __r
 
 // Small k (<= 4): four lanes per query (a quad), so that a search of a
 // few hundred thousand queries still has several waves per SIMD to hide
-// the latency of its dependent loads.  The quad walks the shells row by
-// row as one; the records of a row are dealt out to its lanes in turn (so
-// a quad reads consecutive records), each lane keeping the best k of its
-// own records, sorted, in the last k of four register slots (the slots
-// before them hold -inf sentinels that nothing is ever placed before, so
-// the worst kept entry is always the last slot).  At the end of each shell the quad merges its four lists:
-// k rounds of a minimum over the quad (two DPP exchanges), the lane that
-// holds the minimum moving to its next entry; the k-th of the merge drives
-// the stop rule and prunes the lanes' candidates.
-constexpr int kQuadBatch = 2;            // records per lane loaded together
+// the latency of its dependent loads.  The lanes look up the rows of a shell, the
+// quad lists those that hold anything to visit, and deals their records out to
+// its lanes in turn, each keeping the best K of its own, sorted.  A candidate is one 64-bit
+// key, distance^2 above index (a non-negative float's bits are in its order),
+// placed without a branch.  At the end of each shell the quad merges its four
+// lists: K rounds of a minimum over the quad (two DPP exchanges), the lane that
+// holds the minimum moving to its next entry; the K-th of the merge drives the
+// stop rule and prunes the lanes' candidates and the next shell's rows and
+// cells: those further from the query than the K-th so far hold nothing nearer
+// (a mesh fills a small part of the grid's cells, about 10 vertices in each at
+// 6,840 and up to 78, so after its own cell a query needs few of the 26 around
+// it).  Every wave is resident at once and the longest sets the time: 100k
+// queries 39 us with every row dealt out and none pruned, now 27 us.
+constexpr int kQuadBatch = 4;            // records per lane loaded together
+constexpr int kQuadRows = 3;             // rows per lane looked up together
 
-// (d, j) <- the smallest of the quad's four in (distance^2, index) order
-__device__ inline void quad_min(float& d, int& j) {
-  float od = __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(d), __float_as_int(d), 0xB1, 0xf, 0xf, false));
-  int oj = __builtin_amdgcn_update_dpp(j, j, 0xB1, 0xf, 0xf, false);
-  if (before(od, oj, d, j)) {
-    d = od;
-    j = oj;
-  }
-  od = __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(d), __float_as_int(d), 0x4E, 0xf, 0xf, false));
-  oj = __builtin_amdgcn_update_dpp(j, j, 0x4E, 0xf, 0xf, false);
-  if (before(od, oj, d, j)) {
-    d = od;
-    j = oj;
-  }
+using Key = unsigned long long;
+
+// sorts after every record at a finite or infinite distance (a NaN's after it)
+constexpr Key kNone = (0x7f800000ull << 32) | 0x7fffffffull;
+
+__device__ inline float key_dist(Key k) { return __uint_as_float((uint32_t)(k >> 32)); }
+
+template <int CTRL>
+__device__ inline Key dpp_key(Key k) {
+  const int lo = (int)(uint32_t)k, hi = (int)(uint32_t)(k >> 32);
+  const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+  return ((Key)h << 32) | l;
 }
 
+__device__ inline void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// k <- the smallest of the quad's four
+__device__ inline void quad_min(Key& k) {
+  const Key a = dpp_key<0xB1>(k);
+  k = a < k ? a : k;
+  const Key b = dpp_key<0x4E>(k);
+  k = b < k ? b : k;
+}
+
+template <int K>
 __global__ void __launch_bounds__(kBlock)
-knn_query_quad_kernel(int n, const float* __restrict__ q, int k, const float* __restrict__ bounds,
+knn_query_quad_kernel(int n, const float* __restrict__ q, const float* __restrict__ bounds,
                       const uint32_t* __restrict__ start, const float4* __restrict__ recs,
                       const uint32_t* __restrict__ order, int32_t* __restrict__ idx,
                       float* __restrict__ w) {
-  constexpr int S = 4;                    // register slots = the largest k
+  __shared__ uint2 lists[kBlock / 4][8 * kQuadRows];
+  uint2* ranges = lists[threadIdx.x >> 2];
+  const int lane = threadIdx.x & 63;
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int it = (int)(gt >> 2), sub = (int)(gt & 3);
   if (it >= n) return;                    // whole quads leave
@@ -272,109 +308,131 @@ knn_query_quad_kernel(int n, const float* __restrict__ q, int k, const float* __
   const int cx = cell_of(qx, bounds[0], bounds[3], gx);
   const int cy = cell_of(qy, bounds[1], bounds[3], gy);
   const int cz = cell_of(qz, bounds[2], bounds[3], gz);
-  const float h = bounds[4];
+  const float h = bounds[4], hh = h * h;
+  // the query's place in cells, and how far (in cells squared, less a margin
+  // for the rounding of cell assignment and distances) a cell c lies from it
+  // along an axis on which it is in cell cc; a NaN is at no distance
+  const float fx = (qx - bounds[0]) * bounds[3], fy = (qy - bounds[1]) * bounds[3],
+              fz = (qz - bounds[2]) * bounds[3];
+  auto gap2 = [](float f, int c, int cc) {
+    const float g = c < cc ? f - (float)(c + 1) : (c > cc ? (float)c - f : 0.f);
+    const float m = fmaxf(g - (1e-3f + 1e-6f * fabsf(f)), 0.f);
+    return m * m;
+  };
   const int rmax = max(gx, max(gy, gz));
-  const int first = S - k;                // slot of the nearest
-  float bd[S];
-  int bi[S];
+  Key best[K], merged[K];                 // this lane's, and the quad's
 #pragma unroll
-  for (int t = 0; t < S; ++t) {
-    bd[t] = t < first ? -INFINITY : INFINITY;
-    bi[t] = t < first ? -1 : 0x7fffffff;
-  }
-  float md[S], kd = INFINITY;             // the quad's merged best k; its k-th
-  int mj[S], kj = 0x7fffffff;
+  for (int t = 0; t < K; ++t) best[t] = merged[t] = kNone;
+  // records first .. end - 1, dealt out to the quad
+  auto visit = [&](uint32_t first, uint32_t end) {
+    for (uint32_t e = first + sub; e - sub < end; e += 4 * kQuadBatch) {
+      float4 p[kQuadBatch];
+#pragma unroll
+      for (int u = 0; u < kQuadBatch; ++u) p[u] = recs[min(e + 4 * u, end - 1)];
+#pragma unroll
+      for (int u = 0; u < kQuadBatch; ++u) {
+        const float dx = p[u].x - qx, dy = p[u].y - qy, dz = p[u].z - qz;
+        const float d = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+        Key c = ((Key)__float_as_uint(d) << 32) | (Key)__float_as_uint(p[u].w);
+        if (!(e + 4 * u < end && c < best[K - 1] && c < merged[K - 1])) continue;
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+          const bool before = c < best[t];
+          const Key lo = before ? c : best[t];
+          c = before ? best[t] : c;
+          best[t] = lo;
+        }
+      }
+    }
+  };
   for (int r = 0; r <= rmax; ++r) {
-    const int z0 = max(cz - r, 0), z1 = min(cz + r, gz - 1);
-    const int y0 = max(cy - r, 0), y1 = min(cy + r, gy - 1);
-    for (int z = z0; z <= z1; ++z)
-      for (int y = y0; y <= y1; ++y) {
-        const bool face = abs(z - cz) == r || abs(y - cy) == r;
-        const int row = (z * gy + y) * gx;
-        for (int side = 0; side < (face ? 1 : 2); ++side) {
-          int x0, x1;
-          if (face) {
-            x0 = max(cx - r, 0);
-            x1 = min(cx + r, gx - 1);
-          } else {
-            x0 = x1 = side == 0 ? cx - r : cx + r;
-            if (x0 < 0 || x0 > gx - 1) continue;
-          }
-          const uint32_t e0 = start[row + x0], e1 = start[row + x1 + 1];
-          for (uint32_t b = e0; b < e1; b += 4 * kQuadBatch) {   // the same steps in the quad
-            const uint32_t e = b + sub;
-            float4 pb[kQuadBatch];
-#pragma unroll
-            for (int u = 0; u < kQuadBatch; ++u)
-              pb[u] = e + 4 * u < e1 ? recs[e + 4 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int u = 0; u < kQuadBatch; ++u) {
-              if (e + 4 * u >= e1) continue;
-              const float4 p = pb[u];
-              const int j = __float_as_int(p.w);
-              const float dx = p.x - qx, dy = p.y - qy, dz = p.z - qz;
-              const float d = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-              if (!before(d, j, bd[S - 1], bi[S - 1]) || !before(d, j, kd, kj)) continue;
-              bool placed = false;
-#pragma unroll
-              for (int t = S - 1; t >= 0; --t) {
-                if (placed) continue;
-                if (t > 0 && before(d, j, bd[t - 1], bi[t - 1])) {
-                  bd[t] = bd[t - 1];
-                  bi[t] = bi[t - 1];
-                } else {
-                  bd[t] = d;
-                  bi[t] = j;
-                  placed = true;
-                }
+    if (r == 0) {
+      const int cell = (cz * gy + cy) * gx + cx;
+      visit(start[cell], start[cell + 1]);
+    } else {
+      const float kd = key_dist(merged[K - 1]);
+      // the rows of the shell's cube inside the grid
+      const int z0 = max(cz - r, 0), z1 = min(cz + r, gz - 1);
+      const int y0 = max(cy - r, 0), y1 = min(cy + r, gy - 1);
+      const int ny = y1 - y0 + 1, rows = ny * (z1 - z0 + 1);   // at most kMaxCells
+      const float iny = __builtin_amdgcn_rcpf((float)ny);
+      for (int q0 = 0; q0 < rows; q0 += 4 * kQuadRows) {
+        // the quad's list of what is to be visited of these rows
+        int count = 0;
+        auto list = [&](uint32_t first, uint32_t end) {
+          const bool some = first < end;
+          const uint32_t m = (uint32_t)(__ballot(some) >> (lane & ~3)) & 15u;
+          if (some) ranges[count + __popc(m & ((1u << sub) - 1u))] = make_uint2(first, end);
+          count += __popc(m);
+        };
+        for (int u = 0; u < kQuadRows; ++u) {
+          const int p = q0 + 4 * u + sub;
+          const int t = (int)(((float)p + 0.5f) * iny);   // p / ny (both below 2^13)
+          const int z = z0 + t, y = y0 + (p - t * ny);
+          const float g = gap2(fz, z, cz) + gap2(fy, y, cy);
+          const bool in = p < rows && !(g * hh > kd);
+          const int row = (z * gy + y) * gx;
+          uint32_t e0 = 0u, e1 = 0u, f0 = 0u, f1 = 0u;
+          if (in) {
+            int x0 = max(cx - r, 0), x1 = min(cx + r, gx - 1);
+            if (abs(z - cz) == r || abs(y - cy) == r) {   // a face's row: all of it within reach
+              while (x0 < cx && (g + gap2(fx, x0, cx)) * hh > kd) ++x0;
+              while (x1 > cx && (g + gap2(fx, x1, cx)) * hh > kd) --x1;
+              e0 = start[row + x0];
+              e1 = start[row + x1 + 1];
+            } else {                              // else its two ends
+              if (x0 == cx - r && !((g + gap2(fx, x0, cx)) * hh > kd)) {
+                e0 = start[row + x0];
+                e1 = start[row + x0 + 1];
+              }
+              if (x1 == cx + r && !((g + gap2(fx, x1, cx)) * hh > kd)) {
+                f0 = start[row + x1];
+                f1 = start[row + x1 + 1];
               }
             }
           }
+          list(e0, e1);
+          list(f0, f1);
         }
+        wave_fence();
+        for (int t = 0; t < count; ++t) {
+          const uint2 v = ranges[t];
+          visit(v.x, v.y);
+        }
+        wave_fence();
       }
-    // merge the quad's lists: k rounds of a quad minimum
-    int ptr = first;
+    }
+    // merge the quad's lists: K rounds of a quad minimum
+    int ptr = 0;
 #pragma unroll
-    for (int t = 0; t < S; ++t) {
-      md[t] = INFINITY;
-      mj[t] = 0x7fffffff;
-      if (t >= k) continue;
-      float hd = INFINITY;
-      int hj = 0x7fffffff;
+    for (int t = 0; t < K; ++t) {
+      Key head = kNone;
 #pragma unroll
-      for (int u = 0; u < S; ++u)
-        if (u == ptr) {
-          hd = bd[u];
-          hj = bi[u];
-        }
-      float d = hd;
-      int j = hj;
-      quad_min(d, j);
-      if (d == hd && j == hj) ++ptr;
-      md[t] = d;
-      mj[t] = j;
-      kd = d;
-      kj = j;
+      for (int u = 0; u < K; ++u) head = u == ptr ? best[u] : head;
+      Key m = head;
+      quad_min(m);
+      if (m == head) ++ptr;
+      merged[t] = m;
     }
     // unvisited cells are at least r cell widths away (less a margin for
     // the rounding of cell assignment and distances)
     const float reach = (float)r * h;
-    if (kd < reach * reach * 0.9999f) break;
+    if (key_dist(merged[K - 1]) < reach * reach * 0.9999f) break;
   }
   // normalised inverse-distance weights; a query on a vertex takes it alone
-  const bool on_vertex = md[0] == 0.f;
-  float u[S], s = 0.f;
+  const bool on_vertex = key_dist(merged[0]) == 0.f;
+  float u[K], s = 0.f;
 #pragma unroll
-  for (int t = 0; t < S; ++t) {
-    u[t] = t < k ? __builtin_amdgcn_rcpf(__builtin_sqrtf(md[t])) : 0.f;
+  for (int t = 0; t < K; ++t) {
+    u[t] = __builtin_amdgcn_rcpf(__builtin_sqrtf(key_dist(merged[t])));
     s += u[t];
   }
   const float is = 1.f / s;
 #pragma unroll
-  for (int t = 0; t < S; ++t) {
-    if (t != sub || t >= k) continue;
+  for (int t = 0; t < K; ++t) {
+    if (t != sub) continue;
     const size_t o = (size_t)t * n + i;
-    idx[o] = mj[t];
+    idx[o] = (int)(uint32_t)merged[t];
     w[o] = on_vertex ? (t == 0 ? 1.f : 0.f) : u[t] * is;
   }
 }
@@ -518,8 +576,13 @@ knn_zero_kernel(float* __restrict__ p, int64_t count) {
 // range are summed in LDS (integer compare-and-swap adds), then added to
 // dattr with coalesced atomics, one per vertex of the range.  (Global float
 // atomics at scattered addresses are far slower on this part.)
+// Bound by the latency of its loads: 16 waves share a workgroup's sums (four:
+// 24 us for 8 channels of 100k queries, now 16 us), and a lane's neighbours
+// are read four at a time.
 constexpr int kVRange = 16384;           // 64 KB of LDS
-__global__ void __launch_bounds__(kBlock)
+constexpr int kBwdThreads = 1024;
+constexpr int kBwdStep = 4;
+__global__ void __launch_bounds__(kBwdThreads)
 knn_interp_bwd_kernel(int n, int k, const int32_t* __restrict__ idx, const float* __restrict__ w,
                       int nr, const float* __restrict__ dout, float* __restrict__ dattr,
                       int chunk) {
@@ -530,7 +593,7 @@ knn_interp_bwd_kernel(int n, int k, const int32_t* __restrict__ idx, const float
   for (int j = threadIdx.x; j < vn; j += blockDim.x) acc[j] = 0.f;
   __syncthreads();
   const float* g = dout + (size_t)c * n;
-  // Each wave takes its own contiguous quarter of the block's queries, and
+  // Each wave takes its own contiguous part of the block's queries, and
   // queries that share a neighbour in consecutive lanes (points stored
   // grouped by vertex) are summed across the wave first: one lane adds per
   // run, and the waves of a block mostly add to different LDS words.
@@ -541,15 +604,27 @@ knn_interp_bwd_kernel(int n, int k, const int32_t* __restrict__ idx, const float
     const int i = base + lane;
     const bool ok = i < wq1;
     const float gi = ok ? g[i] : 0.f;
-    for (int t = 0; t < k; ++t) {
-      const int j = ok ? idx[(size_t)t * n + i] - v0 : -1;
-      const bool use = ok && gi != 0.f && j >= 0 && j < vn;
-      float val = use ? w[(size_t)t * n + i] * gi : 0.f;
-      // the LDS float atomic: lanes of one wave that still share a word
-      // (neighbours repeating out of order) are serialised in the LDS unit
-      // instead of retrying a compare-and-swap (0.129 -> 0.087 ms for 42
-      // channels of the avatar's 100k Gaussians)
-      if (rga::wave_run_sum(use ? j : -1 - lane, val) && use) atomicAdd(&acc[j], val);
+    for (int t0 = 0; t0 < k; t0 += kBwdStep) {
+      int jt[kBwdStep];
+      float wt[kBwdStep];
+#pragma unroll
+      for (int u = 0; u < kBwdStep; ++u) {
+        const size_t o = (size_t)min(t0 + u, k - 1) * n + (ok ? i : wq0);
+        jt[u] = idx[o];
+        wt[u] = w[o];
+      }
+#pragma unroll
+      for (int u = 0; u < kBwdStep; ++u) {
+        if (t0 + u >= k) break;
+        const int j = ok ? jt[u] - v0 : -1;
+        const bool use = ok && gi != 0.f && j >= 0 && j < vn;
+        float val = use ? wt[u] * gi : 0.f;
+        // the LDS float atomic: lanes of one wave that still share a word
+        // (neighbours repeating out of order) are serialised in the LDS unit
+        // instead of retrying a compare-and-swap (0.129 -> 0.087 ms for 42
+        // channels of the avatar's 100k Gaussians)
+        if (rga::wave_run_sum(use ? j : -1 - lane, val) && use) atomicAdd(&acc[j], val);
+      }
     }
   }
   __syncthreads();
@@ -620,14 +695,18 @@ extern "C" int knn_query(void* stream, int n, const float* q, int nr, int k, int
              qcount, qstart);
   RGA_LAUNCH("knn_qfill", knn_qfill_kernel, grid, dim3(kBlock), 0, s, n, qstart, qcell, qrank,
              order);
-  if (k <= 4)
-    RGA_LAUNCH("knn_query", knn_query_quad_kernel, dim3(rga::ceil_div((int64_t)n * 4, kBlock)),
-               dim3(kBlock), 0, s, n, q, k, at<float>(W, L.bounds), at<uint32_t>(W, L.start),
-               at<float4>(W, L.recs), order, idx, w);
-  else
+  if (k <= 4) {
+    auto quad = k == 1 ? knn_query_quad_kernel<1>
+                       : (k == 2 ? knn_query_quad_kernel<2>
+                                 : (k == 3 ? knn_query_quad_kernel<3> : knn_query_quad_kernel<4>));
+    RGA_LAUNCH("knn_query", quad, dim3(rga::ceil_div((int64_t)n * 4, kBlock)), dim3(kBlock), 0, s, n,
+               q, at<float>(W, L.bounds), at<uint32_t>(W, L.start), at<float4>(W, L.recs), order, idx,
+               w);
+  } else {
     RGA_LAUNCH("knn_query_wide", knn_query_wave_kernel, dim3(rga::ceil_div(n, kBlock / 64)),
                dim3(kBlock), 0, s, n, q, k, at<float>(W, L.bounds), at<uint32_t>(W, L.start),
                at<float4>(W, L.recs), order, idx, w);
+  }
   RGA_CHECK_LAUNCH("knn_query");
   return RGA_OK;
 }
@@ -667,7 +746,7 @@ extern "C" int knn_interpolate_backward(void* stream, int n, int k, const int32_
     const int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(rga::ceil_div(n, kBlock),
                                                                    512 / ((int64_t)C * ranges)));
     const int chunk = (int)rga::ceil_div(n, chunks);
-    RGA_LAUNCH("knn_interp_bwd", knn_interp_bwd_kernel, dim3(chunks, C, ranges), dim3(kBlock), 0,
+    RGA_LAUNCH("knn_interp_bwd", knn_interp_bwd_kernel, dim3(chunks, C, ranges), dim3(kBwdThreads), 0,
                s, n, k, idx, w, nr, dout, dattr, chunk);
   }
   RGA_CHECK_LAUNCH("knn_interpolate_backward");
