@@ -14,19 +14,22 @@
 //             the MFMA B operand (one 16-byte load per lane and step), once
 //             in forward order and once transposed for the adjoint; the pose
 //             is folded into the first layer's bias (b_1 + W_1[:, 128:] theta)
-//   forward   one workgroup per 32 vertices, all layers in one kernel: the
-//             activations stay in LDS (two buffers), each wave computes 64
+//   forward   one workgroup per 64 vertices, all layers in one kernel: the
+//             activations stay in LDS, already split, each wave computes 32
 //             of a layer's columns with the weights streaming from L2; the
-//             hidden activations are kept for the adjoint
+//             features and the hidden activations are kept for the weight
+//             gradient, and a bit each (h > 0) for the adjoint
 //   backward  the same shape: dz_5 = ddx, dh = dz W (transposed pack),
 //             dz = dh where h > 0; every dz is kept
 //   wgrad     dW_l = sum over vertices of dz_l h_{l-1}^T: a workgroup per
-//             (layer, chunk of vertices) for the four large layers (the
-//             inputs staged through LDS once per workgroup), a small tiled
-//             kernel for the output layer; partial sums per chunk (no
-//             atomics), then a fixed-order sum over the chunks; the Fourier
-//             features of the first layer are recomputed from x; dW_1's pose
-//             columns are db_1 theta^T and dtheta = W_1[:, 128:]^T db_1
+//             (layer, chunk of vertices), the inputs staged through LDS once
+//             per workgroup; partial sums per chunk (no atomics), then a
+//             fixed-order sum over the chunks; dW_1's pose columns are
+//             db_1 theta^T and dtheta = W_1[:, 128:]^T db_1
+//
+// The kept arrays (163 MB each at 39,780 vertices) are laid out by blocks of 32
+// vertices, [layer][block][column][32], so that every kernel's workgroup moves
+// whole contiguous blocks.
 #include "common.h"
 
 #include <algorithm>
@@ -42,9 +45,20 @@ constexpr int kWidth = RGA_MLP_WIDTH;     // 256
 constexpr int kIn1 = 2 * kFreqs + kPose;  // 200
 constexpr int kLayers = 5;
 constexpr int kParams = RGA_MLP_PARAMS;
-constexpr int kAS = kWidth + 4;           // LDS row stride of the activations (floats)
-constexpr int kMaxChunks = 51;   // five layer workgroups per chunk: 255 fit the 256 CUs at once
-constexpr int kWaves = 4;
+constexpr int kAS = kWidth + 8;           // LDS row stride of the activations (bf16)
+constexpr int kRows = 32;                 // vertices per block
+// forward and adjoint: a workgroup of eight waves, two blocks, each wave 32
+// columns of a layer (NQ tiles of 16) for all 64 rows (RT tiles)
+constexpr int kWaves = 8;
+constexpr int kWgRows = 64;
+constexpr int kRT = kWgRows / 16;
+constexpr int kNQ = kWidth / 16 / kWaves;
+constexpr int kWgBlocks = kWgRows / kRows;
+// Chunks of vertices per layer of the weight gradient: its workgroups fit the
+// 256 CUs at once, and the layers' shares are as their work (the first has half
+// the columns, the last reads half and multiplies little).
+__host__ __device__ constexpr int max_chunks(int l) { return l == 0 ? 40 : (l < 4 ? 58 : 40); }
+constexpr int kMaxChunks = 58;
 
 // parameter layout: W_1 [256][200], b_1, W_2 [256][256], b_2, W_3, b_3, W_4, b_4, W_5 [3][256], b_5
 __host__ __device__ constexpr int n_out(int l) { return l < 4 ? kWidth : 3; }
@@ -78,15 +92,22 @@ __host__ __device__ constexpr int t_off(int l) {
 constexpr int kPackElems = t_off(kLayers);   // per hi and lo
 
 struct MlpLayout {
-  int nvp, chunks, chunk_len;
-  size_t pack, bias, h, dz, part, total;
+  int nvp, least;          // padded vertices; at most this many chunks per layer
+  size_t pack, bias, feat, h, mask, dz, part, total;
 };
+
+// chunks of a layer, and the vertices of each (whole blocks)
+__host__ __device__ inline int chunks_of(int l, int least) {
+  return max_chunks(l) < least ? max_chunks(l) : least;
+}
+__host__ __device__ inline int chunk_len(int nvp, int chunks) {
+  return (nvp / kRows + chunks - 1) / chunks * kRows;
+}
 
 MlpLayout mlp_layout(int nv) {
   MlpLayout L{};
   L.nvp = (int)rga::align_up((size_t)(nv > 0 ? nv : 1), 32);
-  L.chunks = std::max(1, std::min(kMaxChunks, L.nvp / 256));
-  L.chunk_len = (int)rga::align_up((size_t)rga::ceil_div(L.nvp, L.chunks), 32);
+  L.least = std::max(1, std::min(kMaxChunks, L.nvp / 256));
   const size_t V = (size_t)L.nvp;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -96,9 +117,11 @@ MlpLayout mlp_layout(int nv) {
   };
   L.pack = take((size_t)2 * kPackElems * 2);
   L.bias = take((size_t)kLayers * kWidth * 4);
+  L.feat = take((size_t)2 * kFreqs * V * 4);
   L.h = take((size_t)4 * kWidth * V * 4);
+  L.mask = take((size_t)4 * kWidth * (V / kRows) * 4);
   L.dz = take(((size_t)4 * kWidth + 16) * V * 4);
-  L.part = take((size_t)L.chunks * kParams * 4);
+  L.part = take((size_t)L.least * kParams * 4);
   L.total = o;
   return L;
 }
@@ -177,6 +200,7 @@ mlp_pack_kernel(const float* __restrict__ P, const float* __restrict__ theta,
       float b = 0.f;
       if (l == 0) {
         b = P[b_off(0) + n];
+#pragma unroll 24
         for (int t = 0; t < kPose; ++t) b = fmaf(P[w_off(0) + n * kIn1 + 2 * kFreqs + t], theta[t], b);
       } else if (n < n_out(l)) {
         b = P[b_off(l) + n];
@@ -194,175 +218,256 @@ __device__ inline float fourier_arg(const float* __restrict__ freqs, int j, floa
   return 2.f * a;
 }
 
-// One layer's product for a workgroup's 32 rows: wave w takes the NQ
-// column tiles from `ct0`; A comes from the LDS activations (two row tiles),
-// the operand fragments from global memory, those of the next reduction
-// step loaded before the products of the current one.
+// Weight fragments (hi, lo) of NQ column tiles at one reduction step.
 template <int NQ>
-__device__ inline void layer_mm(const float (*Ain)[kAS], const bf16x8* __restrict__ bh,
-                                const bf16x8* __restrict__ bl, int fo, int KS, int ct0,
-                                f32x4 (&acc)[2][NQ]) {
-  const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[rt][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 ch[NQ], cl[NQ];
+struct Frags {
+  bf16x8 h[NQ], l[NQ];
+};
+
+template <int NQ>
+__device__ inline void frags_load(Frags<NQ>& F, const bf16x8* __restrict__ bh,
+                                  const bf16x8* __restrict__ bl, int fo, int KS, int ct0, int ks) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    const int fi = fo + ((ct0 + q) * KS) * 64 + lane;
-    ch[q] = bh[fi];
-    cl[q] = bl[fi];
-  }
-  for (int ks = 0; ks < KS; ++ks) {
-    bf16x8 nh[NQ], nl[NQ];
-    if (ks + 1 < KS) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int fi = fo + ((ct0 + q) * KS + ks + 1) * 64 + lane;
-        nh[q] = bh[fi];
-        nl[q] = bl[fi];
-      }
-    }
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      float av[8];
-      load8(&Ain[rt * 16 + row][ks * 32 + 8 * g], av);
-      bf16x8 ah, al;
-      split8(av, ah, al);
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) acc[rt][q] = mfma3(ah, al, ch[q], cl[q], acc[rt][q]);
-    }
-    if (ks + 1 < KS) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        ch[q] = nh[q];
-        cl[q] = nl[q];
-      }
-    }
+    const int fi = fo + ((ct0 + q) * KS + ks) * 64 + lane;
+    F.h[q] = bh[fi];
+    F.l[q] = bl[fi];
   }
 }
 
-constexpr int kRows = 32;                // vertices per workgroup
+// The activations of a workgroup's rows, split.  (Split where they are made:
+// split where they are read, every wave repeated it for all rows.)
+struct Act {
+  __bf16 h[kWgRows][kAS], l[kWgRows][kAS];
+};
 
-__global__ void __launch_bounds__(256)
-mlp_forward_kernel(int nv, int nvp, const float* __restrict__ x, const float* __restrict__ freqs,
-                   const __bf16* __restrict__ phi, const __bf16* __restrict__ plo,
-                   const float* __restrict__ bias, float* __restrict__ H, float* __restrict__ out) {
-  __shared__ __align__(16) float act[2][kRows][kAS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = lane & 15, g = lane >> 4;
-  const int r0 = blockIdx.x * kRows;     // < nvp by the grid
-  // Fourier features: lane = frequency, rows wave, wave + 4, ...
-  for (int r = wave; r < kRows; r += kWaves) {
-    const int v = r0 + r;
-    const bool in = v < nv;
-    const float x0 = in ? x[v] : 0.f, x1 = in ? x[nv + v] : 0.f, x2 = in ? x[2 * nv + v] : 0.f;
-    const float f = fourier_arg(freqs, lane, x0, x1, x2);
-    act[0][r][lane] = sinpif(f);
-    act[0][r][kFreqs + lane] = cospif(f);
+__device__ inline void act_put(Act& A, int r, int n, float v) {
+  const __bf16 h = (__bf16)v;
+  A.h[r][n] = h;
+  A.l[r][n] = (__bf16)(v - (float)h);
+}
+
+// One layer's product for a workgroup's rows: wave w takes the kNQ column
+// tiles from `ct0`; the activations come from LDS, the weights from global
+// memory, those of the next reduction step loaded before the products of the
+// current one.  F holds the first step's on entry, and on exit those of the
+// next product's first step (`nfo`, `nKS`; none if nKS is 0).
+__device__ inline void layer_mm(const Act& A, const bf16x8* __restrict__ bh,
+                                const bf16x8* __restrict__ bl, int fo, int KS, int nfo, int nKS,
+                                int ct0, Frags<kNQ>& F, f32x4 (&acc)[kRT][kNQ]) {
+  const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+    for (int q = 0; q < kNQ; ++q) acc[rt][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int ks = 0; ks < KS; ++ks) {
+    Frags<kNQ> N;
+    if (ks + 1 < KS)
+      frags_load<kNQ>(N, bh, bl, fo, KS, ct0, ks + 1);
+    else if (nKS > 0)
+      frags_load<kNQ>(N, bh, bl, nfo, nKS, ct0, 0);
+    else
+      N = F;
+#pragma unroll
+    for (int rt = 0; rt < kRT; ++rt) {
+      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&A.h[rt * 16 + row][ks * 32 + 8 * g]);
+      const bf16x8 al = *reinterpret_cast<const bf16x8*>(&A.l[rt * 16 + row][ks * 32 + 8 * g]);
+#pragma unroll
+      for (int q = 0; q < kNQ; ++q) acc[rt][q] = mfma3(ah, al, F.h[q], F.l[q], acc[rt][q]);
+    }
+    F = N;
   }
-  __syncthreads();
+}
+
+// Forward and adjoint: the products take 22 us of the matrix units at 39,780
+// vertices, the kept arrays 32 us of memory each way; the rest is the latency of
+// a workgroup's steps and stores (one alone takes 30 and 20 us, and 2.4 follow
+// each other on a CU in pairs).  Activations split where they are made, one LDS
+// set instead of two, sign bits instead of the activations in the adjoint and
+// contiguous blocks: 100 -> 80 us and 110 -> 70 us.  (Twice the rows per
+// workgroup halves the weights' traffic at the same time; three more steps of
+// weights in flight do not fit the registers.)
+__global__ void __launch_bounds__(64 * kWaves, 4)
+mlp_forward_kernel(int nv, int nblk, const float* __restrict__ x, const float* __restrict__ freqs,
+                   const __bf16* __restrict__ phi, const __bf16* __restrict__ plo,
+                   const float* __restrict__ bias, float* __restrict__ feat,
+                   float* __restrict__ H, uint32_t* __restrict__ mask, float* __restrict__ out) {
+  __shared__ __align__(16) Act act;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = lane & 15, g = lane >> 4;
+  const int blk0 = kWgBlocks * blockIdx.x, r0 = blk0 * kRows;
   const bf16x8* bh = reinterpret_cast<const bf16x8*>(phi);
   const bf16x8* bl = reinterpret_cast<const bf16x8*>(plo);
-  int cur = 0;
-  for (int l = 0; l < kLayers - 1; ++l) {
-    f32x4 acc[2][4];
-    layer_mm<4>(act[cur], bh, bl, f_off(l) / 8, f_k(l) / 32, 4 * wave, acc);
+  Frags<kNQ> F;
+  frags_load<kNQ>(F, bh, bl, f_off(0) / 8, f_k(0) / 32, kNQ * wave, 0);
+  // Fourier features: lane = frequency, eight rows per wave
+  {
+    constexpr int U = kWgRows / kWaves;
+    const int u0 = U * wave;
+    float sn[U], cs[U];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int n = (4 * wave + q) * 16 + row;
+    for (int u = 0; u < U; ++u) {
+      const int v = r0 + u0 + u;
+      const bool in = v < nv;
+      const int vc = in ? v : 0;
+      const float x0 = in ? x[vc] : 0.f, x1 = in ? x[nv + vc] : 0.f, x2 = in ? x[2 * nv + vc] : 0.f;
+      const float f = fourier_arg(freqs, lane, x0, x1, x2);
+      sn[u] = sinpif(f);
+      cs[u] = cospif(f);
+      act_put(act, u0 + u, lane, sn[u]);
+      act_put(act, u0 + u, kFreqs + lane, cs[u]);
+    }
+    const int blk = blk0 + u0 / kRows;
+    if (blk < nblk) {
+      float* fs = feat + ((size_t)blk * 2 * kFreqs + lane) * kRows + u0 % kRows;
+      float* fc = fs + kFreqs * kRows;
+#pragma unroll
+      for (int u = 0; u < U; u += 4) {
+        *reinterpret_cast<float4*>(fs + u) = make_float4(sn[u], sn[u + 1], sn[u + 2], sn[u + 3]);
+        *reinterpret_cast<float4*>(fc + u) = make_float4(cs[u], cs[u + 1], cs[u + 2], cs[u + 3]);
+      }
+    }
+  }
+  __syncthreads();
+  for (int l = 0; l < kLayers - 1; ++l) {
+    f32x4 acc[kRT][kNQ];
+    const bool last = l == kLayers - 2;
+    layer_mm(act, bh, bl, f_off(l) / 8, f_k(l) / 32, f_off(l + 1) / 8, last ? 0 : f_k(l + 1) / 32,
+             kNQ * wave, F, acc);
+    __syncthreads();                     // every wave is done with the inputs
+#pragma unroll
+    for (int q = 0; q < kNQ; ++q) {
+      const int n = (kNQ * wave + q) * 16 + row;
       const float bn = bias[l * kWidth + n];
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        float hv[4];
+      for (int b = 0; b < kWgBlocks; ++b) {
+        uint32_t on = 0u;
+        const size_t at = ((size_t)l * nblk + blk0 + b) * kWidth + n;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = rt * 16 + 4 * g + i;
-          const float h = fmaxf(acc[rt][q][i] + bn, 0.f);
-          act[cur ^ 1][r][n] = h;
-          hv[i] = r0 + r < nv ? h : 0.f;
+        for (int t = 0; t < 2; ++t) {
+          float hv[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int r = 16 * t + 4 * g + i;
+            const float h = fmaxf(acc[2 * b + t][q][i] + bn, 0.f);
+            act_put(act, kRows * b + r, n, h);
+            hv[i] = r0 + kRows * b + r < nv ? h : 0.f;
+            on |= hv[i] > 0.f ? 1u << r : 0u;
+          }
+          if (blk0 + b < nblk)
+            *reinterpret_cast<float4*>(H + at * kRows + 16 * t + 4 * g) =
+                make_float4(hv[0], hv[1], hv[2], hv[3]);
         }
-        *reinterpret_cast<float4*>(H + ((size_t)l * kWidth + n) * nvp + r0 + rt * 16 + 4 * g) =
-            make_float4(hv[0], hv[1], hv[2], hv[3]);
+        on |= __shfl_xor(on, 16);
+        on |= __shfl_xor(on, 32);
+        if (g == 0 && blk0 + b < nblk) mask[at] = on;
       }
     }
     __syncthreads();
-    cur ^= 1;
   }
-  if (wave == 0) {                       // the output layer: one 16-column tile
-    f32x4 acc[2][1];
-    layer_mm<1>(act[cur], bh, bl, f_off(kLayers - 1) / 8, f_k(kLayers - 1) / 32, 0, acc);
+  if (wave < kRT) {                      // the output layer: one column tile, a row tile per wave
+    constexpr int KS = f_k(kLayers - 1) / 32;
+    Frags<KS> W;                         // (tile 0 of each reduction step)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int fi = f_off(kLayers - 1) / 8 + ks * 64 + lane;
+      W.h[ks] = bh[fi];
+      W.l[ks] = bl[fi];
+    }
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&act.h[wave * 16 + row][ks * 32 + 8 * g]);
+      const bf16x8 al = *reinterpret_cast<const bf16x8*>(&act.l[wave * 16 + row][ks * 32 + 8 * g]);
+      acc = mfma3(ah, al, W.h[ks], W.l[ks], acc);
+    }
     if (row < 3)
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int v = r0 + rt * 16 + 4 * g + i;
-          if (v < nv) out[(size_t)row * nv + v] = acc[rt][0][i] + bias[(kLayers - 1) * kWidth + row];
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int v = r0 + wave * 16 + 4 * g + i;
+        if (v < nv) out[(size_t)row * nv + v] = acc[i] + bias[(kLayers - 1) * kWidth + row];
+      }
   }
 }
 
-__global__ void __launch_bounds__(256)
-mlp_backward_kernel(int nv, int nvp, const float* __restrict__ ddx, const __bf16* __restrict__ phi,
-                    const __bf16* __restrict__ plo, const float* __restrict__ H,
-                    float* __restrict__ dZ) {
-  __shared__ __align__(16) float act[2][kRows][kAS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ void __launch_bounds__(64 * kWaves, 4)
+mlp_backward_kernel(int nv, int nblk, const float* __restrict__ ddx,
+                    const __bf16* __restrict__ phi, const __bf16* __restrict__ plo,
+                    const uint32_t* __restrict__ mask, float* __restrict__ dZ) {
+  __shared__ __align__(16) Act act;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row = lane & 15, g = lane >> 4;
-  const int r0 = blockIdx.x * kRows;
-  float* dZ5 = dZ + (size_t)4 * kWidth * nvp;
-  // dz_5 = ddx, as 32 reduction columns (3 used)
-  for (int t = threadIdx.x; t < kRows * 32; t += blockDim.x) {
-    const int r = t >> 5, c = t & 31, v = r0 + r;
-    const float d = (c < 3 && v < nv) ? ddx[(size_t)c * nv + v] : 0.f;
-    act[0][r][c] = d;
-    if (c < 16) dZ5[(size_t)c * nvp + v] = d;
-  }
-  __syncthreads();
+  const int blk0 = kWgBlocks * blockIdx.x, r0 = blk0 * kRows;
   const bf16x8* bh = reinterpret_cast<const bf16x8*>(phi);
   const bf16x8* bl = reinterpret_cast<const bf16x8*>(plo);
-  int cur = 0;
+  Frags<kNQ> F;
+  frags_load<kNQ>(F, bh, bl, t_off(kLayers - 1) / 8, t_k(kLayers - 1) / 32, kNQ * wave, 0);
+  // dz_5 = ddx, as 32 reduction columns (3 used)
+  for (int t = threadIdx.x; t < kWgRows * 32; t += blockDim.x) {
+    const int r = t % kWgRows, c = t / kWgRows, v = r0 + r;
+    const float d = (c < 3 && v < nv) ? ddx[(size_t)c * nv + v] : 0.f;
+    act_put(act, r, c, d);
+    const int blk = blk0 + r / kRows;
+    if (c < 16 && blk < nblk)
+      dZ[((size_t)4 * nblk * kWidth + (size_t)blk * 16 + c) * kRows + r % kRows] = d;
+  }
+  __syncthreads();
   for (int l = kLayers - 1; l >= 1; --l) {
-    f32x4 acc[2][4];
-    layer_mm<4>(act[cur], bh, bl, t_off(l) / 8, t_k(l) / 32, 4 * wave, acc);
+    f32x4 acc[kRT][kNQ];
+    uint32_t on[kWgBlocks][kNQ];
+#pragma unroll
+    for (int b = 0; b < kWgBlocks; ++b)
+#pragma unroll
+      for (int q = 0; q < kNQ; ++q)
+        on[b][q] = mask[((size_t)(l - 1) * nblk + min(blk0 + b, nblk - 1)) * kWidth +
+                        (kNQ * wave + q) * 16 + row];
+    layer_mm(act, bh, bl, t_off(l) / 8, t_k(l) / 32, t_off(l - 1) / 8, l > 1 ? t_k(l - 1) / 32 : 0,
+             kNQ * wave, F, acc);
+    __syncthreads();
     // dz of hidden layer l - 1 (the input of layer l): dh where h > 0
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int n = (4 * wave + q) * 16 + row;
+    for (int q = 0; q < kNQ; ++q) {
+      const int n = (kNQ * wave + q) * 16 + row;
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        const size_t o = ((size_t)(l - 1) * kWidth + n) * nvp + r0 + rt * 16 + 4 * g;
-        const float4 h = *reinterpret_cast<const float4*>(H + o);
-        const float hv[4] = {h.x, h.y, h.z, h.w};
-        float dv[4];
+      for (int b = 0; b < kWgBlocks; ++b)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          dv[i] = hv[i] > 0.f ? acc[rt][q][i] : 0.f;
-          act[cur ^ 1][rt * 16 + 4 * g + i][n] = dv[i];
+        for (int t = 0; t < 2; ++t) {
+          float dv[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int r = 16 * t + 4 * g + i;
+            dv[i] = (on[b][q] >> r) & 1u ? acc[2 * b + t][q][i] : 0.f;
+            act_put(act, kRows * b + r, n, dv[i]);
+          }
+          if (blk0 + b < nblk)
+            *reinterpret_cast<float4*>(dZ + (((size_t)(l - 1) * nblk + blk0 + b) * kWidth + n) * kRows +
+                                       16 * t + 4 * g) = make_float4(dv[0], dv[1], dv[2], dv[3]);
         }
-        *reinterpret_cast<float4*>(dZ + o) = make_float4(dv[0], dv[1], dv[2], dv[3]);
-      }
     }
     __syncthreads();
-    cur ^= 1;
   }
 }
 
 // dW_l of one layer over one chunk of vertices, the whole layer per
 // workgroup so that every operand row is read once per chunk (a workgroup
-// per 64 x 128 tile re-reads dz twice and h four times); blockIdx.x = the
-// layer, so all five run side by side: the first layer's Fourier columns
-// (256 x 128, features recomputed from x once per chunk step instead of
-// once per tile), the hidden layers (256 x 256, h_{l-1} from the forward)
-// and the output layer (3 x 256, its dz padded to 16 rows).  Eight waves,
-// each RT row tiles x NCT column tiles of 16 x 16.  Both operands of a
-// 32-vertex step are split into bf16 hi / lo fragments in LDS (A = dz
-// rows, B = the layer's inputs), double-buffered: each thread loads its
-// share of the next step into registers before this step's MFMAs and
-// splits and stores it after them, so the loads' latency is spent under
-// the products.  The db sums come from the same loads.
+// per 64 x 128 tile re-reads dz twice and h four times); all five layers run
+// side by side: the first layer's Fourier columns (256 x 128), the hidden
+// layers (256 x 256, h_{l-1} from the forward) and the output layer (3 x 256,
+// its dz padded to 16 rows).  Eight waves, each RT row tiles x NCT column
+// tiles of 16 x 16.  Both operands of a 32-vertex step are split into bf16
+// hi / lo fragments in LDS (A = dz rows, B = the layer's inputs),
+// double-buffered: each thread loads its share of the next step into
+// registers before this step's MFMAs and splits and stores it after them, so
+// the loads' latency is spent under the products.  The db sums come from the
+// same loads.
+// Bound by the reading of the kept arrays (340 MB, 3.6 TB/s): 110 -> 96 us at
+// 39,780 vertices by reading contiguous blocks, keeping the features (20 MB;
+// computed again they made the first layer's workgroups the slowest) and
+// dividing the chunks by the layers' work.
 constexpr int kLayerThreads = 512;
 constexpr int kLayerWaves = kLayerThreads / 64;
 constexpr int kFragA = 16 * 64;   // A fragments per step buffer (256 rows)
@@ -373,27 +478,22 @@ struct WgradLds {
   bf16x8 b[2][2][kFragB];   // [buffer][hi, lo][column tile * 64 + lane]
 };
 
-template <bool FIRST, int NRT, int RT, int NCT>
-__device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const float* x,
-                                   const float* freqs, const float* H, const float* dZ,
-                                   float* part, WgradLds& S) {
-  constexpr int NQ = FIRST ? 2 * kFreqs / 16 : kWidth / 16;   // the layer's input column tiles
+template <int NQ, int NRT, int RT, int NCT>
+__device__ inline void wgrad_layer(int l, int c, int v0, int v1, int nvp, const float* hin,
+                                   const float* dZ, float* part, WgradLds& S) {
   constexpr int NRG = kLayerWaves * NCT / NQ;                  // row groups of waves
   static_assert(NRG * RT == NRT, "the waves cover the layer's rows");
   constexpr int FA = NRT * 64, FB = NQ * 64;                   // fragments per step
   constexpr int PA = (FA + kLayerThreads - 1) / kLayerThreads;  // per thread
-  constexpr int PB = FIRST ? 0 : FB / kLayerThreads;            // loaded per thread (B)
+  constexpr int PB = FB / kLayerThreads;                        // loaded per thread (B)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = lane & 15, g = lane >> 4;
-  const int c = blockIdx.y;
   const int n0 = 16 * RT * (wave % NRG), q0 = NCT * (wave / NRG);
   const int nrows = l < 4 ? kWidth : 16;
   const float* dz = dZ + (size_t)l * kWidth * nvp;
-  const float* hin = H + (size_t)(FIRST ? 0 : l - 1) * kWidth * nvp;
-  const int v0 = c * chunk_len, v1 = min(nvp, v0 + chunk_len);
   // fragment f = 64 t + L of either operand: row (or column) 16 t + L % 16,
   // vertices vb + 8 (L / 16) .. + 7 (the MFMA operand order)
-  float ra[PA][8], rb[PB > 0 ? PB : 1][8];
+  float ra[PA][8], rb[PB][8];
   float dsum[PA];
 #pragma unroll
   for (int p = 0; p < PA; ++p) dsum[p] = 0.f;
@@ -401,9 +501,9 @@ __device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const 
 #pragma unroll
     for (int p = 0; p < PA; ++p) {
       const int f = threadIdx.x + p * kLayerThreads;
-      const int n = 16 * (f >> 6) + (f & 15), va = vb + 8 * ((f & 63) >> 4);
+      const int n = 16 * (f >> 6) + (f & 15), va = 8 * ((f & 63) >> 4);
       if (f < FA && n < nrows) {
-        load8(dz + (size_t)n * nvp + va, ra[p]);
+        load8(dz + (size_t)vb * nrows + n * kRows + va, ra[p]);
       } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) ra[p][e] = 0.f;
@@ -412,11 +512,11 @@ __device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const 
 #pragma unroll
     for (int p = 0; p < PB; ++p) {
       const int f = threadIdx.x + p * kLayerThreads;
-      const int col = 16 * (f >> 6) + (f & 15), va = vb + 8 * ((f & 63) >> 4);
-      load8(hin + (size_t)col * nvp + va, rb[p]);
+      const int col = 16 * (f >> 6) + (f & 15), va = 8 * ((f & 63) >> 4);
+      load8(hin + (size_t)vb * 16 * NQ + col * kRows + va, rb[p]);
     }
   };
-  auto store = [&](int buf, int vb) {
+  auto store = [&](int buf) {
 #pragma unroll
     for (int p = 0; p < PA; ++p) {
       const int f = threadIdx.x + p * kLayerThreads;
@@ -429,32 +529,13 @@ __device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const 
         for (int e = 0; e < 8; ++e) dsum[p] += ra[p][e];
       }
     }
-    if constexpr (FIRST) {
-      for (int f = threadIdx.x; f < FB; f += kLayerThreads) {
-        const int col = 16 * (f >> 6) + (f & 15), va = vb + 8 * ((f & 63) >> 4);
-        float b[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int v = va + e;
-          const bool in = v < nv;
-          const float x0 = in ? x[v] : 0.f, x1 = in ? x[nv + v] : 0.f, x2 = in ? x[2 * nv + v] : 0.f;
-          const float fa = fourier_arg(freqs, col & (kFreqs - 1), x0, x1, x2);
-          b[e] = col < kFreqs ? sinpif(fa) : cospif(fa);
-        }
-        bf16x8 h, lo;
-        split8(b, h, lo);
-        S.b[buf][0][f] = h;
-        S.b[buf][1][f] = lo;
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < PB; ++p) {
-        const int f = threadIdx.x + p * kLayerThreads;
-        bf16x8 h, lo;
-        split8(rb[p], h, lo);
-        S.b[buf][0][f] = h;
-        S.b[buf][1][f] = lo;
-      }
+    for (int p = 0; p < PB; ++p) {
+      const int f = threadIdx.x + p * kLayerThreads;
+      bf16x8 h, lo;
+      split8(rb[p], h, lo);
+      S.b[buf][0][f] = h;
+      S.b[buf][1][f] = lo;
     }
   };
   f32x4 acc[RT][NCT];
@@ -465,7 +546,7 @@ __device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const 
   int buf = 0;
   if (v0 < v1) {
     load(v0);
-    store(0, v0);
+    store(0);
   }
   __syncthreads();
   for (int vb = v0; vb < v1; vb += 32) {
@@ -487,7 +568,7 @@ __device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const 
     }
     // the other buffer's readers all passed the barrier that ended the
     // previous step
-    if (more) store(buf ^ 1, vb + 32);
+    if (more) store(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
@@ -518,63 +599,81 @@ __device__ inline void wgrad_layer(int l, int nv, int nvp, int chunk_len, const 
 }
 
 __global__ void __launch_bounds__(kLayerThreads)
-mlp_wgrad_layer_kernel(int nv, int nvp, int chunk_len, const float* __restrict__ x,
-                       const float* __restrict__ freqs, const float* __restrict__ H,
-                       const float* __restrict__ dZ, float* __restrict__ part) {
+mlp_wgrad_layer_kernel(int nvp, int least, const float* __restrict__ feat,
+                       const float* __restrict__ H, const float* __restrict__ dZ,
+                       float* __restrict__ part) {
   __shared__ WgradLds S;
-  const int l = blockIdx.x;
+  // the workgroups run over the layers' chunks, the full layers first
+  int l = 1, c = blockIdx.x;
+  while (c >= chunks_of(l, least)) {
+    c -= chunks_of(l, least);
+    l = l == 3 ? 0 : (l == 0 ? 4 : l + 1);
+  }
+  const int len = chunk_len(nvp, chunks_of(l, least));
+  const int v0 = min(nvp, c * len), v1 = min(nvp, v0 + len);
+  const float* hin = l == 0 ? feat : H + (size_t)(l - 1) * kWidth * nvp;
   if (l == 0)
-    wgrad_layer<true, 16, 4, 4>(l, nv, nvp, chunk_len, x, freqs, H, dZ, part, S);
+    wgrad_layer<2 * kFreqs / 16, 16, 4, 4>(l, c, v0, v1, nvp, hin, dZ, part, S);
   else if (l < 4)
-    wgrad_layer<false, 16, 4, 8>(l, nv, nvp, chunk_len, x, freqs, H, dZ, part, S);
+    wgrad_layer<kWidth / 16, 16, 4, 8>(l, c, v0, v1, nvp, hin, dZ, part, S);
   else
-    wgrad_layer<false, 1, 1, 2>(l, nv, nvp, chunk_len, x, freqs, H, dZ, part, S);
+    wgrad_layer<kWidth / 16, 1, 1, 2>(l, c, v0, v1, nvp, hin, dZ, part, S);
+}
+
+// Sum of one parameter's partials over the chunks, in order (the loads of 16
+// are in flight together: one at a time, the sums of 51 chunks took 27 us).
+__device__ inline float chunk_sum(const float* __restrict__ part, int p, int chunks) {
+  float s = 0.f;
+  int c = 0;
+  for (; c + 16 <= chunks; c += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(c + u) * kParams + p];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; c < chunks; ++c) s += part[(size_t)c * kParams + p];
+  return s;
 }
 
 // dparams = sum over the chunks (fixed order); W_1's pose columns are
-// db_1 theta^T (the pose is shared by every vertex)
-__global__ void __launch_bounds__(256)
-mlp_reduce_kernel(int chunks, const float* __restrict__ theta, const float* __restrict__ part,
-                  float* __restrict__ dP) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kParams) return;
-  const int k = p % kIn1;
-  if (p < b_off(0) && k >= 2 * kFreqs) {
-    const int n = p / kIn1;
-    float db = 0.f;
-    for (int c = 0; c < chunks; ++c) db += part[(size_t)c * kParams + b_off(0) + n];
-    dP[p] = db * theta[k - 2 * kFreqs];
-  } else {
-    float s = 0.f;
-    for (int c = 0; c < chunks; ++c) s += part[(size_t)c * kParams + p];
-    dP[p] = s;
-  }
-}
-
+// db_1 theta^T (the pose is shared by every vertex).  The first workgroup:
 // dtheta = W_1[:, 128:]^T db_1 (db_1 summed over the chunks first; the
-// 256-term products in four fixed quarters, then added in order)
-constexpr int kDthThreads = 320;
-__global__ void __launch_bounds__(kDthThreads)
-mlp_dtheta_kernel(int chunks, const float* __restrict__ P, const float* __restrict__ part,
+// 256-term products in four fixed quarters, then added in order).
+__global__ void __launch_bounds__(256)
+mlp_reduce_kernel(int least, const float* __restrict__ theta, const float* __restrict__ P,
+                  const float* __restrict__ part, float* __restrict__ dP,
                   float* __restrict__ dtheta) {
-  __shared__ float db[kWidth];
-  __shared__ float quarter[4][kPose];
-  const int t = threadIdx.x;
-  if (t < kWidth) {
-    float s = 0.f;
-    for (int c = 0; c < chunks; ++c) s += part[(size_t)c * kParams + b_off(0) + t];
-    db[t] = s;
+  if (blockIdx.x == 0) {
+    __shared__ float db[kWidth];
+    __shared__ float quarter[4 * kPose];
+    static_assert(kWidth == 256, "a thread per bias");
+    db[threadIdx.x] = chunk_sum(part, b_off(0) + threadIdx.x, chunks_of(0, least));
+    __syncthreads();
+    for (int t = threadIdx.x; t < 4 * kPose; t += 256) {
+      const int k = t % kPose, q = t / kPose;
+      float a = 0.f;
+#pragma unroll 16
+      for (int n = 64 * q; n < 64 * q + 64; ++n)
+        a = fmaf(P[w_off(0) + n * kIn1 + 2 * kFreqs + k], db[n], a);
+      quarter[t] = a;
+    }
+    __syncthreads();
+    if (threadIdx.x < kPose) {
+      const float* q = quarter + threadIdx.x;
+      dtheta[threadIdx.x] = ((q[0] + q[kPose]) + q[2 * kPose]) + q[3 * kPose];
+    }
+    return;
   }
-  __syncthreads();
-  if (t < 4 * kPose) {
-    const int k = t % kPose, q = t / kPose;
-    float a = 0.f;
-    for (int n = 64 * q; n < 64 * q + 64; ++n)
-      a = fmaf(P[w_off(0) + n * kIn1 + 2 * kFreqs + k], db[n], a);
-    quarter[q][k] = a;
-  }
-  __syncthreads();
-  if (t < kPose) dtheta[t] = ((quarter[0][t] + quarter[1][t]) + quarter[2][t]) + quarter[3][t];
+  const int p = (blockIdx.x - 1) * blockDim.x + threadIdx.x;
+  if (p >= kParams) return;
+  const int l = p < w_off(1) ? 0 : (p < w_off(4) ? 1 : 4);    // (layers 1 to 3 have alike many)
+  const int chunks = chunks_of(l, least);
+  const int k = p % kIn1;
+  if (p < b_off(0) && k >= 2 * kFreqs)
+    dP[p] = chunk_sum(part, b_off(0) + p / kIn1, chunks) * theta[k - 2 * kFreqs];
+  else
+    dP[p] = chunk_sum(part, p, chunks);
 }
 
 }  // namespace
@@ -600,8 +699,9 @@ extern "C" int mlp_forward(void* stream, int nv, const float* x, const float* fr
              at<float>(ws, L.bias));
   // with no vertices the kernel still clears the kept activations of the
   // padding rows, which the adjoint reads
-  RGA_LAUNCH("mlp_fwd", mlp_forward_kernel, dim3(L.nvp / kRows), dim3(64 * kWaves), 0, s, nv, L.nvp, x, freqs, hi, lo, at<float>(ws, L.bias),
-               at<float>(ws, L.h), dx);
+  RGA_LAUNCH("mlp_fwd", mlp_forward_kernel, dim3(rga::ceil_div(L.nvp, kWgRows)), dim3(64 * kWaves), 0,
+             s, nv, L.nvp / kRows, x, freqs, hi, lo, at<float>(ws, L.bias), at<float>(ws, L.feat),
+             at<float>(ws, L.h), at<uint32_t>(ws, L.mask), dx);
   RGA_CHECK_LAUNCH("mlp_forward");
   return RGA_OK;
 }
@@ -621,14 +721,14 @@ extern "C" int mlp_backward(void* stream, int nv, const float* x, const float* f
   float* part = at<float>(ws, L.part);
   // with no vertices every partial sum is zero: the backward and the
   // weight-gradient kernels still run over the (zero) padding rows
-  RGA_LAUNCH("mlp_bwd", mlp_backward_kernel, dim3(L.nvp / kRows), dim3(64 * kWaves), 0, s, nv, L.nvp, ddx, hi, lo, at<float>(ws, L.h),
-             at<float>(ws, L.dz));
-  RGA_LAUNCH("mlp_wgrad", mlp_wgrad_layer_kernel, dim3(kLayers, L.chunks), dim3(kLayerThreads), 0,
-             s, nv, L.nvp, L.chunk_len, x, freqs, at<float>(ws, L.h), at<float>(ws, L.dz), part);
-  RGA_LAUNCH("mlp_reduce", mlp_reduce_kernel, dim3(rga::ceil_div(kParams, 256)), dim3(256), 0, s,
-             L.chunks, theta, part, dparams);
-  RGA_LAUNCH("mlp_dtheta", mlp_dtheta_kernel, dim3(1), dim3(kDthThreads), 0, s, L.chunks, params,
-             part, dtheta);
+  RGA_LAUNCH("mlp_bwd", mlp_backward_kernel, dim3(rga::ceil_div(L.nvp, kWgRows)), dim3(64 * kWaves), 0,
+             s, nv, L.nvp / kRows, ddx, hi, lo, at<uint32_t>(ws, L.mask), at<float>(ws, L.dz));
+  int groups = 0;
+  for (int l = 0; l < kLayers; ++l) groups += chunks_of(l, L.least);
+  RGA_LAUNCH("mlp_wgrad", mlp_wgrad_layer_kernel, dim3(groups), dim3(kLayerThreads), 0, s, L.nvp,
+             L.least, at<float>(ws, L.feat), at<float>(ws, L.h), at<float>(ws, L.dz), part);
+  RGA_LAUNCH("mlp_reduce", mlp_reduce_kernel, dim3(1 + rga::ceil_div(kParams, 256)), dim3(256), 0, s,
+             L.least, theta, params, part, dparams, dtheta);
   RGA_CHECK_LAUNCH("mlp_backward");
   return RGA_OK;
 }
