@@ -6,15 +6,15 @@
 //   preprocess        1 thread / splat: camera transform, covariance, conic,
 //                     opacity-aware tile rectangle, packed 48-byte record;
 //                     also clears the frame's ranges, counters and sums
-//   depth sort        stable LSD radix sort of (depth bits, index) over n:
+//   depth sort        stable LSD radix sort of (depth bits, index):
 //                     3 passes of 11-bit digits, each [upsweep of per-block
 //                     digit counts, per-digit scan, ranked scatter]; culled
-//                     splats carry key 0xFFFFFFFF
-//   offsets           exclusive scan of tiles-touched in depth order -> D
+//                     splats carry key 0xFFFFFFFF and leave with the first
+//   touched sums      tiles touched by each block of splats in depth order
 //   duplicate         one (tile, splat) entry per touched tile, emitted in
-//                     depth order
+//                     depth order -> D
 //   tile sort         stable LSD radix sort of the entries by tile id (one
-//                     pass up to 2048 tiles) -> per tile, entries in
+//                     pass up to 4096 tiles) -> per tile, entries in
 //                     (depth bits, index) order
 //   ranges            tile boundaries in the sorted entries (written by the
 //                     tile sort's scatter when it takes one pass)
@@ -22,8 +22,8 @@
 //                     consecutive 64-entry sub-chunks of the tile's list side
 //                     by side and stop as soon as the block has; the adjoint
 //                     over the sub-chunks that were composited
-// Stable ranking inside a radix pass uses wave64 ballots (11 ballots give
-// the lanes that share a digit) and mbcnt-style lane masks.
+// Stable ranking inside a radix pass uses wave64 ballots (one per digit bit
+// gives the lanes that share a digit) and mbcnt-style lane masks.
 #include "common.h"
 
 #include <algorithm>
@@ -43,9 +43,13 @@ constexpr int kBlocks = 4;       // 8 x 8 pixel blocks of a tile
 constexpr int kGrad = 16;        // floats per splat of the adjoint sums (9 used, one 64-byte line)
 constexpr float kHalfNegLog2e = -0.72134752f;   // -log2(e) / 2
 constexpr float kInvHalfLog2e = 1.38629436f;    // 2 / log2(e) = 2 ln 2
-constexpr int kDigitBits = 11;   // radix digit width of the tile sort: 2048 bins
+// Digit widths of the tile sort: one pass of the narrowest that holds the tiles
+// up to 4096 of them, two of 7 bits up to 16,384 and of 8 up to 65,536 (4,624
+// tiles, 3.4 million entries: two passes of 11 bits 185 us with their scans, of 7
+// bits 70: the digit tables are 16 times smaller), else of 11.
+constexpr int kDigitBits = 11;
 constexpr int kRadix = 1 << kDigitBits;
-constexpr int kWideBits = 12;    // one tile pass of 4096 bins for 2049 .. 4096 tiles
+constexpr int kMaxBits = 12;
 constexpr int kDepthBits = 11;   // digit width of the depth sort: 3 passes over 32-bit keys
 constexpr int kDepthPasses = (32 + kDepthBits - 1) / kDepthBits;
 
@@ -65,7 +69,7 @@ struct Layout {
   size_t nlive, mask, state, part, part_t, total;
   int tiles_x, tiles_y, nb_n, nb_cap, nb_max, tile_passes;
   int parts;       // parts a tile's list is walked in
-  int tile_bits;   // digit width of a one-pass tile sort: kDigitBits or kWideBits
+  int tile_bits;   // digit width of the tile sort: 7, 8, 10, 11 or 12
 };
 
 Layout make_layout(int n, int width, int height, int64_t cap) {
@@ -78,8 +82,9 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   L.nb_max = L.nb_n > L.nb_cap ? L.nb_n : L.nb_cap;
   int bits = 0;
   while ((1ll << bits) < tiles) ++bits;
-  L.tile_passes = bits <= kWideBits ? 1 : (bits <= 2 * kDigitBits ? 2 : 3);
-  L.tile_bits = (bits > kDigitBits && bits <= kWideBits) ? kWideBits : kDigitBits;
+  L.tile_passes = bits <= kMaxBits ? 1 : (bits <= 2 * kDigitBits ? 2 : 3);
+  L.tile_bits = bits > 16 ? kDigitBits
+                          : (bits > 14 || bits <= 8 ? 8 : (bits > kMaxBits ? 7 : (bits <= 10 ? 10 : bits)));
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -105,12 +110,12 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   L.tk1 = take(C * 4);
   L.tv1 = take(C * 4);
   L.ranges = take((size_t)tiles * 8);
-  L.hist = take((size_t)L.nb_max * (1 << kWideBits) * 4);
-  L.binoff = take((size_t)L.nb_max * (1 << kWideBits) * 4);
-  L.bintot = take((1 << kWideBits) * 4);
+  L.hist = take((size_t)L.nb_max * (1 << kMaxBits) * 4);
+  L.binoff = take((size_t)L.nb_max * (1 << kMaxBits) * 4);
+  L.bintot = take((1 << kMaxBits) * 4);
   L.bsum = take((size_t)L.nb_n * 4);
-  L.boff = take((size_t)L.nb_n * 4);
-  L.count = take(32);   // int64 [0] = D; uint32 [4] = scan ticket
+  L.boff = take((size_t)L.nb_n * 4);   // (kept: sizes a caller has computed stay enough)
+  L.count = take(32);   // int64 [0] = D, [3] = splats that touch a tile
   L.grad = take(N * kGrad * 4);   // adjoint sums per splat: mean2d, conic, opacity, colour
   // blend state: tile t's sub-chunk m of its list [start, end) has the slot
   // start / 64 + t + m, distinct for every (tile, sub-chunk)
@@ -148,6 +153,7 @@ CamDev to_dev(const rga_camera* c) {
   return d;
 }
 
+constexpr uint32_t kCulled = 0xFFFFFFFFu;   // depth key of a splat that touches no tile
 constexpr uint32_t kNoPart = 0xFFFFFFFFu;   // a part not finished (the bits of a NaN)
 
 // exp for the scales: Cody-Waite reduction by ln 2, degree-7 Taylor
@@ -365,7 +371,7 @@ preprocess_kernel(int n, CamDev cam, int TX, int TY, const float* __restrict__ x
     for (int q = 0; q < 3; ++q) grad[(size_t)g * (kGrad / 4) + q] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   fp64[g] = used64;
-  keys[g] = cnt > 0 ? __float_as_uint(G.Z) : 0xFFFFFFFFu;
+  keys[g] = cnt > 0 ? __float_as_uint(G.Z) : kCulled;
   vals[g] = (uint32_t)g;
 }
 
@@ -403,11 +409,17 @@ __device__ inline int64_t live_count(const int64_t* cnt_ptr, int64_t fixed, int6
   return c < cap ? c : cap;
 }
 
-// Digits of BITS bits: 32-bit depth keys take 3 passes of 11 bits, tile keys
-// of up to 2048 tiles 1 pass.
+// The digit tables hold a block's 2^BITS counts side by side, or (narrow digits,
+// whose tables are short) a digit's counts of all nb blocks, so that the scan
+// reads and writes whole lines: 1,655 blocks of 128 digits 13 -> 5 us.
+template <int BITS>
+__device__ inline size_t table_at(int block, int d, int nb) {
+  return BITS <= 8 ? (size_t)d * nb + block : (size_t)block * (1 << BITS) + d;
+}
 
-// Per-block digit histogram (LDS integer atomics), digits of BITS bits.
-template <int ITEMS, int BITS>
+// Per-block digit histogram (LDS integer atomics), digits of BITS bits.  With
+// LIVE the items of key kCulled are left out (by the scatter too).
+template <int ITEMS, int BITS, bool LIVE = false>
 __global__ void __launch_bounds__(kRadixThreads)
 radix_upsweep(const uint32_t* __restrict__ keys, const int64_t* cnt_ptr, int64_t fixed,
               int64_t cap, int shift, uint32_t* __restrict__ hist) {
@@ -420,11 +432,14 @@ radix_upsweep(const uint32_t* __restrict__ keys, const int64_t* cnt_ptr, int64_t
   __syncthreads();
   for (int r = 0; r < ITEMS; ++r) {
     const int64_t i = base + (int64_t)r * kRadixThreads + threadIdx.x;
-    if (i < count) atomicAdd(&h[(keys[i] >> shift) & (kRadix - 1)], 1u);
+    if (i < count) {
+      const uint32_t k = keys[i];
+      if (!LIVE || k != kCulled) atomicAdd(&h[(k >> shift) & (kRadix - 1)], 1u);
+    }
   }
   __syncthreads();
   for (int d = threadIdx.x; d < kRadix; d += kRadixThreads)
-    hist[(size_t)blockIdx.x * kRadix + d] = h[d];
+    hist[table_at<BITS>(blockIdx.x, d, gridDim.x)] = h[d];
 }
 
 // Exclusive scan of each digit's counts over the blocks that hold items
@@ -439,6 +454,7 @@ radix_binscan(const uint32_t* __restrict__ hist, int nb, const int64_t* cnt_ptr,
               uint32_t* __restrict__ bintot) {
   constexpr int kRadix = 1 << BITS;
   constexpr int kHeld = 8;
+  static_assert(BITS > 8, "a table of blocks");
   __shared__ uint32_t wtot[4][8];
   const int dl = threadIdx.x & 7, c = threadIdx.x >> 3;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -484,6 +500,46 @@ radix_binscan(const uint32_t* __restrict__ hist, int nb, const int64_t* cnt_ptr,
   }
 }
 
+// The same for narrow digits: one workgroup per digit walks its row of the table,
+// four blocks per thread at a time.
+template <int BITS>
+__global__ void __launch_bounds__(256)
+radix_rowscan(const uint32_t* __restrict__ hist, int nb, const int64_t* cnt_ptr, int64_t fixed,
+              int64_t cap, int block_items, uint32_t* __restrict__ binoff,
+              uint32_t* __restrict__ bintot) {
+  __shared__ uint32_t wtot[2][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t count = live_count(cnt_ptr, fixed, cap);
+  const int nbl = (int)min((int64_t)nb, (count + block_items - 1) / block_items);
+  const uint32_t* in = hist + (size_t)blockIdx.x * nb;
+  uint32_t* out = binoff + (size_t)blockIdx.x * nb;
+  uint32_t carry = 0u;
+  for (int j0 = 0, r = 0; j0 < nbl; j0 += 1024, r ^= 1) {
+    const int j = j0 + 4 * threadIdx.x;
+    uint32_t v[4], s = 0u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = j + q < nbl ? in[j + q] : 0u;
+      s += v[q];
+    }
+    const uint32_t incl = rga::wave_scan(s);
+    if (lane == 63) wtot[r][wave] = incl;
+    __syncthreads();
+    uint32_t run = carry + incl - s;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      run += w < wave ? wtot[r][w] : 0u;
+      carry += wtot[r][w];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (j + q < nbl) out[j + q] = run;
+      run += v[q];
+    }
+  }
+  if (threadIdx.x == 0) bintot[blockIdx.x] = carry;
+}
+
 // Stable scatter of one block.  Each wave owns a contiguous run of
 // 64 ITEMS items (so the block's order is wave by wave, round by round, lane
 // by lane) and keeps them in registers.  Pass 1: per round, items with the
@@ -496,26 +552,34 @@ radix_binscan(const uint32_t* __restrict__ hist, int nb, const int64_t* cnt_ptr,
 // written over the wave's counts; after a second barrier each wave scatters
 // its rounds with no further barrier: position = running start of the digit
 // + rank, and the group's lowest lane advances the running start (the
-// wave's LDS operations complete in order).
-template <int ITEMS, int BITS>
+// wave's LDS operations complete in order).  Narrow digits (16 items of 2048 and
+// more each) are first put in order in LDS, so that a wave stores runs of a
+// digit side by side: stored one by one, each item was a write of its own at the
+// L2 (3.4 million entries, two passes of 7 bits: 51 -> 35 us).
+template <int ITEMS, int BITS, bool LIVE = false>
 __global__ void __launch_bounds__(kRadixThreads)
 radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                 uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                 const int64_t* cnt_ptr, int64_t fixed, int64_t cap, int shift,
                 const uint32_t* __restrict__ binoff, const uint32_t* __restrict__ bintot,
-                int32_t* __restrict__ ranges, int nranges) {
+                int32_t* __restrict__ ranges, int nranges, int64_t* __restrict__ live, int nb) {
   constexpr int kRadix = 1 << BITS;
   constexpr int kWavesR = kRadixThreads / 64;
-  constexpr int kPer = kRadix / kRadixThreads;   // digits per thread in the digit scan
-  static_assert(kPer >= 1, "at least one digit per thread");
+  // digits per thread in the digit scan (the threads past the digits have none)
+  constexpr int kPer = (kRadix + kRadixThreads - 1) / kRadixThreads;
+  constexpr bool kNarrow = BITS <= 8;
   __shared__ uint32_t run[kWavesR][kRadix];
-  __shared__ uint32_t wtot[kWavesR];
+  __shared__ uint32_t wtot[kWavesR], ltot[kWavesR];
+  __shared__ uint32_t shift_to[kNarrow ? kRadix : 1];
+  __shared__ uint2 sorted[kNarrow ? kRadixThreads * ITEMS : 1];
+  uint32_t mine = 0u;   // items of this thread's digit in the block
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t count = live_count(cnt_ptr, fixed, cap);
-  const int64_t blk = (int64_t)blockIdx.x * (kRadixThreads * ITEMS);
+  const int block = blockIdx.x;
+  const int64_t blk = (int64_t)block * (kRadixThreads * ITEMS);
   // block 0 of a one-pass tile sort writes the ranges even when there are no
   // entries
-  if (blk >= count && !(ranges && blockIdx.x == 0)) return;
+  if (blk >= count && !(ranges && block == 0)) return;
   uint32_t* wrun = run[wave];
   for (int d = lane; d < kRadix; d += 64) wrun[d] = 0u;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -530,7 +594,7 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
   }
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
-    const bool ok = wbeg + 64 * r + lane < count;
+    const bool ok = wbeg + 64 * r + lane < count && (!LIVE || key[r] != kCulled);
     const uint32_t d = (key[r] >> shift) & (kRadix - 1);
     uint64_t peers = __ballot(ok);
 #pragma unroll
@@ -551,7 +615,7 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
   uint32_t s = 0;
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
-    tot[q] = bintot[tid * kPer + q];
+    tot[q] = tid * kPer + q < kRadix ? bintot[tid * kPer + q] : 0u;
     s += tot[q];
   }
   uint32_t incl = s;
@@ -567,20 +631,72 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
     const int d = tid * kPer + q;
+    if (d >= kRadix) break;
     // a one-pass tile sort: digit d is tile d, and its entries land at
     // [start of the digit, + its total)
-    if (ranges && blockIdx.x == 0 && d < nranges) {
+    if (ranges && block == 0 && d < nranges) {
       ranges[2 * d] = (int32_t)start;
       ranges[2 * d + 1] = (int32_t)(start + tot[q]);
     }
-    uint32_t acc = start + binoff[(size_t)blockIdx.x * kRadix + d];
+    uint32_t acc = start + binoff[table_at<BITS>(block, d, nb)];
+    if constexpr (kNarrow) {
+      shift_to[d] = acc;
+      for (int w = 0; w < kWavesR; ++w) mine += run[w][d];
+    } else {
 #pragma unroll
-    for (int w = 0; w < kWavesR; ++w) {
-      const uint32_t h = run[w][d];
-      run[w][d] = acc;
-      acc += h;
+      for (int w = 0; w < kWavesR; ++w) {
+        const uint32_t h = run[w][d];
+        run[w][d] = acc;
+        acc += h;
+      }
     }
     start += tot[q];
+  }
+  if (LIVE && block == 0 && tid == kRadixThreads - 1) *live = (int64_t)start;
+  if constexpr (kNarrow) {
+    // the digits' places in the block, and how far each is from its place in
+    // the output
+    const uint32_t li = rga::wave_scan(mine);
+    if (lane == 63) ltot[wave] = li;
+    __syncthreads();
+    uint32_t at = li - mine, items = 0u;
+#pragma unroll
+    for (int w = 0; w < kWavesR; ++w) {
+      at += w < wave ? ltot[w] : 0u;
+      items += ltot[w];
+    }
+    if (tid < kRadix) {
+      shift_to[tid] -= at;
+#pragma unroll
+      for (int w = 0; w < kWavesR; ++w) {
+        const uint32_t h = run[w][tid];
+        run[w][tid] = at;
+        at += h;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      if (info[r] != 0xFFFFFFFFu) {
+        const uint32_t d = (key[r] >> shift) & (kRadix - 1);
+        const uint32_t rank = info[r] & 63u, group = info[r] >> 6;
+        const uint32_t pos = wrun[d] + rank;
+        sorted[pos] = make_uint2(key[r], val[r]);
+        if (rank == 0) wrun[d] += group;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const uint32_t i = (uint32_t)(r * kRadixThreads + tid);
+      if (i < items) {
+        const uint2 e = sorted[i];
+        const uint32_t pos = i + shift_to[(e.x >> shift) & (kRadix - 1)];
+        kout[pos] = e.x;
+        vout[pos] = e.y;
+      }
+    }
+    return;
   }
   __syncthreads();
 #pragma unroll
@@ -596,92 +712,130 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
   }
 }
 
-// ---- exclusive scan of tiles-touched in depth order -> offsets, D ---------
-// Exclusive scan of tiles-touched in depth order, in one launch: every block
-// sums its items, publishes the sum and takes a ticket; the block that takes
-// the last ticket scans the block sums in a fixed order (deterministic) and
-// writes the offsets and D.  No block waits for another.  `done` is zeroed
-// on the stream before the launch.
-__global__ void __launch_bounds__(kRadixThreads)
-touched_scan_kernel(int n, const uint32_t* __restrict__ order, const int32_t* __restrict__ touched,
-                    uint32_t* __restrict__ bsum, uint32_t* __restrict__ boff,
-                    int64_t* __restrict__ count, uint32_t* __restrict__ done) {
-  __shared__ uint32_t red[kRadixThreads];
-  __shared__ uint64_t part[kRadixThreads];
-  __shared__ bool last;
-  const int64_t blk = (int64_t)blockIdx.x * kBlockN;
-  uint32_t s = 0;
-  for (int r = 0; r < kItemsN; ++r) {
-    const int64_t i = blk + (int64_t)r * kRadixThreads + threadIdx.x;
-    if (i < n) s += (uint32_t)touched[order[i]];
-  }
-  red[threadIdx.x] = s;
+// ---- entries: one per (splat, tile touched), in depth order -----------------
+// Tiles touched by each block of kBlockN splats in depth order (those that touch
+// any come first: *live of them).
+__global__ void __launch_bounds__(kBlockN)
+touched_sum_kernel(const int64_t* __restrict__ live, const uint32_t* __restrict__ order,
+                   const int32_t* __restrict__ touched, uint32_t* __restrict__ bsum) {
+  __shared__ uint32_t red[kBlockN / 64];
+  const int64_t n = *live, i = (int64_t)blockIdx.x * kBlockN + threadIdx.x;
+  if ((int64_t)blockIdx.x * kBlockN >= n) return;
+  const uint32_t v = rga::wave_scan(i < n ? (uint32_t)touched[order[i]] : 0u);
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int o = kRadixThreads / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    bsum[blockIdx.x] = red[0];
-    __threadfence();                                   // publish before the ticket
-    last = atomicAdd(done, 1u) == gridDim.x - 1;
+    uint32_t s = 0u;
+#pragma unroll
+    for (int w = 0; w < kBlockN / 64; ++w) s += red[w];
+    bsum[blockIdx.x] = s;
   }
-  __syncthreads();
-  if (!last) return;
-  __threadfence();                                     // see every block's sum
-  const int nb = gridDim.x;
-  const int chunk = (nb + kRadixThreads - 1) / kRadixThreads;
-  const int j0 = threadIdx.x * chunk, j1 = min(nb, j0 + chunk);
-  uint64_t t = 0;
-  for (int j = j0; j < j1; ++j) t += bsum[j];
-  part[threadIdx.x] = t;
-  __syncthreads();
-  for (int o = 1; o < kRadixThreads; o <<= 1) {
-    const uint64_t v = threadIdx.x >= o ? part[threadIdx.x - o] : 0ull;
-    __syncthreads();
-    part[threadIdx.x] += v;
-    __syncthreads();
-  }
-  uint64_t run = threadIdx.x ? part[threadIdx.x - 1] : 0ull;
-  for (int j = j0; j < j1; ++j) {
-    boff[j] = (uint32_t)(run < 0xFFFFFFFFull ? run : 0xFFFFFFFFull);
-    run += bsum[j];
-  }
-  if (threadIdx.x == kRadixThreads - 1) count[0] = (int64_t)part[kRadixThreads - 1];
 }
 
-// One thread per splat in depth order (blocks of kBlockN, as in the
-// offsets scan): a workgroup scan of tiles-touched (wave scans, then the
-// sixteen wave totals) gives each splat its first entry.
+// One thread per splat in depth order: the sums of the blocks before and a
+// workgroup scan of tiles-touched (wave scans, then the waves' totals) give each
+// splat its first entry; the last block knows D.  Then one thread per entry,
+// kDupChunk entries at a time: a splat marks its first entry in LDS, a running
+// maximum over the marks gives every entry its splat, and the entries leave in
+// whole lines.  With one thread storing each splat's entries the 3.4 million of
+// 300k splats took 49 us, now 17.
+constexpr int kDupItems = 8;
+constexpr int kDupChunk = kBlockN * kDupItems;
+
 __global__ void __launch_bounds__(kBlockN)
-duplicate_kernel(int n, int TX, int64_t cap, const uint32_t* __restrict__ order,
-                 const int32_t* __restrict__ touched, const int32_t* __restrict__ rect,
-                 const uint32_t* __restrict__ boff, uint32_t* __restrict__ tkeys,
-                 uint32_t* __restrict__ tvals) {
-  __shared__ uint32_t wt[kBlockN / 64];
+duplicate_kernel(int n, int TX, int64_t cap, const int64_t* __restrict__ live,
+                 const uint32_t* __restrict__ order, const int32_t* __restrict__ touched,
+                 const int32_t* __restrict__ rect, const uint32_t* __restrict__ bsum,
+                 uint32_t* __restrict__ tkeys, uint32_t* __restrict__ tvals,
+                 int64_t* __restrict__ total) {
+  constexpr int kW = kBlockN / 64;
+  __shared__ uint32_t wt[kW];
+  __shared__ uint64_t wb[kW];
+  __shared__ int wm[kW];
+  __shared__ __align__(16) uint16_t own[kDupChunk];   // 1 + the entry's splat in the block
+  __shared__ uint32_t splat[kBlockN], begin[kBlockN], corner[kBlockN], width[kBlockN];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t i = (int64_t)blockIdx.x * kBlockN + tid;
+  const int64_t nl = *live, i0 = (int64_t)blockIdx.x * kBlockN, i = i0 + tid;
+  if (i0 >= nl) return;
+  uint64_t before = 0ull;
+  for (int j = tid; j < (int)blockIdx.x; j += kBlockN) before += bsum[j];
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) before += __shfl_xor(before, o, 64);
   uint32_t g = 0u, cnt = 0u;
-  if (i < n) {
+  if (i < nl) {
     g = order[i];
     cnt = (uint32_t)touched[g];
   }
   const uint32_t incl = rga::wave_scan(cnt);
   if (lane == 63) wt[wave] = incl;
+  if (lane == 0) wb[wave] = before;
+  splat[tid] = g;
+  if (cnt > 0u) {
+    const int x0 = rect[g], y0 = rect[n + g];
+    corner[tid] = (uint32_t)(y0 * TX + x0);
+    width[tid] = (uint32_t)(rect[2 * n + g] - x0 + 1);
+  }
   __syncthreads();
-  uint32_t before = 0u;
-  for (int w = 0; w < wave; ++w) before += wt[w];
-  if (cnt == 0u) return;
-  uint64_t off = (uint64_t)boff[blockIdx.x] + before + (incl - cnt);
-  const int x0 = rect[g], y0 = rect[n + g], x1 = rect[2 * n + g], y1 = rect[3 * n + g];
-  for (int ty = y0; ty <= y1; ++ty)
-    for (int tx = x0; tx <= x1; ++tx) {
-      if ((int64_t)off < cap) {
-        tkeys[off] = (uint32_t)(ty * TX + tx);
-        tvals[off] = g;
-      }
-      ++off;
+  uint64_t base = 0ull;
+  uint32_t first = incl - cnt, sum = 0u;
+#pragma unroll
+  for (int v = 0; v < kW; ++v) {
+    base += wb[v];
+    first += v < wave ? wt[v] : 0u;
+    sum += wt[v];
+  }
+  begin[tid] = first;
+  if (tid == 0 && i0 + kBlockN >= nl) *total = (int64_t)(base + sum);
+  for (uint32_t c0 = 0u; c0 < sum && (int64_t)(base + c0) < cap; c0 += kDupChunk) {
+    uint4* mine = reinterpret_cast<uint4*>(own) + tid;   // kDupItems marks
+    static_assert(kDupItems == 8, "eight marks of two bytes");
+    *mine = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    // a splat's mark: at its first entry, or at the chunk's if it began before
+    if (cnt > 0u && first < c0 + kDupChunk && first + cnt > c0)
+      own[first > c0 ? first - c0 : 0u] = (uint16_t)(tid + 1);
+    __syncthreads();
+    const uint4 q = *mine;
+    const uint32_t words[4] = {q.x, q.y, q.z, q.w};
+    int m[kDupItems], top = 0;
+#pragma unroll
+    for (int u = 0; u < kDupItems; ++u) {
+      top = max(top, (int)((words[u >> 1] >> (16 * (u & 1))) & 0xFFFFu));
+      m[u] = top;
     }
+    int run = top;                       // inclusive maximum over the wave
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(run, o, 64);
+      if (lane >= o) run = max(run, t);
+    }
+    if (lane == 63) wm[wave] = run;
+    int prev = __shfl_up(run, 1, 64);
+    if (lane == 0) prev = 0;
+    __syncthreads();
+    for (int v = 0; v < wave; ++v) prev = max(prev, wm[v]);
+#pragma unroll
+    for (int u = 0; u < kDupItems; ++u) m[u] = max(m[u], prev);
+    *mine = make_uint4((uint32_t)m[0] | (uint32_t)m[1] << 16, (uint32_t)m[2] | (uint32_t)m[3] << 16,
+                       (uint32_t)m[4] | (uint32_t)m[5] << 16, (uint32_t)m[6] | (uint32_t)m[7] << 16);
+    __syncthreads();
+    const uint32_t left = min((uint32_t)kDupChunk, sum - c0);
+#pragma unroll
+    for (int u = 0; u < kDupItems; ++u) {
+      const uint32_t e = (uint32_t)(u * kBlockN + tid);
+      const int64_t off = (int64_t)(base + c0) + e;
+      if (e >= left || off >= cap) continue;
+      const int o = (int)own[e] - 1;
+      const uint32_t k = c0 + e - begin[o], w = width[o];
+      // k / w from an approximate reciprocal, put right (k is below 2^24)
+      uint32_t y = (uint32_t)((float)k * __builtin_amdgcn_rcpf((float)w));
+      y -= y * w > k ? 1u : 0u;
+      y += k - y * w >= w ? 1u : 0u;
+      tkeys[off] = corner[o] + y * (uint32_t)TX + (k - y * w);
+      tvals[off] = splat[o];
+    }
+    __syncthreads();
+  }
 }
 
 __global__ void __launch_bounds__(256)
@@ -694,11 +848,12 @@ __global__ void __launch_bounds__(256)
 tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, int64_t cap,
                    int32_t* __restrict__ ranges) {
   const int64_t count = live_count(cnt_ptr, 0, cap);
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const uint32_t t = tkeys[i];
-  if (i == 0 || tkeys[i - 1] != t) ranges[2 * t] = (int32_t)i;
-  if (i == count - 1 || tkeys[i + 1] != t) ranges[2 * t + 1] = (int32_t)(i + 1);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t t = tkeys[i];
+    if (i == 0 || tkeys[i - 1] != t) ranges[2 * t] = (int32_t)i;
+    if (i == count - 1 || tkeys[i + 1] != t) ranges[2 * t + 1] = (int32_t)(i + 1);
+  }
 }
 
 // ---- blend ------------------------------------------------------------------
@@ -1696,63 +1851,62 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
                L.parts > 1 ? tiles * kBlocks * L.parts * 16 : (int64_t)0);
     // depth sort: 3 passes of 11 bits over n 32-bit keys (4 passes of 8
     // bits, with 8x smaller digit tables, take longer: the passes are
-    // latency-bound launches)
+    // latency-bound launches).  The first leaves out the culled splats (half of
+    // an avatar's face away), the rest of the binning has the others only.
+    int64_t* live = cnt + 3;
     for (int pass = 0; pass < kDepthPasses; ++pass) {
       const int shift = kDepthBits * pass;
-      RGA_LAUNCH("radix_upsweep", (radix_upsweep<kItemsN, kDepthBits>), dim3(L.nb_n), dim3(kRadixThreads), 0, s, k0,
-                 (const int64_t*)nullptr, (int64_t)n, (int64_t)n, shift, hist);
-      RGA_LAUNCH("radix_binscan", radix_binscan<kDepthBits>, dim3((1 << kDepthBits) / 8), dim3(256), 0, s, hist, L.nb_n,
-                 (const int64_t*)nullptr, (int64_t)n, (int64_t)n, kBlockN, binoff, bintot);
-      RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsN, kDepthBits>), dim3(L.nb_n), dim3(kRadixThreads), 0, s, k0,
-                 v0, k1, v1, (const int64_t*)nullptr, (int64_t)n, (int64_t)n, shift, binoff, bintot,
-                 (int32_t*)nullptr, 0);
+      const int64_t* count = pass > 0 ? live : nullptr;
+      auto up = pass > 0 ? radix_upsweep<kItemsN, kDepthBits> : radix_upsweep<kItemsN, kDepthBits, true>;
+      auto down = pass > 0 ? radix_downsweep<kItemsN, kDepthBits>
+                           : radix_downsweep<kItemsN, kDepthBits, true>;
+      RGA_LAUNCH("radix_upsweep", up, dim3(L.nb_n), dim3(kRadixThreads), 0, s, k0, count, (int64_t)n,
+                 (int64_t)n, shift, hist);
+      RGA_LAUNCH("radix_binscan", radix_binscan<kDepthBits>, dim3((1 << kDepthBits) / 8), dim3(256), 0, s,
+                 hist, L.nb_n, count, (int64_t)n, (int64_t)n, kBlockN, binoff, bintot);
+      RGA_LAUNCH("radix_downsweep", down, dim3(L.nb_n), dim3(kRadixThreads), 0, s, k0, v0, k1, v1, count,
+                 (int64_t)n, (int64_t)n, shift, binoff, bintot, (int32_t*)nullptr, 0, live, L.nb_n);
       uint32_t* t = k0; k0 = k1; k1 = t;
       t = v0; v0 = v1; v1 = t;
     }
-    // v0 now holds the splat indices in (depth, index) order
+    // v0 now holds the live splats' indices in (depth, index) order
     uint32_t* bsum = at<uint32_t>(ws, L.bsum);
-    uint32_t* boff = at<uint32_t>(ws, L.boff);
-    RGA_LAUNCH("touched_scan", touched_scan_kernel, dim3(L.nb_n), dim3(kRadixThreads), 0, s, n, v0,
-               at<int32_t>(ws, L.touched), bsum, boff, cnt,
-               reinterpret_cast<uint32_t*>(cnt) + 4);
+    RGA_LAUNCH("touched_sum", touched_sum_kernel, dim3(L.nb_n), dim3(kBlockN), 0, s, live, v0,
+               at<int32_t>(ws, L.touched), bsum);
     uint32_t* tk0 = at<uint32_t>(ws, L.tk0);
     uint32_t* tv0 = at<uint32_t>(ws, L.tv0);
     uint32_t* tk1 = at<uint32_t>(ws, L.tk1);
     uint32_t* tv1 = at<uint32_t>(ws, L.tv1);
     RGA_LAUNCH("splat_duplicate", duplicate_kernel, dim3(L.nb_n), dim3(kBlockN), 0, s, n,
-               L.tiles_x, capacity, v0, at<int32_t>(ws, L.touched), at<int32_t>(ws, L.rect), boff,
-               tk0, tv0);
-    if (L.tile_passes == 1 && L.tile_bits == kWideBits) {
-      // 2049 .. 4096 tiles: one pass of 12-bit digits, whose scatter also
-      // writes the tile ranges
-      constexpr int kWide = 1 << kWideBits;
-      RGA_LAUNCH("radix_upsweep", (radix_upsweep<kItemsD, kWideBits>), dim3(L.nb_cap),
-                 dim3(kRadixThreads), 0, s, tk0, (const int64_t*)cnt, (int64_t)0, capacity, 0, hist);
-      RGA_LAUNCH("radix_binscan", radix_binscan<kWideBits>, dim3(kWide / 8), dim3(256), 0, s, hist,
-                 L.nb_cap, (const int64_t*)cnt, (int64_t)0, capacity, kBlockD, binoff, bintot);
-      RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsD, kWideBits>), dim3(L.nb_cap),
-                 dim3(kRadixThreads), 0, s, tk0, tv0, tk1, tv1, (const int64_t*)cnt, (int64_t)0,
-                 capacity, 0, binoff, bintot, ranges, (int)tiles);
-      uint32_t* t = tk0; tk0 = tk1; tk1 = t;
-      t = tv0; tv0 = tv1; tv1 = t;
-    }
-    for (int pass = 0; pass < L.tile_passes && L.tile_bits == kDigitBits; ++pass) {
-      const int shift = kDigitBits * pass;
-      RGA_LAUNCH("radix_upsweep", (radix_upsweep<kItemsD, kDigitBits>), dim3(L.nb_cap), dim3(kRadixThreads), 0, s, tk0,
+               L.tiles_x, capacity, live, v0, at<int32_t>(ws, L.touched), at<int32_t>(ws, L.rect), bsum,
+               tk0, tv0, cnt);
+    // with one tile pass its scatter also writes the tile ranges
+    const bool one = L.tile_passes == 1;
+    for (int pass = 0; pass < L.tile_passes; ++pass) {
+      const int shift = L.tile_bits * pass;
+      auto up = L.tile_bits == 7 ? radix_upsweep<kItemsD, 7> : L.tile_bits == 8 ? radix_upsweep<kItemsD, 8>
+                : (L.tile_bits == 10 ? radix_upsweep<kItemsD, 10>
+                   : (L.tile_bits == 11 ? radix_upsweep<kItemsD, 11> : radix_upsweep<kItemsD, 12>));
+      auto scan = L.tile_bits == 7 ? radix_rowscan<7> : L.tile_bits == 8 ? radix_rowscan<8>
+                  : (L.tile_bits == 10 ? radix_binscan<10>
+                     : (L.tile_bits == 11 ? radix_binscan<11> : radix_binscan<12>));
+      auto down = L.tile_bits == 7 ? radix_downsweep<kItemsD, 7> : L.tile_bits == 8 ? radix_downsweep<kItemsD, 8>
+                  : (L.tile_bits == 10 ? radix_downsweep<kItemsD, 10>
+                     : (L.tile_bits == 11 ? radix_downsweep<kItemsD, 11> : radix_downsweep<kItemsD, 12>));
+      RGA_LAUNCH("radix_upsweep", up, dim3(L.nb_cap), dim3(kRadixThreads), 0, s, tk0,
                  (const int64_t*)cnt, (int64_t)0, capacity, shift, hist);
-      RGA_LAUNCH("radix_binscan", radix_binscan<kDigitBits>, dim3(kRadix / 8), dim3(256), 0, s, hist, L.nb_cap,
+      RGA_LAUNCH("radix_binscan", scan, dim3((1 << L.tile_bits) / (L.tile_bits <= 8 ? 1 : 8)), dim3(256), 0, s, hist, L.nb_cap,
                  (const int64_t*)cnt, (int64_t)0, capacity, kBlockD, binoff, bintot);
-      // with one tile pass its scatter also writes the tile ranges
-      const bool one = L.tile_passes == 1;
-      RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsD, kDigitBits>), dim3(L.nb_cap), dim3(kRadixThreads), 0, s, tk0,
-                 tv0, tk1, tv1, (const int64_t*)cnt, (int64_t)0, capacity, shift, binoff, bintot,
-                 one ? ranges : (int32_t*)nullptr, one ? (int)tiles : 0);
+      RGA_LAUNCH("radix_downsweep", down, dim3(L.nb_cap), dim3(kRadixThreads), 0, s, tk0, tv0, tk1, tv1,
+                 (const int64_t*)cnt, (int64_t)0, capacity, shift, binoff, bintot,
+                 one ? ranges : (int32_t*)nullptr, one ? (int)tiles : 0, (int64_t*)nullptr, L.nb_cap);
       uint32_t* t = tk0; tk0 = tk1; tk1 = t;
       t = tv0; tv0 = tv1; tv1 = t;
     }
-    if (L.tile_passes > 1)
-      RGA_LAUNCH("tile_ranges", tile_ranges_kernel, dim3(rga::ceil_div(capacity, 256)), dim3(256), 0,
-                 s, tk0, (const int64_t*)cnt, capacity, ranges);
+    if (!one)
+      RGA_LAUNCH("tile_ranges", tile_ranges_kernel,
+                 dim3(std::min<int64_t>(rga::ceil_div(capacity, 256), 2048)), dim3(256), 0, s, tk0,
+                 (const int64_t*)cnt, capacity, ranges);
   }
   RGA_CHECK_LAUNCH("splat_bin");
   return RGA_OK;
@@ -1884,7 +2038,7 @@ extern "C" int vertex_order(void* stream, int n, const int32_t* vidx, int nv, in
                (const int64_t*)nullptr, (int64_t)n, (int64_t)n, kBlockN, binoff, bintot);
     RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsN, kDigitBits>), dim3(L.nb), dim3(kRadixThreads), 0, s,
                k0, v0, k1, vout, (const int64_t*)nullptr, (int64_t)n, (int64_t)n, shift, binoff,
-               bintot, (int32_t*)nullptr, 0);
+               bintot, (int32_t*)nullptr, 0, (int64_t*)nullptr, L.nb);
     uint32_t* t = k0; k0 = k1; k1 = t;
     t = v0; v0 = v1; v1 = t;
   }

@@ -1,0 +1,89 @@
+"""The binning over every digit width of its tile sort (one pass of 8, 10, 11 and
+12 bits, two of 7, 8 and 11; the largest and smallest number of tiles of each),
+with culled and back-facing splats, splats of one tile and of thousands, equal
+depths, no live splat at all, block sizes of the splats and a capacity that cuts
+the entries off.
+
+D, the tile ranges and every list are those of the definition, bit for bit: live
+splats by (depth bits, index), one entry per tile of a splat's rectangle row by
+row, the first `capacity` of them sorted stably by tile (the projection's
+rectangles and depths are tested elsewhere against the oracle and are read back
+here)."""
+
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_10707_amd import rga, synth
+
+pytestmark = pytest.mark.gpu
+
+# width, height, splats, share of them that face the camera
+CASES = [(64, 64, 3000, 0.6), (256, 256, 512, 1.0), (272, 256, 513, 0.5), (512, 512, 3000, 0.6),
+         (528, 512, 3000, 0.6), (1024, 528, 3000, 0.6), (1024, 1024, 1, 1.0), (1024, 1024, 3000, 0.6),
+         (1040, 1024, 3000, 0.6), (2048, 2048, 2000, 0.6), (2064, 2048, 2000, 0.6),
+         (4096, 4096, 700, 0.6), (16384, 1040, 700, 0.6), (512, 512, 3000, 0.0), (1, 1, 40, 0.5),
+         (300, 200, 5000, 0.5)]
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a)).cuda()
+
+
+def _bin(cam, a, front, capacity):
+    n = len(front)
+    ws = rga.SplatWorkspace(n, cam.width, cam.height, capacity, "cuda")
+    rga.splat_bin(cam, *(dev(v) for v in a), dev(front), ws)
+    st = ws.state()
+    tiles = st.tiles_x * st.tiles_y
+    get = lambda p, shape: ws.view(p, shape, torch.int32).cpu().numpy()
+    D = ws.count()
+    return (D, get(st.rect, (4, n)), get(st.touched, (n,)), get(st.depth, (n,)),
+            get(st.ranges, (tiles, 2)), get(st.sorted, (min(D, capacity),)), st.tiles_x)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_lists(case):
+    print(f"[binning] {case}", flush=True)
+    W, H, n, share = case
+    rng = np.random.default_rng(W + H + n)
+    cam = dataclasses.replace(synth.default_camera(W, H), fx=1.6 * W, fy=1.6 * H)
+    x = rng.uniform(-0.9, 0.9, (3, n)).astype(np.float32)
+    x[2] = np.round(8 * x[2]) / 8                              # depths tie
+    A = np.tile(np.eye(3, dtype=np.float32).reshape(9, 1), (1, n))
+    q = rng.normal(size=(4, n)).astype(np.float32)
+    log_s = rng.normal(-5.5, 0.5, (3, n)).astype(np.float32)
+    log_s[:, rng.random(n) < 0.01] = -1.5                      # a few cover much of the image
+    opac = rng.uniform(0.001, 0.9, n).astype(np.float32)       # some below 1/255: culled
+    front = (rng.random(n) < share).astype(np.uint8)
+    a = (x, A, q, log_s, opac)
+    capacity = 1 << 22
+    for part in (1, 2):                                        # all entries, then half of them
+        D, rect, touched, depth, ranges, got, tx = _bin(cam, a, front, capacity)
+        assert D <= 1 << 22 and (share > 0 or D == 0)
+        order = np.lexsort((np.arange(n), depth.view(np.uint32)))
+        order = order[touched[order] > 0]
+        tile, splat = [], []
+        for g in order:
+            x0, y0, x1, y1 = rect[:, g]
+            t = (np.arange(y0, y1 + 1)[:, None] * tx + np.arange(x0, x1 + 1)[None]).reshape(-1)
+            assert len(t) == touched[g]
+            tile.append(t)
+            splat.append(np.full(len(t), g))
+        tile = np.concatenate(tile) if tile else np.zeros(0, int)
+        splat = np.concatenate(splat) if splat else np.zeros(0, int)
+        assert D == len(tile)
+        tile, splat = tile[:capacity], splat[:capacity]
+        by = np.argsort(tile, kind="stable")
+        assert np.array_equal(got, splat[by])
+        count = np.bincount(tile, minlength=len(ranges))
+        end = np.cumsum(count)
+        full = count > 0
+        assert np.array_equal(ranges[full, 0], (end - count)[full])
+        assert np.array_equal(ranges[full, 1], end[full])
+        assert np.array_equal(ranges[~full, 0], ranges[~full, 1])
+        if D < 2:
+            break
+        capacity = D // 2
