@@ -712,6 +712,137 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
   }
 }
 
+// ---- depth sort of few splats -----------------------------------------------
+// The whole sort in one workgroup's LDS, with the live count and the sums of
+// tiles touched: the same stable LSD order in passes of 8 bits (one whose digit
+// is the same in every key is left out; culled splats sort last by their key).
+// Each of the sixteen waves owns a contiguous run of the items.  It stands for ten
+// launches, which bound small frames on the device and on the host: 2,000
+// Gaussians' training step 168 -> 136 us, 4,096 splats forward and back 94 -> 76 us
+// (13 and 19 us in here; twice as many would take as long as the launches).
+constexpr int kSmallSort = 4096;
+
+__global__ void __launch_bounds__(1024)
+small_sort_kernel(int n, const uint32_t* __restrict__ keys, const int32_t* __restrict__ touched,
+                  uint32_t* __restrict__ order, uint32_t* __restrict__ bsum,
+                  int64_t* __restrict__ live) {
+  constexpr int kW = 16, kR = kSmallSort / 1024;
+  __shared__ uint32_t key[2][kSmallSort];
+  __shared__ uint16_t idx[2][kSmallSort];
+  __shared__ uint16_t run[kW][256];
+  __shared__ uint32_t wt[4], bs[kSmallSort / kBlockN], alive, all_or, all_and;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const int rounds = (n + 1023) / 1024;
+  if (tid < kSmallSort / kBlockN) bs[tid] = 0u;
+  if (tid == 0) {
+    alive = 0u;
+    all_or = 0u;
+    all_and = ~0u;
+  }
+  __syncthreads();
+  {
+    uint32_t o = 0u, a = ~0u, count = 0u;
+    for (int r = 0; r < rounds; ++r) {
+      const int i = 1024 * r + tid;
+      const uint32_t k = i < n ? keys[i] : kCulled;
+      key[0][i] = k;
+      idx[0][i] = (uint16_t)i;
+      count += (uint32_t)__popcll(__ballot(k != kCulled));
+      if (k != kCulled) {
+        o |= k;
+        a &= k;
+      }
+    }
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+      o |= __shfl_xor(o, s, 64);
+      a &= __shfl_xor(a, s, 64);
+    }
+    if (lane == 0) {
+      atomicAdd(&alive, count);
+      atomicOr(&all_or, o);
+      atomicAnd(&all_and, a);
+    }
+  }
+  __syncthreads();
+  // (culled keys are all ones: with any of them every digit differs, unless it is
+  // all ones in the live keys too, so the live keys' own bits decide and the
+  // last pass, of the sign and exponent, parts the culled)
+  const uint32_t differ = all_or ^ all_and;
+  const bool some_culled = alive != (uint32_t)(1024 * rounds);
+  int cur = 0;
+  for (int shift = 0; shift < 32; shift += 8) {
+    if (((differ >> shift) & 0xFFu) == 0u && !(shift == 24 && some_culled)) continue;
+    if (tid < 512) reinterpret_cast<uint4*>(&run[0][0])[tid] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    uint32_t k[kR], info[kR];
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      if (r >= rounds) break;
+      k[r] = key[cur][64 * (wave * rounds + r) + lane];
+      const uint32_t d = (k[r] >> shift) & 0xFFu;
+      uint64_t peers = ~0ull;
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t m = __ballot(bit);
+        peers &= bit ? m : ~m;
+      }
+      const uint32_t rank = __popcll(peers & lt), group = __popcll(peers);
+      if (rank == 0) run[wave][d] = (uint16_t)(run[wave][d] + group);
+      info[r] = rank | (group << 8);
+    }
+    __syncthreads();
+    uint32_t total = 0u, incl = 0u;
+    if (tid < 256) {
+#pragma unroll
+      for (int w = 0; w < kW; ++w) total += run[w][tid];
+      incl = rga::wave_scan(total);
+      if (lane == 63) wt[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t at = incl - total;
+      for (int w = 0; w < wave; ++w) at += wt[w];
+#pragma unroll
+      for (int w = 0; w < kW; ++w) {
+        const uint32_t c = run[w][tid];
+        run[w][tid] = (uint16_t)at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      if (r >= rounds) break;
+      const uint32_t d = (k[r] >> shift) & 0xFFu;
+      const uint32_t rank = info[r] & 0xFFu, group = info[r] >> 8;
+      const uint32_t at = run[wave][d], pos = at + rank;
+      key[cur ^ 1][pos] = k[r];
+      idx[cur ^ 1][pos] = idx[cur][64 * (wave * rounds + r) + lane];
+      if (rank == 0) run[wave][d] = (uint16_t)(at + group);
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+  const int nl = (int)alive;
+  for (int r = 0; r < rounds; ++r) {
+    const int i = 1024 * r + tid;
+    uint32_t t = 0u;
+    if (i < nl) {
+      const uint32_t g = idx[cur][i];
+      order[i] = g;
+      t = (uint32_t)touched[g];
+    }
+    const uint32_t s = rga::wave_scan(t);
+    if (lane == 63) atomicAdd(&bs[i / kBlockN], s);
+  }
+  __syncthreads();
+  if (tid < (nl + kBlockN - 1) / kBlockN) bsum[tid] = bs[tid];
+  if (tid == 0) *live = nl;
+}
+
 // ---- entries: one per (splat, tile touched), in depth order -----------------
 // Tiles touched by each block of kBlockN splats in depth order (those that touch
 // any come first: *live of them).
@@ -1854,7 +1985,12 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
     // latency-bound launches).  The first leaves out the culled splats (half of
     // an avatar's face away), the rest of the binning has the others only.
     int64_t* live = cnt + 3;
-    for (int pass = 0; pass < kDepthPasses; ++pass) {
+    uint32_t* bsum = at<uint32_t>(ws, L.bsum);
+    const bool small = n <= kSmallSort;
+    if (small)
+      RGA_LAUNCH("small_sort", small_sort_kernel, dim3(1), dim3(1024), 0, s, n, k0,
+                 at<int32_t>(ws, L.touched), v0, bsum, live);
+    for (int pass = 0; pass < kDepthPasses && !small; ++pass) {
       const int shift = kDepthBits * pass;
       const int64_t* count = pass > 0 ? live : nullptr;
       auto up = pass > 0 ? radix_upsweep<kItemsN, kDepthBits> : radix_upsweep<kItemsN, kDepthBits, true>;
@@ -1870,8 +2006,8 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
       t = v0; v0 = v1; v1 = t;
     }
     // v0 now holds the live splats' indices in (depth, index) order
-    uint32_t* bsum = at<uint32_t>(ws, L.bsum);
-    RGA_LAUNCH("touched_sum", touched_sum_kernel, dim3(L.nb_n), dim3(kBlockN), 0, s, live, v0,
+    if (!small)
+      RGA_LAUNCH("touched_sum", touched_sum_kernel, dim3(L.nb_n), dim3(kBlockN), 0, s, live, v0,
                at<int32_t>(ws, L.touched), bsum);
     uint32_t* tk0 = at<uint32_t>(ws, L.tk0);
     uint32_t* tv0 = at<uint32_t>(ws, L.tv0);
