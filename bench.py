@@ -13,7 +13,7 @@ Prints one JSON line.  `value` is the fwd+bwd time per step (ms/iter) of
 the FP32 form; `render_fps` is the forward-only frame rate with visibility
 recomputed per frame, `render_fps_no_vis` with visibility cached per pose.
 The same figures for the BF16X3 form of the shading contraction (bf16 hi +
-lo operands on MFMA) sit under `bf16x3`, and `image_error_vs_fp64` gives
+lo operands, on MFMA or, as here, on the FP32 kernel) sit under `bf16x3`, and `image_error_vs_fp64` gives
 each form's image PSNR against the FP64 oracle (with the oracle's emulation
 of plain bf16 operands beside it).
 """
@@ -572,13 +572,15 @@ def measure_form(args, s, d, precision: str, capacity=None):
 
     # the roofline entry is the step's longest kernel, the blend adjoint
     # here; beside it the shading kernel of the form (the FP32 adjoint, or
-    # the BF16X3 form's MFMA forward: both forms' adjoints replay the tape),
+    # the BF16X3 form's forward: both forms' adjoints replay the tape),
     # timed on a few eager steps after the timed region (the longer of the
     # two becomes the entry)
     if args.kernel:
         kernels = [args.kernel]
     elif precision == "bf16x3":
-        kernels = ["blend_bwd", "shade_fwd_bf16x3"]
+        K = s["he"] * s["we"]
+        mfma = K > 512 or (K <= 128 and s["n"] >= 32768)
+        kernels = ["blend_bwd", "shade_fwd_bf16x3" if mfma else "shade_fwd"]
     else:
         kernels = ["blend_bwd", "shade_bwd"]
     kernel = kernels[0]

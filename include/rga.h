@@ -42,7 +42,7 @@ extern "C" {
 #define RGA_EUNSUPPORTED (-4)  /* configuration outside the supported range  */
 
 #define RGA_FP32 0             /* shading contraction in FP32 on VALU        */
-#define RGA_BF16X3 1           /* shading contraction on BF16 MFMA, hi+lo split */
+#define RGA_BF16X3 1           /* shading contraction on BF16 MFMA, hi+lo split (or FP32, same factors) */
 
 /* Pinhole camera, world -> camera x_c = R x + t (row-major R), camera frame
  * x right, y down, z forward; pixel (i, j) has its centre at (i+0.5, j+0.5). */
@@ -191,7 +191,10 @@ int mesh_visibility_noalloc(void* stream, int nv, int nf, const float* verts,
  * hv, wv     the view grid (a coarser lat-long grid dividing he x we): texel
  *            (r, c) uses view (r*hv/he)*wv + c*wv/we
  * cam_pos    host float[3], camera centre in world space
- * precision  RGA_FP32 or RGA_BF16X3
+ * precision  RGA_FP32 or RGA_BF16X3 (the contraction's factors are split into
+ *            bf16 hi + lo; it runs on MFMA beyond 512 directions, and for at
+ *            most 128 in one or two texels per view of 32768 Gaussians or more;
+ *            else on the FP32 kernel, the faster one then)
  * color      [3][n] out;  front [n] uint8 out
  * tape       NULL, or tape_bytes >= shade_tape_bytes(n, he, we) of device
  *            memory (16-byte aligned) that receives the live (Gaussian,
@@ -228,8 +231,8 @@ size_t shade_tape_bytes(int n, int he, int we);
  * count, env, cam_pos, the grids): the live pairs are read from it, which
  * gives the same sums with less work.  A tape from other inputs gives wrong
  * gradients (it is not checked).  Given a tape the adjoint is the FP32
- * replay in either form (for RGA_BF16X3 the tape of its MFMA forward); the
- * MFMA adjoint runs for RGA_BF16X3 without one.                             */
+ * replay in either form (for RGA_BF16X3 the tape of its forward); the MFMA
+ * adjoint runs for RGA_BF16X3 without one.                                  */
 size_t shade_gaussians_workspace(int n, int he, int we);
 int shade_gaussians_backward(void* stream, int n, const float* x, const float* nrm,
                              const float* albedo, const float* rough, const float* tint,

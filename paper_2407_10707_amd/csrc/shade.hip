@@ -19,9 +19,9 @@
 // visibility) pairs, in the order and 64-pair groups of its walk; the
 // adjoint of the same inputs then replays them instead of walking every
 // direction again (same pairs, same lanes, same sums), which removes the
-// direction test, the count rows and the ring from the adjoint.  The BF16X3
-// form's MFMA forward writes the same tape (its pairs in step order), and
-// its adjoint given one is this replay.
+// direction test, the count rows and the ring from the adjoint.  The MFMA
+// forward of the BF16X3 form writes the same tape (its pairs in step order),
+// and the adjoint given one is this replay.
 #include <algorithm>
 
 #include "common.h"
@@ -39,7 +39,8 @@ struct ShadeArgs {
   const float *x, *nrm, *albedo, *rough, *tint, *vw, *env;
   const int32_t* vidx;
   const uint8_t* count;
-  int patch;   // table slots in 4 x 8 texel patches (the MFMA kernels), else texel order
+  int patch;   // table slots in 4 x 8 texel patches (the BF16X3 form), else texel order
+  int split;   // factors of the contraction rounded to bf16 hi + lo (BF16X3 on the FP32 kernel)
   // the live-pair tape (NULL: none): per Gaussian its count and its live
   // (direction, visibility) pairs in the order visited, [n][K]
   int32_t* tape_n;
@@ -61,9 +62,15 @@ __device__ inline int slot_k(int s, int we, int patch) {
   return (4 * pr + (q >> 3)) * we + 8 * pc + (q & 7);
 }
 
+// What the MFMA contraction keeps of a factor: its bf16 part and that of the rest.
+__device__ inline float split2(float w) {
+  const float hi = (float)(__bf16)w;
+  return hi + (float)(__bf16)(w - hi);
+}
+
 // Table in LDS, two float4 per slot s (direction k = slot_k(s)): [s] =
 // (direction x, y, z, view index as int bits), [K + s] = (E = radiance x
-// texel solid angle, r, g, b, and the solid angle).  One 16-byte LDS read
+// texel solid angle, r, g, b, and k as int bits).  One 16-byte LDS read
 // fetches either half.
 __device__ inline void build_table(const ShadeArgs& a, float* tab) {
   float4* t4 = reinterpret_cast<float4*>(tab);
@@ -80,8 +87,13 @@ __device__ inline void build_table(const ShadeArgs& a, float* tab) {
     const float area = band * st;
     const int view = ((r * a.hv) / a.he) * a.wv + (c * a.wv) / a.we;
     t4[sl] = make_float4(st * sp, ct, st * cp, __int_as_float(view));
-    t4[K + sl] = make_float4(a.env[3 * k] * area, a.env[3 * k + 1] * area,
-                             a.env[3 * k + 2] * area, area);
+    float e[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      e[i] = a.env[3 * k + i] * area;
+      if (a.split) e[i] = split2(e[i]);
+    }
+    t4[K + sl] = make_float4(e[0], e[1], e[2], __int_as_float(k));
   }
 }
 
@@ -564,9 +576,14 @@ shade_fwd_kernel(ShadeArgs a, int cap, float* __restrict__ color, uint8_t* __res
       const int nlive = live_walk(G, tab, K, V, L.qk, L.qv, lane, lt,
                                   [&](int k, float v, bool on, int base) {
         if (on) {
-          if (trow) trow[base + lane] = make_uint2((uint32_t)k, __float_as_uint(v));
           Pair P;
           pair_eval(G, tab, K, k, v, P);
+          if (trow)
+            trow[base + lane] = make_uint2(__float_as_uint(rad_of(tab, K, k).w), __float_as_uint(v));
+          if (a.split) {
+            P.Wd = split2(P.Wd);
+            P.Ws = split2(P.Ws);
+          }
           sd0 = fmaf(P.Wd, P.E[0], sd0);
           sd1 = fmaf(P.Wd, P.E[1], sd1);
           sd2 = fmaf(P.Wd, P.E[2], sd2);
@@ -1268,6 +1285,34 @@ const void* fp32_kernel_of(bool adjoint, bool taped) {
   return reinterpret_cast<const void*>(shade_fwd_kernel<NQ, WAVES>);
 }
 
+// texels per view along the azimuth that the MFMA kernels read in whole words
+// (1 or 2), 0 for any other view grid
+int view_ratio(int he, int we, int hv, int wv) {
+  return (hv == he && we == wv) ? 1 : ((hv == he && we == 2 * wv && we % 8 == 0) ? 2 : 0);
+}
+
+// 4 x 8 texel patches where they divide the map
+int patches(int he, int we) { return (he % 4 == 0 && we % 8 == 0) ? 1 : 0; }
+
+// Whether the forward of a BF16X3 call runs on MFMA.  Three output channels
+// leave the matrix units idle; what counts is the BRDF weights, which the MFMA
+// kernel evaluates for whole patches of 16 Gaussians x 32 directions and the FP32
+// kernel for the live pairs alone, after a walk and a set-up per Gaussian.  So few
+// directions go to MFMA, in one or two texels per view, if there are Gaussians to
+// fill the chip; 129 to 512, fewer Gaussians and other view grids to the FP32
+// kernel.  MFMA -> FP32: 300k Gaussians 128 directions 56 -> 80 us, 256 102 -> 97;
+// 100k 512 100 -> 57, in other view grids 237 -> 56; 30k 128 14 us both, 500 17 -> 9.
+// The FP32 kernel then walks the same patches, so the tape is the same, and rounds
+// the factors as MFMA takes them (3 us of the 57): a Gaussian's colour does not
+// hang on how many there are.  What is left is the sums' order, 5e-7 of a colour,
+// which dx and dn (sums that cancel) amplify to 4e-4 of their rms at worst; it
+// grows with the terms, to 9e-4 at 2048 directions, so beyond 512 the form keeps
+// to MFMA (828 us against 160 at 100k: RGA_FP32 is the form to ask for there).
+bool forward_on_mfma(const ShadeArgs& a) {
+  if (fp32_lds(a.K, a.V, false, false, 8) + 16 * 64 > kLdsMax - kLdsStatic || a.K > 512) return true;
+  return a.K <= 128 && a.n >= 32768 && view_ratio(a.he, a.we, a.hv, a.wv) > 0;
+}
+
 struct Launch {
   const void* kernel;
   int waves, grid, cap;
@@ -1360,6 +1405,7 @@ ShadeArgs make_args(int n, const float* x, const float* nrm, const float* albedo
   a.vidx = vidx;
   a.count = count;
   a.patch = 0;
+  a.split = 0;
   a.tape_n = nullptr;
   a.tape = nullptr;
   return a;
@@ -1406,8 +1452,15 @@ extern "C" int shade_gaussians(void* stream, int n, const float* x, const float*
   if (precision == RGA_BF16X3) {
     if (a.K % 32 != 0)
       return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians: BF16X3 needs a multiple of 32 directions");
-    const int ratio = (hv == he && we == wv) ? 1 : ((hv == he && we == 2 * wv && we % 8 == 0) ? 2 : 0);
-    a.patch = (he % 4 == 0 && we % 8 == 0) ? 1 : 0;
+    const size_t lds = (size_t)8 * a.K * sizeof(float) + (size_t)6 * a.K * 2 + kMWaves * 512 * 4;
+    if (lds > 150 * 1024) return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians: too many directions");
+  }
+  if (precision == RGA_BF16X3) {
+    a.patch = patches(he, we);
+    a.split = !forward_on_mfma(a);
+  }
+  if (precision == RGA_BF16X3 && !a.split) {
+    const int ratio = view_ratio(he, we, hv, wv);
     const size_t lds = (size_t)8 * a.K * sizeof(float) + (size_t)6 * a.K * 2 + kMWaves * 512 * 4;
     static bool mattr = false;
     if (!mattr) {
@@ -1415,7 +1468,6 @@ extern "C" int shade_gaussians(void* stream, int n, const float* x, const float*
                           hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
       mattr = true;
     }
-    if (lds > 150 * 1024) return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians: too many directions");
     int ncu = 0, dev = 0;
     hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
@@ -1432,7 +1484,7 @@ extern "C" int shade_gaussians(void* stream, int n, const float* x, const float*
     return RGA_OK;
   }
   const size_t need = fp32_need(a.K, a.V, false, false);
-  if (need > 152 * 1024)
+  if (precision == RGA_FP32 && need > 152 * 1024)
     return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians: %d directions and %d views need %zu B of LDS",
                      a.K, a.V, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1480,12 +1532,12 @@ extern "C" int shade_gaussians_backward(void* stream, int n, const float* x, con
   if (precision == RGA_BF16X3 && !a.tape) {
     if (a.K % 32 != 0)
       return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians_backward: BF16X3 needs a multiple of 32 directions");
-    const int ratio = (hv == he && we == wv) ? 1 : ((hv == he && we == 2 * wv && we % 8 == 0) ? 2 : 0);
-    a.patch = (he % 4 == 0 && we % 8 == 0) ? 1 : 0;
     const size_t lds = (size_t)11 * a.K * sizeof(float) + (size_t)6 * a.K * 2 +
                        (size_t)kMWaves * (4096 + 384 + 2048);
     if (lds > 150 * 1024)
       return rga::fail(RGA_EUNSUPPORTED, "shade_gaussians_backward: too many directions");
+    const int ratio = view_ratio(he, we, hv, wv);
+    a.patch = patches(he, we);
     static bool mattr = false;
     if (!mattr) {
       hipFuncSetAttribute(reinterpret_cast<const void*>(shade_bwd_mfma_kernel),
