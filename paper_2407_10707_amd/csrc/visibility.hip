@@ -25,7 +25,9 @@ namespace {
 constexpr int kMaxRes = 128;
 constexpr int kRasterThreads = 1024;
 constexpr int kWideWords = 1 << 18;
-constexpr int kRingFaces = 2;
+constexpr int kRing = 256;               // entries of a raster wave's ring
+constexpr int kGroup = 2;                // steps tested together; 63 + 64 kGroup <= kRing
+constexpr int kRingFaces = 1;
 
 __device__ inline void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -65,9 +67,33 @@ struct Proj {
   float c[3], rho, irho, t[3], b[3], d[3], scale;
 };
 
-__device__ inline void project(const Proj& P, const float* __restrict__ v, int nv, int i,
-                               int32_t& U, int32_t& V, float& z) {
-  const float q0 = v[i] - P.c[0], q1 = v[nv + i] - P.c[1], q2 = v[2 * nv + i] - P.c[2];
+// The vertices: the caller's [3][nv], or the frame kernel's copy of 16 bytes
+// each, which a triangle reads by three loads instead of nine (the addresses of
+// 64 triangles lie in up to 64 lines, one of which the CU's cache serves per
+// cycle).
+struct Verts {
+  const float* v;
+  const float4* v4;
+  int nv;
+};
+
+template <bool V4>
+__device__ inline void vertex(const Verts& m, int i, float (&q)[3]) {
+  if constexpr (V4) {
+    const float4 x = m.v4[i];
+    q[0] = x.x;
+    q[1] = x.y;
+    q[2] = x.z;
+  } else {
+    q[0] = m.v[i];
+    q[1] = m.v[m.nv + i];
+    q[2] = m.v[2 * m.nv + i];
+  }
+}
+
+__device__ inline void project(const Proj& P, const float (&x)[3], int32_t& U, int32_t& V,
+                               float& z) {
+  const float q0 = x[0] - P.c[0], q1 = x[1] - P.c[1], q2 = x[2] - P.c[2];
   const float pu = fmaf(P.t[2], q2, fmaf(P.t[1], q1, P.t[0] * q0));
   const float pv = fmaf(P.b[2], q2, fmaf(P.b[1], q1, P.b[0] * q0));
   const float pd = fmaf(P.d[2], q2, fmaf(P.d[1], q1, P.d[0] * q0));
@@ -77,6 +103,12 @@ __device__ inline void project(const Proj& P, const float* __restrict__ v, int n
   U = (int32_t)rintf(u * 256.f);
   V = (int32_t)rintf(w * 256.f);
   z = P.rho - pd;
+}
+
+// the depth alone
+__device__ inline float depth(const Proj& P, const float (&x)[3]) {
+  const float q0 = x[0] - P.c[0], q1 = x[1] - P.c[1], q2 = x[2] - P.c[2];
+  return P.rho - fmaf(P.d[2], q2, fmaf(P.d[1], q1, P.d[0] * q0));
 }
 
 __device__ inline unsigned long long depth_key(float bz, int f) {
@@ -126,8 +158,9 @@ __device__ void raster_tri_wide(unsigned long long* zb, int res, int f, int64_t 
 // both axes (64 pixels): every coordinate difference inside the box (and
 // one sample step past it) is below 2^14 + 256, so each edge-function
 // product is below 2^29 and the edge functions are exact in 32-bit
-// integers.  They are stepped incrementally
-// along a row (exact integer updates), and the top-left rule becomes a
+// integers (and its factors fit the 24-bit multiplier, which takes a quarter of
+// the 32-bit one's time).  They are stepped incrementally along rows and from
+// row to row (exact integer updates), and the top-left rule becomes a
 // sign test after subtracting 1 from the edges a sample on them does not
 // belong to.  Same integers, same depth arithmetic as the wide form.
 __device__ inline void raster_tri(unsigned long long* zb, int res, int f, int32_t x0, int32_t y0,
@@ -139,7 +172,7 @@ __device__ inline void raster_tri(unsigned long long* zb, int res, int f, int32_
     raster_tri_wide(zb, res, f, x0, y0, z0, x1, y1, z1, x2, y2, z2);
     return;
   }
-  int32_t area = (x1 - x0) * (y2 - y0) - (y1 - y0) * (x2 - x0);
+  int32_t area = __mul24(x1 - x0, y2 - y0) - __mul24(y1 - y0, x2 - x0);
   if (area == 0) return;
   if (area < 0) {
     int32_t tx = x1, ty = y1;
@@ -161,13 +194,13 @@ __device__ inline void raster_tri(unsigned long long* zb, int res, int f, int32_
   const int32_t c1 = (a1 < 0 || (a1 == 0 && b1 < 0)) ? 0 : 1;   // edge v2 -> v0
   const int32_t c2 = (a2 < 0 || (a2 == 0 && b2 < 0)) ? 0 : 1;   // edge v0 -> v1
   const float ia = 1.f / (float)area;   // barycentric weights w_e / area
-  const int32_t sx0 = 256 * i_lo + 128;
+  const int32_t sx = 256 * i_lo + 128, sy = 256 * j_lo + 128;
+  int32_t r0 = __mul24(a0, sx - x1) + __mul24(b0, sy - y1) - c0;
+  int32_t r1 = __mul24(a1, sx - x2) + __mul24(b1, sy - y2) - c1;
+  int32_t r2 = __mul24(a2, sx - x0) + __mul24(b2, sy - y0) - c2;
+  unsigned long long* row = zb + __mul24(j_lo, res);
   for (int j = j_lo; j <= j_hi; ++j) {
-    const int32_t sy = 256 * j + 128;
-    int32_t w0 = a0 * (sx0 - x1) + b0 * (sy - y1) - c0;
-    int32_t w1 = a1 * (sx0 - x2) + b1 * (sy - y2) - c1;
-    int32_t w2 = a2 * (sx0 - x0) + b2 * (sy - y0) - c2;
-    unsigned long long* row = zb + j * res;
+    int32_t w0 = r0, w1 = r1, w2 = r2;
     for (int i = i_lo; i <= i_hi; ++i) {
       if ((w0 | w1 | w2) >= 0) {
         const float bz = fmaf((float)(w2 + c2), z2, fmaf((float)(w1 + c1), z1,
@@ -178,6 +211,10 @@ __device__ inline void raster_tri(unsigned long long* zb, int res, int f, int32_
       w1 += 256 * a1;
       w2 += 256 * a2;
     }
+    r0 += 256 * b0;
+    r1 += 256 * b1;
+    r2 += 256 * b2;
+    row += res;
   }
 }
 
@@ -202,27 +239,51 @@ __device__ inline float wave_extreme(float v) {
 }
 
 // Workgroups [0, kBoxes): partial bounding boxes of the vertices (lo, hi per
-// axis, six floats each); workgroup kBoxes + b: the lowest and highest vertex
-// of the triangles of batch b.  (min and max are exact and independent of the
-// reduction order.)  One workgroup over 39,780 vertices took 16 us.
+// axis, six floats each) and, for the raster, a copy of 16 bytes per vertex
+// (v4, if there is room).  The other workgroups write the triangles as the byte
+// offsets of three entries of the raster's table: where that holds all vertices
+// (nv <= cap) workgroup kBoxes + i 1024 of them, else workgroup kBoxes + b those
+// of batch b, counted from the batch's lowest vertex, if its range of vertices
+// fits.  (min and max are exact and independent of the reduction order.)  One
+// workgroup over 39,780 vertices took 16 us.
 constexpr int kBoxes = 16;
-constexpr int kBatch = 8192;             // triangles per batch, a multiple of the raster's threads
+constexpr int kBatch = 16384;            // triangles per batch, a multiple of the raster's threads
 
 __global__ void __launch_bounds__(1024)
 frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restrict__ faces,
-             float* __restrict__ boxes, int2* __restrict__ ranges) {
+             int cap, float* __restrict__ boxes, int2* __restrict__ ranges,
+             uint2* __restrict__ packed, float4* __restrict__ v4) {
   __shared__ float ext[6][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (blockIdx.x >= kBoxes) {
+  const int b = (int)blockIdx.x - kBoxes;
+  auto pack = [&](int f, int i0, int i1, int i2) {
+    packed[f] = make_uint2((uint32_t)(2 * i0) | ((uint32_t)(2 * i1) << 16), (uint32_t)(2 * i2));
+  };
+  if (b >= 0 && nv <= cap) {
+    const int f = b * 1024 + (int)threadIdx.x;
+    if (f < nf)
+      pack(f, rga::clampi(faces[3 * f], 0, nv - 1), rga::clampi(faces[3 * f + 1], 0, nv - 1),
+           rga::clampi(faces[3 * f + 2], 0, nv - 1));
+    return;
+  }
+  if (b >= 0) {
     __shared__ int lo16[16], hi16[16];
-    const int b = blockIdx.x - kBoxes;
-    const int e1 = 3 * min(kBatch, nf - b * kBatch);
-    const int32_t* f = faces + (size_t)3 * kBatch * b;
+    int t[kBatch / 1024][3];
     int lo = nv - 1, hi = 0;
-    for (int i = threadIdx.x; i < e1; i += 1024) {
-      const int x = rga::clampi(f[i], 0, nv - 1);
-      lo = min(lo, x);
-      hi = max(hi, x);
+#pragma unroll
+    for (int q = 0; q < kBatch / 1024; ++q) {
+      const int f = min(b * kBatch + q * 1024 + (int)threadIdx.x, nf - 1);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) t[q][c] = faces[3 * f + c];
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch / 1024; ++q) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        t[q][c] = rga::clampi(t[q][c], 0, nv - 1);
+        lo = min(lo, t[q][c]);
+        hi = max(hi, t[q][c]);
+      }
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -234,12 +295,16 @@ frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restr
       hi16[wave] = hi;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int w = 1; w < 16; ++w) {
-        lo = min(lo, lo16[w]);
-        hi = max(hi, hi16[w]);
-      }
-      ranges[b] = make_int2(lo, hi);
+    for (int w = 0; w < 16; ++w) {
+      lo = min(lo, lo16[w]);
+      hi = max(hi, hi16[w]);
+    }
+    if (threadIdx.x == 0) ranges[b] = make_int2(lo, hi);
+    if (hi - lo >= cap) return;
+#pragma unroll
+    for (int q = 0; q < kBatch / 1024; ++q) {
+      const int f = b * kBatch + q * 1024 + (int)threadIdx.x;
+      if (f < nf) pack(f, t[q][0] - lo, t[q][1] - lo, t[q][2] - lo);
     }
     return;
   }
@@ -247,12 +312,14 @@ frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restr
 #pragma unroll
   for (int a = 0; a < 3; ++a) lo3[a] = hi3[a] = v[a * nv];
   for (int i = blockIdx.x * 1024 + threadIdx.x; i < nv; i += kBoxes * 1024) {
+    float c[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const float c = v[a * nv + i];
-      lo3[a] = fminf(lo3[a], c);
-      hi3[a] = fmaxf(hi3[a], c);
+      c[a] = v[a * nv + i];
+      lo3[a] = fminf(lo3[a], c[a]);
+      hi3[a] = fmaxf(hi3[a], c[a]);
     }
+    if (v4) v4[i] = make_float4(c[0], c[1], c[2], 0.f);
   }
   float r[6];
 #pragma unroll
@@ -300,165 +367,209 @@ __device__ inline void frame_of(const float* __restrict__ boxes, Proj& P) {
   P.rho = rr;
 }
 
-// One workgroup per view; bound by vector issue (90 % of the issue slots at
-// 12,960 triangles and 1024 views: 119 us).
-//
-// RING: most triangles of a mesh finer than the raster cover no sample (94 %
-// at 79k triangles and 128^2).  A triangle is first tested by the samples of
-// its bounding box alone, which needs the fixed-point coordinates of its
-// vertices; those that pass are gathered in an LDS ring per wave and
-// rasterized by whole waves.  The vertices of a batch of triangles, where
-// their range fits the LDS left beside the z-buffer (`cap`), are projected
-// once into a table of 16-bit pairs there (a mesh's triangles and vertices
-// are numbered alike, so a batch uses a short range; each vertex is used by
-// six triangles), else each triangle projects its own.  (A finite vertex lies
-// inside the frame's sphere of 1 / 1.01 of rho, so its coordinates lie in
-// 0 .. 256 res <= 32768; a NaN projects to 0.)  79k triangles, 1024 views:
-// 474 -> 365 us, 512 views 250 -> 194 us.
-constexpr int kRing = 128;
+// A vertex's place between the sample centres 256 i + 128, for one axis: how many
+// are below it and, in bit 7, whether it lies on one (for x in 0 .. 32640).
+__device__ inline uint32_t place(int32_t x) {
+  return (uint32_t)(x + 127) >> 8 | ((x & 255) == 128 ? 0x80u : 0u);
+}
 
-template <bool RING>
+// A workgroup rasterizes views blockIdx.x, + gridDim.x, ...: one fits a CU (its
+// z-buffer takes 128 KB of the 160 at 128^2), and a new one for every view cost
+// 6 of 116 us at four views each.  Bound by vector issue, of which the rasterizer
+// takes some 240 instructions per wave of triangles, and by its addresses.
+//
+// RING: many triangles of a mesh cover no sample (41 % at 13k triangles and
+// 128^2, 96 % at 79k).  Each is tested first, by its bounding box alone: that
+// holds a sample centre on an axis unless the places of the three vertices are
+// equal there and on no centre.  Those that pass are gathered in an LDS ring per
+// wave and rasterized by whole waves.  Where the range of a batch's vertices fits
+// the LDS left beside the z-buffer (`cap`), their places, a byte per axis, are
+// computed once into a table there (a mesh's triangles and vertices are numbered
+// alike, so a batch uses a short range; each vertex is used by six triangles),
+// else by each triangle.  A finite vertex lies inside the frame's sphere of
+// 1 / 1.01 of rho, so its coordinates lie in 0 .. 255 res, and a NaN projects to
+// 0; where that does not hold (rho from squares below the normal floats, view
+// directions that are not unit vectors) there is no table.  1024 views at 128^2,
+// in place -> 4-byte coordinates in the table, tested axis by axis -> this: 79k
+// triangles 474 -> 365 -> 260 us; 512 views 241 -> 194 -> 139 us.
+__host__ __device__ inline int ring_bytes() {
+  return (int)sizeof(uint16_t) * kRing * (kRasterThreads / 64);
+}
+__host__ __device__ inline int table_bytes(int cap) { return (2 * cap + 15) / 16 * 16; }
+
+template <bool RING, bool V4>
 __global__ void __launch_bounds__(kRasterThreads)
-raster_kernel(int nv, int nf, const float* __restrict__ verts, const int32_t* __restrict__ faces,
-              const float* __restrict__ dirs, int res, const float* __restrict__ boxes,
-              const int2* __restrict__ ranges, int cap, uint32_t* __restrict__ bits_vm /*[V][nwv]*/,
-              int nwv, int shadow, float bias_px) {
+raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
+              int views, const float* __restrict__ dirs, int res, const float* __restrict__ boxes,
+              const int2* __restrict__ ranges, const uint2* __restrict__ packed, int cap,
+              uint32_t* __restrict__ bits_vm /*[V][nwv]*/, int nwv, int shadow, float bias_px) {
+  // the table first: its byte offsets are LDS addresses
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned long long* zb = reinterpret_cast<unsigned long long*>(smem);
-  uint32_t* mark = reinterpret_cast<uint32_t*>(smem + sizeof(unsigned long long) * res * res);
-  uint16_t* rings = reinterpret_cast<uint16_t*>(mark + nwv);
-  uint32_t* tab = mark + nwv + kRing / 2 * (kRasterThreads / 64);
-  const int view = blockIdx.x;
+  unsigned long long* zb =
+      reinterpret_cast<unsigned long long*>(smem + (RING ? table_bytes(cap) + ring_bytes() : 0));
+  const int nv = verts.nv, pixels = res * res;
+  uint32_t* mark = reinterpret_cast<uint32_t*>(zb + pixels);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Proj P;
   frame_of(boxes, P);
   P.irho = 1.f / P.rho;
-  P.d[0] = dirs[3 * view];
-  P.d[1] = dirs[3 * view + 1];
-  P.d[2] = dirs[3 * view + 2];
-  basis(P.d, P.t, P.b);
   P.scale = 0.5f * (float)res;
-  for (int p = threadIdx.x; p < res * res; p += blockDim.x) zb[p] = ~0ull;
-  for (int w = threadIdx.x; w < nwv; w += blockDim.x) mark[w] = 0u;
-  __syncthreads();
-  uint16_t* ring = rings + kRing * wave;
-  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  int head = 0, tail = 0;
-  int base = 0;                           // first triangle the ring's entries count from
-  auto raster = [&](int f) {
-    const int i0 = rga::clampi(faces[3 * f], 0, nv - 1);
-    const int i1 = rga::clampi(faces[3 * f + 1], 0, nv - 1);
-    const int i2 = rga::clampi(faces[3 * f + 2], 0, nv - 1);
-    int32_t x0, y0, x1, y1, x2, y2;
-    float z0, z1, z2;
-    project(P, verts, nv, i0, x0, y0, z0);
-    project(P, verts, nv, i1, x1, y1, z1);
-    project(P, verts, nv, i2, x2, y2, z2);
-    raster_tri(zb, res, f, x0, y0, z0, x1, y1, z1, x2, y2, z2);
+  auto corner = [&](int i, int32_t& U, int32_t& V, float& z) {
+    float q[3];
+    vertex<V4>(verts, i, q);
+    project(P, q, U, V, z);
   };
-  // the ring's next 64 entries (those that exist); entry = 64 x the step of
-  // the wave's walk + its lane there
-  auto flush = [&]() {
-    wave_fence();
-    if (head + lane < tail) {
-      const int en = ring[(head + lane) & (kRing - 1)];
-      raster(base + (en >> 6) * kRasterThreads + 64 * wave + (en & 63));
-    }
-    head = min(head + 64, tail);
-    wave_fence();
-  };
-  if constexpr (!RING) {
-    for (int f = threadIdx.x; f < nf; f += kRasterThreads) raster(f);
-  }
-  for (int f0 = 0, b = 0; RING && f0 < nf; f0 += kBatch, ++b) {
-    const int f1 = min(nf, f0 + kBatch);
-    int lo = 0;
-    bool table = false;
-    if (cap > 0) {
-      const int2 r = ranges[b];
-      lo = r.x;
-      table = r.y - r.x < cap;
-      if (table) {
-        if (b > 0) __syncthreads();       // the last batch's table is done with
-        for (int i = lo + threadIdx.x; i <= r.y; i += blockDim.x) {
-          int32_t U, V;
-          float z;
-          project(P, verts, nv, i, U, V, z);
-          tab[i - lo] = ((uint32_t)U & 0xFFFFu) | ((uint32_t)V << 16);
-        }
-        __syncthreads();
-      }
-    }
-    if (f0 - base >= 1024 * kRasterThreads) {   // the ring's 16-bit entries start over
-      while (head < tail) flush();
-      base = f0;
-    }
-    for (int f = f0 + threadIdx.x; f - lane < f1; f += kRasterThreads) {
-      bool keep = false;
-      int i0 = 0, i1 = 0, i2 = 0;
-      int32_t x0, y0, x1, y1, x2, y2;
-      if (f < f1) {
-        i0 = rga::clampi(faces[3 * f], 0, nv - 1);
-        i1 = rga::clampi(faces[3 * f + 1], 0, nv - 1);
-        i2 = rga::clampi(faces[3 * f + 2], 0, nv - 1);
-        if (table) {
-          const uint32_t a = tab[i0 - lo], c = tab[i1 - lo], d = tab[i2 - lo];
-          x0 = (int32_t)(a & 0xFFFFu);
-          x1 = (int32_t)(c & 0xFFFFu);
-          x2 = (int32_t)(d & 0xFFFFu);
-          y0 = (int32_t)(a >> 16);
-          y1 = (int32_t)(c >> 16);
-          y2 = (int32_t)(d >> 16);
-        } else {
-          float z;
-          project(P, verts, nv, i0, x0, y0, z);
-          project(P, verts, nv, i1, x1, y1, z);
-          project(P, verts, nv, i2, x2, y2, z);
-        }
-        const int32_t mnx = min(x0, min(x1, x2)), mxx = max(x0, max(x1, x2));
-        const int32_t mny = min(y0, min(y1, y2)), mxy = max(y0, max(y1, y2));
-        // some sample centre 256 i + 128 in both extents (as raster_tri)
-        keep = max(0, -((128 - mnx) >> 8)) <= min(res - 1, (mxx - 128) >> 8) &&
-               max(0, -((128 - mny) >> 8)) <= min(res - 1, (mxy - 128) >> 8);
-      }
-      const uint64_t m = __ballot(keep);
-      if (keep)
-        ring[(tail + __popcll(m & below)) & (kRing - 1)] =
-            (uint16_t)(((f - base) / kRasterThreads) << 6 | lane);
-      tail += __popcll(m);
-      if (tail - head >= 64) flush();
-    }
-  }
-  while (head < tail) flush();
-  __syncthreads();
-  if (shadow) {
-    // shadow-mapping test: the vertex's depth against the depth map's
-    // sample in the pixel it projects into, plus bias_px pixel widths; an
-    // empty sample occludes nothing
-    const float bias = bias_px * (2.f * P.rho) / (float)res;
-    for (int i = threadIdx.x; i < nv; i += blockDim.x) {
+  auto fill = [&](int lo, int hi) {
+    for (int i = lo + threadIdx.x; i <= hi; i += kRasterThreads) {
       int32_t U, V;
       float z;
-      project(P, verts, nv, i, U, V, z);
-      const int px = rga::clampi(U >> 8, 0, res - 1), py = rga::clampi(V >> 8, 0, res - 1);
-      const unsigned long long k = zb[py * res + px];
-      if (k == ~0ull || z <= __uint_as_float((uint32_t)(k >> 32)) + bias)
-        atomicOr(&mark[i >> 5], 1u << (i & 31));
+      corner(i, U, V, z);
+      reinterpret_cast<uint16_t*>(smem)[i - lo] = (uint16_t)(place(U) | place(V) << 8);
     }
-  } else {
-    for (int p = threadIdx.x; p < res * res; p += blockDim.x) {
-      const unsigned long long k = zb[p];
-      if (k == ~0ull) continue;
-      const int f = (int)(uint32_t)(k & 0xffffffffull);
-      for (int c = 0; c < 3; ++c) {
-        const int vi = rga::clampi(faces[3 * f + c], 0, nv - 1);
-        atomicOr(&mark[vi >> 5], 1u << (vi & 31));
+  };
+  for (int w = threadIdx.x; w < nwv; w += kRasterThreads) mark[w] = 0u;
+  for (int view = blockIdx.x; view < views; view += gridDim.x) {
+    P.d[0] = dirs[3 * view];
+    P.d[1] = dirs[3 * view + 1];
+    P.d[2] = dirs[3 * view + 2];
+    basis(P.d, P.t, P.b);
+    // (see above; a table's entries hold what the frame keeps its vertices to)
+    const bool tables = RING && cap > 0 && P.irho < 1e17f &&
+                        P.t[0] * P.t[0] + P.t[1] * P.t[1] + P.t[2] * P.t[2] < 1.001f &&
+                        P.b[0] * P.b[0] + P.b[1] * P.b[1] + P.b[2] * P.b[2] < 1.001f;
+    const bool whole = tables && nv <= cap;
+    // (the next view's z-buffer is cleared as the marks are taken)
+    if (view == (int)blockIdx.x || shadow)
+      for (int p = threadIdx.x; p < pixels; p += kRasterThreads) zb[p] = ~0ull;
+    if (whole) fill(0, nv - 1);
+    __syncthreads();
+    auto raster = [&](int f) {
+      const int i0 = rga::clampi(faces[3 * f], 0, nv - 1);
+      const int i1 = rga::clampi(faces[3 * f + 1], 0, nv - 1);
+      const int i2 = rga::clampi(faces[3 * f + 2], 0, nv - 1);
+      int32_t x0, y0, x1, y1, x2, y2;
+      float z0, z1, z2;
+      corner(i0, x0, y0, z0);
+      corner(i1, x1, y1, z1);
+      corner(i2, x2, y2, z2);
+      raster_tri(zb, res, f, x0, y0, z0, x1, y1, z1, x2, y2, z2);
+    };
+    if constexpr (!RING) {
+      for (int f = threadIdx.x; f < nf; f += kRasterThreads) raster(f);
+    }
+    uint16_t* ring = reinterpret_cast<uint16_t*>(smem + table_bytes(cap)) + kRing * wave;
+    int head = 0, tail = 0;
+    int base = 0;                           // first triangle the ring's entries count from
+    for (int f0 = 0, b = 0; RING && f0 < nf; f0 += kBatch, ++b) {
+      const int f1 = min(nf, f0 + kBatch);
+      bool table = whole;
+      if (tables && !whole) {
+        const int2 r = ranges[b];
+        table = r.y - r.x < cap;
+        if (table) {
+          if (b > 0) __syncthreads();       // the last batch's table is done with
+          fill(r.x, r.y);
+          __syncthreads();
+        }
+      }
+      // the wave's triangles: lane's of fw, fw + kRasterThreads, ... below f1 (counts
+      // are the same in all lanes: the ring's ends stay in scalar registers)
+      const int fw = f0 + 64 * wave;
+      constexpr int per = kGroup * kRasterThreads;
+      const int groups = max(1, (f1 - fw + per - 1) / per);
+      // the ring is emptied after the last batch and where its 16-bit entries end
+      const bool drain = f1 == nf || f0 + kBatch - base >= 1024 * kRasterThreads;
+      for (int g = 0; g < groups; ++g) {
+        const int fg = fw + per * g;
+        bool keep[kGroup];
+        if (table) {
+          uint2 t[kGroup];
+  #pragma unroll
+          for (int q = 0; q < kGroup; ++q)
+            t[q] = *reinterpret_cast<const uint2*>(
+                reinterpret_cast<const char*>(packed) +
+                8u * (uint32_t)min(fg + lane + kRasterThreads * q, f1 - 1));
+  #pragma unroll
+          for (int q = 0; q < kGroup; ++q) {
+            const uint32_t a = *reinterpret_cast<const uint16_t*>(smem + (t[q].x & 0xFFFFu));
+            const uint32_t c = *reinterpret_cast<const uint16_t*>(smem + (t[q].x >> 16));
+            const uint32_t d = *reinterpret_cast<const uint16_t*>(smem + t[q].y);
+            const uint32_t w = (a ^ c) | (a ^ d) | (a & 0x8080u);
+            keep[q] = (w & 0xFFu) != 0u && w > 0xFFu;
+          }
+        } else {
+  #pragma unroll
+          for (int q = 0; q < kGroup; ++q) {
+            const int f = min(fg + lane + kRasterThreads * q, f1 - 1);
+            int32_t x0, y0, x1, y1, x2, y2;
+            float z;
+            corner(rga::clampi(faces[3 * f], 0, nv - 1), x0, y0, z);
+            corner(rga::clampi(faces[3 * f + 1], 0, nv - 1), x1, y1, z);
+            corner(rga::clampi(faces[3 * f + 2], 0, nv - 1), x2, y2, z);
+            const int32_t mnx = min(x0, min(x1, x2)), mxx = max(x0, max(x1, x2));
+            const int32_t mny = min(y0, min(y1, y2)), mxy = max(y0, max(y1, y2));
+            keep[q] = max(0, -((128 - mnx) >> 8)) <= min(res - 1, (mxx - 128) >> 8) &&
+                      max(0, -((128 - mny) >> 8)) <= min(res - 1, (mxy - 128) >> 8);
+          }
+        }
+  #pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+          const bool k = keep[q] && fg + lane + kRasterThreads * q < f1;
+          const uint64_t m = __ballot(k);
+          // entry = 64 x the wave's step + its lane there
+          const int step = (fg - 64 * wave - base) / kRasterThreads + q;
+          const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, tail));
+          if (k) ring[at & (kRing - 1)] = (uint16_t)(step << 6 | lane);
+          tail += __popcll(m);
+        }
+        const int need = drain && g == groups - 1 ? 1 : 64;
+        while (tail - head >= need) {
+          wave_fence();
+          if (head + lane < tail) {
+            const int en = ring[(head + lane) & (kRing - 1)];
+            raster(base + 64 * wave + (en >> 6) * kRasterThreads + (en & 63));
+          }
+          head = min(head + 64, tail);
+          wave_fence();
+        }
+      }
+      if (drain) base = f0 + kBatch;
+    }
+    __syncthreads();
+    if (shadow) {
+      // shadow-mapping test: the vertex's depth against the depth map's
+      // sample in the pixel it projects into, plus bias_px pixel widths; an
+      // empty sample occludes nothing
+      const float bias = bias_px * (2.f * P.rho) / (float)res;
+      for (int i = threadIdx.x; i < nv; i += blockDim.x) {
+        int32_t U, V;
+        float z;
+        corner(i, U, V, z);
+        const int px = rga::clampi(U >> 8, 0, res - 1), py = rga::clampi(V >> 8, 0, res - 1);
+        const unsigned long long k = zb[py * res + px];
+        if (k == ~0ull || z <= __uint_as_float((uint32_t)(k >> 32)) + bias)
+          atomicOr(&mark[i >> 5], 1u << (i & 31));
+      }
+    } else {
+      for (int p = threadIdx.x; p < pixels; p += kRasterThreads) {
+        const unsigned long long k = zb[p];
+        if (k == ~0ull) continue;
+        zb[p] = ~0ull;
+        const int f = (int)(uint32_t)(k & 0xffffffffull);
+        for (int c = 0; c < 3; ++c) {
+          const int vi = rga::clampi(faces[3 * f + c], 0, nv - 1);
+          atomicOr(&mark[vi >> 5], 1u << (vi & 31));
+        }
       }
     }
+    __syncthreads();
+    for (int w = threadIdx.x; w < nwv; w += kRasterThreads) {
+      bits_vm[(size_t)view * nwv + w] = mark[w];
+      mark[w] = 0u;
+    }
   }
-  __syncthreads();
-  for (int w = threadIdx.x; w < nwv; w += blockDim.x) bits_vm[(size_t)view * nwv + w] = mark[w];
 }
 
 // view-major [V][nwv] (bit i&31 of word i>>5 = vertex i) -> vertex-major
@@ -638,12 +749,24 @@ VisLayout vis_layout(int nv, int V) {
 
 }  // namespace
 
+// (beyond the layout: room for the raster's copy of the vertices and for twice
+// as many packed triangles, which it does without in a smaller workspace)
 extern "C" size_t mesh_visibility_workspace(int nv, int V) {
   if (nv < 1 || V < 1) return 0;
-  return vis_layout(nv, V).total;
+  const VisLayout L = vis_layout(nv, V);
+  return std::max(L.total, L.raw + 1024 + (size_t)33 * nv);
 }
 
 namespace {
+
+// compute units of the current device (256 if it does not say)
+int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+    n = 256;
+  return n;
+}
 
 int visibility_impl(void* stream, int nv, int nf, const float* verts, const int32_t* faces, int V,
                     const float* view_dirs, int res, const int32_t* knn, int kv,
@@ -672,34 +795,47 @@ int visibility_impl(void* stream, int nv, int nf, const float* verts, const int3
   const size_t zm = sizeof(unsigned long long) * (size_t)res * res + 4 * (size_t)L.nwv;
   if (zm > 160 * 1024)
     return rga::fail(RGA_EUNSUPPORTED, "mesh_visibility: %d vertices need too much LDS", nv);
-  // Where most triangles cover no sample they go through the rings, if the LDS
-  // has room for them (1024 views at 128^2, in place -> rings: 79k triangles
-  // 474 -> 365 us, 27k 194 -> 200 us, 13k 119 -> 139 us).
-  const size_t rings = sizeof(uint16_t) * kRing * (kRasterThreads / 64);
+  // From one triangle per sample on they go through the rings, if the LDS has
+  // room for them (in place -> rings: 1024 views at 128^2, 27k triangles 182 ->
+  // 151 us, 13k 110 us either way; 64 views at 64^2, 13k 24 -> 21 us, 952 11 ->
+  // 12 us, and the frame kernel 1 us more).
+  const size_t rings = ring_bytes();
   const bool ring = nf > kRingFaces * res * res && zm + rings <= 160 * 1024;
+  // the partial boxes, the vertices' copy, the batches' ranges and the packed
+  // triangles live in the filters' buffers, which are written after the raster
+  // only; without room for them, or with a table too small to be of use, every
+  // triangle projects its own.  (In place the copy pays from more than one view
+  // per CU on: 13k triangles, 1024 views 114 -> 110 us; 5k, 64 views 31.5 -> 32 us
+  // with the frame kernel.)
+  char* const end = w + ws_bytes;
+  float* boxes = reinterpret_cast<float*>(w + L.raw);
+  float4* v4 = reinterpret_cast<float4*>(boxes + 8 * kBoxes);
+  const int batches = (int)rga::ceil_div(nf, kBatch);
+  int2* ranges = reinterpret_cast<int2*>(v4 + nv);
+  uint2* packed = reinterpret_cast<uint2*>(ranges + batches);
+  int64_t cap = ring ? std::min<int64_t>((160 * 1024 - (int64_t)(zm + rings)) / 16 * 8, nv) : 0;
+  if (cap < 1024 && cap < nv) cap = 0;
+  cap = std::min<int64_t>(cap, 32768);
+  if (nf >= 1 << 28 || reinterpret_cast<char*>(packed + nf) > end) cap = 0;
+  if (reinterpret_cast<char*>(v4 + nv) > end || !(ring || V > 256)) v4 = nullptr;
+  const int packers = cap == 0 ? 0 : (int)(nv <= cap ? rga::ceil_div(nf, 1024) : batches);
+  const size_t lds = zm + (ring ? rings + table_bytes((int)cap) : 0);
+  auto raster = ring ? (v4 ? raster_kernel<true, true> : raster_kernel<true, false>)
+                     : (v4 ? raster_kernel<false, true> : raster_kernel<false, false>);
   static bool attr_set = false;
   if (!attr_set) {
-    for (const void* k : {reinterpret_cast<const void*>(raster_kernel<true>),
-                          reinterpret_cast<const void*>(raster_kernel<false>)})
-      hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    for (auto k : {raster_kernel<true, true>, raster_kernel<true, false>,
+                   raster_kernel<false, true>, raster_kernel<false, false>})
+      hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
-  // the partial boxes and the batches' ranges live in the filters' buffers,
-  // which are written after the raster only; without room for the ranges, or
-  // with a table too small to be of use, every triangle projects its own
-  float* boxes = reinterpret_cast<float*>(m1);
-  int2* ranges = reinterpret_cast<int2*>(boxes + 6 * kBoxes);
-  const int batches = (int)rga::ceil_div(nf, kBatch);
-  const size_t room = L.total - L.m1 - 6 * kBoxes * sizeof(float);
-  int64_t cap = ring ? std::min<int64_t>((160 * 1024 - (int64_t)(zm + rings)) / 4, nv) : 0;
-  if (cap < 1024 && cap < nv) cap = 0;
-  if (batches * sizeof(int2) > room) cap = 0;
-  const size_t lds = zm + (ring ? rings : 0) + 4 * (size_t)cap;
-  RGA_LAUNCH("vis_frame", frame_kernel, dim3(kBoxes + (cap > 0 ? batches : 0)), dim3(1024), 0, s, nv,
-             nf, verts, faces, boxes, ranges);
-  auto raster = ring ? raster_kernel<true> : raster_kernel<false>;
-  RGA_LAUNCH("vis_raster", raster, dim3(V), dim3(kRasterThreads), lds, s, nv, nf, verts,
-             faces, view_dirs, res, boxes, ranges, (int)cap, vm, L.nwv, shadow, bias_px);
+  RGA_LAUNCH("vis_frame", frame_kernel, dim3(kBoxes + packers), dim3(1024), 0, s, nv,
+             nf, verts, faces, (int)cap, boxes, ranges, packed, v4);
+  const Verts mesh = {verts, v4, nv};
+  const int grid = std::min(V, compute_units());
+  RGA_LAUNCH("vis_raster", raster, dim3(grid), dim3(kRasterThreads), lds, s, mesh, nf, faces,
+             V, view_dirs, res, boxes, ranges, packed, (int)cap, vm, L.nwv, shadow, bias_px);
   const int64_t tw = (int64_t)L.nwv * L.nwV;
   RGA_LAUNCH("vis_transpose", transpose_kernel, dim3(rga::ceil_div(tw * 32, 256)), dim3(256), 0, s, nv,
              V, L.nwv, L.nwV, vm, raw);
