@@ -204,17 +204,6 @@ __device__ inline void gauss_setup(const ShadeArgs& a, const Attr& A, const uint
   }
 }
 
-// Live-direction test for direction k; returns the visibility (0 if dead).
-__device__ inline float live_vis(const GaussCtx& G, const float* tab, int K, int V, int k) {
-  const float4 dv = dir_of(tab, k);
-  const float ci = fmaf(G.nn[2], dv.z, fmaf(G.nn[1], dv.y, G.nn[0] * dv.x));
-  if (!(ci > 0.f)) return 0.f;
-  const int view = __float_as_int(dv.w);
-  const float c0 = (float)G.rows[view], c1 = (float)G.rows[V + view],
-              c2 = (float)G.rows[2 * V + view];
-  return fmaf(G.u2, c2, fmaf(G.u1, c1, G.u0 * c0));
-}
-
 struct Pair {
   float d[3], E[3], ci, ok, hh, nht, s2, den, invh, nh, oh, e2, F, hd, D, G1i, deni, ideni, W0F, W0, Ws,
       Wd;
@@ -457,20 +446,23 @@ __device__ inline void attr_read(float v, Attr& A) {
 // the live ones (n.w_k > 0 and visibility > 0) appended with their
 // visibility to the wave's ring; flush(k, v, on, base) on every whole wave
 // of ring entries as it fills and on the remainder (base = the number of
-// live pairs flushed before).  Returns the number of live pairs.
+// live pairs flushed before).  Returns the number of live pairs.  Two waves of
+// directions are looked up together: each lookup is two dependent LDS reads, for
+// whose latency four waves per SIMD are too few (200k Gaussians, 2048 directions
+// 312 -> 271 us, one at a time without the branches 301, four 267 but 63 us
+// against 60 at 128 directions).
 template <class Flush>
 __device__ inline int live_walk(const GaussCtx& G, const float* tab, int K, int V, int* qk,
-                                float* qv, int lane, uint64_t lt, Flush&& flush) {
+                                float* qv, int lane, Flush&& flush) {
   int head = 0, tail = 0;
-  for (int k0 = 0; k0 < K; k0 += 64) {
-    const int k = k0 + lane;
-    const float v = k < K ? live_vis(G, tab, K, V, k) : 0.f;
+  auto append = [&](int k, float v) {
     const bool live = v > 0.f;
     const uint64_t m = __ballot(live);
+    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, tail));
     if (live) {
-      const int slot = (tail + __popcll(m & lt)) & (kRing - 1);
-      qk[slot] = k;
-      qv[slot] = v;
+      qk[at & (kRing - 1)] = k;
+      qv[at & (kRing - 1)] = v;
     }
     tail += __popcll(m);
     if (tail - head >= 64) {
@@ -480,6 +472,27 @@ __device__ inline int live_walk(const GaussCtx& G, const float* tab, int K, int 
       head += 64;
       wave_fence();
     }
+  };
+  for (int k0 = 0; k0 < K; k0 += 128) {
+    float ci[2], v[2] = {0.f, 0.f};
+    int view[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = k0 + 64 * h + lane;
+      const float4 dv = dir_of(tab, min(k, K - 1));
+      ci[h] = fmaf(G.nn[2], dv.z, fmaf(G.nn[1], dv.y, G.nn[0] * dv.x));
+      if (k >= K) ci[h] = 0.f;
+      view[h] = __float_as_int(dv.w);
+    }
+    if (__ballot(ci[0] > 0.f || ci[1] > 0.f) == 0ull) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float c0 = (float)G.rows[view[h]], c1 = (float)G.rows[V + view[h]],
+                  c2 = (float)G.rows[2 * V + view[h]];
+      v[h] = ci[h] > 0.f ? fmaf(G.u2, c2, fmaf(G.u1, c1, G.u0 * c0)) : 0.f;
+    }
+    append(k0 + lane, v[0]);
+    append(k0 + 64 + lane, v[1]);
   }
   if (tail > head) {
     wave_fence();
@@ -573,7 +586,7 @@ shade_fwd_kernel(ShadeArgs a, int cap, float* __restrict__ color, uint8_t* __res
       float sd0 = 0.f, sd1 = 0.f, sd2 = 0.f, ss0 = 0.f, ss1 = 0.f, ss2 = 0.f;
       // this Gaussian's row of the tape (a wave-uniform address)
       uint2* const trow = a.tape ? a.tape + (size_t)uni(g) * K : nullptr;
-      const int nlive = live_walk(G, tab, K, V, L.qk, L.qv, lane, lt,
+      const int nlive = live_walk(G, tab, K, V, L.qk, L.qv, lane,
                                   [&](int k, float v, bool on, int base) {
         if (on) {
           Pair P;
@@ -1165,7 +1178,7 @@ shade_bwd_kernel(ShadeArgs a, int cap, const float* __restrict__ color,
           w = wn2;
         }
       } else {
-        live_walk(G, tab, K, V, L.qk, L.qv, lane, lt, [&](int k, float v, bool on, int) {
+        live_walk(G, tab, K, V, L.qk, L.qv, lane, [&](int k, float v, bool on, int) {
           if (on) pair_bwd(G, tab, denv_lds, K, k, v, qd, dLo, tint, aop, acc);
         });
       }
@@ -1307,7 +1320,7 @@ int patches(int he, int we) { return (he % 4 == 0 && we % 8 == 0) ? 1 : 0; }
 // hang on how many there are.  What is left is the sums' order, 5e-7 of a colour,
 // which dx and dn (sums that cancel) amplify to 4e-4 of their rms at worst; it
 // grows with the terms, to 9e-4 at 2048 directions, so beyond 512 the form keeps
-// to MFMA (828 us against 160 at 100k: RGA_FP32 is the form to ask for there).
+// to MFMA (828 us against 144 at 100k: RGA_FP32 is the form to ask for there).
 bool forward_on_mfma(const ShadeArgs& a) {
   if (fp32_lds(a.K, a.V, false, false, 8) + 16 * 64 > kLdsMax - kLdsStatic || a.K > 512) return true;
   return a.K <= 128 && a.n >= 32768 && view_ratio(a.he, a.we, a.hv, a.wv) > 0;
