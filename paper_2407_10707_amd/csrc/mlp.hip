@@ -165,48 +165,61 @@ __device__ inline void load8(const float* p, float* v) {
 // Fragment order of an operand with KS reduction steps of 32: element
 // ((ct * KS + ks) * 64 + lane) * 8 + e holds column ct * 16 + lane % 16 and
 // reduction index ks * 32 + 8 (lane / 16) + e.
-__global__ void __launch_bounds__(256)
+// Workgroups of one wave, one group of 8 elements (or one bias) per thread: bound
+// by the latency of the loads, which 256 threads of a workgroup waited for
+// together (12.4 -> 7.5 us with the launch).  The pose's share of the first bias is
+// one chain of kPose products per row, whose rows are brought to LDS in whole
+// lines first (-> 6.9 us).
+constexpr int kPackThreads = 64;
+constexpr int kPackItems = kPackElems / 8 + kLayers * kWidth;
+static_assert(kPackElems / 8 % kPackThreads == 0 && kWidth % kPackThreads == 0,
+              "a workgroup packs one kind");
+
+__global__ void __launch_bounds__(kPackThreads)
 mlp_pack_kernel(const float* __restrict__ P, const float* __restrict__ theta,
                 __bf16* __restrict__ hi, __bf16* __restrict__ lo, float* __restrict__ bias) {
   const int groups = kPackElems / 8;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < groups + kLayers * kWidth;
-       i += gridDim.x * blockDim.x) {
-    if (i < groups) {
-      const int e0 = 8 * i;
-      float v[8];
-      if (e0 < kFwdElems) {
-        int l = 0;
-        while (l + 1 < kLayers && e0 >= f_off(l + 1)) ++l;
-        const int KS = f_k(l) / 32, frag = (e0 - f_off(l)) / 8;
-        const int lane = frag & 63, t = frag >> 6, ks = t % KS, ct = t / KS;
-        const int n = ct * 16 + (lane & 15), kb = ks * 32 + 8 * (lane >> 4);
-        for (int e = 0; e < 8; ++e)
-          v[e] = n < n_out(l) ? P[w_off(l) + n * n_in(l) + kb + e] : 0.f;
-      } else {
-        int l = 1;
-        while (l + 1 < kLayers && e0 >= t_off(l + 1)) ++l;
-        const int KS = t_k(l) / 32, frag = (e0 - t_off(l)) / 8;
-        const int lane = frag & 63, t = frag >> 6, ks = t % KS, ct = t / KS;
-        const int k = ct * 16 + (lane & 15), nb = ks * 32 + 8 * (lane >> 4);
-        for (int e = 0; e < 8; ++e)
-          v[e] = nb + e < n_out(l) ? P[w_off(l) + (nb + e) * n_in(l) + k] : 0.f;
-      }
-      bf16x8 h, l8;
-      split8(v, h, l8);
-      *reinterpret_cast<bf16x8*>(hi + e0) = h;
-      *reinterpret_cast<bf16x8*>(lo + e0) = l8;
+  const int i = blockIdx.x * kPackThreads + threadIdx.x;
+  if (i < groups) {
+    const int e0 = 8 * i;
+    float v[8];
+    if (e0 < kFwdElems) {
+      int l = 0;
+      while (l + 1 < kLayers && e0 >= f_off(l + 1)) ++l;
+      const int KS = f_k(l) / 32, frag = (e0 - f_off(l)) / 8;
+      const int lane = frag & 63, t = frag >> 6, ks = t % KS, ct = t / KS;
+      const int n = ct * 16 + (lane & 15), kb = ks * 32 + 8 * (lane >> 4);
+      for (int e = 0; e < 8; ++e)
+        v[e] = n < n_out(l) ? P[w_off(l) + n * n_in(l) + kb + e] : 0.f;
     } else {
-      const int j = i - groups, l = j / kWidth, n = j % kWidth;
-      float b = 0.f;
-      if (l == 0) {
-        b = P[b_off(0) + n];
-#pragma unroll 24
-        for (int t = 0; t < kPose; ++t) b = fmaf(P[w_off(0) + n * kIn1 + 2 * kFreqs + t], theta[t], b);
-      } else if (n < n_out(l)) {
-        b = P[b_off(l) + n];
-      }
-      bias[j] = b;
+      int l = 1;
+      while (l + 1 < kLayers && e0 >= t_off(l + 1)) ++l;
+      const int KS = t_k(l) / 32, frag = (e0 - t_off(l)) / 8;
+      const int lane = frag & 63, t = frag >> 6, ks = t % KS, ct = t / KS;
+      const int k = ct * 16 + (lane & 15), nb = ks * 32 + 8 * (lane >> 4);
+      for (int e = 0; e < 8; ++e)
+        v[e] = nb + e < n_out(l) ? P[w_off(l) + (nb + e) * n_in(l) + k] : 0.f;
     }
+    bf16x8 h, l8;
+    split8(v, h, l8);
+    *reinterpret_cast<bf16x8*>(hi + e0) = h;
+    *reinterpret_cast<bf16x8*>(lo + e0) = l8;
+  } else {
+    const int j = i - groups, l = j / kWidth, n = j % kWidth;
+    float b = 0.f;
+    if (l == 0) {
+      __shared__ float w[kPackThreads][kPose + 1];
+      const float* rows = P + w_off(0) + (n - (int)threadIdx.x) * kIn1 + 2 * kFreqs;
+#pragma unroll 24
+      for (int q = threadIdx.x; q < kPackThreads * kPose; q += kPackThreads)
+        w[q / kPose][q % kPose] = rows[q / kPose * kIn1 + q % kPose];
+      b = P[b_off(0) + n];
+      __syncthreads();
+      for (int t = 0; t < kPose; ++t) b = fmaf(w[threadIdx.x][t], theta[t], b);
+    } else if (n < n_out(l)) {
+      b = P[b_off(l) + n];
+    }
+    bias[j] = b;
   }
 }
 
@@ -695,8 +708,8 @@ extern "C" int mlp_forward(void* stream, int nv, const float* x, const float* fr
   hipStream_t s = static_cast<hipStream_t>(stream);
   __bf16* hi = at<__bf16>(ws, L.pack);
   __bf16* lo = hi + kPackElems;
-  RGA_LAUNCH("mlp_pack", mlp_pack_kernel, dim3(256), dim3(256), 0, s, params, theta, hi, lo,
-             at<float>(ws, L.bias));
+  RGA_LAUNCH("mlp_pack", mlp_pack_kernel, dim3(kPackItems / kPackThreads), dim3(kPackThreads), 0,
+             s, params, theta, hi, lo, at<float>(ws, L.bias));
   // with no vertices the kernel still clears the kept activations of the
   // padding rows, which the adjoint reads
   RGA_LAUNCH("mlp_fwd", mlp_forward_kernel, dim3(rga::ceil_div(L.nvp, kWgRows)), dim3(64 * kWaves), 0,
