@@ -109,35 +109,20 @@ struct Attr {
   int vidx[3];
 };
 
-// In the wave-per-Gaussian forward (UNI = true) one Gaussian's attributes
-// and derived constants are the same in every lane: they are pinned to
-// scalar registers, which lowers the vector register count enough for one
-// more wave per SIMD.  (The adjoint gains no occupancy from it and pays
-// the extra scalar-to-vector moves, so it keeps them in vector registers;
-// the MFMA kernels hold a different Gaussian per lane row.)
-__device__ inline float uni(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
 __device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <bool UNI, typename T>
-__device__ inline T pin(T v) {
-  if constexpr (UNI) return uni(v);
-  return v;
-}
 
-template <bool UNI>
 __device__ inline void attr_load(const ShadeArgs& a, int g, Attr& A) {
   const int n = a.n, nvm = a.nv - 1;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    A.x[c] = pin<UNI>(a.x[(size_t)c * n + g]);
-    A.m[c] = pin<UNI>(a.nrm[(size_t)c * n + g]);
-    A.alb[c] = pin<UNI>(a.albedo[(size_t)c * n + g]);
-    A.vw[c] = pin<UNI>(a.vw[(size_t)c * n + g]);
-    A.vidx[c] = pin<UNI>(rga::clampi(a.vidx[(size_t)c * n + g], 0, nvm));
+    A.x[c] = a.x[(size_t)c * n + g];
+    A.m[c] = a.nrm[(size_t)c * n + g];
+    A.alb[c] = a.albedo[(size_t)c * n + g];
+    A.vw[c] = a.vw[(size_t)c * n + g];
+    A.vidx[c] = rga::clampi(a.vidx[(size_t)c * n + g], 0, nvm);
   }
-  A.rough = pin<UNI>(a.rough[g]);
-  A.tint = pin<UNI>(a.tint[g]);
+  A.rough = a.rough[g];
+  A.tint = a.tint[g];
 }
 
 // Reciprocal and reciprocal square root on the transcendental unit (about
@@ -154,7 +139,10 @@ struct GaussCtx {
   bool front;
 };
 
-template <bool UNI>
+// (In the wave-per-Gaussian kernels the constants are the same in every lane.
+// They stay in vector registers all the same: to move 19 of them to scalar ones
+// per Gaussian took 4 of 118 us, forward and back, at 100k Gaussians and 512
+// directions, and occupancy does not ask for it.)
 __device__ inline void gauss_setup(const ShadeArgs& a, const Attr& A, const uint8_t* rows,
                                    GaussCtx& G) {
   const float m0 = A.m[0], m1 = A.m[1], m2 = A.m[2];
@@ -183,25 +171,6 @@ __device__ inline void gauss_setup(const ShadeArgs& a, const Attr& A, const uint
   G.u1 = A.vw[1] * ikv;
   G.u2 = A.vw[2] * ikv;
   G.rows = rows;
-  if constexpr (UNI) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      G.nn[c] = uni(G.nn[c]);
-      G.wo[c] = uni(G.wo[c]);
-    }
-    G.co = uni(G.co);
-    G.a2 = uni(G.a2);
-    G.kG = uni(G.kG);
-    G.Go = uni(G.Go);
-    G.Gq = uni(G.Gq);
-    G.inn = uni(G.inn);
-    G.iwo = uni(G.iwo);
-    G.alpha = uni(G.alpha);
-    G.gamma = uni(G.gamma);
-    G.u0 = uni(G.u0);
-    G.u1 = uni(G.u1);
-    G.u2 = uni(G.u2);
-  }
 }
 
 struct Pair {
@@ -582,7 +551,7 @@ shade_fwd_kernel(ShadeArgs a, int cap, float* __restrict__ color, uint8_t* __res
       if (t < entries) gn = load(t);
       wave_fence();
       GaussCtx G;
-      gauss_setup<true>(a, A, L.rows, G);
+      gauss_setup(a, A, L.rows, G);
       float sd0 = 0.f, sd1 = 0.f, sd2 = 0.f, ss0 = 0.f, ss1 = 0.f, ss2 = 0.f;
       // this Gaussian's row of the tape (a wave-uniform address)
       uint2* const trow = a.tape ? a.tape + (size_t)uni(g) * K : nullptr;
@@ -723,9 +692,9 @@ shade_fwd_mfma_kernel(ShadeArgs a, int ratio, float* __restrict__ color,
     const int g = tile * 16 + row;
     const bool have = g < n;
     Attr A;
-    attr_load<false>(a, have ? g : n - 1, A);
+    attr_load(a, have ? g : n - 1, A);
     GaussCtx G;
-    gauss_setup<false>(a, A, nullptr, G);
+    gauss_setup(a, A, nullptr, G);
     const bool on = have && G.front;
     const uint8_t* r0 = a.count + (size_t)A.vidx[0] * V;
     const uint8_t* r1 = a.count + (size_t)A.vidx[1] * V;
@@ -907,9 +876,9 @@ shade_bwd_mfma_kernel(ShadeArgs a, int ratio, const float* __restrict__ color,
     const bool have = g < n;
     const int gc = have ? g : n - 1;
     Attr A;
-    attr_load<false>(a, gc, A);
+    attr_load(a, gc, A);
     GaussCtx G;
-    gauss_setup<false>(a, A, nullptr, G);
+    gauss_setup(a, A, nullptr, G);
     const bool on = have && G.front;
     float dLo[3], aop[3], qd[3];
 #pragma unroll
@@ -1151,7 +1120,7 @@ shade_bwd_kernel(ShadeArgs a, int cap, const float* __restrict__ color,
       if (t < entries) gn = load(t, tln, twn);
       wave_fence();
       GaussCtx G;
-      gauss_setup<true>(a, A, L.rows, G);
+      gauss_setup(a, A, L.rows, G);
       // dL/dL_o: lane c < 3 takes channel c, every lane reads the three
       float dLo[3], aop[3], qd[3];
       {
