@@ -285,7 +285,8 @@ preprocess_kernel(int n, CamDev cam, int TX, int TY, const float* __restrict__ x
                   int32_t* __restrict__ touched, uint8_t* __restrict__ fp64,
                   uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
                   uint32_t* __restrict__ ranges_u32, int64_t nranges, uint32_t* __restrict__ cnt4,
-                  float4* __restrict__ grad, uint4* __restrict__ part_t, int64_t nparts4) {
+                  float4* __restrict__ grad, uint4* __restrict__ part_t, int64_t nparts4,
+                  uint32_t* __restrict__ bsum, int nsums) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   // the frame's tile ranges start empty, its counters at zero, and so do the
   // adjoint's sums of the splats in the lists (below); no part is finished
@@ -293,6 +294,7 @@ preprocess_kernel(int n, CamDev cam, int TX, int TY, const float* __restrict__ x
     part_t[i] = make_uint4(kNoPart, kNoPart, kNoPart, kNoPart);
   if (g < nranges) ranges_u32[g] = 0u;
   if (g < 8) cnt4[g] = 0u;
+  if (g < nsums) bsum[g] = 0u;
   if (g >= n) return;
   Geo G;
   bool okq;
@@ -713,134 +715,59 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
 }
 
 // ---- depth sort of few splats -----------------------------------------------
-// The whole sort in one workgroup's LDS, with the live count and the sums of
-// tiles touched: the same stable LSD order in passes of 8 bits (one whose digit
-// is the same in every key is left out; culled splats sort last by their key).
-// Each of the sixteen waves owns a contiguous run of the items.  It stands for ten
-// launches, which bound small frames on the device and on the host: 2,000
-// Gaussians' training step 168 -> 136 us, 4,096 splats forward and back 94 -> 76 us
-// (13 and 19 us in here; twice as many would take as long as the launches).
-constexpr int kSmallSort = 4096;
+// Every splat's place by counting the keys before its own, with the live count and
+// the sums of tiles touched: n^2 / 64 comparisons of a scalar key with 64 lanes',
+// but one launch with no pass waiting for another, where the radix passes are ten
+// (forward and back on 256^2: 8,000 splats 102 -> 78 us, 16,384 113 -> 98 us, and an
+// LSD sort in one workgroup's LDS took 75 us against 65 at 4,096).  A workgroup
+// places 64 splats, its sixteen waves share the keys: up to one workgroup per CU,
+// beyond which 20,000 take 118 -> 122 us.  (Equal keys keep their order: those before
+// the splat count up to its own key, those after it below.)
+constexpr int kRankSort = 64 * 256;
 
 __global__ void __launch_bounds__(1024)
-small_sort_kernel(int n, const uint32_t* __restrict__ keys, const int32_t* __restrict__ touched,
-                  uint32_t* __restrict__ order, uint32_t* __restrict__ bsum,
-                  int64_t* __restrict__ live) {
-  constexpr int kW = 16, kR = kSmallSort / 1024;
-  __shared__ uint32_t key[2][kSmallSort];
-  __shared__ uint16_t idx[2][kSmallSort];
-  __shared__ uint16_t run[kW][256];
-  __shared__ uint32_t wt[4], bs[kSmallSort / kBlockN], alive, all_or, all_and;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const int rounds = (n + 1023) / 1024;
-  if (tid < kSmallSort / kBlockN) bs[tid] = 0u;
-  if (tid == 0) {
-    alive = 0u;
-    all_or = 0u;
-    all_and = ~0u;
+rank_sort_kernel(int n, const uint32_t* __restrict__ keys, const int32_t* __restrict__ touched,
+                 uint32_t* __restrict__ order, uint32_t* __restrict__ bsum,
+                 int64_t* __restrict__ live) {
+  constexpr int kW = 16;
+  __shared__ uint32_t counts[kW][64], bs[kRankSort / kBlockN], alive;
+  const int lane = threadIdx.x & 63, b = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = 64 * b + lane, groups = (n + 63) / 64;
+  if (threadIdx.x < kRankSort / kBlockN) bs[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) alive = 0u;
+  const uint32_t own = i < n ? keys[i] : kCulled;
+  uint32_t c = 0u;
+  for (int q = wave; q < groups; q += kW) {
+    const uint32_t* __restrict__ k = keys + 64 * q;
+    if (q != b && 64 * q + 64 <= n) {
+      const uint32_t limit = own + (q < b ? 1u : 0u);
+#pragma unroll
+      for (int j = 0; j < 64; ++j) c += k[j] < limit ? 1u : 0u;
+    } else {
+      const int m = min(64, n - 64 * q);
+      for (int j = 0; j < m; ++j) c += k[j] < own + (64 * q + j < i ? 1u : 0u) ? 1u : 0u;
+    }
+  }
+  counts[wave][lane] = c;
+  __syncthreads();
+  if (b == 0) {
+    uint32_t a = 0u;
+    for (int j = threadIdx.x; j - lane < n; j += 64 * kW)
+      a += (uint32_t)__popcll(__ballot(j < n && keys[j] != kCulled));
+    if (lane == 0) atomicAdd(&alive, a);
+  }
+  if (wave == 0 && own != kCulled) {
+    uint32_t at = 0u;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) at += counts[w][lane];
+    order[at] = (uint32_t)i;
+    atomicAdd(&bs[at / kBlockN], (uint32_t)touched[i]);
   }
   __syncthreads();
-  {
-    uint32_t o = 0u, a = ~0u, count = 0u;
-    for (int r = 0; r < rounds; ++r) {
-      const int i = 1024 * r + tid;
-      const uint32_t k = i < n ? keys[i] : kCulled;
-      key[0][i] = k;
-      idx[0][i] = (uint16_t)i;
-      count += (uint32_t)__popcll(__ballot(k != kCulled));
-      if (k != kCulled) {
-        o |= k;
-        a &= k;
-      }
-    }
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-      o |= __shfl_xor(o, s, 64);
-      a &= __shfl_xor(a, s, 64);
-    }
-    if (lane == 0) {
-      atomicAdd(&alive, count);
-      atomicOr(&all_or, o);
-      atomicAnd(&all_and, a);
-    }
-  }
-  __syncthreads();
-  // (culled keys are all ones: with any of them every digit differs, unless it is
-  // all ones in the live keys too, so the live keys' own bits decide and the
-  // last pass, of the sign and exponent, parts the culled)
-  const uint32_t differ = all_or ^ all_and;
-  const bool some_culled = alive != (uint32_t)(1024 * rounds);
-  int cur = 0;
-  for (int shift = 0; shift < 32; shift += 8) {
-    if (((differ >> shift) & 0xFFu) == 0u && !(shift == 24 && some_culled)) continue;
-    if (tid < 512) reinterpret_cast<uint4*>(&run[0][0])[tid] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    uint32_t k[kR], info[kR];
-#pragma unroll
-    for (int r = 0; r < kR; ++r) {
-      if (r >= rounds) break;
-      k[r] = key[cur][64 * (wave * rounds + r) + lane];
-      const uint32_t d = (k[r] >> shift) & 0xFFu;
-      uint64_t peers = ~0ull;
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
-      }
-      const uint32_t rank = __popcll(peers & lt), group = __popcll(peers);
-      if (rank == 0) run[wave][d] = (uint16_t)(run[wave][d] + group);
-      info[r] = rank | (group << 8);
-    }
-    __syncthreads();
-    uint32_t total = 0u, incl = 0u;
-    if (tid < 256) {
-#pragma unroll
-      for (int w = 0; w < kW; ++w) total += run[w][tid];
-      incl = rga::wave_scan(total);
-      if (lane == 63) wt[wave] = incl;
-    }
-    __syncthreads();
-    if (tid < 256) {
-      uint32_t at = incl - total;
-      for (int w = 0; w < wave; ++w) at += wt[w];
-#pragma unroll
-      for (int w = 0; w < kW; ++w) {
-        const uint32_t c = run[w][tid];
-        run[w][tid] = (uint16_t)at;
-        at += c;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kR; ++r) {
-      if (r >= rounds) break;
-      const uint32_t d = (k[r] >> shift) & 0xFFu;
-      const uint32_t rank = info[r] & 0xFFu, group = info[r] >> 8;
-      const uint32_t at = run[wave][d], pos = at + rank;
-      key[cur ^ 1][pos] = k[r];
-      idx[cur ^ 1][pos] = idx[cur][64 * (wave * rounds + r) + lane];
-      if (rank == 0) run[wave][d] = (uint16_t)(at + group);
-    }
-    __syncthreads();
-    cur ^= 1;
-  }
-  const int nl = (int)alive;
-  for (int r = 0; r < rounds; ++r) {
-    const int i = 1024 * r + tid;
-    uint32_t t = 0u;
-    if (i < nl) {
-      const uint32_t g = idx[cur][i];
-      order[i] = g;
-      t = (uint32_t)touched[g];
-    }
-    const uint32_t s = rga::wave_scan(t);
-    if (lane == 63) atomicAdd(&bs[i / kBlockN], s);
-  }
-  __syncthreads();
-  if (tid < (nl + kBlockN - 1) / kBlockN) bsum[tid] = bs[tid];
-  if (tid == 0) *live = nl;
+  if (threadIdx.x < kRankSort / kBlockN && bs[threadIdx.x] != 0u)
+    atomicAdd(&bsum[threadIdx.x], bs[threadIdx.x]);
+  if (b == 0 && threadIdx.x == 0) *live = alive;
 }
 
 // ---- entries: one per (splat, tile touched), in depth order -----------------
@@ -1972,23 +1899,24 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
     RGA_LAUNCH("splat_fill", fill_u32, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(cnt),
                (int64_t)8, 0u);
   } else {
-    // the projection also clears the tile ranges and the counters
+    const bool small = n <= kRankSort;
+    uint32_t* bsum = at<uint32_t>(ws, L.bsum);
+    // the projection also clears the tile ranges, the counters and, for the sort
+    // of few splats, the sums of tiles touched
     const int64_t pre_threads = std::max<int64_t>(std::max<int64_t>(n, 2 * tiles), 8);
     RGA_LAUNCH("splat_preprocess", preprocess_kernel, dim3(rga::ceil_div(pre_threads, 256)),
                dim3(256), 0, s, n, cd, L.tiles_x, L.tiles_y, x, A, quat, log_s, opac, front, at<float4>(ws, L.rec), at<float>(ws, L.mean2d), at<float>(ws, L.conic),
                at<float>(ws, L.depth), at<int32_t>(ws, L.rect), at<int32_t>(ws, L.touched),
                at<uint8_t>(ws, L.fp64), k0, v0, reinterpret_cast<uint32_t*>(ranges), 2 * tiles,
                reinterpret_cast<uint32_t*>(cnt), at<float4>(ws, L.grad), at<uint4>(ws, L.part_t),
-               L.parts > 1 ? tiles * kBlocks * L.parts * 16 : (int64_t)0);
+               L.parts > 1 ? tiles * kBlocks * L.parts * 16 : (int64_t)0, bsum, small ? L.nb_n : 0);
     // depth sort: 3 passes of 11 bits over n 32-bit keys (4 passes of 8
     // bits, with 8x smaller digit tables, take longer: the passes are
     // latency-bound launches).  The first leaves out the culled splats (half of
     // an avatar's face away), the rest of the binning has the others only.
     int64_t* live = cnt + 3;
-    uint32_t* bsum = at<uint32_t>(ws, L.bsum);
-    const bool small = n <= kSmallSort;
     if (small)
-      RGA_LAUNCH("small_sort", small_sort_kernel, dim3(1), dim3(1024), 0, s, n, k0,
+      RGA_LAUNCH("rank_sort", rank_sort_kernel, dim3(rga::ceil_div(n, 64)), dim3(1024), 0, s, n, k0,
                  at<int32_t>(ws, L.touched), v0, bsum, live);
     for (int pass = 0; pass < kDepthPasses && !small; ++pass) {
       const int shift = kDepthBits * pass;

@@ -26,11 +26,13 @@ CASES = [(64, 64, 3000, 0.6), (256, 256, 512, 1.0), (272, 256, 513, 0.5), (512, 
          (1040, 1024, 3000, 0.6), (2048, 2048, 2000, 0.6), (2064, 2048, 2000, 0.6),
          (4096, 4096, 700, 0.6), (16384, 1040, 700, 0.6), (512, 512, 3000, 0.0), (1, 1, 40, 0.5),
          (300, 200, 5000, 0.5)]
-# few splats are sorted by one workgroup, more by the general passes
-CASES += [(256, 128, n, 0.7) for n in (1, 63, 64, 65, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097)]
-CASES += [(W, H, 4200, 0.6) for W, H in ((64, 64), (256, 256), (512, 512), (528, 512), (1024, 528),
+# few splats are placed by counting keys, more by the general passes
+CASES += [(256, 128, n, 0.7) for n in (1, 63, 64, 65, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097,
+                                       16383, 16384, 16385)]
+CASES += [(W, H, 16500, 0.6) for W, H in ((64, 64), (256, 256), (512, 512), (528, 512), (1024, 528),
                                          (1040, 1024), (2064, 2048))]
-CASES += [(256, 128, 4200, 0.0), (256, 128, 4200, 1.0), (256, 128, 1024, 1.0)]
+CASES += [(256, 128, 16500, 0.0), (256, 128, 16500, 1.0), (256, 128, 1024, 1.0),
+          (256, 128, 1024, 0.0)]
 
 
 def dev(a):
