@@ -570,11 +570,10 @@ def measure_form(args, s, d, precision: str, capacity=None):
         torch.cuda.synchronize()
         run = graph.replay
 
-    # the roofline entry is the step's longest kernel, the blend adjoint
-    # here; beside it the shading kernel of the form (the FP32 adjoint, or
-    # the BF16X3 form's forward: both forms' adjoints replay the tape),
-    # timed on a few eager steps after the timed region (the longer of the
-    # two becomes the entry)
+    # the roofline entries are the blend adjoint and the shading kernel of
+    # the form (the FP32 adjoint, or the BF16X3 form's forward: both forms'
+    # adjoints replay the tape), which is timed on a few eager steps after
+    # the timed region; the longer of the two becomes the entry
     if args.kernel:
         kernels = [args.kernel]
     elif precision == "bf16x3":

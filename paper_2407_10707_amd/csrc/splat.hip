@@ -6,11 +6,13 @@
 //   preprocess        1 thread / splat: camera transform, covariance, conic,
 //                     opacity-aware tile rectangle, packed 48-byte record;
 //                     also clears the frame's ranges, counters and sums
-//   depth sort        stable LSD radix sort of (depth bits, index):
+//   depth sort        of (depth bits, index): up to 16,384 splats by counting
+//                     the keys before each, else a stable LSD radix sort in
 //                     3 passes of 11-bit digits, each [upsweep of per-block
 //                     digit counts, per-digit scan, ranked scatter]; culled
 //                     splats carry key 0xFFFFFFFF and leave with the first
 //   touched sums      tiles touched by each block of splats in depth order
+//                     (with few splats the depth sort adds them up)
 //   duplicate         one (tile, splat) entry per touched tile, emitted in
 //                     depth order -> D
 //   tile sort         stable LSD radix sort of the entries by tile id (one
@@ -18,10 +20,10 @@
 //                     (depth bits, index) order
 //   ranges            tile boundaries in the sorted entries (written by the
 //                     tile sort's scatter when it takes one pass)
-//   blend             one workgroup per 8 x 8 pixel block: its waves composite
-//                     consecutive 64-entry sub-chunks of the tile's list side
-//                     by side and stop as soon as the block has; the adjoint
-//                     over the sub-chunks that were composited
+//   blend             one workgroup per 8 x 8 pixel block walks the tile's list
+//                     until the block has stopped, each wave for one of its
+//                     4 x 4 sub-blocks; the adjoint over the 64-entry
+//                     sub-chunks that were composited
 // Stable ranking inside a radix pass uses wave64 ballots (one per digit bit
 // gives the lanes that share a digit) and mbcnt-style lane masks.
 #include "common.h"
