@@ -112,3 +112,15 @@ def test_visibility_small_workspace(V, less):
     assert call(size) == 0
     _equal(count, raw, v, f, d, 64, knn)
     assert call(layout - 1) == -2
+
+
+# several views in a workgroup, whose z-buffer the depth test leaves as it is
+@pytest.mark.parametrize("nf", [200, 900])
+def test_shadow_maps_share_workgroups(nf):
+    print(f"[vis meshes] shadow {nf}", flush=True)
+    v, f, d, knn = _mesh(7, 4, nf, 517, "body")
+    count, raw = rga.mesh_visibility(dev(v), dev(f), dev(d), 16, dev(knn), want_raw=True,
+                                     shadow_bias_px=1.5)
+    eraw, ecnt = cpu.mesh_visibility_shadow(v, f, d, 16, knn, 1.5)
+    assert np.array_equal(raw.cpu().numpy().view(np.uint32), eraw)
+    assert np.array_equal(count.cpu().numpy(), ecnt)
