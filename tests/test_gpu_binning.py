@@ -33,6 +33,8 @@ CASES += [(W, H, 16500, 0.6) for W, H in ((64, 64), (256, 256), (512, 512), (528
                                          (1040, 1024), (2064, 2048))]
 CASES += [(256, 128, 16500, 0.0), (256, 128, 16500, 1.0), (256, 128, 1024, 1.0),
           (256, 128, 1024, 0.0)]
+# many splats take longer blocks
+CASES += [(256, 128, 131071, 0.2), (256, 128, 131072, 0.2), (1024, 528, 132099, 0.2)]
 
 
 def dev(a):
