@@ -215,6 +215,14 @@ int shade_gaussians(void* stream, int n, const float* x, const float* nrm, const
                     const uint8_t* count, int nv, int kv, int he, int we, int hv, int wv,
                     const float* env, const float* cam_pos, int precision, float* color,
                     uint8_t* front, void* tape, size_t tape_bytes);
+/* The same call for a stream with another beside it that is not to wait for
+ * wave slots until this one ends (the same results; it takes half the device
+ * where the whole would be filled).                                        */
+int shade_gaussians_beside(void* stream, int n, const float* x, const float* nrm, const float* albedo,
+                           const float* rough, const float* tint, const int32_t* vidx, const float* vw,
+                           const uint8_t* count, int nv, int kv, int he, int we, int hv, int wv,
+                           const float* env, const float* cam_pos, int precision, float* color,
+                           uint8_t* front, void* tape, size_t tape_bytes);
 
 /* Bytes of a live-pair tape for n Gaussians and an he x we map: an int32
  * count per Gaussian (rounded up to 256 bytes), then 8 bytes per

@@ -171,7 +171,7 @@ class Renderer:
         color, front = rga.shade_gaussians(xo, no, p["albedo"], p["rough"], p["tint"], d["vidx"],
                                            d["vw"], count, s["kv"], s["he"], s["we"], s["hv"],
                                            s["wv"], p["env"], self.cam_pos, self.precision,
-                                           tape=tape)
+                                           tape=tape, beside=self.overlap)
         if self.overlap:
             main.wait_event(self.binned)
             image, T = rga.splat_blend(self.cam, color, self.ws)

@@ -47,6 +47,8 @@ _SIGS = {
     "mesh_visibility_noalloc": (_I, [_VP, _I, _I, _VP, _VP, _I, _VP, _I, _VP, _I, _VP, _VP]),
     "shade_gaussians": (_I, [_VP, _I, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _I, _I, _I, _I, _I,
                              _I, _VP, _VP, _I, _VP, _VP, _VP, _SZ]),
+    "shade_gaussians_beside": (_I, [_VP, _I, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _I, _I, _I, _I, _I,
+                             _I, _VP, _VP, _I, _VP, _VP, _VP, _SZ]),
     "shade_tape_bytes": (_SZ, [_I, _I, _I]),
     "back_face": (_I, [_VP, _I, _VP, _VP, _VP, _VP]),
     "shade_gaussians_workspace": (_SZ, [_I, _I, _I]),
@@ -334,9 +336,10 @@ def _tape(tape):
 
 
 def shade_gaussians(x, nrm, albedo, rough, tint, vidx, vw, count, kv, he, we, hv, wv, env,
-                    cam_pos, precision: str = "fp32", tape=None):
+                    cam_pos, precision: str = "fp32", tape=None, beside: bool = False):
     """tape: None, or a buffer from shade_tape that receives the live pairs
-    (either form) for a shade_gaussians_backward of the same inputs."""
+    (either form) for a shade_gaussians_backward of the same inputs.
+    beside: leave room on the device for work on another stream."""
     n = x.shape[1]
     nv = count.shape[0]
     _f32(x, "x", (3, n))
@@ -351,10 +354,10 @@ def shade_gaussians(x, nrm, albedo, rough, tint, vidx, vw, count, kv, he, we, hv
     color = torch.empty((3, n), dtype=torch.float32, device=x.device)
     front = torch.empty((n,), dtype=torch.uint8, device=x.device)
     cp = (C.c_float * 3)(*[float(v) for v in cam_pos])
-    _check(lib().shade_gaussians(_stream(), n, _p(x), _p(nrm), _p(albedo), _p(rough), _p(tint),
-                                 _p(vidx), _p(vw), _p(count), nv, kv, he, we, hv, wv, _p(env),
-                                 C.addressof(cp), PRECISIONS[precision], _p(color),
-                                 _p(front), *_tape(tape)), "shade_gaussians")
+    call = lib().shade_gaussians_beside if beside else lib().shade_gaussians
+    _check(call(_stream(), n, _p(x), _p(nrm), _p(albedo), _p(rough), _p(tint), _p(vidx), _p(vw),
+                _p(count), nv, kv, he, we, hv, wv, _p(env), C.addressof(cp), PRECISIONS[precision],
+                _p(color), _p(front), *_tape(tape)), "shade_gaussians")
     return color, front
 
 

@@ -68,3 +68,27 @@ def test_repeated_gaussians(case):
             assert torch.allclose(many["denv"].double(), want, rtol=2e-4, atol=0.0)
         else:
             assert bool(torch.isfinite(many["denv"]).all())
+
+
+# the forward that leaves room beside it: the same colours, flags and tape
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("case", [(4097, 8, 16, 4, 8), (20000, 8, 16, 8, 16), (33000, 8, 16, 8, 16),
+                                  (9000, 16, 32, 16, 32)])
+def test_beside(case, precision):
+    print(f"[shade handout] beside {case} {precision}", flush=True)
+    n, he, we, hv, wv = case
+    s = synth.micro_scene(31, BASE, 40, 48, he=he, we=we, hv=hv, wv=wv)
+    xo, no, _ = cpu.lbs_f32(s["skin"], s["jidx"], s["jw"], s["pos"], s["nrm"])
+    _, _, cnt = helpers.oracle_visibility(s)
+    pick = np.arange(n) % BASE
+    a = [dev(np.asarray(p)[..., pick]) for p in (xo, no, s["albedo"], s["rough"], s["tint"],
+                                                 s["vidx"], s["vw"])]
+    rest = (dev(cnt), s["kv"], he, we, hv, wv, dev(s["env"]), s["cam"].centre.astype(np.float32))
+    out = []
+    for beside in (False, True):
+        tape = rga.shade_tape(n, he, we, "cuda")
+        tape.zero_()
+        out.append((*rga.shade_gaussians(*a, *rest, precision=precision, tape=tape, beside=beside),
+                    tape))
+    for one, other in zip(*out):
+        assert torch.equal(one, other)
