@@ -56,22 +56,67 @@ constexpr int kDepthBits = 11;   // digit width of the depth sort: 3 passes over
 constexpr int kDepthPasses = (32 + kDepthBits - 1) / kDepthBits;
 constexpr int kManySplats = 1 << 17;
 
-// Parts a tile's list is walked in (see the blend), so that about 5,000
-// workgroups share the work of few deep lists: the mean number of splats
-// per tile decides, known before the lists are.  (A list's length is about
-// half of it times the tiles a splat touches, over the share of the tiles
-// that the avatar covers.)
-inline int list_parts(int64_t n, int64_t tiles) {
-  if (n < 192 * tiles || tiles > 512) return 1;
-  return n < 1024 * tiles ? 4 : (tiles > 64 ? 8 : 32);
+// Deep lists are walked in parts, side by side (see the blend): a list of two part
+// lengths or more, which are 1,024 entries (a walk of 22 us, where the launches of a
+// frame's other steps take longer than a shorter one saves) or, so that all parts
+// together are about as many workgroups as the chip holds, 1/256 of all entries.
+// What decides is each list's own length, known on the device: the mean over an
+// image's tiles says nothing of an avatar that covers a few of them.
+constexpr int kPart = 1024;
+constexpr int kParts = 256;      // of all lists, about
+constexpr int kListParts = 128;  // of one list
+constexpr int kPartBits = 7;     // an item of the part list: tile << kPartBits | part
+
+__device__ inline uint32_t part_length(int64_t entries) {   // (at most 2^31 - 1)
+  static_assert(kParts == 256, "a shift");
+  const uint32_t v = ((uint32_t)entries + 255u) >> 8;
+  return v > kPart ? (v + kSub - 1) / kSub * kSub : kPart;
+}
+
+__device__ inline bool is_deep(int L, uint32_t part) { return (uint32_t)L >= 2 * part; }
+
+// parts of a deep list of L entries
+__device__ inline int list_parts(int L, uint32_t part) {
+  return (int)min(((uint32_t)L + part - 1) / part, (uint32_t)kListParts);
+}
+
+// Room for the parts: lists of more than two lengths each have at most half as
+// many parts again as whole lengths.  None where no list can be that long.
+inline int part_slots(int64_t n, int64_t cap) {
+  if (n < 2 * kPart) return 0;
+  return (int)std::min<int64_t>(kParts, cap / kPart) * 3 / 2 + 1;
+}
+
+// What the blend keeps of the parts, one array behind the other (one address keeps
+// its scalar registers free): per (place, block, pixel) the (C, T) of a part, then
+// the (C, T) before it; T alone for the parts beside it; per (first place, block)
+// the number of arrived parts; per (place, block) the sub-chunks entered; the
+// items, a deep list's parts but the first; the lists' first places by tile.
+constexpr int kPartWords = kBlocks * 64 + kBlocks;   // cleared per place: T and arrivals
+
+struct Parts {
+  char* ws;
+  int slots;               // 0: no list can be deep
+  __device__ float4* state() const { return reinterpret_cast<float4*>(ws); }
+  __device__ __host__ uint32_t* T() const {
+    return reinterpret_cast<uint32_t*>(ws + (size_t)slots * kBlocks * 64 * 16);
+  }
+  __device__ uint32_t* arrived() const { return T() + (size_t)slots * kBlocks * 64; }
+  __device__ uint32_t* live() const { return arrived() + slots * kBlocks; }
+  __device__ uint32_t* items() const { return live() + slots * kBlocks; }
+  __device__ uint32_t* base() const { return items() + slots; }
+};
+
+inline size_t parts_bytes(int slots, int64_t tiles) {
+  return slots ? (size_t)slots * (kBlocks * 64 * 16 + 4 * (kPartWords + kBlocks + 1)) + 4 * tiles : 0;
 }
 
 struct Layout {
   size_t rec, mean2d, conic, depth, rect, touched, fp64, keys0, vals0, keys1, vals1, offs;
   size_t tk0, tv0, tk1, tv1, ranges, hist, binoff, bintot, bsum, boff, count, grad;
-  size_t nlive, mask, state, part, part_t, total;
+  size_t nlive, mask, state, part, total;
   int tiles_x, tiles_y, nb_n, nb_cap, nb_max, tile_passes;
-  int parts;       // parts a tile's list is walked in
+  int slots;       // parts that the deep lists have room for
   int tile_bits;   // digit width of the tile sort: 7, 8, 10, 11 or 12
 };
 
@@ -118,17 +163,17 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   L.bintot = take((1 << kMaxBits) * 4);
   L.bsum = take((size_t)L.nb_n * 4);
   L.boff = take((size_t)L.nb_n * 4);   // (kept: sizes a caller has computed stay enough)
-  L.count = take(32);   // int64 [0] = D, [3] = splats that touch a tile
+  L.count = take(32);   // int64 [0] = D, [1] = places and items of the deep lists (32 bits each),
+                        // [3] = splats that touch a tile
   L.grad = take(N * kGrad * 4);   // adjoint sums per splat: mean2d, conic, opacity, colour
   // blend state: tile t's sub-chunk m of its list [start, end) has the slot
   // start / 64 + t + m, distinct for every (tile, sub-chunk)
   const size_t slots = C / kSub + (size_t)tiles + 1;
-  L.parts = list_parts(n, tiles);
-  L.nlive = take((size_t)tiles * kBlocks * L.parts * 4);
+  L.nlive = take((size_t)tiles * kBlocks * 4);
   L.mask = take(slots * kBlocks * 8);
   L.state = take(slots * 4 * 256 * 4);
-  L.part = take(L.parts > 1 ? (size_t)tiles * kBlocks * L.parts * 64 * 16 : 0);
-  L.part_t = take(L.parts > 1 ? (size_t)tiles * kBlocks * L.parts * 64 * 4 : 0);
+  L.slots = part_slots(n, cap);
+  L.part = take(parts_bytes(L.slots, tiles));
   L.total = o;
   return L;
 }
@@ -408,6 +453,15 @@ __device__ inline SplatRec load_rec(const float4* __restrict__ rec, const float*
   return R;
 }
 
+// A tile's deep list of L entries among the parts; `next` gives out the places and
+// the items (two words behind D, or LDS where one workgroup has all lists).
+__device__ inline void deep_list(const Parts& P, uint32_t* next, int t, int L, uint32_t part) {
+  const int k = list_parts(L, part);
+  P.base()[t] = atomicAdd(next, (uint32_t)k);
+  uint32_t* const item = P.items() + atomicAdd(next + 1, (uint32_t)(k - 1));
+  for (int y = 1; y < k; ++y) item[y - 1] = (uint32_t)t << kPartBits | (uint32_t)y;
+}
+
 // ---- radix sort (reduce-then-scan, stable) ----------------------------------
 __device__ inline int64_t live_count(const int64_t* cnt_ptr, int64_t fixed, int64_t cap) {
   int64_t c = cnt_ptr ? *cnt_ptr : fixed;
@@ -567,14 +621,15 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
                 uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                 const int64_t* cnt_ptr, int64_t fixed, int64_t cap, int shift,
                 const uint32_t* __restrict__ binoff, const uint32_t* __restrict__ bintot,
-                int32_t* __restrict__ ranges, int nranges, int64_t* __restrict__ live, int nb) {
+                int32_t* __restrict__ ranges, int nranges, Parts P, uint32_t* __restrict__ items,
+                int64_t* __restrict__ live, int nb) {
   constexpr int kRadix = 1 << BITS;
   constexpr int kWavesR = kRadixThreads / 64;
   // digits per thread in the digit scan (the threads past the digits have none)
   constexpr int kPer = (kRadix + kRadixThreads - 1) / kRadixThreads;
   constexpr bool kNarrow = BITS <= 8;
   __shared__ uint32_t run[kWavesR][kRadix];
-  __shared__ uint32_t wtot[kWavesR], ltot[kWavesR];
+  __shared__ uint32_t wtot[kWavesR], ltot[kWavesR], deep_next[2];
   __shared__ uint32_t shift_to[kNarrow ? kRadix : 1];
   __shared__ uint2 sorted[kNarrow ? kRadixThreads * ITEMS : 1];
   uint32_t mine = 0u;   // items of this thread's digit in the block
@@ -587,6 +642,8 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
   if (blk >= count && !(ranges && block == 0)) return;
   uint32_t* wrun = run[wave];
   for (int d = lane; d < kRadix; d += 64) wrun[d] = 0u;
+  if (tid < 2) deep_next[tid] = 0u;
+  const uint32_t part = part_length(count);
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const int64_t wbeg = blk + (int64_t)wave * 64 * ITEMS;
   uint32_t key[ITEMS], val[ITEMS], info[ITEMS];
@@ -642,6 +699,10 @@ radix_downsweep(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ v
     if (ranges && block == 0 && d < nranges) {
       ranges[2 * d] = (int32_t)start;
       ranges[2 * d + 1] = (int32_t)(start + tot[q]);
+      if (P.slots && is_deep((int)tot[q], part)) {
+        deep_list(P, deep_next, d, (int)tot[q], part);
+        atomicAdd(items, (uint32_t)(list_parts((int)tot[q], part) - 1));
+      }
     }
     uint32_t acc = start + binoff[table_at<BITS>(block, d, nb)];
     if constexpr (kNarrow) {
@@ -907,13 +968,25 @@ fill_u32(uint32_t* __restrict__ p, int64_t count, uint32_t v) {
 
 __global__ void __launch_bounds__(256)
 tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, int64_t cap,
-                   int32_t* __restrict__ ranges) {
+                   int32_t* __restrict__ ranges, Parts P,
+                   uint32_t* __restrict__ next) {
   const int64_t count = live_count(cnt_ptr, 0, cap);
+  const uint32_t part = part_length(count);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t t = tkeys[i];
     if (i == 0 || tkeys[i - 1] != t) ranges[2 * t] = (int32_t)i;
-    if (i == count - 1 || tkeys[i + 1] != t) ranges[2 * t + 1] = (int32_t)(i + 1);
+    if (i == count - 1 || tkeys[i + 1] != t) {
+      ranges[2 * t + 1] = (int32_t)(i + 1);
+      if (P.slots && i + 1 >= 2 * (int64_t)part && tkeys[i + 1 - 2 * (int64_t)part] == t) {
+        int64_t lo = 0, hi = i + 1 - 2 * (int64_t)part;   // the list's first entry: search
+        while (lo < hi) {
+          const int64_t m = (lo + hi) / 2;
+          if (tkeys[m] < t) lo = m + 1; else hi = m;
+        }
+        deep_list(P, next, (int)t, (int)(i + 1 - lo), part);
+      }
+    }
   }
 }
 
@@ -945,17 +1018,24 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // block) the entries that can reach pixels not stopped before it; per block
 // the number of sub-chunks that some pixel entered.
 //
-// Where the blocks alone would not keep the CUs busy until the longest list is
-// done (list_parts: 50k splats on 200^2 take 58 us in 4 parts, 73 us in one,
-// 200k on 200^2 106 us in 8 and 262 us), a list is walked in parts side by side, each from T = 1,
-// C = 0; a join finds every part's incoming (C, T) per pixel and the part in
-// which the pixel stops, and a restart walks that part's sub-chunk with the
-// stop again from its true state.  The states of such a list are relative to
-// their part.  A part leaves its pixels' T where the later parts of the block
-// look for it once a round (no one waits for it): pixels that the earlier
-// parts finished so far have stopped for certain need no walk any more.  The
-// join decides on its own; what it reads of a part that ended early lies past
-// the stop.
+// A deep list (is_deep) is walked in parts side by side, each from T = 1, C = 0:
+// the first by the block's own workgroup, the others by workgroups behind those of
+// the blocks, so that they wait for slots, not the other way round.  The last of a
+// block's workgroups to arrive (counted; none waits) finds every part's incoming
+// (C, T) per pixel and the part in which the pixel stops, and walks that part's
+// sub-chunk with the stop again from its true state.  The states of such a list
+// are relative to their part.  A part leaves its pixels' T where the later parts of
+// the block look for it before they start: pixels that the earlier parts finished
+// so far have stopped for certain need no walk any more.  The join decides on its
+// own; what it reads of a part that ended early lies past the stop.
+// One walk takes 22 ns per entry where pixels do not stop, as at an avatar's rim.
+// Kernels of a forward and adjoint, every list in one walk -> deep ones in parts:
+// 300k splats on 8 tiles of 1080^2, the longest list 101,728 entries, 4,040 -> 390
+// us; on 40 tiles of 512^2, 25,667 entries, 770 -> 335; 30k on 39 tiles, 2,576
+// entries, 211 -> 214; 100k on 372 tiles, 4,570 entries, 274 -> 275; 300k on 1,627
+// tiles, no deep list, 580 -> 587 (the join's registers leave six waves per SIMD
+// instead of seven).  Equal parts of all of an image's lists, chosen by their mean:
+// 100k on 128^2 345 -> 260, 200k on 200^2 320 -> 292.
 constexpr float kPastStop = -2.f;
 
 // One front-to-back compositing step for the pixel centre (px, py), written
@@ -985,19 +1065,36 @@ __device__ inline float blend_step(const float4& a, const float4& c1, float px, 
   return w;
 }
 
-// The 8 x 8 block (tile, index in the tile) of a blend workgroup: the four
-// blocks of a tile, which read the same records, follow each other on one XCD
-// (workgroups with equal index mod 8), and neighbouring tiles go to different
-// ones.  The grid is block_grid(tiles) workgroups.
+// The 8 x 8 block (tile, index in the tile) of a blend workgroup, and the part of
+// the tile's list it walks: the four blocks of a tile, which read the same
+// records, follow each other on one XCD (workgroups with equal index mod 8), and
+// neighbouring tiles go to different ones; the same of the items (a tile's further
+// part), which come behind block_grid(tiles) workgroups for the first parts.
 struct PixelBlock {
-  int t, blk, ox, oy;     // tile, block in the tile, first pixel
+  int t, blk, ox, oy;     // tile (-1: none), block in the tile, first pixel
+  int y;                  // part
   __device__ inline int id() const { return kBlocks * t + blk; }
 };
-__device__ inline PixelBlock pixel_block(int TX) {
+__device__ inline PixelBlock pixel_block(int index, int TX, int tiles, const Parts& P,
+                                         const int64_t* counters) {
   PixelBlock b;
-  const int k = blockIdx.x >> 3;
-  b.t = (k >> 2) * 8 + (blockIdx.x & 7);
+  const int first = (tiles + 7) / 8 * 8 * kBlocks;
+  b.y = 0;
+  const int e = index < first ? index : index - first;
+  const int k = e >> 3;
+  b.t = (k >> 2) * 8 + (e & 7);
   b.blk = k & 3;
+  if (index >= first) {
+    if (b.t < (int)((uint64_t)counters[1] >> 32)) {
+      const uint32_t item = P.items()[b.t];
+      b.t = (int)(item >> kPartBits);
+      b.y = (int)(item & ((1u << kPartBits) - 1u));
+    } else {
+      b.t = -1;
+    }
+  } else if (b.t >= tiles) {
+    b.t = -1;
+  }
   b.ox = (b.t % TX) * kTile + 8 * (b.blk & 1);
   b.oy = (b.t / TX) * kTile + 8 * (b.blk >> 1);
   return b;
@@ -1046,14 +1143,157 @@ __device__ inline float quad_sum(float v) {
   return v + quad<0x4E>(v);
 }
 
-template <int P>
+// Of four entries in a pixel's lanes, front to back: the product of the factors up
+// to this lane's, and before it (quad_perm [0, 0, 1, 2], then [0, 1, 0, 1]).
+__device__ inline float quad_product(float m, int e, float& before) {
+  const float m1 = m * quad<0x90>(m);
+  m = e >= 1 ? m1 : m;
+  const float m2 = m * quad<0x44>(m);
+  m = e >= 2 ? m2 : m;
+  const float ml = quad<0x90>(m);
+  before = e >= 1 ? ml : 1.f;
+  return m;
+}
+
+// What a block's workgroups leave for the one that arrives last goes past the L2 of
+// their XCD, and is read past that of the reader's (device-scope accesses), and the
+// arrivals are counted once it is there: a fence instead would write the L2 back
+// for each of them (1,000 parts: 290 us).
+template <typename T>
+__device__ inline void put_shared(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline T get_shared(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void shared_is_out() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The parts of a block joined, by the workgroup that arrived last.  Each part's
+// (C, T) becomes the (C, T) before it, with the code of T_in that only flips signs:
+// T_in for a whole part, -T_in for the part where the pixel stops (its own walk
+// stopped, or T_in T < 1e-4), kPastStop past it (the first wave, lane = pixel).
+// Pixels that stop in the first part, walked from the true T = 1, and pixels that
+// never stop are written at once; the others walk the sub-chunk of their part in
+// which they stop -- T_in T >= 1e-4 before it, not after it -- from that state with
+// the stop: each pixel its own, four lanes and entries at a time as in the blend.
+// (A pixel that does not stop there because of rounding ends with the sub-chunk.)
+__device__ inline void blend_join(int W, int H, const PixelBlock& B, int parts, int home, int per,
+                                  int start, int slot0, int L, int n,
+                                  const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
+                                  const float* __restrict__ color, const float* state, const Parts& P,
+                                  float* image, float* Tfinal, float4* before, int* stops) {
+  const int lane = threadIdx.x & 63, e = lane & 3;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t HW = (size_t)H * W;
+  if (wave == 0) {
+    const int px = B.ox + (lane & 7), py = B.oy + (lane >> 3);
+    const bool inside = px < W && py < H;
+    float4* p = P.state() + (size_t)home * 64 + lane;
+    float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Tout = 1.f;
+    bool active = inside, first = false;
+    int stop_part = -1;
+    float4 in = make_float4(0.f, 0.f, 0.f, 0.f);   // (C, T) before the part of the stop
+    for (int y0 = 0; y0 < parts; y0 += 4) {
+      float4 r[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint64_t* f = reinterpret_cast<const uint64_t*>(p + min(y0 + u, parts - 1) * kBlocks * 64);
+        const uint64_t a = get_shared(f), b = get_shared(f + 1);
+        r[u] = make_float4(__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32)),
+                           __uint_as_float((uint32_t)b), __uint_as_float((uint32_t)(b >> 32)));
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int y = y0 + u;
+        if (y >= parts) continue;
+        const bool stop = active && (r[u].w < 0.f || T * r[u].w < 1e-4f);
+        p[y * kBlocks * 64] = make_float4(C0, C1, C2, active ? (stop ? -T : T) : kPastStop);
+        if (stop) {
+          active = false;
+          first = y == 0;
+          stop_part = y > 0 ? y : -1;
+          in = make_float4(C0, C1, C2, T);
+        }
+        if (active || (stop && y == 0)) {
+          C0 = fmaf(T, r[u].x, C0);
+          C1 = fmaf(T, r[u].y, C1);
+          C2 = fmaf(T, r[u].z, C2);
+          T = active ? T * r[u].w : T;
+          Tout = active ? T : -r[u].w;
+        }
+      }
+    }
+    if (inside && (active || first)) {
+      const size_t q = (size_t)py * W + px;
+      image[q] = C0;
+      image[HW + q] = C1;
+      image[2 * HW + q] = C2;
+      Tfinal[q] = Tout;
+    }
+    before[lane] = in;
+    stops[lane] = stop_part;
+  }
+  __syncthreads();
+  const int bx = 4 * (wave & 1) + ((lane >> 2) & 3), by = 4 * (wave >> 1) + (lane >> 4);
+  const float4 in = before[8 * by + bx];
+  const int y = stops[8 * by + bx];
+  if (y < 0) return;                       // (a pixel's four lanes)
+  const float* const st = state + (size_t)slot0 * 1024 + 64 * B.blk + 8 * by + bx;
+  // the last sub-chunk entered with T_in T >= 1e-4 (T falls along the part)
+  int sub = per * y;
+  for (int hi = sub + min((int)get_shared(P.live() + home + kBlocks * y), per); hi - sub > 1;) {
+    const int m = (sub + hi) / 2;
+    const bool above = in.w * get_shared(st + (size_t)m * 1024 + 768) >= 1e-4f;
+    sub = above ? m : sub;
+    hi = above ? hi : m;
+  }
+  const float* const sj = st + (size_t)sub * 1024;
+  float T = in.w * get_shared(sj + 768), Tl = T;
+  float C0 = 0.f, C1 = 0.f, C2 = 0.f;
+  const float base = e < 3 ? fmaf(in.w, get_shared(sj + 256 * e), e == 0 ? in.x : (e == 1 ? in.y : in.z)) : 0.f;
+  const float fpx = (float)(B.ox + bx) + 0.5f, fpy = (float)(B.oy + by) + 0.5f;
+  const int e0 = sub * kSub + e;
+  auto index = [&](int i) { return sorted[start + min(e0 + 4 * i, L - 1)]; };
+  SplatRec R = load_rec(rec, color, n, index(0));
+  uint32_t g1 = index(1), g2 = index(2);
+#pragma unroll 1
+  for (int i = 0; i < kSub / 4; ++i) {
+    const SplatRec N = load_rec(rec, color, n, g1);
+    g1 = g2;
+    g2 = index(i + 3);
+    const float dx = R.r0.x - fpx, dy = R.r0.y - fpy;
+    const float e2 = fmaf(R.r0.z * dx, dx, fmaf(R.r1.x * dy, dy, (R.r0.w * dx) * dy));
+    const float alpha = fminf(0.99f, R.r1.y * __builtin_amdgcn_exp2f(e2));
+    const bool use = e2 <= 0.f && alpha >= 1.f / 255.f && e0 + 4 * i < L;
+    float ml;
+    const float m = quad_product(use ? 1.f - alpha : 1.f, e, ml);
+    const float after = T * m, prior = T * ml;
+    const bool on = use && after >= 1e-4f;
+    const float w = on ? alpha * prior : 0.f;
+    C0 = fmaf(R.r1.z, w, C0);
+    C1 = fmaf(R.r1.w, w, C1);
+    C2 = fmaf(R.r2.x, w, C2);
+    Tl = on ? after : Tl;
+    T = quad<0xFF>(after);
+    R = N;
+  }
+  C0 = quad_sum(C0);
+  C1 = quad_sum(C1);
+  C2 = quad_sum(C2);
+  Tl = fminf(Tl, quad<0xB1>(Tl));
+  Tl = fminf(Tl, quad<0x4E>(Tl));
+  const size_t q = (size_t)(B.oy + by) * W + B.ox + bx;
+  (e == 3 ? Tfinal : image + e * HW)[q] = e == 3 ? Tl : base + (e == 0 ? C0 : (e == 1 ? C1 : C2));
+}
+
 __global__ void __launch_bounds__(256)
 blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__ ranges,
              const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
              const float* __restrict__ color, const int64_t* __restrict__ counters,
              int64_t capacity, float* __restrict__ state, uint64_t* __restrict__ mask,
-             uint32_t* __restrict__ nlive, float4* __restrict__ part, uint32_t* part_t,
-             float* __restrict__ image, float* __restrict__ Tfinal) {
+             uint32_t* __restrict__ nlive, Parts P, float* __restrict__ image,
+             float* __restrict__ Tfinal) {
   constexpr int kRound = 4 * kSub;        // entries per round
   // the staged records of two rounds, each with an entry past them with
   // opacity 0 that fills up a step of four
@@ -1065,15 +1305,14 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
   // lane e (the e-th of either four) follow each other
   __shared__ uint16_t lists[4][kRound];
   __shared__ int open[2][4];              // sub-chunks entered in the round, per wave; 0: stopped
-  const PixelBlock B = pixel_block(TX);
-  if (B.t >= tiles) return;
+  const PixelBlock B = pixel_block(blockIdx.x, TX, tiles, P, counters);
+  if (B.t < 0) return;
   const int lane = threadIdx.x & 63, e = lane & 3;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // this lane's pixel in the block, wave w having the sub-block (w & 1, w >> 1)
   const int bx = 4 * (wave & 1) + ((lane >> 2) & 3), by = 4 * (wave >> 1) + (lane >> 4);
   const int px = B.ox + bx, py = B.oy + by;
   const bool inside = px < W && py < H;
-  const size_t pi = (size_t)B.id() * P + blockIdx.y;
   // lane e < 3 of a pixel writes channel e, lane 3 the transmittance
   auto put_pixel = [&](float c0, float c1, float c2, float T) {
     const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
@@ -1084,14 +1323,26 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
   // the frame is poisoned (NaN) rather than silently wrong
   if (counters[0] > capacity) {
     const float nan = __builtin_nanf("");
-    if (blockIdx.y == 0) put_pixel(nan, nan, nan, nan);
-    if (threadIdx.x == 0) nlive[pi] = 0u;
+    if (B.y == 0) {
+      put_pixel(nan, nan, nan, nan);
+      if (threadIdx.x == 0) nlive[B.id()] = 0u;
+    }
     return;
   }
   const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
   const int slot0 = start / kSub + B.t;
-  const int per = kSub * part_subs(L, P);
-  const int a0 = min(L, per * (int)blockIdx.y), a1 = min(L, a0 + per);
+  // this workgroup's entries; of a deep list its part, the place of the first
+  // part's block and of its own
+  int parts = 1, per = L, a0 = 0, a1 = L, home = 0, place = 0;
+  const uint32_t part = part_length(counters[0]);
+  if (is_deep(L, part)) {
+    parts = list_parts(L, part);
+    per = kSub * part_subs(L, parts);
+    a0 = min(L, per * B.y);
+    a1 = min(L, a0 + per);
+    home = kBlocks * (int)P.base()[B.t] + B.blk;
+    place = home + kBlocks * B.y;
+  }
   const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
   if (threadIdx.x < 2) {
     s0[threadIdx.x][kRound] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1121,30 +1372,29 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
     if (m) nl = (c0 - a0) / kSub + m;
     return ((open[r][0] | open[r][1]) | (open[r][2] | open[r][3])) & 1;   // some wave goes on
   };
-  // the T of the block's earlier parts at this pixel, as far as they are
-  // finished, looked up a round ahead
-  uint32_t seen[P > 1 ? P - 1 : 1];
-  auto look = [&]() {
-    if constexpr (P > 1) {
+  // A further part first looks what the block's earlier ones (the first 32) have
+  // left at this pixel, as far as they are finished: with less than the stop's T
+  // before it the pixel needs no walk (a margin for the order of the product).
+  bool walk = true;
+  if (B.y > 0) {
+    uint32_t seen[8];
+    float before = 1.f;
 #pragma unroll
-      for (int y = 0; y < P - 1; ++y)
-        if (y < (int)blockIdx.y)
-          seen[y] = __hip_atomic_load(part_t + ((size_t)B.id() * P + y) * 64 + 8 * by + bx,
-                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int u = 0; u < 8; ++u) {
+      seen[u] = kNoPart;
+      if (4 * u + e < B.y)
+        seen[u] = get_shared(P.T() + (uint32_t)((home + kBlocks * (4 * u + e)) * 64 + 8 * by + bx));
     }
-  };
-  look();
-  int par = 0, c0 = a0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (seen[u] != kNoPart) before *= __uint_as_float(seen[u]);
+    before *= quad<0xB1>(before);
+    before *= quad<0x4E>(before);
+    if (before < 0.9e-4f) T = 0.f;
+    walk = __syncthreads_or(T >= 1e-4f);
+  }
+  int par = 0, c0 = walk ? a0 : a1 + 1;
   for (; c0 < a1; c0 += kRound, par ^= 1) {
-    if constexpr (P > 1) {
-      float before = 1.f;
-#pragma unroll
-      for (int y = 0; y < P - 1; ++y)
-        if (y < (int)blockIdx.y && seen[y] != kNoPart) before *= __uint_as_float(seen[y]);
-      // (a margin for the order of the product)
-      if (before * T < 0.9e-4f) T = 0.f;
-      look();
-    }
     {
       const bool ok = c0 - a0 + mine < a1;
 #pragma unroll
@@ -1201,7 +1451,10 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
         const float c0s = quad_sum(C0), c1s = quad_sum(C1), c2s = quad_sum(C2);
         float* st = state + (size_t)(slot0 + c0 / kSub + q) * 1024 + 64 * B.blk + 8 * by + bx;
         const float v = e == 0 ? c0s : (e == 1 ? c1s : (e == 2 ? c2s : (T >= 1e-4f ? T : kPastStop)));
-        st[256 * e] = v;
+        if (parts > 1)
+          put_shared(st + 256 * e, v);
+        else
+          st[256 * e] = v;
       }
       if (!live) continue;
       entered = q + 1;
@@ -1223,15 +1476,9 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
           const float e2 = fmaf(a[u].z * dx, dx, fmaf(c1[u].x * dy, dy, (a[u].w * dx) * dy));
           const float alpha = fminf(0.99f, c1[u].y * __builtin_amdgcn_exp2f(e2));
           const bool use = e2 <= 0.f && alpha >= 1.f / 255.f;
-          // product of 1 - alpha over the entries up to this lane's, and
-          // before it (quad_perm [0, 0, 1, 2], then [0, 1, 0, 1])
-          float m = use ? 1.f - alpha : 1.f;
-          const float m1 = m * quad<0x90>(m);
-          m = e >= 1 ? m1 : m;
-          const float m2 = m * quad<0x44>(m);
-          m = e >= 2 ? m2 : m;
-          const float ml = quad<0x90>(m);
-          const float after = T * m, before = T * (e >= 1 ? ml : 1.f);
+          float ml;
+          const float m = quad_product(use ? 1.f - alpha : 1.f, e, ml);
+          const float after = T * m, before = T * ml;
           const bool on = use && after >= 1e-4f;
           const float w = on ? alpha * before : 0.f;
           C0 = fmaf(c1[u].z, w, C0);
@@ -1252,7 +1499,7 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
     const int on = __ballot(T >= 1e-4f) != 0ull ? 1 : 0;
     if (lane == 0) open[par][wave] = 2 * entered + on;
   }
-  if (c0 >= a1 && a1 > a0) {              // the list ended: its last round's masks
+  if (walk && c0 >= a1 && a1 > a0) {      // the list ended: its last round's masks
     __syncthreads();
     finish(par ^ 1, c0 - kRound);
   }
@@ -1261,152 +1508,30 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
   C2 = quad_sum(C2);
   Tl = fminf(Tl, quad<0xB1>(Tl));
   Tl = fminf(Tl, quad<0x4E>(Tl));
-  if constexpr (P > 1) {
-    if (e == 0) {
-      const bool whole = T >= 1e-4f || !inside;
-      part[pi * 64 + 8 * by + bx] = make_float4(C0, C1, C2, whole ? T : -Tl);
-      __hip_atomic_store(part_t + pi * 64 + 8 * by + bx, __float_as_uint(whole ? T : 0.f),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  } else {
+  if (B.y == 0 && threadIdx.x == 0) nlive[B.id()] = (uint32_t)nl;
+  if (parts == 1) {
     put_pixel(C0, C1, C2, Tl);
+    return;
   }
-  if (threadIdx.x == 0) nlive[pi] = (uint32_t)nl;
-}
-
-// Join of a list's parts (one thread per pixel): each part's (C, T) becomes
-// the (C, T) before it, with the code of T_in that only flips signs: T_in for
-// a whole part, -T_in for the part where the pixel stops (its own walk
-// stopped, or T_in T < 1e-4), kPastStop past it.  Pixels that stop in the
-// first part, walked from the true T = 1, and pixels that never stop are
-// written here.
-template <int P>
-__global__ void __launch_bounds__(256)
-blend_join_kernel(int W, int H, int TX, float4* __restrict__ part,
-                  const int64_t* __restrict__ counters, int64_t capacity,
-                  float* __restrict__ image, float* __restrict__ Tfinal) {
-  if (counters[0] > capacity) return;     // poisoned
-  const int t = blockIdx.x, blk = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int px = (t % TX) * kTile + 8 * (blk & 1) + (lane & 7);
-  const int py = (t / TX) * kTile + 8 * (blk >> 1) + (lane >> 3);
-  const bool inside = px < W && py < H;
-  float4* p = part + (size_t)(kBlocks * t + blk) * P * 64 + lane;
-  float4 r[P];
-#pragma unroll
-  for (int y = 0; y < P; ++y) r[y] = p[64 * y];
-  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Tout = 1.f;
-  bool active = inside, done = false;
-#pragma unroll
-  for (int y = 0; y < P; ++y) {
-    const bool stop = active && (r[y].w < 0.f || T * r[y].w < 1e-4f);
-    p[64 * y] = make_float4(C0, C1, C2, active ? (stop ? -T : T) : kPastStop);
-    if (stop) {
-      active = false;
-      if (y == 0) {
-        C0 = r[0].x;
-        C1 = r[0].y;
-        C2 = r[0].z;
-        Tout = -r[0].w;
-        done = true;
-      }
-    }
-    if (active) {
-      C0 = fmaf(T, r[y].x, C0);
-      C1 = fmaf(T, r[y].y, C1);
-      C2 = fmaf(T, r[y].z, C2);
-      T *= r[y].w;
-    }
+  if (e == 0) {
+    const bool whole = T >= 1e-4f || !inside;
+    const size_t q = (size_t)place * 64 + 8 * by + bx;
+    uint64_t* const f = reinterpret_cast<uint64_t*>(P.state() + q);
+    put_shared(f, (uint64_t)__float_as_uint(C1) << 32 | __float_as_uint(C0));
+    put_shared(f + 1, (uint64_t)__float_as_uint(whole ? T : -Tl) << 32 | __float_as_uint(C2));
+    put_shared(P.T() + q, __float_as_uint(whole ? T : 0.f));
   }
-  if (inside && (active || done)) {
-    const size_t q = (size_t)py * W + px, HW = (size_t)H * W;
-    image[q] = C0;
-    image[HW + q] = C1;
-    image[2 * HW + q] = C2;
-    Tfinal[q] = active ? T : Tout;
-  }
-}
-
-// Restart (kSplitsPart workgroups per block and part after the first, their
-// waves over the part's sub-chunks; lane = pixel): the pixels whose walk stops in a
-// sub-chunk -- T_in T >= 1e-4 before it, not after it -- walk it from that
-// state with the exact stop rule and are written.  (A pixel whose stop test
-// does not fire there because of rounding ends with the sub-chunk.)
-__global__ void __launch_bounds__(256)
-blend_restart_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__ ranges,
-                     const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
-                     const float* __restrict__ color, const float* __restrict__ state,
-                     const uint64_t* __restrict__ mask, const uint32_t* __restrict__ nlive,
-                     const float4* __restrict__ part, float* __restrict__ image,
-                     float* __restrict__ Tfinal) {
-  // the staged records, and one past them with opacity 0
-  __shared__ float4 s0[4][kSub + 1], s1[4][kSub + 1];
-  __shared__ float s2[4][kSub + 1];
-  const PixelBlock B = pixel_block(TX);
-  if (B.t >= tiles || blockIdx.y == 0) return;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const size_t pi = (size_t)B.id() * gridDim.y + blockIdx.y;
-  const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
-  const int slot0 = start / kSub + B.t;
-  const int per = part_subs(L, gridDim.y), m0 = per * blockIdx.y;
-  const int nl = min((int)nlive[pi], per);   // 0 in a poisoned frame
-  const int j0 = wave + 4 * blockIdx.z;
-  if (j0 >= nl) return;
-  const float4 base = part[pi * 64 + lane];
-  const bool mine = base.w < 0.f && base.w >= -1.f;
-  if (__ballot(mine) == 0ull) return;
-  const float Tin = -base.w;
-  const int px = B.ox + (lane & 7), py = B.oy + (lane >> 3);
-  const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
-  if (lane == 0) {
-    s0[wave][kSub] = make_float4(0.f, 0.f, 0.f, 0.f);
-    s1[wave][kSub] = make_float4(0.f, 0.f, 0.f, 0.f);
-    s2[wave][kSub] = 0.f;
-  }
-  for (int j = j0; j < nl; j += 4 * gridDim.z) {
-    const size_t slot = (size_t)slot0 + m0 + j;
-    const float* st = state + slot * 1024 + 64 * B.blk + lane;
-    float T = Tin * st[768];
-    const float Tn = j + 1 < nl ? Tin * st[1024 + 768] : -1.f;
-    const bool here = mine && T >= 1e-4f && !(Tn >= 1e-4f);
-    if (__ballot(here) == 0ull) continue;
-    uint64_t mm = mask[slot * kBlocks + B.blk];
-    mm = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(mm >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((int)mm);
-    const int en = (m0 + j) * kSub + lane;
-    if (((mm >> lane) & 1ull) && en < L) {
-      const SplatRec R = load_rec(rec, color, n, sorted[start + en]);
-      s0[wave][lane] = R.r0;
-      s1[wave][lane] = R.r1;
-      s2[wave][lane] = R.r2.x;
-    }
-    float C0 = fmaf(Tin, st[0], base.x), C1 = fmaf(Tin, st[256], base.y),
-          C2 = fmaf(Tin, st[512], base.z);
-    wave_fence();
-    bool stopped = !here;
-    while (mm && __ballot(!stopped) != 0ull) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = mm ? (int)__builtin_ctzll(mm) : kSub;
-        mm &= mm - 1;
-        bool applied;
-        float alpha, dx, dy, G, araw;
-        const float4 c1 = s1[wave][k];
-        const float w = blend_step(s0[wave][k], c1, fpx, fpy, T, stopped, applied, alpha, dx, dy, G, araw);
-        C0 = fmaf(c1.z, w, C0);
-        C1 = fmaf(c1.w, w, C1);
-        C2 = fmaf(s2[wave][k], w, C2);
-      }
-    }
-    if (here) {
-      const size_t p = (size_t)py * W + px, HW = (size_t)H * W;
-      image[p] = C0;
-      image[HW + p] = C1;
-      image[2 * HW + p] = C2;
-      Tfinal[p] = T;
-    }
-    wave_fence();   // the next sub-chunk's records replace these
-  }
+  if (threadIdx.x == 0) put_shared(P.live() + place, (uint32_t)nl);
+  shared_is_out();
+  __syncthreads();
+  int* const turn = &open[0][0];
+  uint32_t* const arrived = P.arrived() + home;   // from kNoPart on
+  if (threadIdx.x == 0) *turn = (int)(atomicAdd(arrived, 1u) + 2u);
+  __syncthreads();
+  if (*turn != parts) return;
+  if (threadIdx.x == 0) *arrived = kNoPart;   // for another blend of the same lists
+  blend_join(W, H, B, parts, home, per / kSub, start, slot0, L, n, sorted, rec, color, state, P, image,
+             Tfinal, &s0[0][0], reinterpret_cast<int*>(&s2[0][0]));
 }
 
 // Workgroups per block of the adjoint (a block's sub-chunks are dealt out to
@@ -1414,7 +1539,7 @@ blend_restart_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __re
 // with many blocks fewer do, since every further workgroup of a short list
 // is started for nothing.
 inline int splits(int64_t tiles) { return tiles >= 4096 ? 2 : 4; }
-constexpr int kSplitsPart = 2;           // the same, per part of a list walked in parts
+constexpr int kSplitsPart = 2;           // the same, per further part of a deep list
 
 // ---- adjoint: blend ----------------------------------------------------------
 // One workgroup per 8 x 8 pixel block again; its waves take the sub-chunks
@@ -1442,33 +1567,37 @@ blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restri
                  const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
                  const float* __restrict__ color, const float* __restrict__ state,
                  const uint64_t* __restrict__ mask, const uint32_t* __restrict__ nlive,
-                 const float4* __restrict__ part, const float* __restrict__ image,
-                 const float* __restrict__ dimage, float* __restrict__ grad) {
+                 const int64_t* __restrict__ counters, int64_t capacity, Parts P, int nsplit,
+                 const float* __restrict__ image, const float* __restrict__ dimage,
+                 float* __restrict__ grad) {
   __shared__ float4 s0[4][kSub], s1[4][kSub];
   __shared__ float s2[4][kSub];
   __shared__ uint32_t sg[4][kSub];
-  const PixelBlock B = pixel_block(TX);
-  if (B.t >= tiles) return;
+  // first nsplit times the workgroups of the blocks, then kSplitsPart times those
+  // of the items; of a part's sub-chunks each takes every so many'th four
+  const int blocks = (tiles + 7) / 8 * 8 * kBlocks, items = (P.slots + 7) / 8 * 8 * kBlocks;
+  const bool own = (int)blockIdx.x < nsplit * blocks;
+  const int unit = own ? blocks : items, at = own ? blockIdx.x : blockIdx.x - nsplit * blocks;
+  const int split = (at >= unit) + (at >= 2 * unit) + (at >= 3 * unit);
+  const PixelBlock B = pixel_block((own ? 0 : blocks) + at - split * unit, TX, tiles, P, counters);
+  if (B.t < 0) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int myslot = lane >> 3, col = lane & 7;
   const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
   const int slot0 = start / kSub + B.t;
-  // the sub-chunks of this workgroup: every gridDim.y-th four of the list's,
-  // or, of a list walked in parts, every gridDim.z-th four of part blockIdx.y's
-  int first, end, step;
+  const int step = 4 * (own ? nsplit : kSplitsPart);
+  int first = wave + 4 * split, end = own ? (int)nlive[B.id()] : first + 1;
+  if (first >= end || counters[0] > capacity) return;
+  const uint32_t part = part_length(counters[0]);
   float4 base = make_float4(0.f, 0.f, 0.f, 1.f);
-  if (part) {
-    const int per = part_subs(L, gridDim.y);
-    const size_t pi = (size_t)B.id() * gridDim.y + blockIdx.y;
-    first = per * blockIdx.y + wave + 4 * blockIdx.z;
-    end = per * blockIdx.y + min((int)nlive[pi], per);
-    step = 4 * gridDim.z;
-    base = part[pi * 64 + lane];
-  } else {
-    first = wave + 4 * blockIdx.y;
-    end = nlive[B.id()];
-    step = 4 * gridDim.y;
+  if (is_deep(L, part)) {
+    const int parts = list_parts(L, part);
+    const int place = kBlocks * ((int)P.base()[B.t] + B.y) + B.blk;
+    const int per = part_subs(L, parts), m0 = per * B.y;
+    first += m0;
+    end = m0 + min((int)P.live()[place], per);
+    base = P.state()[(size_t)place * 64 + lane];
   }
   end = min(end, (L + kSub - 1) / kSub);
   if (first >= end) return;
@@ -1802,6 +1931,8 @@ VertexOrderLayout vertex_order_layout(int n) {
   return L;
 }
 
+Parts parts_of(void* ws, const Layout& L) { return Parts{at<char>(ws, L.part), L.slots}; }
+
 int check_common(const char* fn, int n, const rga_camera* cam, const void* ws, size_t ws_bytes,
                  int64_t cap, Layout& L) {
   if (n < 0) return rga::fail(RGA_EINVAL, "%s: n < 0", fn);
@@ -1911,8 +2042,8 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
                dim3(256), 0, s, n, cd, L.tiles_x, L.tiles_y, x, A, quat, log_s, opac, front, at<float4>(ws, L.rec), at<float>(ws, L.mean2d), at<float>(ws, L.conic),
                at<float>(ws, L.depth), at<int32_t>(ws, L.rect), at<int32_t>(ws, L.touched),
                at<uint8_t>(ws, L.fp64), k0, v0, reinterpret_cast<uint32_t*>(ranges), 2 * tiles,
-               reinterpret_cast<uint32_t*>(cnt), at<float4>(ws, L.grad), at<uint4>(ws, L.part_t),
-               L.parts > 1 ? tiles * kBlocks * L.parts * 16 : (int64_t)0, bsum, small ? L.nb_n : 0);
+               reinterpret_cast<uint32_t*>(cnt), at<float4>(ws, L.grad), reinterpret_cast<uint4*>(parts_of(ws, L).T()),
+               (int64_t)L.slots * kPartWords / 4, bsum, small ? L.nb_n : 0);
     // depth sort: 3 passes of 11 bits over n 32-bit keys (4 passes of 8
     // bits, with 8x smaller digit tables, take longer: the passes are
     // latency-bound launches).  The first leaves out the culled splats (half of
@@ -1942,7 +2073,7 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
       RGA_LAUNCH("radix_binscan", radix_binscan<kDepthBits>, dim3((1 << kDepthBits) / 8), dim3(256), 0, s,
                  hist, nb, count, (int64_t)n, (int64_t)n, block, binoff, bintot);
       RGA_LAUNCH("radix_downsweep", down, dim3(nb), dim3(kRadixThreads), 0, s, k0, v0, k1, v1, count,
-                 (int64_t)n, (int64_t)n, shift, binoff, bintot, (int32_t*)nullptr, 0, live, nb);
+                 (int64_t)n, (int64_t)n, shift, binoff, bintot, (int32_t*)nullptr, 0, Parts{}, (uint32_t*)nullptr, live, nb);
       uint32_t* t = k0; k0 = k1; k1 = t;
       t = v0; v0 = v1; v1 = t;
     }
@@ -1976,14 +2107,16 @@ extern "C" int splat_bin(void* stream, int n, const rga_camera* cam, const float
                  (const int64_t*)cnt, (int64_t)0, capacity, kBlockD, binoff, bintot);
       RGA_LAUNCH("radix_downsweep", down, dim3(L.nb_cap), dim3(kRadixThreads), 0, s, tk0, tv0, tk1, tv1,
                  (const int64_t*)cnt, (int64_t)0, capacity, shift, binoff, bintot,
-                 one ? ranges : (int32_t*)nullptr, one ? (int)tiles : 0, (int64_t*)nullptr, L.nb_cap);
+                 one ? ranges : (int32_t*)nullptr, one ? (int)tiles : 0, parts_of(ws, L),
+                 reinterpret_cast<uint32_t*>(cnt) + 3, (int64_t*)nullptr, L.nb_cap);
       uint32_t* t = tk0; tk0 = tk1; tk1 = t;
       t = tv0; tv0 = tv1; tv1 = t;
     }
     if (!one)
       RGA_LAUNCH("tile_ranges", tile_ranges_kernel,
                  dim3(std::min<int64_t>(rga::ceil_div(capacity, 256), 2048)), dim3(256), 0, s, tk0,
-                 (const int64_t*)cnt, capacity, ranges);
+                 (const int64_t*)cnt, capacity, ranges, parts_of(ws, L),
+                 reinterpret_cast<uint32_t*>(cnt) + 2);
   }
   RGA_CHECK_LAUNCH("splat_bin");
   return RGA_OK;
@@ -2004,24 +2137,10 @@ extern "C" int splat_blend(void* stream, int n, const rga_camera* cam, const flo
   int64_t* cnt = at<int64_t>(ws, L.count);
   int32_t* ranges = at<int32_t>(ws, L.ranges);
   const uint32_t* sorted = at<uint32_t>(ws, (L.tile_passes & 1) ? L.tv1 : L.tv0);
-  float4* part = at<float4>(ws, L.part);
-  auto blend = blend_kernel<1>;
-  auto join = blend_join_kernel<4>;
-  if (L.parts == 4) blend = blend_kernel<4>;
-  if (L.parts == 8) blend = blend_kernel<8>, join = blend_join_kernel<8>;
-  if (L.parts == 32) blend = blend_kernel<32>, join = blend_join_kernel<32>;
-  RGA_LAUNCH("blend", blend, dim3(block_grid(tiles), L.parts), dim3(256), 0, s, W, H, L.tiles_x,
-             (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color, cnt, capacity,
-             at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive), part,
-             at<uint32_t>(ws, L.part_t), image, T_final);
-  if (L.parts > 1) {
-    RGA_LAUNCH("blend_join", join, dim3(tiles), dim3(256), 0, s, W, H, L.tiles_x, part, cnt,
-               capacity, image, T_final);
-    RGA_LAUNCH("blend_restart", blend_restart_kernel, dim3(block_grid(tiles), L.parts, kSplitsPart),
-               dim3(256), 0, s, W, H, L.tiles_x, (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color,
-               at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive), part,
-               image, T_final);
-  }
+  RGA_LAUNCH("blend", blend_kernel, dim3(block_grid(tiles) + block_grid(L.slots)), dim3(256), 0, s, W, H,
+             L.tiles_x, (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color, cnt, capacity,
+             at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive),
+             parts_of(ws, L), image, T_final);
   RGA_CHECK_LAUNCH("splat_blend");
   return RGA_OK;
 }
@@ -2062,14 +2181,13 @@ extern "C" int splat_backward(void* stream, int n, const rga_camera* cam, const 
   float* grad = at<float>(ws, L.grad);
   const int64_t tiles = (int64_t)L.tiles_x * L.tiles_y;
   const uint32_t* sorted = at<uint32_t>(ws, (L.tile_passes & 1) ? L.tv1 : L.tv0);
+  const int nsplit = splits(tiles);
   RGA_LAUNCH("blend_bwd", blend_bwd_kernel,
-             L.parts > 1 ? dim3(block_grid(tiles), L.parts, kSplitsPart)
-                         : dim3(block_grid(tiles), splits(tiles)),
-             dim3(256), 0, s,
+             dim3(nsplit * block_grid(tiles) + kSplitsPart * block_grid(L.slots)), dim3(256), 0, s,
              cam->width, cam->height, L.tiles_x, (int)tiles, n, at<int32_t>(ws, L.ranges), sorted,
              at<float4>(ws, L.rec), color, at<float>(ws, L.state), at<uint64_t>(ws, L.mask),
-             at<uint32_t>(ws, L.nlive),
-             L.parts > 1 ? at<float4>(ws, L.part) : (float4*)nullptr, image, dimage, grad);
+             at<uint32_t>(ws, L.nlive), (const int64_t*)at<int64_t>(ws, L.count), capacity,
+             parts_of(ws, L), nsplit, image, dimage, grad);
   RGA_LAUNCH("preprocess_bwd", preprocess_bwd_kernel, dim3(rga::ceil_div(n, 256)), dim3(256), 0, s,
              n, cd, x, A, quat, log_s, opac, front, at<int32_t>(ws, L.touched), grad, dx, dquat,
              dlog_s, dopac, dcolor, dA, (const int64_t*)at<int64_t>(ws, L.count), capacity);
@@ -2115,7 +2233,7 @@ extern "C" int vertex_order(void* stream, int n, const int32_t* vidx, int nv, in
                (const int64_t*)nullptr, (int64_t)n, (int64_t)n, kBlockN, binoff, bintot);
     RGA_LAUNCH("radix_downsweep", (radix_downsweep<kItemsN, kDigitBits>), dim3(L.nb), dim3(kRadixThreads), 0, s,
                k0, v0, k1, vout, (const int64_t*)nullptr, (int64_t)n, (int64_t)n, shift, binoff,
-               bintot, (int32_t*)nullptr, 0, (int64_t*)nullptr, L.nb);
+               bintot, (int32_t*)nullptr, 0, Parts{}, (uint32_t*)nullptr, (int64_t*)nullptr, L.nb);
     uint32_t* t = k0; k0 = k1; k1 = t;
     t = v0; v0 = v1; v1 = t;
   }
