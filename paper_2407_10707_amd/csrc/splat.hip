@@ -114,7 +114,7 @@ inline size_t parts_bytes(int slots, int64_t tiles) {
 struct Layout {
   size_t rec, mean2d, conic, depth, rect, touched, fp64, keys0, vals0, keys1, vals1, offs;
   size_t tk0, tv0, tk1, tv1, ranges, hist, binoff, bintot, bsum, boff, count, grad;
-  size_t nlive, mask, state, part, total;
+  size_t nlive, last, mask, state, part, total;
   int tiles_x, tiles_y, nb_n, nb_cap, nb_max, tile_passes;
   int slots;       // parts that the deep lists have room for
   int tile_bits;   // digit width of the tile sort: 7, 8, 10, 11 or 12
@@ -170,6 +170,7 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   // start / 64 + t + m, distinct for every (tile, sub-chunk)
   const size_t slots = C / kSub + (size_t)tiles + 1;
   L.nlive = take((size_t)tiles * kBlocks * 4);
+  L.last = take((size_t)tiles * kBlocks * 64 * 4);
   L.mask = take(slots * kBlocks * 8);
   L.state = take(slots * 4 * 256 * 4);
   L.slots = part_slots(n, cap);
@@ -1016,7 +1017,8 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // What the adjoint needs is left per (sub-chunk of 64 entries, pixel): the
 // (C, T) before it, T negative once the pixel has stopped; per (sub-chunk,
 // block) the entries that can reach pixels not stopped before it; per block
-// the number of sub-chunks that some pixel entered.
+// the number of sub-chunks that some pixel entered; per pixel T after the last
+// entry that counted.
 //
 // A deep list (is_deep) is walked in parts side by side, each from T = 1, C = 0:
 // the first by the block's own workgroup, the others by workgroups behind those of
@@ -1038,14 +1040,14 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // 100k on 128^2 345 -> 260, 200k on 200^2 320 -> 292.
 constexpr float kPastStop = -2.f;
 
-// One front-to-back compositing step for the pixel centre (px, py), written
-// with selects instead of divergent branches: an entry is skipped when its
-// exponent is positive or its alpha is below 1/255, and the walk stops at
-// the first entry that would take T below 1e-4.  Returns the weight
-// alpha * T (0 if the entry is skipped or the walk has stopped); `applied`
-// tells whether the entry contributed.
-__device__ inline float blend_step(const float4& a, const float4& c1, float px, float py, float& T,
-                                   bool& stopped, bool& applied, float& alpha, float& dx,
+// One front-to-back compositing step of the adjoint for the pixel centre (px, py),
+// written with selects instead of divergent branches: an entry is skipped when its
+// exponent is positive or its alpha is below 1/255, and the walk stops at the first
+// entry that would take T below `last` (stop_after).  Returns the weight alpha * T
+// (0 if the entry is skipped or the walk has stopped); `applied` tells whether the
+// entry contributed.
+__device__ inline float blend_step(const float4& a, const float4& c1, float px, float py, float last,
+                                   float& T, bool& stopped, bool& applied, float& alpha, float& dx,
                                    float& dy, float& G, float& araw) {
   dx = a.x - px;
   dy = a.y - py;
@@ -1057,13 +1059,19 @@ __device__ inline float blend_step(const float4& a, const float4& c1, float px, 
   alpha = fminf(0.99f, araw);
   const bool use = !stopped && e2 <= 0.f && alpha >= 1.f / 255.f;
   const float Tn = T * (1.f - alpha);
-  const bool stop = use && Tn < 1e-4f;
+  const bool stop = use && Tn < last;
   stopped = stopped || stop;
   applied = use && !stop;
   const float w = applied ? alpha * T : 0.f;
   T = applied ? Tn : T;
   return w;
 }
+
+// The forward multiplies T in another order than the adjoint, so within the rounding
+// of 1e-4 the two could stop one entry apart.  The forward keeps its T after the last
+// entry that counted; one more that is used takes it down by 1/255 at least, so the
+// adjoint stops halfway between.
+__device__ inline float stop_after(float T) { return T * (1.f - 0x1p-9f); }
 
 // The 8 x 8 block (tile, index in the tile) of a blend workgroup, and the part of
 // the tile's list it walks: the four blocks of a tile, which read the same
@@ -1182,7 +1190,8 @@ __device__ inline void blend_join(int W, int H, const PixelBlock& B, int parts, 
                                   int start, int slot0, int L, int n,
                                   const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
                                   const float* __restrict__ color, const float* state, const Parts& P,
-                                  float* image, float* Tfinal, float4* before, int* stops) {
+                                  float* last, float* image, float* Tfinal, float4* before,
+                                  int* stops) {
   const int lane = threadIdx.x & 63, e = lane & 3;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t HW = (size_t)H * W;
@@ -1230,6 +1239,7 @@ __device__ inline void blend_join(int W, int H, const PixelBlock& B, int parts, 
       image[HW + q] = C1;
       image[2 * HW + q] = C2;
       Tfinal[q] = Tout;
+      last[B.id() * 64 + lane] = Tout;
     }
     before[lane] = in;
     stops[lane] = stop_part;
@@ -1285,6 +1295,7 @@ __device__ inline void blend_join(int W, int H, const PixelBlock& B, int parts, 
   Tl = fminf(Tl, quad<0x4E>(Tl));
   const size_t q = (size_t)(B.oy + by) * W + B.ox + bx;
   (e == 3 ? Tfinal : image + e * HW)[q] = e == 3 ? Tl : base + (e == 0 ? C0 : (e == 1 ? C1 : C2));
+  if (e == 3) last[B.id() * 64 + 8 * by + bx] = Tl;
 }
 
 __global__ void __launch_bounds__(256)
@@ -1292,7 +1303,7 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
              const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
              const float* __restrict__ color, const int64_t* __restrict__ counters,
              int64_t capacity, float* __restrict__ state, uint64_t* __restrict__ mask,
-             uint32_t* __restrict__ nlive, Parts P, float* __restrict__ image,
+             uint32_t* __restrict__ nlive, float* __restrict__ last, Parts P, float* __restrict__ image,
              float* __restrict__ Tfinal) {
   constexpr int kRound = 4 * kSub;        // entries per round
   // the staged records of two rounds, each with an entry past them with
@@ -1511,6 +1522,7 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
   if (B.y == 0 && threadIdx.x == 0) nlive[B.id()] = (uint32_t)nl;
   if (parts == 1) {
     put_pixel(C0, C1, C2, Tl);
+    if (e == 3) last[B.id() * 64 + 8 * by + bx] = Tl;
     return;
   }
   if (e == 0) {
@@ -1530,8 +1542,8 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
   __syncthreads();
   if (*turn != parts) return;
   if (threadIdx.x == 0) *arrived = kNoPart;   // for another blend of the same lists
-  blend_join(W, H, B, parts, home, per / kSub, start, slot0, L, n, sorted, rec, color, state, P, image,
-             Tfinal, &s0[0][0], reinterpret_cast<int*>(&s2[0][0]));
+  blend_join(W, H, B, parts, home, per / kSub, start, slot0, L, n, sorted, rec, color, state, P, last,
+             image, Tfinal, &s0[0][0], reinterpret_cast<int*>(&s2[0][0]));
 }
 
 // Workgroups per block of the adjoint (a block's sub-chunks are dealt out to
@@ -1567,7 +1579,8 @@ blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restri
                  const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
                  const float* __restrict__ color, const float* __restrict__ state,
                  const uint64_t* __restrict__ mask, const uint32_t* __restrict__ nlive,
-                 const int64_t* __restrict__ counters, int64_t capacity, Parts P, int nsplit,
+                 const float* __restrict__ last, const int64_t* __restrict__ counters, int64_t capacity,
+                 Parts P, int nsplit,
                  const float* __restrict__ image, const float* __restrict__ dimage,
                  float* __restrict__ grad) {
   __shared__ float4 s0[4][kSub], s1[4][kSub];
@@ -1613,7 +1626,7 @@ blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restri
     g1 = dimage[HW + p];
     g2 = dimage[2 * HW + p];
   }
-  const float Tin = fabsf(base.w);
+  const float Tin = fabsf(base.w), stop = stop_after(last[B.id() * 64 + lane]);
   // a sub-chunk's loads (entry indices, then the masks, records and states)
   // are issued while the one before is walked
   auto index = [&](int sub) {
@@ -1675,7 +1688,7 @@ blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restri
           const float Tb = T;
           bool applied;
           float alpha, dx, dy, G, araw;
-          const float w = blend_step(a, c1, fpx, fpy, T, done, applied, alpha, dx, dy, G, araw);
+          const float w = blend_step(a, c1, fpx, fpy, stop, T, done, applied, alpha, dx, dy, G, araw);
           Q = fmaf(-gc, w, Q);
           const float dal = fmaf(gc, Tb, -(Q * __builtin_amdgcn_rcpf(1.f - alpha)));   // alpha <= 0.99
           const float dp = applied && araw <= 0.99f ? dal * alpha : 0.f;   // unless clamped
@@ -2140,7 +2153,7 @@ extern "C" int splat_blend(void* stream, int n, const rga_camera* cam, const flo
   RGA_LAUNCH("blend", blend_kernel, dim3(block_grid(tiles) + block_grid(L.slots)), dim3(256), 0, s, W, H,
              L.tiles_x, (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color, cnt, capacity,
              at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive),
-             parts_of(ws, L), image, T_final);
+             at<float>(ws, L.last), parts_of(ws, L), image, T_final);
   RGA_CHECK_LAUNCH("splat_blend");
   return RGA_OK;
 }
@@ -2186,8 +2199,8 @@ extern "C" int splat_backward(void* stream, int n, const rga_camera* cam, const 
              dim3(nsplit * block_grid(tiles) + kSplitsPart * block_grid(L.slots)), dim3(256), 0, s,
              cam->width, cam->height, L.tiles_x, (int)tiles, n, at<int32_t>(ws, L.ranges), sorted,
              at<float4>(ws, L.rec), color, at<float>(ws, L.state), at<uint64_t>(ws, L.mask),
-             at<uint32_t>(ws, L.nlive), (const int64_t*)at<int64_t>(ws, L.count), capacity,
-             parts_of(ws, L), nsplit, image, dimage, grad);
+             at<uint32_t>(ws, L.nlive), at<float>(ws, L.last), (const int64_t*)at<int64_t>(ws, L.count),
+             capacity, parts_of(ws, L), nsplit, image, dimage, grad);
   RGA_LAUNCH("preprocess_bwd", preprocess_bwd_kernel, dim3(rga::ceil_div(n, 256)), dim3(256), 0, s,
              n, cd, x, A, quat, log_s, opac, front, at<int32_t>(ws, L.touched), grad, dx, dquat,
              dlog_s, dopac, dcolor, dA, (const int64_t*)at<int64_t>(ws, L.count), capacity);
