@@ -30,6 +30,7 @@
 // is the loads' latency at four waves per SIMD.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace {
@@ -62,7 +63,10 @@ Window window() {
   return w;
 }
 
-// The tile of a workgroup.  Workgroups that share a remainder modulo 8 run on
+// Workgroups per row of the grid (a dimension holds less than 2^32 threads).
+constexpr int kGridX = 1 << 23;
+
+// The tile of a workgroup (the count of them: none).  Workgroups that share a remainder modulo 8 run on
 // the same XCD and take one contiguous eighth of the tiles (row by row), so
 // that a tile's halo and the cache lines its rows share with its neighbours are
 // in the XCD's L2.
@@ -72,8 +76,9 @@ struct Tile {
 
 __device__ inline Tile tile_of(int tx, int ty, int count) {
   const int per = (count + 7) / 8;
+  const int block = blockIdx.y * kGridX + blockIdx.x;
   Tile t;
-  t.index = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  t.index = block >= 8 * per ? count : (block % 8) * per + block / 8;
   const int row = t.index / tx;
   t.x0 = kTW * (t.index - row * tx);
   t.ch = row / ty;
@@ -301,7 +306,7 @@ ssim_bwd_kernel(int C, int H, int W, int tx, int ty, Window win, Final f, float 
   const int ch = tile.ch, x0 = tile.x0, y0 = tile.y0;
   const size_t HW = (size_t)H * W;
   // (the first workgroup also forms the loss: a launch of its own took 5 us)
-  if (blockIdx.x == 0) {
+  if (blockIdx.x == 0 && blockIdx.y == 0) {
     loss_of(f, smem);
     __syncthreads();
   }
@@ -378,7 +383,8 @@ extern "C" int image_loss(void* stream, int C, int H, int W, const float* image,
                                          rga::align_up((size_t)3 * C * H * W * 4, 256));
   const int tx = (int)rga::ceil_div(W, kTW), ty = (int)rga::ceil_div(H, kTH);
   const int nb = (int)tiles(C, H, W);
-  const dim3 grid((unsigned)rga::align_up(nb, 8));
+  const int64_t blocks = (int64_t)rga::align_up(nb, 8);
+  const dim3 grid((unsigned)std::min<int64_t>(blocks, kGridX), (unsigned)rga::ceil_div(blocks, kGridX));
   const double count = (double)C * H * W;
   RGA_LAUNCH("ssim_fwd", ssim_fwd_kernel, grid, dim3(kThreads), 0, s, C, H, W, tx, ty, win, image, target, abc,
              part);
