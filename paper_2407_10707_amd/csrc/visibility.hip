@@ -509,8 +509,10 @@ raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
             corner(rga::clampi(faces[3 * f + 2], 0, nv - 1), x2, y2, z);
             const int32_t mnx = min(x0, min(x1, x2)), mxx = max(x0, max(x1, x2));
             const int32_t mny = min(y0, min(y1, y2)), mxy = max(y0, max(y1, y2));
-            keep[q] = max(0, -((128 - mnx) >> 8)) <= min(res - 1, (mxx - 128) >> 8) &&
-                      max(0, -((128 - mny) >> 8)) <= min(res - 1, (mxy - 128) >> 8);
+            // (a coordinate may be the lowest integer: what lies left of the frame
+            // lies left of its first sample)
+            keep[q] = max(0, -((128 - max(mnx, 0)) >> 8)) <= min(res - 1, (mxx - 128) >> 8) &&
+                      max(0, -((128 - max(mny, 0)) >> 8)) <= min(res - 1, (mxy - 128) >> 8);
           }
         }
   #pragma unroll
