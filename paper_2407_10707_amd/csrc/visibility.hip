@@ -27,12 +27,17 @@ constexpr int kRasterThreads = 1024;
 constexpr int kWideWords = 1 << 18;
 constexpr int kRing = 256;               // entries of a raster wave's ring
 constexpr int kGroup = 2;                // steps tested together; 63 + 64 kGroup <= kRing
-constexpr int kRingFaces = 1;
+constexpr int kRingFaces = 4096;         // the fewest triangles that go through the rings
 
 __device__ inline void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a value that is the same in all lanes, in a scalar register
+__device__ inline float uni(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 __device__ inline void basis(const float* d, float* t, float* b) {
@@ -103,12 +108,6 @@ __device__ inline void project(const Proj& P, const float (&x)[3], int32_t& U, i
   U = (int32_t)rintf(u * 256.f);
   V = (int32_t)rintf(w * 256.f);
   z = P.rho - pd;
-}
-
-// the depth alone
-__device__ inline float depth(const Proj& P, const float (&x)[3]) {
-  const float q0 = x[0] - P.c[0], q1 = x[1] - P.c[1], q2 = x[2] - P.c[2];
-  return P.rho - fmaf(P.d[2], q2, fmaf(P.d[1], q1, P.d[0] * q0));
 }
 
 __device__ inline unsigned long long depth_key(float bz, int f) {
@@ -238,11 +237,25 @@ __device__ inline float wave_extreme(float v) {
   return v;
 }
 
-// Workgroups [0, kBoxes): partial bounding boxes of the vertices (lo, hi per
-// axis, six floats each) and, for the raster, a copy of 16 bytes per vertex
-// (v4, if there is room).  The other workgroups write the triangles as the byte
-// offsets of three entries of the raster's table: where that holds all vertices
-// (nv <= cap) workgroup kBoxes + i 1024 of them, else workgroup kBoxes + b those
+// Centre and radius of the frame of a bounding box (lo, hi).
+__device__ inline void frame_from(const float (&r)[6], Proj& P) {
+  float e[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    P.c[a] = (r[a] + r[3 + a]) * 0.5f;
+    e[a] = r[3 + a] - r[a];
+  }
+  float rr = 1.01f * (0.5f * sqrtf(fmaf(e[2], e[2], fmaf(e[1], e[1], e[0] * e[0]))));
+  if (!(rr > 0.f)) rr = 1.f;
+  P.rho = rr;
+}
+
+// Workgroups [0, nbox): partial bounding boxes of the vertices (lo, hi per axis, six
+// floats each; where there is one, the frame behind kBoxes of them) and, for the
+// raster, a copy of 16 bytes per vertex (v4, if there is room).  The other workgroups
+// write the triangles as the byte offsets of three entries of the raster's table: where
+// that holds all vertices
+// (nv <= cap) workgroup nbox + i 1024 of them, else workgroup nbox + b those
 // of batch b, counted from the batch's lowest vertex, if its range of vertices
 // fits.  (min and max are exact and independent of the reduction order.)  One
 // workgroup over 39,780 vertices took 16 us.
@@ -250,12 +263,12 @@ constexpr int kBoxes = 16;
 constexpr int kBatch = 16384;            // triangles per batch, a multiple of the raster's threads
 
 __global__ void __launch_bounds__(1024)
-frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restrict__ faces,
+frame_kernel(int nv, int nf, int nbox, const float* __restrict__ v, const int32_t* __restrict__ faces,
              int cap, float* __restrict__ boxes, int2* __restrict__ ranges,
              uint2* __restrict__ packed, float4* __restrict__ v4) {
   __shared__ float ext[6][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b = (int)blockIdx.x - kBoxes;
+  const int b = (int)blockIdx.x - nbox;
   auto pack = [&](int f, int i0, int i1, int i2) {
     packed[f] = make_uint2((uint32_t)(2 * i0) | ((uint32_t)(2 * i1) << 16), (uint32_t)(2 * i2));
   };
@@ -311,7 +324,7 @@ frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restr
   float lo3[3], hi3[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) lo3[a] = hi3[a] = v[a * nv];
-  for (int i = blockIdx.x * 1024 + threadIdx.x; i < nv; i += kBoxes * 1024) {
+  for (int i = blockIdx.x * 1024 + threadIdx.x; i < nv; i += nbox * 1024) {
     float c[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -337,6 +350,20 @@ frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restr
     for (int w = 1; w < 16; ++w)
       x = threadIdx.x < 3 ? fminf(x, ext[threadIdx.x][w]) : fmaxf(x, ext[threadIdx.x][w]);
     boxes[6 * blockIdx.x + threadIdx.x] = x;
+    if (nbox == 1) ext[threadIdx.x][0] = x;
+  }
+  if (nbox > 1 || wave > 0) return;
+  wave_fence();
+  if (threadIdx.x == 0) {
+    float box[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) box[q] = ext[q][0];
+    Proj P;
+    frame_from(box, P);
+    boxes[6 * kBoxes] = P.c[0];
+    boxes[6 * kBoxes + 1] = P.c[1];
+    boxes[6 * kBoxes + 2] = P.c[2];
+    boxes[6 * kBoxes + 3] = P.rho;
   }
 }
 
@@ -345,7 +372,7 @@ frame_kernel(int nv, int nf, const float* __restrict__ v, const int32_t* __restr
 // diagonal.
 __device__ inline void frame_of(const float* __restrict__ boxes, Proj& P) {
   static_assert(kBoxes == 16, "one box per lane of a row");
-  float r[6], e[3];
+  float r[6];
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
     const bool mx = q >= 3;
@@ -357,14 +384,7 @@ __device__ inline void frame_of(const float* __restrict__ boxes, Proj& P) {
     x = op(x, dpp_same<0x128, 0xf>(x));
     r[q] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
   }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    P.c[a] = (r[a] + r[3 + a]) * 0.5f;
-    e[a] = r[3 + a] - r[a];
-  }
-  float rr = 1.01f * (0.5f * sqrtf(fmaf(e[2], e[2], fmaf(e[1], e[1], e[0] * e[0]))));
-  if (!(rr > 0.f)) rr = 1.f;
-  P.rho = rr;
+  frame_from(r, P);
 }
 
 // A vertex's place between the sample centres 256 i + 128, for one axis: how many
@@ -373,10 +393,11 @@ __device__ inline uint32_t place(int32_t x) {
   return (uint32_t)(x + 127) >> 8 | ((x & 255) == 128 ? 0x80u : 0u);
 }
 
-// A workgroup rasterizes views blockIdx.x, + gridDim.x, ...: one fits a CU (its
-// z-buffer takes 128 KB of the 160 at 128^2), and a new one for every view cost
-// 6 of 116 us at four views each.  Bound by vector issue, of which the rasterizer
-// takes some 240 instructions per wave of triangles, and by its addresses.
+// A workgroup rasterizes views blockIdx.x, + gridDim.x, ...: one fits a CU at 128^2
+// (its z-buffer takes 128 KB of the 160), and a new one for every view cost 6 of 116
+// us at four views each; with ONE it has one view, in 64 registers, so that two fit a
+// CU where the z-buffer leaves room for another.  Bound by vector issue, of which the
+// rasterizer takes some 240 instructions per wave of triangles, and by its addresses.
 //
 // RING: many triangles of a mesh cover no sample (41 % at 13k triangles and
 // 128^2, 96 % at 79k).  Each is tested first, by its bounding box alone: that
@@ -397,10 +418,10 @@ __host__ __device__ inline int ring_bytes() {
 }
 __host__ __device__ inline int table_bytes(int cap) { return (2 * cap + 15) / 16 * 16; }
 
-template <bool RING, bool V4>
-__global__ void __launch_bounds__(kRasterThreads)
+template <bool RING, bool V4, bool ONE>
+__global__ void __launch_bounds__(kRasterThreads, ONE ? 8 : 4)
 raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
-              int views, const float* __restrict__ dirs, int res, const float* __restrict__ boxes,
+              int views, const float* __restrict__ dirs, int res, int nbox, const float* __restrict__ boxes,
               const int2* __restrict__ ranges, const uint2* __restrict__ packed, int cap,
               uint32_t* __restrict__ bits_vm /*[V][nwv]*/, int nwv, int shadow, float bias_px) {
   // the table first: its byte offsets are LDS addresses
@@ -412,9 +433,25 @@ raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Proj P;
-  frame_of(boxes, P);
+  if (ONE && nbox == 1) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) P.c[a] = boxes[6 * kBoxes + a];
+    P.rho = boxes[6 * kBoxes + 3];
+  } else {
+    frame_of(boxes, P);
+  }
   P.irho = 1.f / P.rho;
   P.scale = 0.5f * (float)res;
+  // (with ONE what all lanes share is in scalar registers; where a CU's only workgroup
+  // takes four views in turn that costs 90 us instead of 87)
+  auto uniform = [](float& v) {
+    if constexpr (ONE) v = uni(v);
+  };
+#pragma unroll
+  for (int a = 0; a < 3; ++a) uniform(P.c[a]);
+  uniform(P.rho);
+  uniform(P.irho);
+  uniform(P.scale);
   auto corner = [&](int i, int32_t& U, int32_t& V, float& z) {
     float q[3];
     vertex<V4>(verts, i, q);
@@ -434,13 +471,18 @@ raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
     P.d[1] = dirs[3 * view + 1];
     P.d[2] = dirs[3 * view + 2];
     basis(P.d, P.t, P.b);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      uniform(P.t[a]);
+      uniform(P.b[a]);
+    }
     // (see above; a table's entries hold what the frame keeps its vertices to)
     const bool tables = RING && cap > 0 && P.irho < 1e17f &&
                         P.t[0] * P.t[0] + P.t[1] * P.t[1] + P.t[2] * P.t[2] < 1.001f &&
                         P.b[0] * P.b[0] + P.b[1] * P.b[1] + P.b[2] * P.b[2] < 1.001f;
     const bool whole = tables && nv <= cap;
     // (the next view's z-buffer is cleared as the marks are taken)
-    if (view == (int)blockIdx.x || shadow)
+    if (ONE || view == (int)blockIdx.x || shadow)
       for (int p = threadIdx.x; p < pixels; p += kRasterThreads) zb[p] = ~0ull;
     if (whole) fill(0, nv - 1);
     __syncthreads();
@@ -558,7 +600,7 @@ raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
       for (int p = threadIdx.x; p < pixels; p += kRasterThreads) {
         const unsigned long long k = zb[p];
         if (k == ~0ull) continue;
-        zb[p] = ~0ull;
+        if (!ONE) zb[p] = ~0ull;
         const int f = (int)(uint32_t)(k & 0xffffffffull);
         for (int c = 0; c < 3; ++c) {
           const int vi = rga::clampi(faces[3 * f + c], 0, nv - 1);
@@ -569,8 +611,9 @@ raster_kernel(Verts verts, int nf, const int32_t* __restrict__ faces,
     __syncthreads();
     for (int w = threadIdx.x; w < nwv; w += kRasterThreads) {
       bits_vm[(size_t)view * nwv + w] = mark[w];
-      mark[w] = 0u;
+      if (!ONE) mark[w] = 0u;
     }
+    if constexpr (ONE) return;   // (it has this view alone)
   }
 }
 
@@ -797,12 +840,26 @@ int visibility_impl(void* stream, int nv, int nf, const float* verts, const int3
   const size_t zm = sizeof(unsigned long long) * (size_t)res * res + 4 * (size_t)L.nwv;
   if (zm > 160 * 1024)
     return rga::fail(RGA_EUNSUPPORTED, "mesh_visibility: %d vertices need too much LDS", nv);
-  // From one triangle per sample on they go through the rings, if the LDS has
-  // room for them (in place -> rings: 1024 views at 128^2, 27k triangles 182 ->
-  // 151 us, 13k 110 us either way; 64 views at 64^2, 13k 24 -> 21 us, 952 11 ->
-  // 12 us, and the frame kernel 1 us more).
+  // A workgroup has one view where two workgroups' LDS fits a CU (up to 100^2 samples
+  // in place, 94^2 through the rings, with half of the LDS for each one's table): one's
+  // clearing, marking and tails run beside the other's triangles (1024 views, one per
+  // CU -> two: in place 1k triangles at 96^2 62 -> 49 us, 3.6k 67 -> 58; through the
+  // rings 13.6k at 64^2 93 -> 81, 79k 257 -> 213); and in place where there are no more
+  // views than CUs (1k triangles at 128^2, 256 views 41.6 -> 40.2; through the rings
+  // 27k at 64^2 51.0 -> 52.4).  Else a workgroup per CU takes the views in turn.
+  // From one triangle per sample and 4,096 of them on, they go through the rings, if
+  // the LDS has room for them; from two per sample on where that costs the second
+  // workgroup (1024 views, in place -> rings: 79k at 128^2 526 -> 344 us, 13.6k at
+  // 64^2 109 -> 81, 3.6k at 48^2 47 -> 50, 27k at 96^2 177 -> 157 but 13.6k 109 ->
+  // 117; 256 views, 3.6k at 48^2 31 -> 32).
   const size_t rings = ring_bytes();
-  const bool ring = nf > kRingFaces * res * res && zm + rings <= 160 * 1024;
+  const int cus = compute_units();
+  const size_t whole = 160 * 1024, half = whole / 2;
+  const bool pairs = V > cus && V < 1 << 21;   // (a launch's threads count to 2^32)
+  const bool pair_ring = pairs && zm + rings + 2048 <= half, pair_place = pairs && zm <= half;
+  const int least = (pair_place && !pair_ring ? 2 : 1) * res * res;
+  const bool ring = nf > kRingFaces && nf > least && zm + rings <= whole;
+  const bool one = ring ? pair_ring : pair_place || V <= cus;
   // the partial boxes, the vertices' copy, the batches' ranges and the packed
   // triangles live in the filters' buffers, which are written after the raster
   // only; without room for them, or with a table too small to be of use, every
@@ -815,29 +872,38 @@ int visibility_impl(void* stream, int nv, int nf, const float* verts, const int3
   const int batches = (int)rga::ceil_div(nf, kBatch);
   int2* ranges = reinterpret_cast<int2*>(v4 + nv);
   uint2* packed = reinterpret_cast<uint2*>(ranges + batches);
-  int64_t cap = ring ? std::min<int64_t>((160 * 1024 - (int64_t)(zm + rings)) / 16 * 8, nv) : 0;
+  int64_t cap = ring ? std::min<int64_t>(((one ? half : whole) - zm - rings) / 16 * 8, nv) : 0;
   if (cap < 1024 && cap < nv) cap = 0;
   cap = std::min<int64_t>(cap, 32768);
   if (nf >= 1 << 28 || reinterpret_cast<char*>(packed + nf) > end) cap = 0;
-  if (reinterpret_cast<char*>(v4 + nv) > end || !(ring || V > 256)) v4 = nullptr;
+  if (reinterpret_cast<char*>(v4 + nv) > end || !(ring || V > cus)) v4 = nullptr;
+  // One workgroup takes the bounding box of few vertices and forms the frame: where a
+  // workgroup has one view, joining partial boxes in it takes longer (2 us) than the
+  // box does (1024 views of 13.6k triangles at 64^2 84 -> 81 us).
+  const int nbox = one && nv <= 8192 ? 1 : kBoxes;
   const int packers = cap == 0 ? 0 : (int)(nv <= cap ? rga::ceil_div(nf, 1024) : batches);
   const size_t lds = zm + (ring ? rings + table_bytes((int)cap) : 0);
-  auto raster = ring ? (v4 ? raster_kernel<true, true> : raster_kernel<true, false>)
-                     : (v4 ? raster_kernel<false, true> : raster_kernel<false, false>);
+  auto raster =
+      one ? (ring ? (v4 ? raster_kernel<true, true, true> : raster_kernel<true, false, true>)
+                  : (v4 ? raster_kernel<false, true, true> : raster_kernel<false, false, true>))
+          : (ring ? (v4 ? raster_kernel<true, true, false> : raster_kernel<true, false, false>)
+                  : (v4 ? raster_kernel<false, true, false> : raster_kernel<false, false, false>));
   static bool attr_set = false;
   if (!attr_set) {
-    for (auto k : {raster_kernel<true, true>, raster_kernel<true, false>,
-                   raster_kernel<false, true>, raster_kernel<false, false>})
+    for (auto k : {raster_kernel<true, true, false>, raster_kernel<true, false, false>,
+                   raster_kernel<false, true, false>, raster_kernel<false, false, false>,
+                   raster_kernel<true, true, true>, raster_kernel<true, false, true>,
+                   raster_kernel<false, true, true>, raster_kernel<false, false, true>})
       hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
-  RGA_LAUNCH("vis_frame", frame_kernel, dim3(kBoxes + packers), dim3(1024), 0, s, nv,
-             nf, verts, faces, (int)cap, boxes, ranges, packed, v4);
+  RGA_LAUNCH("vis_frame", frame_kernel, dim3(nbox + packers), dim3(1024), 0, s, nv,
+             nf, nbox, verts, faces, (int)cap, boxes, ranges, packed, v4);
   const Verts mesh = {verts, v4, nv};
-  const int grid = std::min(V, compute_units());
+  const int grid = one ? V : std::min(V, cus);
   RGA_LAUNCH("vis_raster", raster, dim3(grid), dim3(kRasterThreads), lds, s, mesh, nf, faces,
-             V, view_dirs, res, boxes, ranges, packed, (int)cap, vm, L.nwv, shadow, bias_px);
+             V, view_dirs, res, nbox, boxes, ranges, packed, (int)cap, vm, L.nwv, shadow, bias_px);
   const int64_t tw = (int64_t)L.nwv * L.nwV;
   RGA_LAUNCH("vis_transpose", transpose_kernel, dim3(rga::ceil_div(tw * 32, 256)), dim3(256), 0, s, nv,
              V, L.nwv, L.nwV, vm, raw);
