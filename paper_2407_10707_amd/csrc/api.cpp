@@ -28,6 +28,14 @@ int check_launch(const char* what) {
   return RGA_OK;
 }
 
+int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+    n = 256;
+  return n;
+}
+
 namespace {
 struct Rec {
   std::string name;

@@ -12,6 +12,8 @@ namespace rga {
 int fail(int code, const char* fmt, ...);
 // Check the launch that was just issued; returns RGA_OK or RGA_EHIP.
 int check_launch(const char* what);
+// Compute units of the current device (256 if it does not say).
+int compute_units();
 
 // Optional event timing around kernel launches (see rga_timing_enable).
 bool timing_on();

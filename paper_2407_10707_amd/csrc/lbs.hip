@@ -104,6 +104,7 @@ namespace {
 // joints of its 512 slots one after the other (Gaussians that are neighbours
 // share them) and adds each joint's wave sum into its own LDS row.  The waves'
 // rows, then the workgroups' rows, are added in a fixed order (no atomics).
+// A workgroup adds up the joints [per blockIdx.y, + per) of its chunk.
 // Every input is read once: with a workgroup per joint and chunk that read all
 // indices and skipped the other joints', 100k Gaussians and 24 joints took
 // 33 us and the sum over the chunks 12 us, now 9 and 4 us.
@@ -112,12 +113,13 @@ constexpr int kPoseLane = 2;                                   // Gaussians per 
 constexpr int kPoseChunk = kPoseWaves * 64 * kPoseLane;        // per workgroup
 
 __global__ void __launch_bounds__(kPoseWaves * 64)
-lbs_pose_grad_kernel(int n, int J, const int32_t* __restrict__ jidx, const float* __restrict__ jw,
+lbs_pose_grad_kernel(int n, int n_joints, int per, const int32_t* __restrict__ jidx, const float* __restrict__ jw,
                      const float* __restrict__ x, const float* __restrict__ disp,
                      const float* __restrict__ nrm, const float* __restrict__ dxo,
                      const float* __restrict__ dno, const float* __restrict__ dA,
                      float* __restrict__ part) {
-  extern __shared__ float rows[];                              // [wave][J][12]
+  extern __shared__ float rows[];                              // [wave][joint][12]
+  const int j0 = blockIdx.y * per, J = min(per, n_joints - j0);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int k = threadIdx.x; k < kPoseWaves * J * 12; k += blockDim.x) rows[k] = 0.f;
@@ -134,7 +136,7 @@ lbs_pose_grad_kernel(int n, int J, const int32_t* __restrict__ jidx, const float
     // (slots that add nothing: no weight, or no such joint)
 #pragma unroll
     for (int sl = 0; sl < 4; ++sl) {
-      id[k][sl] = jidx[(size_t)sl * n + c];
+      id[k][sl] = jidx[(size_t)sl * n + c] - j0;
       w[k][sl] = jw[(size_t)sl * n + c];
     }
 #pragma unroll
@@ -205,7 +207,7 @@ lbs_pose_grad_kernel(int n, int J, const int32_t* __restrict__ jidx, const float
     float t = rows[k];
 #pragma unroll
     for (int v = 1; v < kPoseWaves; ++v) t += rows[v * J * 12 + k];
-    part[(size_t)blockIdx.x * J * 12 + k] = t;
+    part[((size_t)blockIdx.x * n_joints + j0) * 12 + k] = t;
   }
 }
 
@@ -526,8 +528,16 @@ extern "C" int lbs_skin_pose_grad(void* stream, int n, int n_joints, const int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int chunks = pose_chunks(n);
   float* part = static_cast<float*>(ws);
-  RGA_LAUNCH("lbs_pose_grad", lbs_pose_grad_kernel, dim3(chunks), dim3(kPoseWaves * 64),
-             (size_t)kPoseWaves * n_joints * 12 * sizeof(float), s, n, n_joints, jidx, jw, x, disp, nrm,
+  // Joints are split over workgroups while the chunks alone leave CUs idle, down to four
+  // a workgroup: the walk over a wave's joints is as long as they are many there (256
+  // joints in no order, one workgroup per chunk -> split: 300 Gaussians 83 -> 14 us, 20k
+  // 85 -> 23, 60k 86 -> 44; 24 joints 19 -> 13), and every workgroup of a chunk reads all
+  // of it (100k Gaussians in the body's order, 24 joints, one workgroup 13.4 us, two 14.9).
+  const int cus = rga::compute_units();
+  const int split = std::min((n_joints + 3) / 4, std::max(1, 3 * cus / 2 / chunks));
+  const int per = rga::ceil_div(n_joints, split);
+  RGA_LAUNCH("lbs_pose_grad", lbs_pose_grad_kernel, dim3(chunks, rga::ceil_div(n_joints, per)), dim3(kPoseWaves * 64),
+             (size_t)kPoseWaves * per * 12 * sizeof(float), s, n, n_joints, per, jidx, jw, x, disp, nrm,
              dx_out, dn_out, dA, part);
   RGA_LAUNCH("lbs_pose_grad_final", lbs_pose_grad_final, dim3(rga::ceil_div(12 * n_joints, 64)),
              dim3(1024), 0, s, n_joints, chunks, part, dskin);

@@ -804,15 +804,6 @@ extern "C" size_t mesh_visibility_workspace(int nv, int V) {
 
 namespace {
 
-// compute units of the current device (256 if it does not say)
-int compute_units() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-    n = 256;
-  return n;
-}
-
 int visibility_impl(void* stream, int nv, int nf, const float* verts, const int32_t* faces, int V,
                     const float* view_dirs, int res, const int32_t* knn, int kv,
                     uint32_t* raw_bits, uint8_t* count, void* ws, size_t ws_bytes, int shadow,
@@ -853,7 +844,7 @@ int visibility_impl(void* stream, int nv, int nf, const float* verts, const int3
   // 64^2 109 -> 81, 3.6k at 48^2 47 -> 50, 27k at 96^2 177 -> 157 but 13.6k 109 ->
   // 117; 256 views, 3.6k at 48^2 31 -> 32).
   const size_t rings = ring_bytes();
-  const int cus = compute_units();
+  const int cus = rga::compute_units();
   const size_t whole = 160 * 1024, half = whole / 2;
   const bool pairs = V > cus && V < 1 << 21;   // (a launch's threads count to 2^32)
   const bool pair_ring = pairs && zm + rings + 2048 <= half, pair_place = pairs && zm <= half;
