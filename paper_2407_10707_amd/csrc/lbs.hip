@@ -251,8 +251,8 @@ namespace {
 // (parent outside 0..j-1) has G = R, P = J; skin_j = [G_j | P_j - G_j J_j].
 // One workgroup, a thread per joint (at most 256): the Rodrigues matrices, then
 // the chain one depth of the tree at a time, its joints in parallel.  Bound by
-// latency (one thread walked the joints in order: 24 joints 14 us, the adjoint
-// 35 us; now 8 and 13 us).
+// latency (one thread walked the joints in order: 24 joints of a body 14 us, the
+// adjoint 34; now 7.5 and 10).
 __device__ inline void rodrigues(const float* th, float* R, float& a, float& b, float& ap,
                                  float& bp) {
   const float t2 = fmaf(th[2], th[2], fmaf(th[1], th[1], th[0] * th[0]));
@@ -304,36 +304,54 @@ __device__ inline int parent_of(const int32_t* parents, int j) {
 static_assert(kMaxJoints <= kBlock, "a thread per joint");
 
 struct Chain {
-  float R[kMaxJoints][9], G[kMaxJoints][9], P[kMaxJoints][3];
+  float G[kMaxJoints][9], P[kMaxJoints][3];
   float at[kMaxJoints][3];   // rest joints
   int parent[kMaxJoints];
+  int jump[2][kMaxJoints];   // 512 times the way up to an ancestor, and that one + 1
   int deepest;
 };
 
-// The Rodrigues factors and depth of this thread's joint.
+// This thread's joint: Rodrigues factors and matrix, the rest position and its offset
+// from the parent's, G and P, parent and depth.
 struct Joint {
   float a, b, ap, bp;
+  float R[9], at[3], off[3], G[9], P[3];
   int p, depth;
 };
 
-__device__ Joint forward_chain(int J, const float* theta, const float* joints,
-                               const int32_t* parents, Chain& ch) {
+// The depths take log2 J rounds, in which a joint jumps to its ancestor's ancestor, and
+// a step of the chain reads its parent's G and P alone (one chain of 256 joints: 154 us
+// where each joint walked up through its parents and a step read five tables, 133 where
+// one thread walked all joints, now 60; the adjoint 264, 337 and 155).
+__device__ inline void forward_chain(int J, const float* theta, const float* joints,
+                                     const int32_t* parents, Chain& ch, Joint& t) {
   const int j = threadIdx.x;
-  Joint t = {};
   t.p = -1;
   t.depth = -1;
   if (j == 0) ch.deepest = 0;
+  int mine = 0;
   if (j < J) {
     t.p = parent_of(parents, j);
     ch.parent[j] = t.p;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) ch.at[j][q] = joints[3 * j + q];
-    rodrigues(theta + 3 * j, ch.R[j], t.a, t.b, t.ap, t.bp);
+    for (int q = 0; q < 3; ++q) ch.at[j][q] = t.at[q] = joints[3 * j + q];
+    rodrigues(theta + 3 * j, t.R, t.a, t.b, t.ap, t.bp);
+    mine = t.p < 0 ? 0 : 512 + t.p + 1;
+    ch.jump[0][j] = mine;
   }
   __syncthreads();
+  if (t.p >= 0) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) t.off[q] = t.at[q] - ch.at[t.p][q];
+  }
+  for (int span = 1, from = 0; span < J; span *= 2, from ^= 1) {
+    const int up = mine & 511;
+    if (up > 0) mine += ch.jump[from][up - 1] - up;
+    if (j < J) ch.jump[from ^ 1][j] = mine;
+    __syncthreads();
+  }
   if (j < J) {
-    t.depth = 0;
-    for (int p = t.p; p >= 0; p = ch.parent[p]) ++t.depth;
+    t.depth = mine >> 9;
     if (t.depth > 0) atomicMax(&ch.deepest, t.depth);
   }
   __syncthreads();
@@ -342,41 +360,47 @@ __device__ Joint forward_chain(int J, const float* theta, const float* joints,
     if (t.depth == d) {
       if (t.p < 0) {
 #pragma unroll
-        for (int q = 0; q < 9; ++q) ch.G[j][q] = ch.R[j][q];
+        for (int q = 0; q < 9; ++q) t.G[q] = t.R[q];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) ch.P[j][q] = ch.at[j][q];
+        for (int q = 0; q < 3; ++q) t.P[q] = t.at[q];
       } else {
-        mat3_mul(ch.G[t.p], ch.R[j], ch.G[j]);
+        float Gp[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) Gp[q] = ch.G[t.p][q];
+        mat3_mul(Gp, t.R, t.G);
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
           float v = ch.P[t.p][r];
 #pragma unroll
-          for (int m = 0; m < 3; ++m)
-            v = fmaf(ch.G[t.p][3 * r + m], ch.at[j][m] - ch.at[t.p][m], v);
-          ch.P[j][r] = v;
+          for (int m = 0; m < 3; ++m) v = fmaf(Gp[3 * r + m], t.off[m], v);
+          t.P[r] = v;
         }
       }
+#pragma unroll
+      for (int q = 0; q < 9; ++q) ch.G[j][q] = t.G[q];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) ch.P[j][q] = t.P[q];
     }
     __syncthreads();
   }
-  return t;
 }
 
 __global__ void __launch_bounds__(kBlock)
 pose_skin_kernel(int J, const float* __restrict__ theta, const float* __restrict__ joints,
                  const int32_t* __restrict__ parents, float* __restrict__ skin) {
   __shared__ Chain ch;
-  forward_chain(J, theta, joints, parents, ch);
+  Joint t;
+  forward_chain(J, theta, joints, parents, ch, t);
   const int j = threadIdx.x;
   if (j >= J) return;
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
-    float t = ch.P[j][r];
+    float v = t.P[r];
 #pragma unroll
-    for (int m = 0; m < 3; ++m) t = fmaf(-ch.G[j][3 * r + m], ch.at[j][m], t);
+    for (int m = 0; m < 3; ++m) v = fmaf(-t.G[3 * r + m], t.at[m], v);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) skin[12 * j + 4 * r + c] = ch.G[j][3 * r + c];
-    skin[12 * j + 4 * r + 3] = t;
+    for (int c = 0; c < 3; ++c) skin[12 * j + 4 * r + c] = t.G[3 * r + c];
+    skin[12 * j + 4 * r + 3] = v;
   }
 }
 
@@ -392,7 +416,7 @@ pose_skin_bwd_kernel(int J, const float* __restrict__ theta, const float* __rest
   __shared__ float share[kMaxJoints][12];   // a joint's addition to its parent's dG and dP
   __shared__ int child[kMaxJoints], next[kMaxJoints];   // highest child, next lower sibling
   const int j = threadIdx.x;
-  float dG[9], dP[3], D[9];
+  float dG[9], dP[3], D[9], Gp[9];
   if (j < J) {
     child[j] = -1;
 #pragma unroll
@@ -402,14 +426,17 @@ pose_skin_bwd_kernel(int J, const float* __restrict__ theta, const float* __rest
       for (int c = 0; c < 3; ++c) dG[3 * r + c] = dskin[12 * j + 4 * r + c];
     }
   }
-  const Joint t = forward_chain(J, theta, joints, parents, ch);
+  Joint t;
+  forward_chain(J, theta, joints, parents, ch, t);
   if (j < J) {
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) dG[3 * r + c] -= dP[r] * ch.at[j][c];
+      for (int c = 0; c < 3; ++c) dG[3 * r + c] -= dP[r] * t.at[c];
     int s = -1;
     if (t.p >= 0) {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) Gp[q] = ch.G[t.p][q];
       atomicMax(&child[t.p], j);
       for (int k = t.p + 1; k < j; ++k)
         if (ch.parent[k] == t.p) s = k;
@@ -436,11 +463,11 @@ pose_skin_bwd_kernel(int J, const float* __restrict__ theta, const float* __rest
             float vR = 0.f, vG = 0.f;
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
-              vR = fmaf(ch.G[t.p][3 * m + r], dG[3 * m + c], vR);      // G_p^T dG_j
-              vG = fmaf(dG[3 * r + m], ch.R[j][3 * c + m], vG);        // dG_j R_j^T
+              vR = fmaf(Gp[3 * m + r], dG[3 * m + c], vR);             // G_p^T dG_j
+              vG = fmaf(dG[3 * r + m], t.R[3 * c + m], vG);            // dG_j R_j^T
             }
             D[3 * r + c] = vR;
-            share[j][3 * r + c] = vG + dP[r] * (ch.at[j][c] - ch.at[t.p][c]);
+            share[j][3 * r + c] = vG + dP[r] * t.off[c];
           }
 #pragma unroll
         for (int r = 0; r < 3; ++r) share[j][9 + r] = dP[r];
