@@ -207,17 +207,16 @@ int mesh_visibility_noalloc(void* stream, int nv, int nf, const float* verts,
  * and wv | we; he*we <= 3584 directions; the LDS tables must fit 160 KB:
  * 32 K + 48 V bytes (forward) and 44 K + 48 V + 1536 bytes (adjoint) for
  * K = he*we directions and V views (e.g. 2048 directions with 1024 views).
- * RGA_BF16X3 also needs K % 32 == 0, one or two texels per view (hv == he,
- * we == wv or we == 2 wv), and at most 3296 directions in the forward and
- * 2272 in the adjoint.                                                      */
+ * RGA_BF16X3 also needs K % 32 == 0 and at most 3296 directions in the
+ * forward and 2272 in the adjoint.                                          */
 int shade_gaussians(void* stream, int n, const float* x, const float* nrm, const float* albedo,
                     const float* rough, const float* tint, const int32_t* vidx, const float* vw,
                     const uint8_t* count, int nv, int kv, int he, int we, int hv, int wv,
                     const float* env, const float* cam_pos, int precision, float* color,
                     uint8_t* front, void* tape, size_t tape_bytes);
 /* The same call for a stream with another beside it that is not to wait for
- * wave slots until this one ends (the same results; it takes half the device
- * where the whole would be filled).                                        */
+ * wave slots until this one ends (the same results; the FP32 kernel takes half
+ * the device where it would fill the whole; on MFMA the call is as without). */
 int shade_gaussians_beside(void* stream, int n, const float* x, const float* nrm, const float* albedo,
                            const float* rough, const float* tint, const int32_t* vidx, const float* vw,
                            const uint8_t* count, int nv, int kv, int he, int we, int hv, int wv,

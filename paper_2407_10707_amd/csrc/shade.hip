@@ -1285,11 +1285,17 @@ int patches(int he, int we) { return (he % 4 == 0 && we % 8 == 0) ? 1 : 0; }
 // kernel.  MFMA -> FP32: 300k Gaussians 128 directions 56 -> 80 us, 256 102 -> 97;
 // 100k 512 100 -> 57, in other view grids 237 -> 56; 30k 128 14 us both, 500 17 -> 9.
 // The FP32 kernel then walks the same patches, so the tape is the same, and rounds
-// the factors as MFMA takes them (3 us of the 57): a Gaussian's colour does not
-// hang on how many there are.  What is left is the sums' order, 5e-7 of a colour,
-// which dx and dn (sums that cancel) amplify to 4e-4 of their rms at worst; it
-// grows with the terms, to 9e-4 at 2048 directions, so beyond 512 the form keeps
-// to MFMA (828 us against 144 at 100k: RGA_FP32 is the form to ask for there).
+// the factors as MFMA takes them (3 us of the 57).  What differs is the order of the
+// sums: a colour changes by up to 6e-7 of the colours' rms where the route does, so
+// also from 32,767 Gaussians to 32,768 at 128 directions, and dx and dn, sums that
+// cancel, by up to 1.4e-4 of theirs (1,200 Gaussians, 512 to 2048 directions).  Neither
+// is nearer to FP64: errors in units of the rms, MFMA and the FP32 kernel, 512
+// directions colour 3.9e-7 and 3.9e-7, dx 5.7e-6 and 5.7e-6, dn 6.0e-6 and 4.9e-6; 1024
+// colour 2.8e-7 and 2.6e-7, dx 5.0e-6 and 4.8e-6, dn 6.5e-6 and 5.9e-6; 2048 colour
+// 2.4e-7 and 2.0e-7, dx 1.40e-5 and 1.40e-5, dn 7.9e-6 and 8.2e-6.  So the line at 512
+// is none of accuracy, nor of time (100k Gaussians, 2048 directions: 828 us on MFMA, 144
+// on the FP32 kernel): up to there the form has moved to the FP32 kernel, beyond it runs
+// on MFMA as it always has, and RGA_FP32 is the form to ask for.
 bool forward_on_mfma(const ShadeArgs& a) {
   if (fp32_lds(a.K, a.V, false, false, 8) + 16 * 64 > kLdsMax - kLdsStatic || a.K > 512) return true;
   return a.K <= 128 && a.n >= 32768 && view_ratio(a.he, a.we, a.hv, a.wv) > 0;
@@ -1306,8 +1312,11 @@ struct Launch {
 // kernel at its LDS size), never more than one wave per Gaussian; beside other
 // work half as many, where two or more fit a CU: a full grid leaves the other
 // stream's short kernels no wave slots until it ends (100k Gaussians, 512
-// directions beside their binning, training step 369 -> 353 us; alone the forward
-// would take 61 us instead of 55).
+// directions beside their binning, training step 381 -> 366 us; alone the forward
+// would take 61 us instead of 55).  Frames and training steps of 20k to 300k Gaussians,
+// 128, 512 and 2048 directions, 128^2 to 1080^2 take 0.91 to 1.00 times as long with
+// the half as with the whole; 1.01 to 1.03 times where the two streams were given one
+// hardware queue, so that nothing overlaps (one pair in four).
 Launch fp32_launch(int n, int K, int V, bool adjoint, bool taped, bool beside) {
   Launch l;
   int dev = 0, ncu = 0;
