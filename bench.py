@@ -13,9 +13,11 @@ Prints one JSON line.  `value` is the fwd+bwd time per step (ms/iter) of
 the FP32 form; `render_fps` is the forward-only frame rate with visibility
 recomputed per frame, `render_fps_no_vis` with visibility cached per pose.
 The same figures for the BF16X3 form of the shading contraction (bf16 hi +
-lo operands, on MFMA or, as here, on the FP32 kernel) sit under `bf16x3`, and `image_error_vs_fp64` gives
-each form's image PSNR against the FP64 oracle (with the oracle's emulation
-of plain bf16 operands beside it).
+lo operands) sit under `bf16x3`; `shading_forward` names the kernel that each
+form's forward ran on (the library chooses MFMA or the FP32 kernel; at this
+workload both forms run on the latter).  `image_error_vs_fp64` gives each
+form's image PSNR against the FP64 oracle (with the oracle's emulation of
+plain bf16 operands beside it).
 """
 
 from __future__ import annotations
@@ -496,6 +498,26 @@ def densify_measure(s, d, reps: int = 20):
     return out
 
 
+def kernel_times(step, names, reps=5):
+    """{name: ms per launch} of those of the named kernels that step() launches."""
+    import torch
+
+    from paper_2407_10707_amd import rga
+    out = {}
+    for name in names:
+        rga.timing_reset()
+        rga.timing_filter(name)
+        rga.timing_enable(True)
+        for _ in range(reps):
+            step()
+        torch.cuda.synchronize()
+        rga.timing_enable(False)
+        ms, cnt = rga.timing_read(name)
+        if cnt:
+            out[name] = ms / cnt
+    return out
+
+
 def measure_form(args, s, d, precision: str, capacity=None):
     """Time the step of one precision form: sizes the splat workspace to the
     frame's duplicates, runs the warm-up, times exactly `args.steps` steps
@@ -577,9 +599,7 @@ def measure_form(args, s, d, precision: str, capacity=None):
     if args.kernel:
         kernels = [args.kernel]
     elif precision == "bf16x3":
-        K = s["he"] * s["we"]
-        mfma = K > 512 or (K <= 128 and s["n"] >= 32768)
-        kernels = ["blend_bwd", "shade_fwd_bf16x3" if mfma else "shade_fwd"]
+        kernels = ["blend_bwd", "shade_fwd", "shade_fwd_bf16x3"]   # (one of the two runs)
     else:
         kernels = ["blend_bwd", "shade_bwd"]
     kernel = kernels[0]
@@ -619,18 +639,10 @@ def measure_form(args, s, d, precision: str, capacity=None):
         per_kernel["sum_of_kernels"] = round(sum(per_kernel.values()), 4)
     k_avg = {kernel: k_ms / k_n}
     timed_where = {kernel: "timed region"}
-    for kn in kernels[1:]:
-        rga.timing_reset()
-        rga.timing_filter(kn)
-        rga.timing_enable(True)
-        for _ in range(5):
-            step()
-        torch.cuda.synchronize()
-        rga.timing_enable(False)
-        ms, cnt = rga.timing_read(kn)
-        if cnt:
-            k_avg[kn] = ms / cnt
-            timed_where[kn] = "5 eager steps after the timed region"
+    others = kernel_times(step, kernels[1:])
+    k_avg.update(others)
+    timed_where.update({kn: "5 eager steps after the timed region" for kn in others})
+    forward = list(kernel_times(step, ["shade_fwd", "shade_fwd_bf16x3"], 1))
 
     # forward-only frame rates (visibility per frame, and cached per pose;
     # a sequence recomputes visibility once per pose)
@@ -708,7 +720,7 @@ def measure_form(args, s, d, precision: str, capacity=None):
     out = {"ms_per_step": round(ms_step, 4), "render_fps": round(fps, 2),
            "render_fps_no_vis": round(fps_nv, 2), "duplicates": D,
            "sequence_frames": frames if args.sequence else None, "roofline": roof,
-           "roofline_other": roof_other}
+           "roofline_other": roof_other, "shading_forward": forward[0]}
     if per_kernel:
         out["per_kernel_ms_per_step"] = per_kernel
     return out, R, p, step, image.cpu().numpy()
@@ -872,12 +884,13 @@ def main():
         "sequence_frames": head["sequence_frames"],
         "roofline": head["roofline"],
         "roofline_other": head["roofline_other"],
+        "shading_forward": head["shading_forward"],
         "cpu_baseline": cpu,
     }
     if other is not None:
         oform = "bf16x3" if args.precision == "fp32" else "fp32"
         out[oform] = {k: other[k] for k in ("ms_per_step", "render_fps", "render_fps_no_vis",
-                                            "roofline", "roofline_other")}
+                                            "roofline", "roofline_other", "shading_forward")}
     out["image_error_vs_fp64"] = err
     out.update({
         "knn": knn,
