@@ -1569,8 +1569,8 @@ constexpr int kSplitsPart = 2;           // the same, per further part of a deep
 // splat's line of the sums in one 32-byte atomic request and one single add
 // (as nine planes they were 64 scattered lines per request).
 //
-// Bound by vector issue (about 500 slots per eight entries): 67 us at 100k /
-// 512^2 and 205 us at 300k / 1080^2, where one item queue over the sub-chunks
+// Bound by vector issue (about 500 slots per eight entries): 61 us at 100k /
+// 512^2 and 207 us at 300k / 1080^2, where one item queue over the sub-chunks
 // of whole lists, most of them past the stop, took 88 and 390 us.  No
 // workgroup waits for another and the waves share nothing; the next
 // sub-chunk's loads are issued before the current one is walked.
@@ -1586,11 +1586,14 @@ blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restri
   __shared__ float4 s0[4][kSub], s1[4][kSub];
   __shared__ float s2[4][kSub];
   __shared__ uint32_t sg[4][kSub];
-  // first nsplit times the workgroups of the blocks, then kSplitsPart times those
-  // of the items; of a part's sub-chunks each takes every so many'th four
+  // first kSplitsPart times the workgroups of the items, then nsplit times those of
+  // the blocks (the items, of long lists, at the end would be a tail: 71 us instead of
+  // 61 at 100k / 512^2 of the avatar); of a part's sub-chunks each takes every so
+  // many'th four
   const int blocks = (tiles + 7) / 8 * 8 * kBlocks, items = (P.slots + 7) / 8 * 8 * kBlocks;
-  const bool own = (int)blockIdx.x < nsplit * blocks;
-  const int unit = own ? blocks : items, at = own ? blockIdx.x : blockIdx.x - nsplit * blocks;
+  const int front = kSplitsPart * items;
+  const bool own = (int)blockIdx.x >= front;
+  const int unit = own ? blocks : items, at = own ? blockIdx.x - front : blockIdx.x;
   const int split = (at >= unit) + (at >= 2 * unit) + (at >= 3 * unit);
   const PixelBlock B = pixel_block((own ? 0 : blocks) + at - split * unit, TX, tiles, P, counters);
   if (B.t < 0) return;
