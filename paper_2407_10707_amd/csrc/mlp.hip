@@ -131,12 +131,6 @@ T* at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // 8 floats -> bf16 high parts and bf16 low parts (the remainders)
 __device__ inline void split8(const float* v, bf16x8& hi, bf16x8& lo) {
 #pragma unroll

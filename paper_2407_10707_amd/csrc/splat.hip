@@ -112,8 +112,8 @@ inline size_t parts_bytes(int slots, int64_t tiles) {
 }
 
 struct Layout {
-  size_t rec, mean2d, conic, depth, rect, touched, fp64, keys0, vals0, keys1, vals1, offs;
-  size_t tk0, tv0, tk1, tv1, ranges, hist, binoff, bintot, bsum, boff, count, grad;
+  size_t rec, mean2d, conic, depth, rect, touched, fp64, keys0, vals0, keys1, vals1;
+  size_t tk0, tv0, tk1, tv1, ranges, hist, binoff, bintot, bsum, count, grad;
   size_t nlive, last, mask, state, part, total;
   int tiles_x, tiles_y, nb_n, nb_cap, nb_max, tile_passes;
   int slots;       // parts that the deep lists have room for
@@ -152,7 +152,6 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   L.vals0 = take(N * 4);
   L.keys1 = take(N * 4);
   L.vals1 = take(N * 4);
-  L.offs = take(N * 4);
   L.tk0 = take(C * 4);
   L.tv0 = take(C * 4);
   L.tk1 = take(C * 4);
@@ -162,7 +161,6 @@ Layout make_layout(int n, int width, int height, int64_t cap) {
   L.binoff = take((size_t)L.nb_max * (1 << kMaxBits) * 4);
   L.bintot = take((1 << kMaxBits) * 4);
   L.bsum = take((size_t)L.nb_n * 4);
-  L.boff = take((size_t)L.nb_n * 4);   // (kept: sizes a caller has computed stay enough)
   L.count = take(32);   // int64 [0] = D, [1] = places and items of the deep lists (32 bits each),
                         // [3] = splats that touch a tile
   L.grad = take(N * kGrad * 4);   // adjoint sums per splat: mean2d, conic, opacity, colour
