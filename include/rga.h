@@ -160,9 +160,10 @@ int mesh_visibility_shadowmap(void* stream, int nv, int nf, const float* verts,
  * visibility of mesh_visibility (same arguments without the workspace, same
  * bit-exact outputs), its workspace taken from a fixed device array of the
  * library, mesh_visibility_noalloc_limit() bytes (32 MiB) per GPU, held from
- * the first call on that GPU until the process ends.  Sizes whose workspace
- * (mesh_visibility_workspace(nv, V)) exceeds that limit return RGA_ECAPACITY
- * before any launch.  Calls that overlap on one GPU (concurrent streams or
+ * the first call on that GPU until the process ends.  Sizes whose masks and
+ * filters do not fit that limit return RGA_ECAPACITY before any launch (they
+ * fit if mesh_visibility_workspace(nv, V) does, which for many vertices and
+ * few views is more than they need).  Calls that overlap on one GPU (concurrent streams or
  * host threads) share the array and race; serialise them.  Allocates
  * nothing and calls no allocating routine.                                  */
 size_t mesh_visibility_noalloc_limit(void);

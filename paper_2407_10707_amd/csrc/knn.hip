@@ -256,8 +256,9 @@ knn_qfill_kernel(int n, const uint32_t* __restrict__ qstart, const uint32_t* __r
 // cells: those further from the query than the K-th so far hold nothing nearer
 // (a mesh fills a small part of the grid's cells, about 10 vertices in each at
 // 6,840 and up to 78, so after its own cell a query needs few of the 26 around
-// it).  Every wave is resident at once and the longest sets the time: 100k
-// queries 39 us with every row dealt out and none pruned, now 27 us.
+// it).  Bound by the chains of dependent loads of its waves: the 100 registers of
+// K = 3 leave four to a SIMD, 4,096 slots for the 6,250 waves of 100k queries, 39 us
+// with every row dealt out and none pruned, now 27 us.
 constexpr int kQuadBatch = 4;            // records per lane loaded together
 constexpr int kQuadRows = 3;             // rows per lane looked up together
 

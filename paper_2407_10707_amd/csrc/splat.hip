@@ -1006,7 +1006,7 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // before the block's stop at 100k Gaussians / 512^2 and 16 % at 300k / 1080^2.
 // (Compositing 256-entry chunks of every list side by side, then combining
 // them per pixel and restarting the chunk with the stop, walked all of them:
-// 85 us at 100k / 512^2 and 416 us at 300k / 1080^2, this 76 and 164 us.)
+// 85 us at 100k / 512^2 and 416 us at 300k / 1080^2, this 72 and 165 us.)
 // Four entries per step shorten the chain of the longest walk (1,250 entries)
 // fourfold, and the 4 x 4 sub-blocks waste fewer lanes on pixels an entry
 // does not reach than 8 x 8 blocks do.  Two steps are taken together: all but
@@ -1029,13 +1029,15 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // so far have stopped for certain need no walk any more.  The join decides on its
 // own; what it reads of a part that ended early lies past the stop.
 // One walk takes 22 ns per entry where pixels do not stop, as at an avatar's rim.
-// Kernels of a forward and adjoint, every list in one walk -> deep ones in parts:
-// 300k splats on 8 tiles of 1080^2, the longest list 101,728 entries, 4,040 -> 390
-// us; on 40 tiles of 512^2, 25,667 entries, 770 -> 335; 30k on 39 tiles, 2,576
-// entries, 211 -> 214; 100k on 372 tiles, 4,570 entries, 274 -> 275; 300k on 1,627
-// tiles, no deep list, 580 -> 587 (the join's registers leave six waves per SIMD
-// instead of seven).  Equal parts of all of an image's lists, chosen by their mean:
-// 100k on 128^2 345 -> 260, 200k on 200^2 320 -> 292.
+// Blend and its adjoint, every list in one walk (or equal parts of all, chosen by
+// their mean, at 128^2 and 200^2) -> deep ones in parts: 300k splats on 8 tiles of
+// 1080^2, the longest list 101,728 entries, 2,248 and 1,620 -> 118 and 88 us; on 40
+// tiles of 512^2, 25,667 entries, 434 and 185 -> 102 and 71; 30k on 39 tiles, 2,576
+// entries, 56 and 36 -> 47 and 38; 100k on 128^2 139 and 80 -> 75 and 48; 200k on
+// 200^2 111 and 75 -> 87 and 74; 100k on 372 tiles, 4,570 entries, 75 and 71 -> 72 and
+// 74; 300k on 1,627 tiles, no deep list, 158 and 207 -> 165 and 211 (the join's
+// registers leave six waves per SIMD instead of seven, and seven by a launch bound
+// cost 100k on 372 tiles 6 us).
 constexpr float kPastStop = -2.f;
 
 // One front-to-back compositing step of the adjoint for the pixel centre (px, py),

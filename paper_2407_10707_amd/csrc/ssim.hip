@@ -24,10 +24,10 @@
 // per output and map, and the products of x and y once per tap).  With 54 rows
 // and their halo every thread has one row piece in the first pass, and its sums
 // stay in registers while the second pass's LDS replaces the first's.  At 3 x
-// 1080 x 1080, forward and adjoint: 51 -> 28 us and 37 -> 29 us so (42 and 34 us
-// where each load of the halo waited for the one before), 27 and 21 us with the
-// tiles divided among the XCDs.  Vector issue is 65 % and 55 % of that; the rest
-// is the loads' latency at four waves per SIMD.
+// 1080 x 1080, forward and adjoint: 52 -> 32 us and 38 -> 23 us, of which the tiles
+// divided among the XCDs are 1 and 8 (42 and 34 us where each load of the halo
+// waited for the one before).  Vector issue is about two thirds and half of that;
+// the rest is the loads' latency at four waves per SIMD.
 #include "common.h"
 
 #include <algorithm>
