@@ -57,20 +57,25 @@ constexpr int kDepthPasses = (32 + kDepthBits - 1) / kDepthBits;
 constexpr int kManySplats = 1 << 17;
 
 // Deep lists are walked in parts, side by side (see the blend): a list of two part
-// lengths or more, which are 1,024 entries (a walk of 22 us, where the launches of a
-// frame's other steps take longer than a shorter one saves) or, so that all parts
+// lengths or more.  Up to 65,536 entries in all a part is 1/64 of them, one workgroup
+// per CU, at least 256; beyond that 1,024 (a walk of 22 us, where the launches of a
+// frame's other steps take longer than a shorter one saves: 100k splats over 500^2,
+// paper's mesh, frame 308 us with 1,024, 312 with 512, 314 with 256; 30k splats on 37
+// tiles, 22,699 entries, blend and adjoint 108, 85 and 73, now 79) or, so that all parts
 // together are about as many workgroups as the chip holds, 1/256 of all entries.
 // What decides is each list's own length, known on the device: the mean over an
 // image's tiles says nothing of an avatar that covers a few of them.
 constexpr int kPart = 1024;
-constexpr int kParts = 256;      // of all lists, about
+constexpr int kPartMin = 256;
+constexpr int kPartsMin = 64;    // of all lists, up to kPart * kPartsMin entries
+constexpr int kParts = 256;      // the same of more entries, about
 constexpr int kListParts = 128;  // of one list
 constexpr int kPartBits = 7;     // an item of the part list: tile << kPartBits | part
 
 __device__ inline uint32_t part_length(int64_t entries) {   // (at most 2^31 - 1)
-  static_assert(kParts == 256, "a shift");
-  const uint32_t v = ((uint32_t)entries + 255u) >> 8;
-  return v > kPart ? (v + kSub - 1) / kSub * kSub : kPart;
+  static_assert(kParts == 256 && kPartsMin == 64, "shifts");
+  const uint32_t n = (uint32_t)entries, few = min(max((n + 63u) >> 6, (uint32_t)kPartMin), (uint32_t)kPart);
+  return (max((n + 255u) >> 8, few) + kSub - 1) / kSub * kSub;
 }
 
 __device__ inline bool is_deep(int L, uint32_t part) { return (uint32_t)L >= 2 * part; }
@@ -83,8 +88,9 @@ __device__ inline int list_parts(int L, uint32_t part) {
 // Room for the parts: lists of more than two lengths each have at most half as
 // many parts again as whole lengths.  None where no list can be that long.
 inline int part_slots(int64_t n, int64_t cap) {
-  if (n < 2 * kPart) return 0;
-  return (int)std::min<int64_t>(kParts, cap / kPart) * 3 / 2 + 1;
+  if (n < 2 * kPartMin) return 0;
+  const int64_t few = std::min<int64_t>(kPartsMin, cap / kPartMin);
+  return (int)std::max(few, std::min<int64_t>(kParts, cap / kPart)) * 3 / 2 + 1;
 }
 
 // What the blend keeps of the parts, one array behind the other (one address keeps
@@ -1031,9 +1037,9 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // One walk takes 22 ns per entry where pixels do not stop, as at an avatar's rim.
 // Blend and its adjoint, every list in one walk (or equal parts of all, chosen by
 // their mean, at 128^2 and 200^2) -> deep ones in parts: 300k splats on 8 tiles of
-// 1080^2, the longest list 101,728 entries, 2,248 and 1,620 -> 118 and 88 us; on 40
+// 1080^2, the longest list 101,728 entries, 2,257 and 1,604 -> 121 and 87 us; on 40
 // tiles of 512^2, 25,667 entries, 434 and 185 -> 102 and 71; 30k on 39 tiles, 2,576
-// entries, 56 and 36 -> 47 and 38; 100k on 128^2 139 and 80 -> 75 and 48; 200k on
+// entries, 56 and 36 -> 40 and 34; 100k on 128^2 139 and 80 -> 75 and 48; 200k on
 // 200^2 111 and 75 -> 87 and 74; 100k on 372 tiles, 4,570 entries, 75 and 71 -> 72 and
 // 74; 300k on 1,627 tiles, no deep list, 158 and 207 -> 165 and 211 (the join's
 // registers leave six waves per SIMD instead of seven, and seven by a launch bound

@@ -1,6 +1,6 @@
 """Deep lists on a few tiles of a larger image, which are walked in parts side by
-side: lists of 2,047 to 2,049 entries (one part or two), of more than 32 parts, of
-more entries than 128 parts of 1,024 hold, beside tiles with short lists and empty
+side: lists of 511 to 513 entries (one part or two), of several parts of 256, of more
+than 32 parts, of more entries than 128 parts of 1,024 hold, beside tiles with short lists and empty
 ones, with the tile sort in one pass and in two (more than 4,096 tiles), splats
 that stop a pixel early and that never do; two blends of one binning, and a frame
 whose lists do not fit the workspace.
@@ -27,7 +27,12 @@ pytestmark = pytest.mark.gpu
 
 # splats in the deep part and elsewhere, image, half extent of the deep part (of the
 # image's height), log scale, opacities, longest list at least
-CASES = [(2047, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 2047),
+CASES = [(511, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 511),
+         (512, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 512),
+         (513, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 513),
+         (700, 500, 70, 45, 0.3, -1.5, (0.005, 0.3), 600),
+         (16_500, 500, 70, 45, 0.2, -3.0, (0.004, 0.012), 16_000),
+         (2047, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 2047),
          (2048, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 2048),
          (2049, 0, 16, 16, 0.4, -2.0, (0.005, 0.06), 2049),
          (2300, 200, 70, 45, 0.3, -1.5, (0.3, 0.95), 2200),
