@@ -1012,7 +1012,7 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // before the block's stop at 100k Gaussians / 512^2 and 16 % at 300k / 1080^2.
 // (Compositing 256-entry chunks of every list side by side, then combining
 // them per pixel and restarting the chunk with the stop, walked all of them:
-// 85 us at 100k / 512^2 and 416 us at 300k / 1080^2, this 72 and 165 us.)
+// 85 us at 100k / 512^2 and 416 us at 300k / 1080^2, this 72 and 162 us.)
 // Four entries per step shorten the chain of the longest walk (1,250 entries)
 // fourfold, and the 4 x 4 sub-blocks waste fewer lanes on pixels an entry
 // does not reach than 8 x 8 blocks do.  Two steps are taken together: all but
@@ -1037,11 +1037,11 @@ tile_ranges_kernel(const uint32_t* __restrict__ tkeys, const int64_t* cnt_ptr, i
 // One walk takes 22 ns per entry where pixels do not stop, as at an avatar's rim.
 // Blend and its adjoint, every list in one walk (or equal parts of all, chosen by
 // their mean, at 128^2 and 200^2) -> deep ones in parts: 300k splats on 8 tiles of
-// 1080^2, the longest list 101,728 entries, 2,257 and 1,604 -> 121 and 87 us; on 40
-// tiles of 512^2, 25,667 entries, 434 and 185 -> 102 and 71; 30k on 39 tiles, 2,576
+// 1080^2, the longest list 101,728 entries, 2,257 and 1,604 -> 107 and 76 us; on 40
+// tiles of 512^2, 25,667 entries, 434 and 185 -> 102 and 67; 30k on 39 tiles, 2,576
 // entries, 56 and 36 -> 40 and 34; 100k on 128^2 139 and 80 -> 75 and 48; 200k on
 // 200^2 111 and 75 -> 87 and 74; 100k on 372 tiles, 4,570 entries, 75 and 71 -> 72 and
-// 74; 300k on 1,627 tiles, no deep list, 158 and 207 -> 165 and 211 (the join's
+// 74; 300k on 1,627 tiles, no deep list, 157 and 202 -> 162 and 202 (the join's
 // registers leave six waves per SIMD instead of seven, and seven by a launch bound
 // cost 100k on 372 tiles 6 us).
 constexpr float kPastStop = -2.f;
@@ -1083,29 +1083,26 @@ __device__ inline float stop_after(float T) { return T * (1.f - 0x1p-9f); }
 // the tile's list it walks: the four blocks of a tile, which read the same
 // records, follow each other on one XCD (workgroups with equal index mod 8), and
 // neighbouring tiles go to different ones; the same of the items (a tile's further
-// part), which come behind block_grid(tiles) workgroups for the first parts.
+// part).  Of an image around an avatar most workgroups find nothing and leave: what
+// they work out before that counts (37,000 of them at 1080^2, the grid's layout taken
+// apart in the kernel 30 instead of 26 us for the adjoint of 4,000 entries).
 struct PixelBlock {
   int t, blk, ox, oy;     // tile (-1: none), block in the tile, first pixel
   int y;                  // part
   __device__ inline int id() const { return kBlocks * t + blk; }
 };
-__device__ inline PixelBlock pixel_block(int index, int TX, int tiles, const Parts& P,
+__device__ inline PixelBlock pixel_block(int e, bool own, int TX, int tiles, const Parts& P,
                                          const int64_t* counters) {
   PixelBlock b;
-  const int first = (tiles + 7) / 8 * 8 * kBlocks;
-  b.y = 0;
-  const int e = index < first ? index : index - first;
   const int k = e >> 3;
   b.t = (k >> 2) * 8 + (e & 7);
   b.blk = k & 3;
-  if (index >= first) {
-    if (b.t < (int)((uint64_t)counters[1] >> 32)) {
-      const uint32_t item = P.items()[b.t];
-      b.t = (int)(item >> kPartBits);
-      b.y = (int)(item & ((1u << kPartBits) - 1u));
-    } else {
-      b.t = -1;
-    }
+  b.y = 0;
+  if (!own) {
+    const bool have = b.t < (int)((uint64_t)counters[1] >> 32);
+    const uint32_t item = have ? P.items()[b.t] : 0u;
+    b.t = have ? (int)(item >> kPartBits) : -1;
+    b.y = (int)(item & ((1u << kPartBits) - 1u));
   } else if (b.t >= tiles) {
     b.t = -1;
   }
@@ -1309,8 +1306,8 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
              const uint32_t* __restrict__ sorted, const float4* __restrict__ rec,
              const float* __restrict__ color, const int64_t* __restrict__ counters,
              int64_t capacity, float* __restrict__ state, uint64_t* __restrict__ mask,
-             uint32_t* __restrict__ nlive, float* __restrict__ last, Parts P, float* __restrict__ image,
-             float* __restrict__ Tfinal) {
+             uint32_t* __restrict__ nlive, float* __restrict__ last, Parts P, int blocks,
+             float* __restrict__ image, float* __restrict__ Tfinal) {
   constexpr int kRound = 4 * kSub;        // entries per round
   // the staged records of two rounds, each with an entry past them with
   // opacity 0 that fills up a step of four
@@ -1322,7 +1319,8 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
   // lane e (the e-th of either four) follow each other
   __shared__ uint16_t lists[4][kRound];
   __shared__ int open[2][4];              // sub-chunks entered in the round, per wave; 0: stopped
-  const PixelBlock B = pixel_block(blockIdx.x, TX, tiles, P, counters);
+  const bool own = (int)blockIdx.x < blocks;
+  const PixelBlock B = pixel_block(blockIdx.x - (own ? 0 : blocks), own, TX, tiles, P, counters);
   if (B.t < 0) return;
   const int lane = threadIdx.x & 63, e = lane & 3;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1347,6 +1345,11 @@ blend_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restrict__
     return;
   }
   const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
+  if (L <= 0) {                           // (most tiles of an image around an avatar)
+    put_pixel(0.f, 0.f, 0.f, 1.f);
+    if (threadIdx.x == 0) nlive[B.id()] = 0u;
+    return;
+  }
   const int slot0 = start / kSub + B.t;
   // this workgroup's entries; of a deep list its part, the place of the first
   // part's block and of its own
@@ -1576,7 +1579,7 @@ constexpr int kSplitsPart = 2;           // the same, per further part of a deep
 // (as nine planes they were 64 scattered lines per request).
 //
 // Bound by vector issue (about 500 slots per eight entries): 61 us at 100k /
-// 512^2 and 207 us at 300k / 1080^2, where one item queue over the sub-chunks
+// 512^2 and 202 us at 300k / 1080^2, where one item queue over the sub-chunks
 // of whole lists, most of them past the stop, took 88 and 390 us.  No
 // workgroup waits for another and the waves share nothing; the next
 // sub-chunk's loads are issued before the current one is walked.
@@ -1586,31 +1589,28 @@ blend_bwd_kernel(int W, int H, int TX, int tiles, int n, const int32_t* __restri
                  const float* __restrict__ color, const float* __restrict__ state,
                  const uint64_t* __restrict__ mask, const uint32_t* __restrict__ nlive,
                  const float* __restrict__ last, const int64_t* __restrict__ counters, int64_t capacity,
-                 Parts P, int nsplit,
+                 Parts P, int front,
                  const float* __restrict__ image, const float* __restrict__ dimage,
                  float* __restrict__ grad) {
   __shared__ float4 s0[4][kSub], s1[4][kSub];
   __shared__ float s2[4][kSub];
   __shared__ uint32_t sg[4][kSub];
-  // first kSplitsPart times the workgroups of the items, then nsplit times those of
-  // the blocks (the items, of long lists, at the end would be a tail: 71 us instead of
-  // 61 at 100k / 512^2 of the avatar); of a part's sub-chunks each takes every so
-  // many'th four
-  const int blocks = (tiles + 7) / 8 * 8 * kBlocks, items = (P.slots + 7) / 8 * 8 * kBlocks;
-  const int front = kSplitsPart * items;
+  // the workgroups of the items before those of the blocks (the items, of long lists,
+  // at the end would be a tail: 71 us instead of 61 at 100k / 512^2 of the avatar); of
+  // a part's sub-chunks each takes every so many'th four
   const bool own = (int)blockIdx.x >= front;
-  const int unit = own ? blocks : items, at = own ? blockIdx.x - front : blockIdx.x;
-  const int split = (at >= unit) + (at >= 2 * unit) + (at >= 3 * unit);
-  const PixelBlock B = pixel_block((own ? 0 : blocks) + at - split * unit, TX, tiles, P, counters);
+  const int split = blockIdx.y;
+  if (!own && split >= kSplitsPart) return;
+  const PixelBlock B = pixel_block(blockIdx.x - (own ? front : 0), own, TX, tiles, P, counters);
   if (B.t < 0) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int myslot = lane >> 3, col = lane & 7;
-  const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
-  const int slot0 = start / kSub + B.t;
-  const int step = 4 * (own ? nsplit : kSplitsPart);
+  const int step = 4 * (own ? (int)gridDim.y : kSplitsPart);
   int first = wave + 4 * split, end = own ? (int)nlive[B.id()] : first + 1;
   if (first >= end || counters[0] > capacity) return;
+  const int start = ranges[2 * B.t], L = ranges[2 * B.t + 1] - start;
+  const int slot0 = start / kSub + B.t;
   const uint32_t part = part_length(counters[0]);
   float4 base = make_float4(0.f, 0.f, 0.f, 1.f);
   if (is_deep(L, part)) {
@@ -2162,7 +2162,7 @@ extern "C" int splat_blend(void* stream, int n, const rga_camera* cam, const flo
   RGA_LAUNCH("blend", blend_kernel, dim3(block_grid(tiles) + block_grid(L.slots)), dim3(256), 0, s, W, H,
              L.tiles_x, (int)tiles, n, ranges, sorted, at<float4>(ws, L.rec), color, cnt, capacity,
              at<float>(ws, L.state), at<uint64_t>(ws, L.mask), at<uint32_t>(ws, L.nlive),
-             at<float>(ws, L.last), parts_of(ws, L), image, T_final);
+             at<float>(ws, L.last), parts_of(ws, L), (int)block_grid(tiles), image, T_final);
   RGA_CHECK_LAUNCH("splat_blend");
   return RGA_OK;
 }
@@ -2203,13 +2203,12 @@ extern "C" int splat_backward(void* stream, int n, const rga_camera* cam, const 
   float* grad = at<float>(ws, L.grad);
   const int64_t tiles = (int64_t)L.tiles_x * L.tiles_y;
   const uint32_t* sorted = at<uint32_t>(ws, (L.tile_passes & 1) ? L.tv1 : L.tv0);
-  const int nsplit = splits(tiles);
   RGA_LAUNCH("blend_bwd", blend_bwd_kernel,
-             dim3(nsplit * block_grid(tiles) + kSplitsPart * block_grid(L.slots)), dim3(256), 0, s,
+             dim3(block_grid(L.slots) + block_grid(tiles), splits(tiles)), dim3(256), 0, s,
              cam->width, cam->height, L.tiles_x, (int)tiles, n, at<int32_t>(ws, L.ranges), sorted,
              at<float4>(ws, L.rec), color, at<float>(ws, L.state), at<uint64_t>(ws, L.mask),
              at<uint32_t>(ws, L.nlive), at<float>(ws, L.last), (const int64_t*)at<int64_t>(ws, L.count),
-             capacity, parts_of(ws, L), nsplit, image, dimage, grad);
+             capacity, parts_of(ws, L), (int)block_grid(L.slots), image, dimage, grad);
   RGA_LAUNCH("preprocess_bwd", preprocess_bwd_kernel, dim3(rga::ceil_div(n, 256)), dim3(256), 0, s,
              n, cd, x, A, quat, log_s, opac, front, at<int32_t>(ws, L.touched), grad, dx, dquat,
              dlog_s, dopac, dcolor, dA, (const int64_t*)at<int64_t>(ws, L.count), capacity);
